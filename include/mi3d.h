@@ -105,7 +105,8 @@ int mi3d_conv3d_wgrad(const mi3d_conv_desc *desc, const void *x, const void *dy,
  * device array of MI3D_STATIC_SCRATCH_BYTES inside the library, which every GPU the library runs on holds from the
  * first call until the process ends.  The call allocates nothing and frees nothing.  A geometry whose weight gradient
  * needs more scratch than that (mi3d_conv3d_workspace_bytes(desc, MI3D_PASS_WGRAD) > MI3D_STATIC_SCRATCH_BYTES)
- * returns MI3D_ERR_WORKSPACE and launches nothing; every layer of the 5-level U-Net at 192^3 and 208^3 fits.  All
+ * returns MI3D_ERR_WORKSPACE and launches nothing, unless it is only the padded copies of channel counts that are not
+ * multiples of 32 that do not fit: the plain kernel, which needs none, then runs (sums in another order); every layer of the 5-level U-Net at 192^3 and 208^3 fits.  All
  * calls on one GPU share the one array: calls that overlap in time on the same GPU (two streams, two threads) race
  * on it and must be serialised by the caller.  x, dy, dw: device pointers as for mi3d_conv3d_wgrad. */
 #define MI3D_STATIC_SCRATCH_BYTES (64u << 20)

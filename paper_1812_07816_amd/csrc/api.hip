@@ -107,6 +107,14 @@ static size_t kernel_workspace(Kernel k, const Geom& g, int pass) {
     return 0;
 }
 
+// The kernel for a given workspace: an embedding whose padded copies do not fit gives way to the plain kernel, which
+// needs none or little (the callers' size query reports what the embedding wants; the static scratch has a fixed size).
+static Kernel choose_within(const Geom& g, int pass, size_t ws_bytes) {
+    const Kernel k = choose(g, pass);
+    if (k == K_EMBED_C && kernel_workspace(k, g, pass) > ws_bytes && kernel_workspace(K_DIRECT, g, pass) <= ws_bytes) return K_DIRECT;
+    return k;
+}
+
 // a, b, out per pass: fwd (x, w, y), dgrad (dy, w, dx), wgrad (x, dy, dw)
 static int run_kernel(Kernel k, const Geom& g, int pass, const void* a, const void* b, void* out, void* ws, size_t ws_bytes, hipStream_t s) {
     switch (k) {
@@ -151,6 +159,10 @@ static bool pair_supported(const Geom& g, int pass) {
 }
 
 // automatic choice for a geometry, used by the entry points and by fallbacks that re-enter with a derived geometry
+bool auto_is_mfma(const Geom& g, int pass) {
+    const Kernel k = choose(g, pass);
+    return k != K_DIRECT && k != K_POINTWISE;
+}
 size_t auto_workspace_bytes(const Geom& g, int pass) { return kernel_workspace(choose(g, pass), g, pass); }
 int auto_conv(const Geom& g, int pass, const void* a, const void* b, void* out, void* ws, size_t ws_bytes, hipStream_t s) {
     return run_kernel(choose(g, pass), g, pass, a, b, out, ws, ws_bytes, s);
@@ -227,8 +239,8 @@ static int conv_entry(const mi3d_conv_desc* desc, int pass, const void* a, const
     }
     if (!a || !b || !out || !aligned16(a) || !aligned16(b) || !aligned16(out) || !aligned16(ws)) return MI3D_ERR_INVALID_ARG;
     if (ws_bytes && !ws) return MI3D_ERR_INVALID_ARG;
-    if (ws_bytes < mi3d_conv3d_workspace_bytes(desc, pass)) return MI3D_ERR_WORKSPACE;
-    Kernel k = choose(g, pass);
+    const Kernel k = choose_within(g, pass, ws_bytes);
+    if (ws_bytes < kernel_workspace(k, g, pass)) return MI3D_ERR_WORKSPACE;
     const bool epilogue = slope != 1.f;
     if (!epilogue) return run_kernel(k, g, pass, a, b, out, ws, ws_bytes, (hipStream_t)stream);
     if (!(slope >= 0.f && slope < 1.f) || (g.dtype != MI3D_BF16 && k != K_F32) || pass == MI3D_PASS_WGRAD) return MI3D_ERR_INVALID_ARG;
@@ -288,7 +300,8 @@ int mi3d_conv3d_wgrad_static(const mi3d_conv_desc* desc, const void* x, const vo
     int st = make_geom(desc, &g);
     if (st) return st;
     // sizes beyond the array are refused before anything is looked up or launched
-    if (mi3d_conv3d_workspace_bytes(desc, MI3D_PASS_WGRAD) > (size_t)MI3D_STATIC_SCRATCH_BYTES) return MI3D_ERR_WORKSPACE;
+    if (kernel_workspace(choose_within(g, MI3D_PASS_WGRAD, MI3D_STATIC_SCRATCH_BYTES), g, MI3D_PASS_WGRAD) > (size_t)MI3D_STATIC_SCRATCH_BYTES)
+        return MI3D_ERR_WORKSPACE;
     void* ws = nullptr;
     st = scratch_of_current_device(&ws);
     if (st) return st;
@@ -315,9 +328,9 @@ int mi3d_conv3d_dgrad_skip(const mi3d_conv_desc* desc, const void* dy, const voi
     if (st) return st;
     if (!dy || !w || !add || !a_in || !dx || !aligned16(dy) || !aligned16(w) || !aligned16(add) || !aligned16(a_in) || !aligned16(dx) || !aligned16(ws))
         return MI3D_ERR_INVALID_ARG;
-    const Kernel k = choose(g, MI3D_PASS_DGRAD);
+    const Kernel k = choose_within(g, MI3D_PASS_DGRAD, ws_bytes);
     if ((g.dtype != MI3D_BF16 && k != K_F32) || !(slope >= 0.f && slope <= 1.f) || (ws_bytes && !ws)) return MI3D_ERR_INVALID_ARG;
-    if (ws_bytes < mi3d_conv3d_workspace_bytes(desc, MI3D_PASS_DGRAD)) return MI3D_ERR_WORKSPACE;
+    if (ws_bytes < kernel_workspace(k, g, MI3D_PASS_DGRAD)) return MI3D_ERR_WORKSPACE;
     if (k == K_F32 || (k == K_DGRAD_S2 && dgrad_s2_fuses_skip(g))) {
         Geom ge = g;
         ge.add = add; ge.ref = a_in; ge.slope = slope;

@@ -1,7 +1,7 @@
-// Fallbacks that run a layer no tuned kernel covers through the stride-1
-// 32-channel MFMA kernels by embedding its operands:
-//   - few input channels (the network's first layer, Cin = 4): x and w are
-//     zero-padded to 32 channels; results are sliced back;
+// Fallbacks that run a layer no tuned kernel covers through the MFMA kernels by
+// embedding its operands:
+//   - channel counts that are not multiples of 32: operands are zero-padded, results
+//     sliced back;
 //   - strided layers: the forward pass is the stride-1 result subsampled;
 //     for the gradients dy is spread onto the stride-1 output grid (zeros in
 //     between), after which dx and dw are exactly the stride-1 gradients.
@@ -12,28 +12,62 @@
 namespace mi3d {
 namespace {
 
-// dst[v][0..CP) = src[v][0..C) followed by zeros; one thread per 8 output channels
-__global__ void __launch_bounds__(256) pad_channels_kernel(const uint16_t* __restrict__ src, uint16_t* __restrict__ dst,
-                                                           long long voxels, int C, int CP) {
-    const int per = CP / 8;
+// Zero-padding of channel rows: dst[v][0..CP) = src[v][0..C) followed by zeros for v < rows, all zeros for the rows up to
+// rows_p.  Two independent jobs share a launch (the activations and the weights of a pass): these passes take a few
+// microseconds each, about what a launch costs.  One thread per 8 channels of dst; rows whose length is a multiple of 8
+// are read 16 bytes at a time.
+struct PadJob {
+    const uint16_t* src;
+    uint16_t* dst;
+    long long rows, rows_p;
+    int C, CP;
+    __host__ __device__ long long threads() const { return rows_p * (CP / 8); }
+};
+__global__ void __launch_bounds__(256) pad_channels_kernel(PadJob a, PadJob b) {
     long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= voxels * per) return;
-    long long v = idx / per;
-    int c0 = (int)(idx % per) * 8;
-    uint16_t o[8];
+    const bool second = idx >= a.threads();
+    if (second) idx -= a.threads();
+    const PadJob& J = second ? b : a;
+    if (idx >= J.threads()) return;
+    const int per = J.CP / 8;
+    const long long v = idx / per;
+    const int c0 = (int)(idx - v * per) * 8;
+    uint4 out = {0, 0, 0, 0};
+    if (v < J.rows) {
+        const uint16_t* src = J.src + v * J.C + c0;
+        if (J.C % 8 == 0) {
+            if (c0 < J.C) out = *(const uint4*)src;
+        } else {
+            uint32_t o[4] = {0, 0, 0, 0};
 #pragma unroll
-    for (int j = 0; j < 8; ++j) o[j] = (c0 + j < C) ? src[v * C + c0 + j] : (uint16_t)0;
-    *(uint4*)(dst + v * CP + c0) = *(const uint4*)o;
+            for (int j = 0; j < 8; ++j)
+                if (c0 + j < J.C) o[j >> 1] |= (uint32_t)src[j] << (16 * (j & 1));
+            out = uint4{o[0], o[1], o[2], o[3]};
+        }
+    }
+    *(uint4*)(J.dst + v * J.CP + c0) = out;
+}
+// the same with rows padded to 4 channels (inputs with fewer than 4 channels): one thread per row
+__global__ void __launch_bounds__(256) pad_to4_kernel(const uint16_t* __restrict__ src, uint16_t* __restrict__ dst, long long rows, long long rows_p, int C) {
+    const long long v = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (v >= rows_p) return;
+    uint32_t o[2] = {0, 0};
+    if (v < rows)
+        for (int j = 0; j < C; ++j) o[j >> 1] |= (uint32_t)src[v * C + j] << (16 * (j & 1));
+    *(uint2*)(dst + v * 4) = uint2{o[0], o[1]};
 }
 
-// dst[v][0..C) = src[v][0..C) of CP-channel rows (T = uint16_t or float)
-template <typename T>
+// dst[v][0..C) = src[v][0..C) of CP-channel rows (T = uint16_t or float), V elements per thread (16 bytes, or one where C
+// is not a multiple of that)
+template <typename T, int V>
 __global__ void __launch_bounds__(256) slice_channels_kernel(const T* __restrict__ src, T* __restrict__ dst, long long voxels, int C, int CP) {
-    long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= voxels * C) return;
-    long long v = idx / C;
-    int c = (int)(idx % C);
-    dst[idx] = src[v * CP + c];
+    const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
+    const int per = C / V;
+    if (idx >= voxels * per) return;
+    const long long v = idx / per;
+    const int c = (int)(idx - v * per) * V;
+    if constexpr (V == 1) dst[v * C + c] = src[v * CP + c];
+    else *(uint4*)(dst + v * C + c) = *(const uint4*)(src + v * CP + c);
 }
 
 // up[n][s*od][s*oh][s*ow][:] = dy[n][od][oh][ow][:], zero elsewhere; up has extents (Du,Hu,Wu).
@@ -81,62 +115,102 @@ unsigned blocks_for(long long n) { return (unsigned)((n + 255) / 256); }
 
 }  // namespace
 
-// ---- few input channels --------------------------------------------------
-static Geom padded_geom(const Geom& g) {
+// ---- channel counts that no MFMA kernel takes --------------------------------
+// The padded layer: channels rounded up to multiples of 32 (stride 2: the data-gradient kernel walks output channels in
+// chunks of 64), or input channels to 4 where the first-layer kernels then apply.
+static Geom padded_geom(const Geom& g, int pass) {
     Geom p = g;
-    p.Cin = 32;
+    p.Cout = (g.Cout + 31) / 32 * 32;
+    if (g.Cin <= 4) {
+        p.Cin = 4;
+        if (pass == MI3D_PASS_FWD ? c4_fwd_supported(p) : pass == MI3D_PASS_DGRAD ? c4_dgrad_supported(p) : c4_wgrad_supported(p)) return p;
+    }
+    p.Cin = (g.Cin + 31) / 32 * 32;
+    if (g.sD == 2 && p.Cout > 32) p.Cout = (p.Cout + 63) / 64 * 64;
     return p;
 }
 
+// bytes of the padded operands and result in the workspace: x-shaped, y-shaped, weight-shaped tensors (0: not padded)
+struct EmbedC {
+    Geom p;
+    size_t xb, yb, wb;
+};
+static EmbedC embed_c_layout(const Geom& g, int pass) {
+    EmbedC e{padded_geom(g, pass), 0, 0, 0};
+    const bool ci = e.p.Cin != g.Cin, co = e.p.Cout != g.Cout;
+    if (ci) e.xb = align256((size_t)g.in_voxels() * e.p.Cin * 2);
+    if (co) e.yb = align256((size_t)g.out_voxels() * e.p.Cout * 2);
+    if (ci || co) e.wb = align256((size_t)e.p.w_elems() * (pass == MI3D_PASS_WGRAD ? 4 : 2));
+    return e;
+}
+
 bool embed_c_supported(const Geom& g, int pass) {
-    if (g.dtype != MI3D_BF16 || g.Cin >= 32) return false;
-    Geom p = padded_geom(g);
-    if (pass == MI3D_PASS_WGRAD) return wgrad_mfma_supported(p);
-    return sp_supported(p, pass);
+    if (g.dtype != MI3D_BF16) return false;
+    const EmbedC e = embed_c_layout(g, pass);
+    if (!e.wb || e.xb + e.yb > (16ull << 30)) return false;   // (copies of more than 16 GiB: the plain kernels need none)
+    return auto_is_mfma(e.p, pass);
 }
 
 size_t embed_c_workspace_bytes(const Geom& g, int pass) {
     if (!embed_c_supported(g, pass)) return 0;
-    Geom p = padded_geom(g);
-    size_t xb = align256((size_t)g.in_voxels() * 32 * 2), wb = align256((size_t)p.w_elems() * 2);
-    if (pass == MI3D_PASS_FWD) return xb + wb + align256(sp_workspace_bytes(p, pass));
-    if (pass == MI3D_PASS_DGRAD) return xb + wb + align256(sp_workspace_bytes(p, pass));   // xb holds dx32
-    return xb + align256((size_t)p.w_elems() * 4) + align256(wgrad_mfma_workspace_bytes(p));
+    const EmbedC e = embed_c_layout(g, pass);
+    return e.xb + e.yb + e.wb + align256(auto_workspace_bytes(e.p, pass));
 }
 
+static int pad_rows(const uint16_t* src, uint16_t* dst, long long rows, long long rows_p, int C, int CP, hipStream_t s) {
+    pad_to4_kernel<<<blocks_for(rows_p), 256, 0, s>>>(src, dst, rows, rows_p, C);
+    return check_launch();
+}
+
+// Bound: the copies are a pass over each operand and one more launch, the plain kernels do one product at a time per thread.
+// The three passes, plain kernels -> this: 48 -> 48 channels at 37 x 50 x 61 34.5 -> 0.22 ms, 8 -> 16 at 6^3 0.140 -> 0.061,
+// 40 -> 48 at 12^3 0.98 -> 0.084, 24 -> 48 at 10^3 with stride 2 0.171 -> 0.064: the padded layer wins at every size, so
+// the plain kernels are left with the geometries no matrix-core kernel takes.
 int embed_c_conv(const Geom& g, int pass, const void* a, const void* b, void* out, void* ws, size_t ws_bytes, hipStream_t s) {
     if (ws_bytes < embed_c_workspace_bytes(g, pass)) return MI3D_ERR_WORKSPACE;
-    Geom p = padded_geom(g);
-    char* base = (char*)ws;
-    const size_t xb = align256((size_t)g.in_voxels() * 32 * 2);
-    uint16_t* x32 = (uint16_t*)base;
-    int st;
-    if (pass == MI3D_PASS_FWD || pass == MI3D_PASS_DGRAD) {
-        const size_t wb = align256((size_t)p.w_elems() * 2);
-        uint16_t* w32 = (uint16_t*)(base + xb);
-        void* rest = base + xb + wb;
-        const size_t rest_bytes = ws_bytes - xb - wb;
-        const long long wrows = g.taps() * g.Cout;  // weight rows of Cin channels
-        const void* w = pass == MI3D_PASS_FWD ? b : b;
-        pad_channels_kernel<<<blocks_for(wrows * 4), 256, 0, s>>>((const uint16_t*)w, w32, wrows, g.Cin, 32);
+    const EmbedC e = embed_c_layout(g, pass);
+    const Geom& p = e.p;
+    uint16_t* xp = (uint16_t*)ws;
+    uint16_t* yp = (uint16_t*)((char*)ws + e.xb);
+    void* wp = (char*)ws + e.xb + e.yb;
+    void* rest = (char*)wp + e.wb;
+    const size_t rest_bytes = ws_bytes - e.xb - e.yb - e.wb;
+    const long long T = g.taps();
+    int st = MI3D_OK;
+    // operands: the activations that are read (x, dy) and the weights, in one launch
+    PadJob jobs[2] = {};
+    int n = 0;
+    auto add = [&](const void* src, void* dst, long long rows, long long rows_p, int C, int CP) {
+        if (CP % 8) st = pad_rows((const uint16_t*)src, (uint16_t*)dst, rows, rows_p, C, CP, s);   // (4 channels)
+        else jobs[n++] = PadJob{(const uint16_t*)src, (uint16_t*)dst, rows, rows_p, C, CP};
+    };
+    const void* x = pass == MI3D_PASS_DGRAD ? nullptr : a;
+    const void* dy = pass == MI3D_PASS_DGRAD ? a : (pass == MI3D_PASS_WGRAD ? b : nullptr);
+    if (x && e.xb) { add(x, xp, g.in_voxels(), g.in_voxels(), g.Cin, p.Cin); x = xp; }
+    if (st) return st;
+    if (dy && e.yb) { add(dy, yp, g.out_voxels(), g.out_voxels(), g.Cout, p.Cout); dy = yp; }
+    if (pass != MI3D_PASS_WGRAD) add(b, wp, T * g.Cout, T * p.Cout, g.Cin, p.Cin);
+    if (st) return st;
+    if (n) {
+        pad_channels_kernel<<<blocks_for(jobs[0].threads() + (n > 1 ? jobs[1].threads() : 0)), 256, 0, s>>>(jobs[0], jobs[1]);
         if ((st = check_launch())) return st;
-        if (pass == MI3D_PASS_FWD) {
-            pad_channels_kernel<<<blocks_for(g.in_voxels() * 4), 256, 0, s>>>((const uint16_t*)a, x32, g.in_voxels(), g.Cin, 32);
-            if ((st = check_launch())) return st;
-            return sp_conv(p, MI3D_PASS_FWD, x32, w32, out, rest, rest_bytes, s);
-        }
-        if ((st = sp_conv(p, MI3D_PASS_DGRAD, a, w32, x32, rest, rest_bytes, s))) return st;  // x32 = dx with 32 channels
-        slice_channels_kernel<uint16_t><<<blocks_for(g.in_voxels() * g.Cin), 256, 0, s>>>(x32, (uint16_t*)out, g.in_voxels(), g.Cin, 32);
+    }
+    // the padded layer, then the channels that were asked for
+    if (pass == MI3D_PASS_WGRAD) {
+        if ((st = auto_conv(p, pass, x, dy, wp, rest, rest_bytes, s))) return st;
+        const long long rows = T * g.Cout;
+        if (g.Cin % 4 == 0) slice_channels_kernel<float, 4><<<blocks_for(rows * (g.Cin / 4)), 256, 0, s>>>((const float*)wp, (float*)out, rows, g.Cin, p.Cin);
+        else slice_channels_kernel<float, 1><<<blocks_for(rows * g.Cin), 256, 0, s>>>((const float*)wp, (float*)out, rows, g.Cin, p.Cin);
         return check_launch();
     }
-    const size_t dwb = align256((size_t)p.w_elems() * 4);
-    float* dw32 = (float*)(base + xb);
-    void* rest = base + xb + dwb;
-    pad_channels_kernel<<<blocks_for(g.in_voxels() * 4), 256, 0, s>>>((const uint16_t*)a, x32, g.in_voxels(), g.Cin, 32);
-    if ((st = check_launch())) return st;
-    if ((st = wgrad_mfma(p, x32, b, dw32, rest, ws_bytes - xb - dwb, s))) return st;
-    const long long wrows = g.taps() * g.Cout;
-    slice_channels_kernel<float><<<blocks_for(wrows * g.Cin), 256, 0, s>>>(dw32, (float*)out, wrows, g.Cin, 32);
+    const bool fwd = pass == MI3D_PASS_FWD;
+    const int C = fwd ? g.Cout : g.Cin, CP = fwd ? p.Cout : p.Cin;
+    uint16_t* padded_out = C != CP ? (fwd ? yp : xp) : (uint16_t*)out;
+    if ((st = auto_conv(p, pass, fwd ? x : dy, wp, padded_out, rest, rest_bytes, s))) return st;
+    if (C == CP) return MI3D_OK;
+    const long long rows = fwd ? g.out_voxels() : g.in_voxels();
+    if (C % 8 == 0) slice_channels_kernel<uint16_t, 8><<<blocks_for(rows * (C / 8)), 256, 0, s>>>(padded_out, (uint16_t*)out, rows, C, CP);
+    else slice_channels_kernel<uint16_t, 1><<<blocks_for(rows * C), 256, 0, s>>>(padded_out, (uint16_t*)out, rows, C, CP);
     return check_launch();
 }
 

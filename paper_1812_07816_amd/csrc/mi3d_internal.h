@@ -109,7 +109,7 @@ size_t s2_fwd_workspace_bytes(const Geom& g);
 int s2_fwd(const Geom& g, const void* x, const void* w, void* y, void* ws, size_t ws_bytes, hipStream_t s);
 
 
-// fallbacks through the stride-1 MFMA kernels: zero-padded input channels, zero-spread dy
+// fallbacks through the MFMA kernels: zero-padded channels, zero-spread dy
 bool embed_c_supported(const Geom& g, int pass);
 size_t embed_c_workspace_bytes(const Geom& g, int pass);
 int embed_c_conv(const Geom& g, int pass, const void* a, const void* b, void* out, void* ws, size_t ws_bytes, hipStream_t s);
@@ -173,6 +173,7 @@ bool f32_wgrad_folds_taps(const Geom& g);   // at most 4 input channels: (tap, c
 bool f32_takes_halves(const Geom& g, int pass);   // the tensor of x's shape as two halves along the channels
 
 // automatic kernel choice for a geometry (a, b, out per pass: fwd (x, w, y), dgrad (dy, w, dx), wgrad (x, dy, dw))
+bool auto_is_mfma(const Geom& g, int pass);   // a matrix-core kernel takes it, directly or behind an embedding
 size_t auto_workspace_bytes(const Geom& g, int pass);
 int auto_conv(const Geom& g, int pass, const void* a, const void* b, void* out, void* ws, size_t ws_bytes, hipStream_t s);
 
