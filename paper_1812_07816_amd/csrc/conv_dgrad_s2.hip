@@ -35,12 +35,11 @@ struct Dg2Params {
     const uint16_t* wpack;  // [cin tile][kd][kh][kw][k16][lane][8]
     uint16_t* dx;
     uint16_t* dump;         // 8 KB that masked store lanes write to instead of dx
-    float* part;            // [cout chunk][voxel][Cin] fp32 partial gradients (Cout > 64)
     const uint16_t* add;    // FUSE: second gradient of dx's shape, added to the rounded result
     const uint16_t* ref;    // FUSE: tensor of dx's shape whose sign selects the factor 1 or slope
     float slope;
     int N, D, H, W, Cin, Cout, Do, Ho, Wo, p;
-    int QD, HT, WT, CiT, NCO;   // ..., cin tiles, cout chunks (of 64 when Cout > 64)
+    int QD, HT, WT, CiT;        // ..., cin tiles
     long long units;
     int nwg;
     // FUSE == 2: per-(workgroup, segment, wave) sums of g and g * xhat, 32 cins each, in the layout of the
@@ -142,14 +141,13 @@ __device__ __forceinline__ uint4 fuse4(uint4 v, uint4 a, uint4 m, float slope) {
 // KK = Cout / 16 k16 steps.  Every MFMA needs its own 1 KB weight fragment from LDS (a tap is used once
 // per wave and step), so the kernel runs at the LDS rate: the fragment reads are issued two groups of
 // three MFMAs ahead of their use from a ring of three register groups.
-// PART: Cout > 64 is contracted in chunks of 64 that are separate work units writing fp32 partial gradients; a second
-// kernel adds the chunks in index order and rounds to bf16.
-// FUSE (not with PART): the gradient of a skip connection.  The pieces of G.add and G.ref at the addresses of the
+// (Cout > 64: the implicit GEMM of conv_ig.hip.)
+// FUSE: the gradient of a skip connection.  The pieces of G.add and G.ref at the addresses of the
 // plane pair's 16 stores are requested before its MFMA work and applied to the rounded result in the store path.
 // FUSE == 2: the skip tensor's producer is a normalised layer (Section 4.1), so no factor is applied (G.slope = 1), and
 // the kernel adds up the two sums that layer's normalisation needs for its backward pass, from the stored gradient
 // and G.ref: every lane keeps the sums of its 16 cins over a segment, a fixed butterfly adds the 32 voxel lanes.
-template <int P, int KK, bool PART, int FUSE = 0>
+template <int P, int KK, int FUSE = 0>
 __global__ void __launch_bounds__(256, 1) dgrad_s2_kernel(Dg2Params G) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     constexpr int SLABS = 2 * KK;
@@ -177,17 +175,15 @@ __global__ void __launch_bounds__(256, 1) dgrad_s2_kernel(Dg2Params G) {
         u0 += q_end - q_start;
         const int wt = (int)(column % G.WT); column /= G.WT;
         const int ht = (int)(column % G.HT); column /= G.HT;
-        const int chunk = PART ? (int)(column % G.NCO) : 0;
-        if (PART) column /= G.NCO;
         const int cit = (int)(column % G.CiT);
         const int n = (int)(column / G.CiT);
         const int rq0 = ht * RP, cq0 = wt * CP;   // first row pair / column pair
 
         __syncthreads();  // previous segment's readers are done
-        if (cit * G.NCO + chunk != cur_cit) {
-            const uint4* src = (const uint4*)(G.wpack + ((long long)cit * G.NCO + chunk) * (W_BYTES / 2));
+        if (cit != cur_cit) {
+            const uint4* src = (const uint4*)(G.wpack + (long long)cit * (W_BYTES / 2));
             for (int i = t; i < W_BYTES / 16; i += 256) ((uint4*)w_lds)[i] = src[i];
-            cur_cit = cit * G.NCO + chunk;
+            cur_cit = cit;
         }
         // load plan: piece q = (voxel v = q / SLABS, slab c = q % SLABS), voxel row-major over 5 x 33
         int goff[NL], loff[NL];
@@ -199,7 +195,7 @@ __global__ void __launch_bounds__(256, 1) dgrad_s2_kernel(Dg2Params G) {
             const int row = v / PC, col = v - row * PC;
             const int gh = rq0 + G.p - 1 + row, gw = cq0 + G.p - 1 + col;
             const bool ok = q < NPIECE && gh >= 0 && gh < G.Ho && gw >= 0 && gw < G.Wo;
-            goff[i] = ok ? (gh * G.Wo + gw) * G.Cout + chunk * (16 * KK) + c * 8 : 0;
+            goff[i] = ok ? (gh * G.Wo + gw) * G.Cout + c * 8 : 0;
             loff[i] = (c * SLABV + row * PITCH + col) * 16;
             valid |= (ok ? 1u : 0u) << i;
         }
@@ -212,7 +208,6 @@ __global__ void __launch_bounds__(256, 1) dgrad_s2_kernel(Dg2Params G) {
             for (int i = 0; i < 16; ++i) st1[i] = st2[i] = 0.f;
         }
         const float inv_stat_slope = FUSE == 2 ? 1.f / G.stat_slope : 1.f;
-        float* pn = PART ? G.part + ((long long)chunk * G.N + n) * G.D * G.H * G.W * G.Cin : nullptr;
 
         uint4 pre[NL];
         unsigned pre_mask = 0;
@@ -326,20 +321,6 @@ __global__ void __launch_bounds__(256, 1) dgrad_s2_kernel(Dg2Params G) {
 #pragma unroll
                 for (int ch = 0; ch < 2; ++ch) {
                     const int ih_ = 2 * rq + (ch == 0 ? G.p : 1 - G.p);
-                    if (PART) {
-                        // fp32 partials: register i of lane (n, h) is cin 8 (i / 4) + 4 h + i % 4; class cw sits in column
-                        // 2 cq + (cw == 0 ? p : 1 - p)
-#pragma unroll
-                        for (int cw = 0; cw < 2; ++cw) {
-                            const int iw_ = 2 * cq + (cw == 0 ? P : 1 - P);
-                            float* ptr = pn + (((long long)id_ * G.H + ih_) * G.W + iw_) * G.Cin + cit * 32 + 4 * (lane >> 5);
-                            float* qf = (id_ < G.D && ih_ < G.H && iw_ < G.W) ? ptr : (float*)G.dump + lane * 32;
-                            const f32x16& a = acc[cd][ch][cw];
-#pragma unroll
-                            for (int g4 = 0; g4 < 4; ++g4) *(float4*)(qf + 8 * g4) = float4{a[4 * g4], a[4 * g4 + 1], a[4 * g4 + 2], a[4 * g4 + 3]};
-                        }
-                        continue;
-                    }
                     uint4 be[2], bo[2];
                     pack_block(acc[cd][ch][0], be);   // class E columns: 2 cq + p
                     pack_block(acc[cd][ch][1], bo);   // class O columns: 2 cq + 1 - p
@@ -406,8 +387,8 @@ __global__ void __launch_bounds__(256, 1) dgrad_s2_kernel(Dg2Params G) {
     }
 }
 
-// [Cout][3][3][3][Cin] -> [cin tile][cout chunk][tap][k16][lane][8]: lane (ci = l % 32, half h) holds couts
-// chunk * 16 KK + 16 kk + 8 h + j; KK k16-steps per chunk
+// [Cout][3][3][3][Cin] -> [cin tile][tap][k16][lane][8]: lane (ci = l % 32, half h) holds couts
+// 16 kk + 8 h + j; KK = Cout / 16
 __global__ void __launch_bounds__(256) dgrad_s2_pack_kernel(const uint16_t* __restrict__ w, uint16_t* __restrict__ wpack, int Cin, int Cout, int KK) {
     const long long total = 27ll * Cin * Cout;
     const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
@@ -417,33 +398,32 @@ __global__ void __launch_bounds__(256) dgrad_s2_pack_kernel(const uint16_t* __re
     const int lane = (int)(r & 63); r >>= 6;
     const int kk = (int)(r % KK); r /= KK;
     const int tap = (int)(r % 27); r /= 27;
-    const int nco = Cout / (16 * KK);
-    const int chunk = (int)(r % nco);
-    const int cit = (int)(r / nco);
+    const int cit = (int)r;
     const int ci = cit * 32 + (lane & 31);
-    const int co = chunk * 16 * KK + kk * 16 + 8 * (lane >> 5) + j;
+    const int co = kk * 16 + 8 * (lane >> 5) + j;
     wpack[idx] = w[((long long)co * 27 + tap) * Cin + ci];
 }
 
 }  // namespace
 
-static size_t dg2_part_offset(const Geom& g) { return (((size_t)g.w_elems() * 2 + 255) & ~(size_t)255) + 8192; }
+static size_t dg2_stat_offset(const Geom& g) { return (((size_t)g.w_elems() * 2 + 255) & ~(size_t)255) + 8192; }
 
 bool dgrad_s2_supported(const Geom& g) {
     if (g.dtype != MI3D_BF16 || g.kD != 3 || g.kH != 3 || g.kW != 3) return false;
     if (g.sD != 2 || g.sH != 2 || g.sW != 2) return false;
     if (g.pD != g.pH || g.pD != g.pW || g.pD > 1) return false;
     if (!g.planes_fit_32bit()) return false;
-    return g.Cin % 32 == 0 && (g.Cout == 32 || g.Cout % 64 == 0);
+    if (g.Cin % 32) return false;
+    return g.Cout == 32 || g.Cout == 64 || (g.Cout % 64 == 0 && ig_supported(g, MI3D_PASS_DGRAD));
 }
 
-// the chunked variant applies the optional derivative factor of the geometry while it sums the chunks
+// the implicit GEMM applies the optional derivative factor of the geometry
 bool dgrad_s2_fuses_factor(const Geom& g) { return dgrad_s2_supported(g) && g.Cout > 64; }
 bool dgrad_s2_fuses_skip(const Geom& g) { return dgrad_s2_supported(g) && g.Cout >= 64; }
-// ... and the unchunked kernel also the sums of the instance-normalisation backward pass of the skip tensor's producer
+// ... and the kernel for Cout = 64 also the sums of the instance-normalisation backward pass of the skip tensor's producer
 bool dgrad_s2_fuses_skip_sums(const Geom& g) { return dgrad_s2_supported(g) && g.Cout == 64; }
 
-// workgroups and the most segments (runs along D inside one patch column) one of them walks, for the unchunked kernel
+// workgroups and the most segments (runs along D inside one patch column) one of them walks, of this kernel
 static void dg2_layout(const Geom& g, long long* units, int* nwg, int* max_seg) {
     const int QD = (g.D + 1) / 2, HT = ((g.H + 1) / 2 + RP - 1) / RP, WT = ((g.W + 1) / 2 + CP - 1) / CP;
     *units = (long long)g.N * (g.Cin / 32) * HT * WT * QD;
@@ -455,8 +435,8 @@ static void dg2_layout(const Geom& g, long long* units, int* nwg, int* max_seg) 
 
 size_t dgrad_s2_workspace_bytes(const Geom& g) {
     if (!dgrad_s2_supported(g)) return 0;
-    size_t b = dg2_part_offset(g);   // packed weights + store dump area
-    if (g.Cout > 64) b += (size_t)(g.Cout / 64) * g.in_voxels() * g.Cin * sizeof(float);
+    if (g.Cout > 64) return ig_workspace_bytes(g, MI3D_PASS_DGRAD);
+    size_t b = dg2_stat_offset(g);   // packed weights + store dump area
     if (g.Cout == 64) {   // partial sums and keys of the variant with the normalisation's sums
         long long units; int nwg, max_seg;
         dg2_layout(g, &units, &nwg, &max_seg);
@@ -467,6 +447,7 @@ size_t dgrad_s2_workspace_bytes(const Geom& g) {
 
 int dgrad_s2(const Geom& g, const void* dy, const void* w, void* dx, void* ws, size_t ws_bytes, hipStream_t s) {
     if (ws_bytes < dgrad_s2_workspace_bytes(g)) return MI3D_ERR_WORKSPACE;
+    if (g.Cout > 64) return ig_conv(g, MI3D_PASS_DGRAD, dy, w, dx, ws, ws_bytes, s);
     const long long total = g.w_elems();
     const int KK = g.Cout == 32 ? 2 : 4;
     dgrad_s2_pack_kernel<<<(unsigned)((total + 255) / 256), 256, 0, s>>>((const uint16_t*)w, (uint16_t*)ws, g.Cin, g.Cout, KK);
@@ -475,7 +456,6 @@ int dgrad_s2(const Geom& g, const void* dy, const void* w, void* dx, void* ws, s
     Dg2Params G;
     G.dy = (const uint16_t*)dy; G.wpack = (const uint16_t*)ws; G.dx = (uint16_t*)dx;
     G.dump = (uint16_t*)((char*)ws + (((size_t)g.w_elems() * 2 + 255) & ~(size_t)255));
-    G.part = (float*)((char*)ws + dg2_part_offset(g));
     G.add = (const uint16_t*)g.add; G.ref = (const uint16_t*)g.ref; G.slope = g.slope;
     // a factor of 1 on both sides of the sign test needs no sign: the store path then reads the added tensor a second
     // time (from the cache) instead of streaming a third tensor of dx's size from memory
@@ -486,7 +466,7 @@ int dgrad_s2(const Geom& g, const void* dy, const void* w, void* dx, void* ws, s
         G.ref = (const uint16_t*)g.ref; G.slope = 1.f; G.stat_slope = g.slope;
         long long units; int n2;
         dg2_layout(g, &units, &n2, &G.max_seg);
-        G.stat_part = (float*)((char*)ws + dg2_part_offset(g));
+        G.stat_part = (float*)((char*)ws + dg2_stat_offset(g));
         G.stat_key = (int*)(G.stat_part + (size_t)n2 * G.max_seg * 4 * 64);
     }
     G.N = g.N; G.D = g.D; G.H = g.H; G.W = g.W; G.Cin = g.Cin; G.Cout = g.Cout;
@@ -495,8 +475,7 @@ int dgrad_s2(const Geom& g, const void* dy, const void* w, void* dx, void* ws, s
     G.HT = ((g.H + 1) / 2 + RP - 1) / RP;
     G.WT = ((g.W + 1) / 2 + CP - 1) / CP;
     G.CiT = g.Cin / 32;
-    G.NCO = g.Cout / (16 * KK);
-    G.units = (long long)g.N * G.CiT * G.NCO * G.HT * G.WT * G.QD;
+    G.units = (long long)g.N * G.CiT * G.HT * G.WT * G.QD;
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     const long long nwg = cus < G.units ? cus : G.units;
@@ -505,42 +484,31 @@ int dgrad_s2(const Geom& g, const void* dy, const void* w, void* dx, void* ws, s
     static std::atomic<bool> attr_set{false};   // set once per process; a second thread racing here repeats an idempotent call
     if (!attr_set) {
         const int max_lds = 27 * 4 * 1024 + 2 * 8 * SLABV * 16;
-        const void* fns[10] = {(const void*)dgrad_s2_kernel<0, 2, false>, (const void*)dgrad_s2_kernel<1, 2, false>,
-                               (const void*)dgrad_s2_kernel<0, 4, false>, (const void*)dgrad_s2_kernel<1, 4, false>,
-                               (const void*)dgrad_s2_kernel<0, 4, true>, (const void*)dgrad_s2_kernel<1, 4, true>,
-                               (const void*)dgrad_s2_kernel<0, 4, false, 1>, (const void*)dgrad_s2_kernel<1, 4, false, 1>,
-                               (const void*)dgrad_s2_kernel<0, 4, false, 2>, (const void*)dgrad_s2_kernel<1, 4, false, 2>};
+        const void* fns[8] = {(const void*)dgrad_s2_kernel<0, 2>, (const void*)dgrad_s2_kernel<1, 2>,
+                               (const void*)dgrad_s2_kernel<0, 4>, (const void*)dgrad_s2_kernel<1, 4>,
+                               (const void*)dgrad_s2_kernel<0, 4, 1>, (const void*)dgrad_s2_kernel<1, 4, 1>,
+                               (const void*)dgrad_s2_kernel<0, 4, 2>, (const void*)dgrad_s2_kernel<1, 4, 2>};
         for (const void* f : fns) {
             hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, max_lds);
             if (e != hipSuccess) { note_hip_error(e); return MI3D_ERR_HIP; }
         }
         attr_set = true;
     }
-    const bool part = G.NCO > 1;
-    const bool fuse = g.add && !part;    // (Cout == 64: the only unchunked shape with an added gradient)
+    const bool fuse = g.add;    // (Cout == 64)
     if (g.add && !dgrad_s2_fuses_skip(g)) return MI3D_ERR_UNSUPPORTED;
     if (sums) {
-        if (g.pD == 0) dgrad_s2_kernel<0, 4, false, 2><<<(unsigned)nwg, 256, lds, s>>>(G);
-        else dgrad_s2_kernel<1, 4, false, 2><<<(unsigned)nwg, 256, lds, s>>>(G);
+        if (g.pD == 0) dgrad_s2_kernel<0, 4, 2><<<(unsigned)nwg, 256, lds, s>>>(G);
+        else dgrad_s2_kernel<1, 4, 2><<<(unsigned)nwg, 256, lds, s>>>(G);
         st = check_launch();
         if (st) return st;
         return sp_stats_finish(G.stat_part, G.stat_key, g.Cin, G.CiT, g.N, G.nwg, G.max_seg, 1.0 / ((double)g.D * g.H * g.W), 0.f, 1, g.stats, s);
     }
-    if (fuse && g.pD == 0) dgrad_s2_kernel<0, 4, false, 1><<<(unsigned)nwg, 256, lds, s>>>(G);
-    else if (fuse) dgrad_s2_kernel<1, 4, false, 1><<<(unsigned)nwg, 256, lds, s>>>(G);
-    else if (part && g.pD == 0) dgrad_s2_kernel<0, 4, true><<<(unsigned)nwg, 256, lds, s>>>(G);
-    else if (part) dgrad_s2_kernel<1, 4, true><<<(unsigned)nwg, 256, lds, s>>>(G);
-    else if (g.pD == 0 && KK == 2) dgrad_s2_kernel<0, 2, false><<<(unsigned)nwg, 256, lds, s>>>(G);
-    else if (g.pD == 0) dgrad_s2_kernel<0, 4, false><<<(unsigned)nwg, 256, lds, s>>>(G);
-    else if (KK == 2) dgrad_s2_kernel<1, 2, false><<<(unsigned)nwg, 256, lds, s>>>(G);
-    else dgrad_s2_kernel<1, 4, false><<<(unsigned)nwg, 256, lds, s>>>(G);
-    st = check_launch();
-    if (st || !part) return st;
-    const long long n = (long long)g.in_voxels() * g.Cin;
-    long long blocks = (n / 8 + 255) / 256;
-    if (blocks > 8192) blocks = 8192;
-    sum_chunks_bf16_kernel<<<(unsigned)blocks, 256, 0, s>>>(G.part, (uint16_t*)dx, n / 8, n, G.NCO, g.slope, (const uint16_t*)g.ref, nullptr, 0,
-                                                            (const uint16_t*)g.add);
+    if (fuse && g.pD == 0) dgrad_s2_kernel<0, 4, 1><<<(unsigned)nwg, 256, lds, s>>>(G);
+    else if (fuse) dgrad_s2_kernel<1, 4, 1><<<(unsigned)nwg, 256, lds, s>>>(G);
+    else if (g.pD == 0 && KK == 2) dgrad_s2_kernel<0, 2><<<(unsigned)nwg, 256, lds, s>>>(G);
+    else if (g.pD == 0) dgrad_s2_kernel<0, 4><<<(unsigned)nwg, 256, lds, s>>>(G);
+    else if (KK == 2) dgrad_s2_kernel<1, 2><<<(unsigned)nwg, 256, lds, s>>>(G);
+    else dgrad_s2_kernel<1, 4><<<(unsigned)nwg, 256, lds, s>>>(G);
     return check_launch();
 }
 

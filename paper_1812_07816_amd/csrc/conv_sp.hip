@@ -64,8 +64,6 @@ struct SpParams {
     const uint16_t* wpack;  // [cout tile][cin chunk][kw][kd][kh][k16][lane][8]
     uint16_t* y;
     uint16_t* dump;         // 8 KB that masked store lanes write to instead of y
-    float* part;            // [cin chunk][voxel][Cout] fp32 partial outputs (chunked variant)
-    int NCH;                // cin chunks of the chunked variant
     float slope;            // LeakyReLU slope applied to the output (1 = none); with ref: the factor where ref <= 0
     const uint16_t* ref;    // MASK variant: tensor of the output's shape whose sign selects the factor 1 or slope
     int N, D, H, W, Cin, Cout, Do, Ho, Wo, pD, pH, pW;
@@ -133,7 +131,6 @@ __device__ __forceinline__ void group_mfma(f32x16 (&acc)[3][RH], const XFrag& x,
 }
 
 __device__ __forceinline__ void convert_rows(const f32x16 (&a)[RH], uint32_t (&o)[RH][8], float slope);
-__device__ __forceinline__ void convert_rows(const f32x16 (&a)[RH], float (&o)[RH][16], float slope);
 
 #define SP_FENCE() __builtin_amdgcn_sched_barrier(0)
 
@@ -201,21 +198,6 @@ __device__ __forceinline__ void convert_rows(const f32x16 (&a)[RH], uint32_t (&o
         }
 }
 
-// chunked variant: the fp32 accumulators are kept as they are (the activation follows the sum of the chunks)
-__device__ __forceinline__ void convert_rows(const f32x16 (&a)[RH], float (&o)[RH][16], float) {
-#pragma unroll
-    for (int r = 0; r < RH; ++r)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) o[r][i] = a[r][i];
-}
-
-// fp32 partial row: accumulator register i of lane (voxel n, half h) is cout 8 (i / 4) + 4 h + i % 4
-__device__ __forceinline__ void store_row(const float (&o)[16], float* p, bool ok, float* dump) {
-    float* q = ok ? p : dump;
-#pragma unroll
-    for (int g4 = 0; g4 < 4; ++g4) *(float4*)(q + 8 * g4) = float4{o[4 * g4], o[4 * g4 + 1], o[4 * g4 + 2], o[4 * g4 + 3]};
-}
-
 // Lanes l and l+32 hold the two interleaved halves of a voxel's 32 couts
 // (4 couts of every group of 8).  Swapping between the lane halves gives each
 // lane 16 consecutive couts, stored as two 16-byte pieces.
@@ -278,21 +260,18 @@ __device__ __forceinline__ void store_row(const uint32_t (&o)[8], uint16_t* p, b
 // kw = k are computed, the slot of kw = k + 2 (mod 3) is refilled from L2 with
 // the block it needs next, two phases ahead of its use, at the price of a
 // barrier per phase and 54 KB of extra L2 traffic per stage.
-// PART (with NC = 1): the 32-channel chunks of Cin are separate work units whose weights (54 KB) stay resident; each
-// writes fp32 partial outputs and a second kernel adds the chunks in index order.  For the deep, small layers this is
-// two to three times faster than streaming the weights of all chunks through LDS for every staged plane.
-// STATS = 1 (forward, not with PART or MASK): the kernel also adds up y and y^2 per output channel (of the bf16 values it
+// STATS = 1 (forward, not with MASK): the kernel also adds up y and y^2 per output channel (of the bf16 values it
 // stores) for the instance normalisation that follows the convolution (Section 4.1).  Every lane keeps the sums of its
 // 16 couts over the rows and planes of a segment; at the end of the segment they are added over the 32 voxel lanes in
 // a fixed butterfly and written as one partial per (workgroup, segment, wave).  A second kernel adds the partials of a
 // (sample, channel) in index order in double.
-// STATS = 2 (data gradient, not with PART or MASK): the same machinery adds up the two sums the backward pass of the
+// STATS = 2 (data gradient, not with MASK): the same machinery adds up the two sums the backward pass of the
 // instance normalisation of the layer below needs: with a = P.ref (that layer's activated output), g = dx * lrelu'(a)
 // and xhat = lrelu^-1(a), the sums of g and of g * xhat per channel.  dx itself is stored unchanged.
-// MASK (data gradient, not with PART): every output element is multiplied by 1 where P.ref is > 0 and by P.slope
+// MASK (data gradient): every output element is multiplied by 1 where P.ref is > 0 and by P.slope
 // elsewhere (LeakyReLU derivative of the layer below) after its rounding to bf16 and rounded again: the bits of the
 // plain kernel followed by an elementwise pass, without that pass's read and write of the gradient.
-template <int NC, bool PART = false, bool MASK = false, int STATS = 0>
+template <int NC, bool MASK = false, int STATS = 0>
 __global__ void __launch_bounds__(NT, NW / 4) sp_conv_kernel(SpParams P) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     constexpr bool STREAM = NC == 0;
@@ -351,19 +330,17 @@ __global__ void __launch_bounds__(NT, NW / 4) sp_conv_kernel(SpParams P) {
         const int lcol = paired ? (lane & 15) + ((lane & 16) ? HALF : 0) : (lane & 31);
         const int lrow = paired && (lane & 16) ? TH : 0;
         const int lane_in_off = ((lane >> 5) * NV + wave * RH * COLS + lcol) * 16;
-        const int chunk0 = PART ? (int)(column % P.NCH) : 0;   // chunked variant: this unit's cin chunk
-        if (PART) column /= P.NCH;
         int ct = (int)(column % P.CT);
         int n = (int)(column / P.CT);
         const int h0 = ht * TH, w0 = wt * TW;
 
-        // packed weights of this cout tile (chunked variant: of this cin chunk of it)
-        const char* wct = (const char*)P.wpack + ((long long)ct * (PART ? P.NCH : nc) + chunk0) * W_BYTES;
+        // packed weights of this cout tile
+        const char* wct = (const char*)P.wpack + (long long)ct * nc * W_BYTES;
         if (STREAM) {  // slots kw = 0, 1 of chunk 0; slot 2 follows during the first phase
             for (int i = t; i < 2 * WPIECES; i += NT) ((uint4*)w_lds)[i] = ((const uint4*)wct)[i];
-        } else if (ct * (PART ? P.NCH : 1) + chunk0 != cur_ct) {  // (re)load the weights; previous readers passed a barrier
+        } else if (ct != cur_ct) {  // (re)load the weights; previous readers passed a barrier
             for (int i = t; i < NC * W_BYTES / 16; i += NT) ((uint4*)w_lds)[i] = ((const uint4*)wct)[i];
-            cur_ct = ct * (PART ? P.NCH : 1) + chunk0;
+            cur_ct = ct;
         }
         // (vector type and no pointer table: with a struct type or an indexed table of sources the pieces were kept
         // in scratch memory, whose loads and stores share the counter of the global loads)
@@ -405,7 +382,6 @@ __global__ void __launch_bounds__(NT, NW / 4) sp_conv_kernel(SpParams P) {
         const uint16_t* xn2 = P.x2 + (long long)n * P.D * plane_elems;
         const int ct_local = ct >= P.ysplit ? ct - P.ysplit : ct;
         uint16_t* yn = (ct >= P.ysplit ? P.y2 : P.y) + (long long)n * P.Do * P.Ho * P.Wo * P.ypitch;
-        const int opitch = PART ? P.Cout : P.ypitch;   // the fp32 partial outputs are dense
         const int nJ = od_end - od_start + 2;
         uint4 pre[DMA ? 1 : NLOAD];
 
@@ -417,7 +393,6 @@ __global__ void __launch_bounds__(NT, NW / 4) sp_conv_kernel(SpParams P) {
         __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)xn, 0, 0, 0x00020000);
         auto begin_stage = [&](int ip, int chunk) {
             const bool inside = ip >= 0 && ip < P.D;
-            chunk += chunk0;
             const bool high = chunk >= P.xsplit;
             if (high) chunk -= P.xsplit;
             pre_base = (high ? xn2 : xn) + (long long)(inside ? ip : 0) * plane_elems + chunk * 32;
@@ -450,12 +425,11 @@ __global__ void __launch_bounds__(NT, NW / 4) sp_conv_kernel(SpParams P) {
             }
         };
         // finished rows wait in outp[] and are stored during the next stage
-        typename std::conditional<PART, float[RH][16], uint32_t[RH][8]>::type outp;
+        uint32_t outp[RH][8];
         long long st_off = 0;     // element offset of row 0 of the pending plane for this lane (before the lane half)
-        float* partn = PART ? P.part + ((long long)chunk0 * P.N + n) * P.Do * P.Ho * P.Wo * P.Cout : nullptr;
         bool st_pending = false;
         const int ow_ = w0 + (paired ? (lane & 15) : (lane & 31));
-        const long long row_pitch = (long long)P.Wo * opitch;
+        const long long row_pitch = (long long)P.Wo * P.ypitch;
         uint4 mk[REF ? RH : 1][2];   // the pieces of ref at the addresses of the pending stores
         const uint16_t* refn = REF ? P.ref + (long long)n * P.Do * P.Ho * P.Wo * P.Cout : nullptr;
         auto load_mask = [&](int r) {     // unconditional, like the stores: masked lanes read the dump area
@@ -482,9 +456,8 @@ __global__ void __launch_bounds__(NT, NW / 4) sp_conv_kernel(SpParams P) {
                     st1[2 * i + 1] += hi; st2[2 * i + 1] = fmaf(hi, hi, st2[2 * i + 1]);
                 }
             }
-            if constexpr (PART) store_row(outp[r], partn + st_off + r * row_pitch + 4 * (lane >> 5), ok, (float*)P.dump + lane * 32);
-            else store_row<MASK, STATS == 2>(outp[r], yn + st_off + r * row_pitch + 16 * (lane >> 5), ok, P.dump + lane * 16, mk[REF ? r : 0], P.slope,
-                                             st1, st2, P.stat_slope, st_pending);
+            store_row<MASK, STATS == 2>(outp[r], yn + st_off + r * row_pitch + 16 * (lane >> 5), ok, P.dump + lane * 16, mk[REF ? r : 0], P.slope,
+                                        st1, st2, P.stat_slope, st_pending);
         };
 
         // every segment starts from cleared accumulators (keeps them dead across segments)
@@ -542,7 +515,7 @@ __global__ void __launch_bounds__(NT, NW / 4) sp_conv_kernel(SpParams P) {
             write_stage(NBUF == 2 ? ((sq + 1) & 1) : 0);                                        \
             if (LAST) {                                                                         \
                 st_pending = jj >= 2;                                                           \
-                st_off = (((long long)(j_ - 2) * P.Ho + h0 + lrow + wave * RH) * P.Wo + ow_) * opitch + (PART ? ct : ct_local) * 32;  \
+                st_off = (((long long)(j_ - 2) * P.Ho + h0 + lrow + wave * RH) * P.Wo + ow_) * P.ypitch + ct_local * 32;            \
             }                                                                                   \
             ++sq;                                                                               \
             /* the loads into the next stage are complete; the 2 RH stores issued after them may still fly */ \
@@ -691,12 +664,12 @@ static int sp_cu_count() {
     return cus;
 }
 
-// Chunked variant (32-channel chunks of the contracted channels as work units, resident weights, fp32 partial
-// outputs): used when the convolution contracts at least 96 channels and has fewer (cout tile, patch, plane) units
-// than two per CU, i.e. on the smallest volumes, where whole-Cin units leave most of the chip idle.  Measured at
-// N = 1 (chunked / streamed weights): 320->320 at 12^3 0.082 / 0.091 ms, 256->256 at 24^3 0.120 / 0.116,
-// 512->256 at 24^3 0.207 / 0.219; with more units the streamed weights win (256->128 at 48^3 0.38 / 0.28).
-static bool sp_use_chunks(const Geom& g, int pass) {
+// Volumes with fewer (cout tile, patch, plane) units than two per CU, for layers that contract at least 96 channels:
+// units of whole planes leave CUs idle, and patches cover small planes badly.  The implicit GEMM of conv_ig.hip takes
+// them.  Forward / data gradient, this kernel's former 32-channel chunks of work -> implicit GEMM (us): 320->320 at 12^3
+// 74 / 74 -> 32 / 37, 256->256 at 16^3 66 / 66 -> 35 / 38, 256->256 at 24^3 101 / 101 -> 69 / 72, 512->256 at 24^3 forward
+// 180 -> 117; with more units it is no faster than this kernel (256->256 at 24^3, N = 2: 144 / 144 with either).
+bool few_units(const Geom& g, int pass) {
     const bool flip = pass == MI3D_PASS_DGRAD;
     const int cin = flip ? g.Cout : g.Cin, cout = flip ? g.Cin : g.Cout;
     const int Do = flip ? g.D : g.Do, Ho = flip ? g.H : g.Ho, Wo = flip ? g.W : g.Wo;
@@ -705,10 +678,9 @@ static bool sp_use_chunks(const Geom& g, int pass) {
     return cin >= 96 && units < 2ll * sp_cu_count();
 }
 
-
 static size_t sp_part_offset(const Geom& g) { return (((size_t)g.w_elems() * 2 + 255) & ~(size_t)255) + 8192; }
 
-// STATS variants (unchunked): workgroups, most segments of a workgroup's unit range, bytes of the partial sums
+// STATS variants: workgroups, most segments of a workgroup's unit range, bytes of the partial sums
 static void sp_stat_layout(const Geom& g, int pass, long long* units, int* nwg, int* max_seg) {
     const bool flip = pass == MI3D_PASS_DGRAD;
     const int cout = flip ? g.Cin : g.Cout, Do = flip ? g.D : g.Do, Ho = flip ? g.H : g.Ho, Wo = flip ? g.W : g.Wo;
@@ -725,21 +697,10 @@ static size_t sp_stat_bytes(const Geom& g, int pass) {
     sp_stat_layout(g, pass, &units, &nwg, &max_seg);
     return (size_t)nwg * max_seg * (NW * 64 * sizeof(float) + sizeof(int)) + 256;
 }
-bool fuses_stats(const Geom& g) { return supported(g, MI3D_PASS_FWD) && !sp_use_chunks(g, MI3D_PASS_FWD); }
-// the data gradient that also delivers the sums of the instance-normalisation backward pass of the layer below
-bool fuses_bwd_sums(const Geom& g) { return supported(g, MI3D_PASS_DGRAD) && !sp_use_chunks(g, MI3D_PASS_DGRAD); }
 
 size_t workspace_bytes(const Geom& g, int pass) {
     if (!supported(g, pass)) return 0;
-    size_t b = sp_part_offset(g);  // packed weights + store dump area
-    if (sp_use_chunks(g, pass)) {
-        const int cin = pass == MI3D_PASS_DGRAD ? g.Cout : g.Cin;
-        const size_t out_elems = pass == MI3D_PASS_DGRAD ? (size_t)g.in_voxels() * g.Cin : (size_t)g.out_voxels() * g.Cout;
-        b += (size_t)(cin / 32) * out_elems * sizeof(float);
-    } else {
-        b += sp_stat_bytes(g, pass);   // partial sums of the STATS variants
-    }
-    return b;
+    return sp_part_offset(g) + sp_stat_bytes(g, pass);   // packed weights, store dump area, partial sums of the STATS variants
 }
 
 // in: activations read (x for fwd, dy for dgrad); out: y or dx
@@ -755,7 +716,6 @@ int conv(const Geom& g, int pass, const void* in, const void* w, void* out, void
     P.wpack = (const uint16_t*)ws;
     P.y = (uint16_t*)out;
     P.dump = (uint16_t*)((char*)ws + (((size_t)g.w_elems() * 2 + 255) & ~(size_t)255));
-    P.part = (float*)((char*)ws + sp_part_offset(g));
     P.N = g.N;
     if (!flip) {
         P.D = g.D; P.H = g.H; P.W = g.W; P.Cin = g.Cin; P.Cout = g.Cout;
@@ -774,21 +734,18 @@ int conv(const Geom& g, int pass, const void* in, const void* w, void* out, void
         if (!flip) { P.x2 = (const uint16_t*)g.hi; P.xpitch = g.Cin / 2; P.xsplit = g.Cin / 64; }
         else { P.y2 = (uint16_t*)g.hi; P.ypitch = g.Cin / 2; P.ysplit = g.Cin / 64; }
     }
-    const bool chunks = sp_use_chunks(g, pass);
-    P.NCH = chunks ? P.Cin / 32 : 1;
     const bool bstat = pass == MI3D_PASS_DGRAD && g.stats;   // sums for the normalisation below; dx itself stays unmasked
-    if (bstat && (chunks || !g.ref || g.hi || !(g.slope > 0.f))) return MI3D_ERR_UNSUPPORTED;
-    const bool mask = pass == MI3D_PASS_DGRAD && g.ref && g.slope != 1.f && !chunks && !bstat;
+    if (bstat && (!g.ref || g.hi || !(g.slope > 0.f))) return MI3D_ERR_UNSUPPORTED;
+    const bool mask = pass == MI3D_PASS_DGRAD && g.ref && g.slope != 1.f && !bstat;
     P.slope = (pass == MI3D_PASS_FWD || mask) ? g.slope : 1.f;
     P.ref = mask || bstat ? (const uint16_t*)g.ref : nullptr;
     P.stat_slope = bstat ? g.slope : 1.f;
-    P.units = (long long)P.N * P.CT * P.NCH * sp_plane_tiles(P.Ho, P.Wo, &P.WTF, &P.HTP) * P.Do;
+    P.units = (long long)P.N * P.CT * sp_plane_tiles(P.Ho, P.Wo, &P.WTF, &P.HTP) * P.Do;
     long long nwg = sp_cu_count();
     if (nwg > P.units) nwg = P.units;
     P.nwg = (int)nwg;
     const bool stat = pass == MI3D_PASS_FWD && g.stats;
-    if (stat && chunks) return MI3D_ERR_UNSUPPORTED;
-    P.stat_part = P.part;   // same place in the workspace as the chunked variant's partial outputs
+    P.stat_part = (float*)((char*)ws + sp_part_offset(g));
     P.max_seg = 1;
     P.stat_key = nullptr;
     if (stat || bstat) {
@@ -804,45 +761,33 @@ int conv(const Geom& g, int pass, const void* in, const void* w, void* out, void
         if (e == hipSuccess) e = hipFuncSetAttribute((const void*)sp_conv_kernel<2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds2);
         if (e == hipSuccess) e = hipFuncSetAttribute((const void*)sp_conv_kernel<0>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds1);
         if (e == hipSuccess) e = hipFuncSetAttribute((const void*)sp_conv_kernel<1, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds1);
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)sp_conv_kernel<1, false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds1);
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)sp_conv_kernel<2, false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds2);
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)sp_conv_kernel<0, false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds1);
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)sp_conv_kernel<1, false, false, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds1);
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)sp_conv_kernel<2, false, false, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds2);
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)sp_conv_kernel<0, false, false, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds1);
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)sp_conv_kernel<1, false, false, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds1);
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)sp_conv_kernel<2, false, false, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds2);
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)sp_conv_kernel<0, false, false, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds1);
+        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)sp_conv_kernel<2, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds2);
+        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)sp_conv_kernel<0, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds1);
+        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)sp_conv_kernel<1, false, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds1);
+        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)sp_conv_kernel<2, false, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds2);
+        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)sp_conv_kernel<0, false, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds1);
+        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)sp_conv_kernel<1, false, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds1);
+        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)sp_conv_kernel<2, false, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds2);
+        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)sp_conv_kernel<0, false, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds1);
         if (e != hipSuccess) { note_hip_error(e); return MI3D_ERR_HIP; }
         attr_set = true;
     }
-    if (chunks) {
-        sp_conv_kernel<1, true><<<(unsigned)nwg, NT, lds1, s>>>(P);
-        st = check_launch();
-        if (st) return st;
-        const long long n = (long long)P.N * P.Do * P.Ho * P.Wo * P.Cout;   // a multiple of 32
-        long long blocks = (n / 8 + 255) / 256;
-        if (blocks > 8192) blocks = 8192;
-        sum_chunks_bf16_kernel<<<(unsigned)blocks, 256, 0, s>>>(P.part, (uint16_t*)out, n / 8, n, P.NCH, g.slope, pass == MI3D_PASS_DGRAD ? (const uint16_t*)g.ref : nullptr,
-                                                                flip && g.hi ? (uint16_t*)g.hi : nullptr, P.Cout, nullptr);
-        return check_launch();
-    }
     if (stat || bstat) {
-        if (stat && nc == 1) sp_conv_kernel<1, false, false, 1><<<(unsigned)nwg, NT, lds1, s>>>(P);
-        else if (stat && nc == 2) sp_conv_kernel<2, false, false, 1><<<(unsigned)nwg, NT, lds2, s>>>(P);
-        else if (stat) sp_conv_kernel<0, false, false, 1><<<(unsigned)nwg, NT, lds1, s>>>(P);
-        else if (nc == 1) sp_conv_kernel<1, false, false, 2><<<(unsigned)nwg, NT, lds1, s>>>(P);
-        else if (nc == 2) sp_conv_kernel<2, false, false, 2><<<(unsigned)nwg, NT, lds2, s>>>(P);
-        else sp_conv_kernel<0, false, false, 2><<<(unsigned)nwg, NT, lds1, s>>>(P);
+        if (stat && nc == 1) sp_conv_kernel<1, false, 1><<<(unsigned)nwg, NT, lds1, s>>>(P);
+        else if (stat && nc == 2) sp_conv_kernel<2, false, 1><<<(unsigned)nwg, NT, lds2, s>>>(P);
+        else if (stat) sp_conv_kernel<0, false, 1><<<(unsigned)nwg, NT, lds1, s>>>(P);
+        else if (nc == 1) sp_conv_kernel<1, false, 2><<<(unsigned)nwg, NT, lds1, s>>>(P);
+        else if (nc == 2) sp_conv_kernel<2, false, 2><<<(unsigned)nwg, NT, lds2, s>>>(P);
+        else sp_conv_kernel<0, false, 2><<<(unsigned)nwg, NT, lds1, s>>>(P);
         st = check_launch();
         if (st) return st;
         sp_stats_finish_kernel<<<P.N * P.CT, 64 * FIN_SLICES, 0, s>>>(P.stat_part, P.stat_key, P.Cout, P.CT, P.nwg, P.max_seg,
                                                           1.0 / ((double)P.Do * P.Ho * P.Wo), g.stats_eps, bstat ? 1 : 0, g.stats);
         return check_launch();
     }
-    if (mask && nc == 1) sp_conv_kernel<1, false, true><<<(unsigned)nwg, NT, lds1, s>>>(P);
-    else if (mask && nc == 2) sp_conv_kernel<2, false, true><<<(unsigned)nwg, NT, lds2, s>>>(P);
-    else if (mask) sp_conv_kernel<0, false, true><<<(unsigned)nwg, NT, lds1, s>>>(P);
+    if (mask && nc == 1) sp_conv_kernel<1, true><<<(unsigned)nwg, NT, lds1, s>>>(P);
+    else if (mask && nc == 2) sp_conv_kernel<2, true><<<(unsigned)nwg, NT, lds2, s>>>(P);
+    else if (mask) sp_conv_kernel<0, true><<<(unsigned)nwg, NT, lds1, s>>>(P);
     else if (nc == 1) sp_conv_kernel<1><<<(unsigned)nwg, NT, lds1, s>>>(P);
     else if (nc == 2) sp_conv_kernel<2><<<(unsigned)nwg, NT, lds2, s>>>(P);
     else sp_conv_kernel<0><<<(unsigned)nwg, NT, lds1, s>>>(P);
@@ -855,8 +800,7 @@ int conv(const Geom& g, int pass, const void* in, const void* w, void* out, void
 namespace th12 {
 size_t workspace_bytes(const Geom& g, int pass);
 int conv(const Geom& g, int pass, const void* in, const void* w, void* out, void* ws, size_t ws_bytes, hipStream_t s);
-bool fuses_stats(const Geom& g);
-bool fuses_bwd_sums(const Geom& g);
+bool few_units(const Geom& g, int pass);
 }  // namespace th12
 
 // 12-row patches where they cover the output plane with fewer rows than 16-row patches do (heights 12, 24, 36, ...),
@@ -888,16 +832,21 @@ int sp_stats_finish(const float* part, const int* key, int Cout, int CT, int N, 
 }
 
 bool sp_supported(const Geom& g, int pass) { return th16::supported(g, pass); }
-// the chunked variant applies the optional derivative factor of the geometry while it sums the chunks, the other
-// variants do in their store path
 bool sp_fuses_dgrad_factor(const Geom& g) { return th16::supported(g, MI3D_PASS_DGRAD); }
-bool sp_fuses_stats(const Geom& g) { return sp_rows12(g, MI3D_PASS_FWD) ? th12::fuses_stats(g) : th16::fuses_stats(g); }
-bool sp_fuses_bwd_sums(const Geom& g) { return sp_rows12(g, MI3D_PASS_DGRAD) ? th12::fuses_bwd_sums(g) : th16::fuses_bwd_sums(g); }
+// volumes too small for whole planes as units of work
+static bool sp_small(const Geom& g, int pass) {
+    return (sp_rows12(g, pass) ? th12::few_units(g, pass) : th16::few_units(g, pass)) && ig_supported(g, pass);
+}
+bool sp_fuses_stats(const Geom& g) { return th16::supported(g, MI3D_PASS_FWD) && !sp_small(g, MI3D_PASS_FWD); }
+// the data gradient that also delivers the sums of the instance-normalisation backward pass of the layer below
+bool sp_fuses_bwd_sums(const Geom& g) { return th16::supported(g, MI3D_PASS_DGRAD) && !sp_small(g, MI3D_PASS_DGRAD); }
 size_t sp_workspace_bytes(const Geom& g, int pass) {
     if (!th16::supported(g, pass)) return 0;
+    if (sp_small(g, pass)) return ig_workspace_bytes(g, pass);
     return sp_rows12(g, pass) ? th12::workspace_bytes(g, pass) : th16::workspace_bytes(g, pass);
 }
 int sp_conv(const Geom& g, int pass, const void* in, const void* w, void* out, void* ws, size_t ws_bytes, hipStream_t s) {
+    if (sp_small(g, pass)) return ig_conv(g, pass, in, w, out, ws, ws_bytes, s);
     return sp_rows12(g, pass) ? th12::conv(g, pass, in, w, out, ws, ws_bytes, s) : th16::conv(g, pass, in, w, out, ws, ws_bytes, s);
 }
 #endif

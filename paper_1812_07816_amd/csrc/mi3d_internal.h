@@ -69,13 +69,6 @@ size_t direct_workspace_bytes(const Geom& g, int pass);
 int direct_fwd(const Geom& g, const void* x, const void* w, void* y, hipStream_t s);
 int direct_dgrad(const Geom& g, const void* dy, const void* w, void* dx, hipStream_t s);
 int direct_wgrad(const Geom& g, const void* x, const void* dy, float* dw, void* ws, size_t ws_bytes, hipStream_t s);
-// y[i] = bf16(act(sum_c part[c * n + i])), chunks added in index order; n8 = n / 8 outputs of 8; act = LeakyReLU with
-// `slope` (ref null) or the factor (ref[i] > 0 ? 1 : slope).  y_hi non-null: the output, `cout` channels per voxel, is
-// written as two tensors of cout / 2 channels per voxel (y the low half, y_hi the high half); cout / 2 % 8 == 0.
-// add non-null (with ref): the sum is rounded to bf16, add[i] is added and the factor applied, then rounded again.
-__global__ void sum_chunks_bf16_kernel(const float* __restrict__ part, uint16_t* __restrict__ y, long long n8, long long n, int nch,
-                                       float slope, const uint16_t* __restrict__ ref, uint16_t* __restrict__ y_hi, int cout,
-                                       const uint16_t* __restrict__ add);
 // out[i] = sum_p part[p*n + i] in a fixed order (bit-reproducible); launch with (n + 15) / 16 blocks of 256
 __global__ void reduce_partials_kernel(const float* __restrict__ part, float* __restrict__ out, long long n, int parts);
 // out[i] = sum_p part[p * n + i] in an order fixed by (n, parts); picks the kernel by the number of parts
@@ -95,6 +88,12 @@ bool dgrad_s2_fuses_skip_sums(const Geom& g);       // stride-2 data gradient wi
 bool c4_fwd_fuses_stats(const Geom& g);     // the first layer's forward kernel delivers them too
 // last step of a per-(sample, channel) reduction of two quantities: means from block sums part[n][block][2][C]
 int instnorm_finish_means(const float* part, int blocks, int C, int N, double inv_v, float* out, hipStream_t s);
+
+
+// implicit GEMM over numbered positions: bf16, 3x3x3, stride 1 and 2 (forward and data gradient), small volumes and many channels
+bool ig_supported(const Geom& g, int pass);
+size_t ig_workspace_bytes(const Geom& g, int pass);
+int ig_conv(const Geom& g, int pass, const void* in, const void* w, void* out, void* ws, size_t ws_bytes, hipStream_t s);
 
 
 // MFMA weight gradient: bf16, 3x3x3, stride 1, channels in multiples of 32

@@ -1,0 +1,48 @@
+"""The implicit GEMM for deep layers (small volumes at stride 1, many channels at stride 2) against the fp64 oracle, at
+the sizes where its tiles can go wrong: positions that end inside a tile and tiles that span samples, channel counts
+that end inside a step or a tile, extents of one, classes of the stride-2 data gradient without voxels, contractions
+split and whole, and operands in two halves that meet inside a step."""
+import pytest
+import torch
+
+from paper_1812_07816_amd import conv3d as mc
+from tests import parity
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # N, D, H, W, Cin, Cout, s, p
+    (1, 1, 1, 1, 96, 96, 1, 1),        # one voxel; 1.5 steps of channels per tap
+    (3, 2, 2, 2, 320, 320, 1, 1),      # a tile of positions spans three samples, contraction split many times
+    (2, 5, 7, 9, 160, 32, 1, 1),       # half a tile of output channels
+    (1, 6, 11, 13, 96, 224, 1, 0),     # no padding: 128-wide tiles with 3/4 of the last in use
+    (1, 4, 9, 9, 128, 192, 1, 2),      # padding 2: outputs larger than the input
+    (2, 9, 10, 11, 64, 96, 2, 1),      # stride 2, odd and even extents, 1.5 steps contracted in the data gradient's tile
+    (1, 1, 5, 1, 64, 128, 2, 1),       # extents of one: six parity classes without a voxel
+    (1, 11, 13, 12, 96, 128, 2, 0),    # stride 2 without padding: the classes' taps are the other way round
+    (1, 33, 31, 35, 64, 192, 2, 1),    # whole contractions (no partial sums)
+]
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_implicit_gemm_matches_oracle(device, case):
+    N, D, H, W, Cin, Cout, s, p = case
+    # bf16 results: one rounding (2^-9 relative) of fp32 sums of at most 8640 products
+    errs = parity.run_case(95, 600 + 10 * CASES.index(case), N, D, H, W, Cin, Cout, 3, s, p, bf16=True, full=True, passes=("fwd", "dgrad"))
+    for q, v in errs.items():
+        assert v <= parity.TOL["bf16"], (case, q, v)
+
+
+@pytest.mark.parametrize("case", [(1, 4, 6, 8, 192, 96), (2, 3, 5, 7, 320, 192)])
+def test_halves_that_meet_inside_a_step_give_the_same_bits(device, case):
+    """Halves of 96 and 160 channels: a step of 64 channels begins in one tensor and ends in the other."""
+    N, D, H, W, Cin, Cout = case
+    desc = mc.make_desc(N, D, H, W, Cin, Cout, 3, 1, 1, torch.bfloat16)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    x, w, dy = (torch.randn(shape, generator=gen, device="cuda").bfloat16() for shape in
+                ((N, D, H, W, Cin), (Cout, 3, 3, 3, Cin), (N, D, H, W, Cout)))
+    lo, hi = x[..., :Cin // 2].contiguous(), x[..., Cin // 2:].contiguous()
+    assert torch.equal(mc.conv3d_fwd_pair(desc, lo, hi, w), mc.conv3d_fwd(desc, x, w))
+    dlo, dhi = torch.empty_like(lo), torch.empty_like(hi)
+    mc.conv3d_dgrad_pair(desc, dy, w, dlo, dhi)
+    assert torch.equal(torch.cat([dlo, dhi], dim=-1), mc.conv3d_dgrad(desc, dy, w))
