@@ -577,25 +577,43 @@ __global__ void __launch_bounds__(NT, NW / 4) sp_conv_kernel(SpParams P) {
 
 // stats[n][c] = (mean, 1 / sqrt(var + eps)) of y over the voxels from the partial sums of the STATS = 1 variant, or
 // (means = 1) the plain means of the two sums of the STATS = 2 variant.  A block of 1024 threads per (sample, cout
-// tile); thread (slice s of 16, sum q, cout c) adds the partials of every sixteenth workgroup in index order in double
-// (key: which (sample, cout tile) a partial belongs to), then the sixteen slices are added in order.
-constexpr int FIN_SLICES = 16;
-__global__ void __launch_bounds__(64 * FIN_SLICES) sp_stats_finish_kernel(const float* __restrict__ part, const int* __restrict__ key, int Cout, int CT,
+// tile); the partials that belong to it (key) are listed in index order, thread (slice s of 64, four columns of the
+// 64 sums) adds every 64th row of them in double, then the slices are added in order.  Bound: latency; keys looked up
+// by all threads at once and rows of 16 bytes per thread requested four at a time took it from 12-18 us to 4-7 us.
+constexpr int FIN_SLICES = 64, FIN_WAVES = FIN_SLICES * 16 / 64;
+__global__ void __launch_bounds__(16 * FIN_SLICES) sp_stats_finish_kernel(const float* __restrict__ part, const int* __restrict__ key, int Cout, int CT,
                                                                           int nwg, int max_seg, double inv_v, float eps, int means, float* __restrict__ stats) {
-    __shared__ double red[FIN_SLICES][64];
-    const int t = threadIdx.x, sl = t >> 6, qc = t & 63;     // qc = 32 q + c
+    __shared__ double red[FIN_SLICES][65];                   // [slice][32 q + c]
+    __shared__ int list[16 * FIN_SLICES], count[FIN_WAVES];
+    const int t = threadIdx.x, sl = t >> 4, c4 = (t & 15) * 4, lane = t & 63, wave = t >> 6;
     const int mine = blockIdx.x;                             // n * CT + ct
-    double a = 0.0;
-    for (int g = sl; g < nwg; g += FIN_SLICES)
-        for (int seg = 0; seg < max_seg; ++seg)
-            if (key[g * max_seg + seg] == mine) {
-                const float* p = part + (((long long)g * max_seg + seg) * NW) * 64;
-                for (int w = 0; w < NW; ++w) a += (double)p[w * 64 + qc];
-            }
-    red[sl][qc] = a;
+    const int keys = nwg * max_seg;
+    double a[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int k0 = 0; k0 < keys; k0 += 16 * FIN_SLICES) {
+        const bool hit = k0 + t < keys && key[k0 + t] == mine;
+        const unsigned long long m = __ballot(hit);
+        if (lane == 0) count[wave] = __popcll(m);
+        __syncthreads();
+        int before = 0, n = 0;
+        for (int i = 0; i < FIN_WAVES; ++i) {
+            before += i < wave ? count[i] : 0;
+            n += count[i];
+        }
+        if (hit) list[before + __popcll(m & ((1ull << lane) - 1))] = k0 + t;
+        __syncthreads();
+#pragma unroll 4
+        for (int i = sl; i < n * NW; i += FIN_SLICES) {
+            const float4 v = *(const float4*)(part + ((long long)list[i / NW] * NW + i % NW) * 64 + c4);
+            a[0] += (double)v.x; a[1] += (double)v.y; a[2] += (double)v.z; a[3] += (double)v.w;
+        }
+        __syncthreads();   // the list is read
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) red[sl][c4 + i] = a[i];
     __syncthreads();
     if (t < 32) {
         double s1 = 0.0, s2 = 0.0;
+#pragma unroll 8
         for (int k = 0; k < FIN_SLICES; ++k) { s1 += red[k][t]; s2 += red[k][32 + t]; }
         const double mean = s1 * inv_v;
         double var = s2 * inv_v - mean * mean;
@@ -781,7 +799,7 @@ int conv(const Geom& g, int pass, const void* in, const void* w, void* out, void
         else sp_conv_kernel<0, false, 2><<<(unsigned)nwg, NT, lds1, s>>>(P);
         st = check_launch();
         if (st) return st;
-        sp_stats_finish_kernel<<<P.N * P.CT, 64 * FIN_SLICES, 0, s>>>(P.stat_part, P.stat_key, P.Cout, P.CT, P.nwg, P.max_seg,
+        sp_stats_finish_kernel<<<P.N * P.CT, 16 * FIN_SLICES, 0, s>>>(P.stat_part, P.stat_key, P.Cout, P.CT, P.nwg, P.max_seg,
                                                           1.0 / ((double)P.Do * P.Ho * P.Wo), g.stats_eps, bstat ? 1 : 0, g.stats);
         return check_launch();
     }
@@ -827,7 +845,7 @@ static bool sp_rows12(const Geom& g, int pass) {
 // kernel has written in the STATS layout (four waves per workgroup): [workgroup][segment][wave][sum, sum of squares][32 couts], key = sample * CT + cout tile
 int sp_stats_finish(const float* part, const int* key, int Cout, int CT, int N, int nwg, int max_seg, double inv_v, float eps, int means,
                     float* stats, hipStream_t s) {
-    th16::sp_stats_finish_kernel<<<N * CT, 64 * th16::FIN_SLICES, 0, s>>>(part, key, Cout, CT, nwg, max_seg, inv_v, eps, means, stats);
+    th16::sp_stats_finish_kernel<<<N * CT, 16 * th16::FIN_SLICES, 0, s>>>(part, key, Cout, CT, nwg, max_seg, inv_v, eps, means, stats);
     return check_launch();
 }
 

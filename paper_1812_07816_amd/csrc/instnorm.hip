@@ -125,28 +125,34 @@ __global__ void __launch_bounds__(256) in_reduce_kernel(const T* __restrict__ a,
 }
 
 // MODE 0: stats[n][c] = (mean, rstd) from the block sums of (z, z^2).  MODE 1: stats2[n][c] = (mean g, mean g xhat).
-// A workgroup serves 16 (n, c) pairs; thread (slice s, pair i) adds blocks s, s + 16, ... in double and the 16 slice
-// sums are added in order (bit-reproducible).
+// A workgroup serves 16 (n, c) pairs; thread (slice s, pair i) adds blocks s, s + 64, ... in double and the 64 slice
+// sums are added in order (bit-reproducible).  Bound: the latency of the chain of loads, a dozen such launches per level and
+// step; with 64 slices and the loads of four blocks requested before their sum 512 blocks take two trips to memory
+// instead of 32 (12 -> 5 us).
+constexpr int FIN_SLICES = 64;
 template <int MODE>
-__global__ void __launch_bounds__(256) in_finish_kernel(const float* __restrict__ part, int blocks, int C, int total, double inv_v, float eps,
-                                                        float* __restrict__ out) {
-    __shared__ double r1[16][17], r2[16][17];
+__global__ void __launch_bounds__(16 * FIN_SLICES) in_finish_kernel(const float* __restrict__ part, int blocks, int C, int total, double inv_v, float eps,
+                                                                    float* __restrict__ out) {
+    __shared__ double r1[FIN_SLICES][17], r2[FIN_SLICES][17];
     const int il = threadIdx.x & 15, sl = threadIdx.x >> 4;
     const int i = blockIdx.x * 16 + il;     // (n, c)
     double s1 = 0.0, s2 = 0.0;
     if (i < total) {
         const int n = i / C, c = i - n * C;
-        for (int b = sl; b < blocks; b += 16) {
-            const float* pb = part + ((long long)n * blocks + b) * 2 * C;
-            s1 += (double)pb[c];
-            s2 += (double)pb[C + c];
+        const float* pn = part + (long long)n * blocks * 2 * C + c;
+#pragma unroll 4
+        for (int b = sl; b < blocks; b += FIN_SLICES) {
+            s1 += (double)pn[(long long)b * 2 * C];
+            s2 += (double)pn[(long long)b * 2 * C + C];
         }
     }
     r1[sl][il] = s1; r2[sl][il] = s2;
     __syncthreads();
     if (sl != 0 || i >= total) return;
     s1 = 0.0; s2 = 0.0;
-    for (int k = 0; k < 16; ++k) { s1 += r1[k][il]; s2 += r2[k][il]; }
+    const int slices = blocks < FIN_SLICES ? blocks : FIN_SLICES;
+#pragma unroll 8
+    for (int k = 0; k < slices; ++k) { s1 += r1[k][il]; s2 += r2[k][il]; }
     if (MODE == 0) {
         const double mean = s1 * inv_v;
         double var = s2 * inv_v - mean * mean;
@@ -223,6 +229,8 @@ __global__ void __launch_bounds__(256) in_bwd_kernel(typename Piece<T>::raw* __r
 bool in_args_ok(int N, size_t voxels, int C) {
     return N > 0 && voxels > 0 && C > 0 && C % 8 == 0 && C <= MAXC && N <= 65535;
 }
+// Voxel ranges of a sample.  (As many as there are voxels on small volumes: the block sums are added in double, and the
+// one-pass variance of a channel with a large offset needs that; a quarter of the ranges costs it a digit.)
 int in_blocks(size_t voxels) { return (int)(voxels < (size_t)IN_BLOCKS ? voxels : (size_t)IN_BLOCKS); }
 unsigned in_grid(long long pieces) {
     long long b = (pieces + 255) / 256;
@@ -235,7 +243,7 @@ bool a16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 // out[n][c] = (mean of the first quantity, mean of the second) from block sums part[n][block][2][C], added in index order
 // in double: the last step of a reduction whose block sums another kernel has written in in_reduce_kernel's layout
 int instnorm_finish_means(const float* part, int blocks, int C, int N, double inv_v, float* out, hipStream_t s) {
-    in_finish_kernel<1><<<(N * C + 15) / 16, 256, 0, s>>>(part, blocks, C, N * C, inv_v, 0.f, out);
+    in_finish_kernel<1><<<(N * C + 15) / 16, 16 * FIN_SLICES, 0, s>>>(part, blocks, C, N * C, inv_v, 0.f, out);
     return check_launch();
 }
 
@@ -249,7 +257,7 @@ int in_stats(const void* z, int N, size_t voxels, int C, float eps, float* stats
     in_reduce_kernel<0, T><<<dim3(blocks, N), 256, 0, (hipStream_t)stream>>>((const T*)z, nullptr, (long long)voxels, C, 1.f, (float*)ws);
     int st = check_launch();
     if (st) return st;
-    in_finish_kernel<0><<<(N * C + 15) / 16, 256, 0, (hipStream_t)stream>>>((const float*)ws, blocks, C, N * C, 1.0 / (double)voxels, eps, stats);
+    in_finish_kernel<0><<<(N * C + 15) / 16, 16 * FIN_SLICES, 0, (hipStream_t)stream>>>((const float*)ws, blocks, C, N * C, 1.0 / (double)voxels, eps, stats);
     return check_launch();
 }
 
@@ -273,7 +281,7 @@ int in_bwd(void* da, const void* a, const float* stats, int N, size_t voxels, in
     in_reduce_kernel<1, T><<<dim3(blocks, N), 256, 0, (hipStream_t)stream>>>((const T*)a, (const T*)da, (long long)voxels, C, slope, part);
     int st = check_launch();
     if (st) return st;
-    in_finish_kernel<1><<<(N * C + 15) / 16, 256, 0, (hipStream_t)stream>>>(part, blocks, C, N * C, 1.0 / (double)voxels, 0.f, sums);
+    in_finish_kernel<1><<<(N * C + 15) / 16, 16 * FIN_SLICES, 0, (hipStream_t)stream>>>(part, blocks, C, N * C, 1.0 / (double)voxels, 0.f, sums);
     if ((st = check_launch())) return st;
     const long long pieces = (long long)voxels * (C / 8);
     in_bwd_kernel<T><<<dim3(in_grid(pieces), N), 256, 0, (hipStream_t)stream>>>((raw*)da, (const raw*)a, stats, sums, pieces, C, slope);
