@@ -107,6 +107,9 @@ static size_t kernel_workspace(Kernel k, const Geom& g, int pass) {
     return 0;
 }
 
+// What a call needs at least: with less than the query reports, the fp32 convolutions run on the fp32 instructions.
+static size_t kernel_min_workspace(Kernel k, const Geom& g, int pass) { return k == K_F32 ? f32_min_workspace_bytes(g, pass) : kernel_workspace(k, g, pass); }
+
 // The kernel for a given workspace: an embedding whose padded copies do not fit gives way to the plain kernel, which
 // needs none or little (the callers' size query reports what the embedding wants; the static scratch has a fixed size).
 static Kernel choose_within(const Geom& g, int pass, size_t ws_bytes) {
@@ -240,7 +243,7 @@ static int conv_entry(const mi3d_conv_desc* desc, int pass, const void* a, const
     if (!a || !b || !out || !aligned16(a) || !aligned16(b) || !aligned16(out) || !aligned16(ws)) return MI3D_ERR_INVALID_ARG;
     if (ws_bytes && !ws) return MI3D_ERR_INVALID_ARG;
     const Kernel k = choose_within(g, pass, ws_bytes);
-    if (ws_bytes < kernel_workspace(k, g, pass)) return MI3D_ERR_WORKSPACE;
+    if (ws_bytes < kernel_min_workspace(k, g, pass)) return MI3D_ERR_WORKSPACE;
     const bool epilogue = slope != 1.f;
     if (!epilogue) return run_kernel(k, g, pass, a, b, out, ws, ws_bytes, (hipStream_t)stream);
     if (!(slope >= 0.f && slope < 1.f) || (g.dtype != MI3D_BF16 && k != K_F32) || pass == MI3D_PASS_WGRAD) return MI3D_ERR_INVALID_ARG;
@@ -300,7 +303,7 @@ int mi3d_conv3d_wgrad_static(const mi3d_conv_desc* desc, const void* x, const vo
     int st = make_geom(desc, &g);
     if (st) return st;
     // sizes beyond the array are refused before anything is looked up or launched
-    if (kernel_workspace(choose_within(g, MI3D_PASS_WGRAD, MI3D_STATIC_SCRATCH_BYTES), g, MI3D_PASS_WGRAD) > (size_t)MI3D_STATIC_SCRATCH_BYTES)
+    if (kernel_min_workspace(choose_within(g, MI3D_PASS_WGRAD, MI3D_STATIC_SCRATCH_BYTES), g, MI3D_PASS_WGRAD) > (size_t)MI3D_STATIC_SCRATCH_BYTES)
         return MI3D_ERR_WORKSPACE;
     void* ws = nullptr;
     st = scratch_of_current_device(&ws);
@@ -330,7 +333,7 @@ int mi3d_conv3d_dgrad_skip(const mi3d_conv_desc* desc, const void* dy, const voi
         return MI3D_ERR_INVALID_ARG;
     const Kernel k = choose_within(g, MI3D_PASS_DGRAD, ws_bytes);
     if ((g.dtype != MI3D_BF16 && k != K_F32) || !(slope >= 0.f && slope <= 1.f) || (ws_bytes && !ws)) return MI3D_ERR_INVALID_ARG;
-    if (ws_bytes < kernel_workspace(k, g, MI3D_PASS_DGRAD)) return MI3D_ERR_WORKSPACE;
+    if (ws_bytes < kernel_min_workspace(k, g, MI3D_PASS_DGRAD)) return MI3D_ERR_WORKSPACE;
     if (k == K_F32 || (k == K_DGRAD_S2 && dgrad_s2_fuses_skip(g))) {
         Geom ge = g;
         ge.add = add; ge.ref = a_in; ge.slope = slope;

@@ -68,6 +68,28 @@ struct GcParams {
 
 __device__ __forceinline__ f32x16 mfma2(float a, float b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
 
+// This lane's position in each of the wave's blocks: row and column inside the tile, inside the plane or not;
+// active: the wave has a position inside the plane (its first one; waves without one issue no MFMA).
+template <int NB>
+__device__ __forceinline__ void gconv_positions(const GcParams& P, int jht, int jwt, int wave, int ln, int& jh0, int& jw0, int& tr0, int& tc0, int& tr1,
+                                                int& tc1, bool& ok0, bool& ok1, bool& active) {
+    const int f0 = (NB * wave) * 32 + ln, f1 = NB == 2 ? f0 + 32 : f0;
+    if (P.flat) {
+        const int base = jht * 256, total = P.Jh * P.Jw;
+        jh0 = base / P.Jw; jw0 = 0;
+        const int r0 = (base + f0) / P.Jw, r1 = (base + f1) / P.Jw;
+        ok0 = base + f0 < total; ok1 = base + f1 < total;
+        tr0 = ok0 ? r0 - jh0 : 0; tc0 = ok0 ? base + f0 - r0 * P.Jw : 0;     // (outside: any staged position)
+        tr1 = ok1 ? r1 - jh0 : 0; tc1 = ok1 ? base + f1 - r1 * P.Jw : 0;
+        active = base + (NB * wave) * 32 < total;
+    } else {
+        jh0 = jht * P.TJH; jw0 = jwt * P.TJW;
+        tr0 = f0 >> P.LW; tc0 = f0 & (P.TJW - 1); tr1 = f1 >> P.LW; tc1 = f1 & (P.TJW - 1);
+        ok0 = jh0 + tr0 < P.Jh && jw0 + tc0 < P.Jw; ok1 = jh0 + tr1 < P.Jh && jw0 + tc1 < P.Jw;
+        active = jh0 + (((NB * wave) * 32) >> P.LW) < P.Jh;
+    }
+}
+
 // The work of one workgroup: tile (n, jd, jht, jwt) of the iteration space, output channel block mt.
 // CB = 32-wide blocks of output channels per workgroup
 template <int CB, int NW, int NB>
@@ -79,27 +101,9 @@ __device__ __forceinline__ void gconv_tile(const GcParams& P, float* lds_f, int 
     float* xs = lds_f;                                         // [prows][pcols][CK + 1]
     float* ws = lds_f + ((P.prows * P.pcols * xp + 3) & ~3);   // [taps of the group][CK][32 CB]
     const int m0 = mt * 32 * CB;
-    // this lane's position in each of the wave's blocks: row and column inside the tile, inside the plane or not;
-    // active: the wave has a position inside the plane (its first one; waves without one issue no MFMA)
     int jh0, jw0, tr0, tc0, tr1, tc1;
     bool ok0, ok1, active;
-    {
-        const int f0 = (NB * wave) * 32 + ln, f1 = NB == 2 ? f0 + 32 : f0;
-        if (P.flat) {
-            const int base = jht * 256, total = P.Jh * P.Jw;
-            jh0 = base / P.Jw; jw0 = 0;
-            const int r0 = (base + f0) / P.Jw, r1 = (base + f1) / P.Jw;
-            ok0 = base + f0 < total; ok1 = base + f1 < total;
-            tr0 = ok0 ? r0 - jh0 : 0; tc0 = ok0 ? base + f0 - r0 * P.Jw : 0;     // (outside: any staged position)
-            tr1 = ok1 ? r1 - jh0 : 0; tc1 = ok1 ? base + f1 - r1 * P.Jw : 0;
-            active = base + (NB * wave) * 32 < total;
-        } else {
-            jh0 = jht * P.TJH; jw0 = jwt * P.TJW;
-            tr0 = f0 >> P.LW; tc0 = f0 & (P.TJW - 1); tr1 = f1 >> P.LW; tc1 = f1 & (P.TJW - 1);
-            ok0 = jh0 + tr0 < P.Jh && jw0 + tc0 < P.Jw; ok1 = jh0 + tr1 < P.Jh && jw0 + tc1 < P.Jw;
-            active = jh0 + (((NB * wave) * 32) >> P.LW) < P.Jh;
-        }
-    }
+    gconv_positions<NB>(P, jht, jwt, wave, ln, jh0, jw0, tr0, tc0, tr1, tc1, ok0, ok1, active);
 
     f32x16 acc[NB][CB];
 #pragma unroll
@@ -189,7 +193,8 @@ __device__ __forceinline__ void gconv_tile(const GcParams& P, float* lds_f, int 
     // The optional operands (second gradient, reference tensor of the derivative) are read 16 bytes at a time (as single
     // floats the stride-2 data gradient with both took 5.5 ms instead of 3.5 at 192^3); a block's operands are
     // requested right where they are used: requesting a whole row's ahead of time costs 15 to 48 registers and, through
-    // the lower occupancy, more than it gains.
+    // the lower occupancy, more than it gains.  (Shared with f32s_gconv_kernel as a function, these lines take 15 registers more
+    // here: the three passes of 64->128 up-sampling at 96^3 874 -> 913 us.)
     const bool vec = (P.out_pitch & 3) == 0;
 #pragma unroll
     for (int r = 0; r < NB; ++r) {
@@ -248,6 +253,315 @@ __global__ void __launch_bounds__(64 * NW, 2) f32_gconv_kernel(GcParams P) {
     const int jd = (int)(u % P.Jd);
     const int n = (int)(u / P.Jd);
     gconv_tile<CB, NW, NB>(P, lds_f, n, jd, jht, jwt, mt);
+}
+
+// ---- fp32 products from bf16 matrix instructions -----------------------------------------------------------------------
+// The same gather convolution with each fp32 operand taken apart into three bf16 numbers, v = a + b + c exactly (a the
+// nearest bf16 to v, b to v - a, c the rest: 3 x 8 significant bits and two signs hold the 24 of v).  Of the nine products
+// the six a a', a b', b a', a c', c a', b b' are formed with v_mfma_f32_32x32x16_bf16 and added in fp32; the three left
+// out are below 2^-26 of the product (|b| <= 2^-9 |v|, |c| <= 2^-18 |v|), a quarter of one fp32 rounding.  An accumulator
+// is rounded 6 times per 16 contracted channels instead of 8 to 16 times.  Measured
+// against 64 bits (2-norm, fp32 instructions -> this kernel): 32->32 at 8 x 48 x 48 5.0e-7 -> 4.3e-7, 320->320 at 5 x 12 x 12
+// 1.5e-6 -> 1.35e-6, 640->32 2.2e-6 -> 2.0e-6.
+//
+// Bound: the fp32 matrix instructions need 64 cycles for 32x32x2, six bf16 ones for 32x32x16 need 6 x 32: a ceiling 2.7
+// times as high.  Forward pass with its packing launch, fp32 instructions -> this kernel: 32->32 at 128^3, N = 2 2225 -> 1444 us
+// (104 -> 161 TFLOP/s), 64->64 at 64^3, N = 2 1060 -> 600 (109 -> 193), 64->32 at 45 x 75 x 91 470 -> 279, 256->256 at 16^3,
+// N = 2 486 -> 217; on the smallest volumes the way of the weights to the few waves at work is the bound, 320->320 at 8^3,
+// N = 2 608 -> 319.
+// A workgroup (4 waves) owns 256 positions x 32 or 64 output channels, a wave two blocks of 32 positions.  A stage is 16
+// contracted channels of one input plane: the patch is requested during the previous stage's MFMAs, taken apart on its way
+// to LDS ([part][voxel][16 channels], 32 bytes per voxel, the two 16-byte halves swapped every 8 voxels so that 16
+// neighbouring voxels cover all banks) and read by all taps of the plane.  Weights are packed in fragment order by
+// f32s_pack_kernel and read from there (L1 / L2) one or two taps ahead of their use.
+//
+// A value the split cannot hold (infinities, NaN, magnitudes from 2^126 and below 2^-100 other than zero, whose parts would
+// overflow or lose bits) sends its stage, or its whole tile if it is a weight, through v_mfma_f32_32x32x2_f32 on the
+// values themselves, so that results are those of the fp32 kernel there too.
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+constexpr int SP_NT = 256, SP_CK = 16;
+constexpr int SP_MAXV = 448;                       // staged voxels (bound of the dispatch rule)
+constexpr int SP_NPX = SP_MAXV * (SP_CK / 4) / SP_NT;   // 16-byte pieces of the patch per thread
+
+struct GsParams {
+    GcParams c;
+    const uint16_t* wsplit;      // [tap][K / 16][Mpad / 32][3 parts][64 lanes][8]
+    const uint32_t* wflag;       // [Mpad / 32][tap][K / 16]: a value of this fragment cannot be split
+    const float* w;              // the layer's own weights: element (m, tap, k) at m * w_m + tap * w_t + k * w_k
+    long long w_m, w_t, w_k;
+    int T;
+    uint32_t taps[MAX_TAPS];     // voxel offset in the patch | index in the layer's tap order << 16 (scalar loads have no bytes)
+};
+
+// Magnitudes whose three parts are exact: zero and 2^-100 ... 2^126.  Zero counts as large in the minimum (0 - 1 wraps).
+struct SplitRange {
+    uint32_t most = 0, least = 0xFFFFFFFFu;
+    __device__ __forceinline__ void add(float v) {
+        const uint32_t u = __builtin_bit_cast(uint32_t, v) & 0x7FFFFFFFu;
+        most = u > most ? u : most;
+        least = u - 1 < least ? u - 1 : least;
+    }
+    __device__ __forceinline__ void add(const float4& v) { add(v.x); add(v.y); add(v.z); add(v.w); }
+    __device__ __forceinline__ bool exceeded() const { return (most >= 0x7E800000u) | (least < 0x0D7FFFFFu); }
+};
+__device__ __forceinline__ uint32_t cvt2(float a, float b) {
+    typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
+    typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
+    f32x2 v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+// the three parts of two values, packed
+__device__ __forceinline__ void split2(float x, float y, uint32_t (&o)[3]) {
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        o[p] = cvt2(x, y);
+        x -= __builtin_bit_cast(float, o[p] << 16);
+        y -= __builtin_bit_cast(float, o[p] & 0xFFFF0000u);
+    }
+}
+__device__ __forceinline__ f32x16 mfma16(bf16x8 a, bf16x8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
+
+// One wave per fragment: 32 output channels x 16 contracted channels of a tap.  grid.x * 4 waves >= T * K / 16 * Mpad / 32.
+__global__ void __launch_bounds__(256) f32s_pack_kernel(const float* __restrict__ w, uint16_t* __restrict__ out, uint32_t* __restrict__ flag, int T, int K,
+                                                        int M, int MB, long long w_m, long long w_t, long long w_k) {
+    const int lane = threadIdx.x & 63, KC = K / SP_CK;
+    const int frag = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (frag >= T * KC * MB) return;
+    const int mb = frag % MB, r = frag / MB, kc = r % KC, tap = r / KC;
+    const int m = mb * 32 + (lane & 31), k0 = kc * SP_CK + 8 * (lane >> 5);
+    float v[8];
+    SplitRange range;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        v[i] = m < M ? w[m * w_m + tap * w_t + (k0 + i) * w_k] : 0.f;
+        range.add(v[i]);
+    }
+    uint32_t o[4][3];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) split2(v[2 * i], v[2 * i + 1], o[i]);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) *(uint4*)(out + (((long long)frag * 3 + p) * 64 + lane) * 8) = uint4{o[0][p], o[1][p], o[2][p], o[3][p]};
+    const bool any = __any(range.exceeded());
+    if (lane == 0) flag[(mb * T + tap) * KC + kc] = any ? 1u : 0u;
+}
+
+// Epilogue of one block of 32 channels from m0 on, at position (jh, jw) of plane jd.
+__device__ __forceinline__ void split_store(const GcParams& P, f32x16 a, int n, int jd, int jh, int jw, int m0, int half) {
+    const int od = P.osd * jd + P.ood, oh = P.osh * jh + P.ooh, ow = P.osw * jw + P.oow;
+    const long long vox = (((long long)n * P.Do + od) * P.Ho + oh) * P.Wo + ow;
+#pragma unroll
+    for (int g4 = 0; g4 < 4; ++g4) {
+        const int c = m0 + 8 * g4 + 4 * half;
+        if (c >= P.M) continue;
+        const bool hi_out = c >= P.out_split, full = (P.out_pitch & 3) == 0 && P.M - c >= 4;
+        const int nv = P.M - c < 4 ? P.M - c : 4;
+        const long long e = vox * P.out_pitch + (hi_out ? c - P.out_split : c);   // (add and ref never come with a split output)
+        float* dst = (hi_out ? P.out2 : P.out) + e;
+        float v[4], ad[4] = {0.f, 0.f, 0.f, 0.f}, rf[4] = {0.f, 0.f, 0.f, 0.f};
+        if (full) {
+            if (P.add) *(float4*)ad = *(const float4*)(P.add + e);
+            if (P.ref) *(float4*)rf = *(const float4*)(P.ref + e);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (P.add && i < nv) ad[i] = P.add[e + i];
+                if (P.ref && i < nv) rf[i] = P.ref[e + i];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float x = a[4 * g4 + i];
+            if (P.add) x += ad[i];
+            v[i] = (P.ref ? rf[i] : x) > 0.f ? x : P.slope * x;
+        }
+        if (full) *(float4*)dst = make_float4(v[0], v[1], v[2], v[3]);
+        else
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (i < nv) dst[i] = v[i];
+    }
+}
+
+// CB = 32-wide blocks of output channels per workgroup, NTC = taps of a plane (every group has that many)
+template <int CB, int NTC>
+__global__ void __launch_bounds__(SP_NT, 2) f32s_gconv_kernel(GsParams Q) {
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const GcParams& P = Q.c;
+    constexpr int NB = 2, WANT = CB == 2 ? 2 : 3, AHEAD = NTC < WANT ? NTC : WANT;   // weight fragments held: this tap's and the next ones'
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int ln = lane & 31, half = lane >> 5;
+    int u = blockIdx.x;
+    const int mt = u % P.MT; u /= P.MT;
+    const int jwt = u % P.JWT; u /= P.JWT;
+    const int jht = u % P.JHT; u /= P.JHT;
+    const int jd = u % P.Jd, n = u / P.Jd;
+    const int m0 = mt * 32 * CB;
+    int jh0, jw0, tr0, tc0, tr1, tc1;
+    bool ok0, ok1, active;
+    gconv_positions<NB>(P, jht, jwt, wave, ln, jh0, jw0, tr0, tc0, tr1, tc1, ok0, ok1, active);
+    const int nvox = P.prows * P.pcols, part = nvox * 32;
+    uint32_t* bad_lds = (uint32_t*)(lds + 3 * part);   // [0], [1]: stage of that parity, [2]: weights
+
+    f32x16 acc[NB][CB];
+#pragma unroll
+    for (int r = 0; r < NB; ++r)
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[r][cb][i] = 0.f;
+
+    // this thread's pieces of the patch: offset inside an input plane, or -1 for zero padding
+    int gofs[SP_NPX];
+#pragma unroll
+    for (int i = 0; i < SP_NPX; ++i) {
+        const int e = t + SP_NT * i, v = e >> 2, pr = v / P.pcols, pc = v - pr * P.pcols;
+        const int ih = jh0 + P.hmin + pr, iw = jw0 + P.wmin + pc;
+        gofs[i] = v < nvox && ih >= 0 && ih < P.Hi && iw >= 0 && iw < P.Wi ? (ih * P.Wi + iw) * P.in_pitch + 4 * (e & 3) : -1;
+    }
+    // groups whose input plane exists (zero planes add nothing)
+    const int KC = P.K / SP_CK;
+    unsigned gmask = 0;
+    for (int g = 0; g < P.ngroups; ++g) {
+        const int id = P.isd * jd + P.gd[g];
+        gmask |= (id >= 0 && id < P.Di ? 1u : 0u) << g;
+    }
+    const int ngv = __popc(gmask), stages = KC * ngv;
+    const long long in_plane = (long long)P.Hi * P.Wi * P.in_pitch;
+    auto stage_group = [&](int s) {   // the (s % ngv)-th existing group
+        unsigned m = gmask;
+        for (int r = s % ngv; r > 0; --r) m &= m - 1;
+        return __ffs(m) - 1;
+    };
+    float4 px[SP_NPX];
+    auto request = [&](int s) {
+        const int c0 = s / ngv * SP_CK, g = stage_group(s);
+        const bool hi_in = c0 >= P.in_split;
+        const float* src = (hi_in ? P.in2 : P.in) + ((long long)n * P.Di + P.isd * jd + P.gd[g]) * in_plane + (hi_in ? c0 - P.in_split : c0);
+#pragma unroll
+        for (int i = 0; i < SP_NPX; ++i) {
+            px[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (gofs[i] >= 0) px[i] = *(const float4*)(src + gofs[i]);
+        }
+    };
+    auto slot = [&](int e) { const int v = e >> 2, q = e & 3; return v * 32 + (((q >> 1) ^ (v >> 3)) & 1) * 16 + (q & 1) * 8; };
+
+    if (t < 3) bad_lds[t] = 0;
+    if (stages > 0) request(0);
+    __syncthreads();
+    // weights that cannot be split
+    {
+        bool bad = false;
+        const int TK = Q.T * KC;
+        for (int cb = 0; cb < CB; ++cb)
+            if (m0 + 32 * cb < P.Mpad)
+                for (int e = t; e < TK; e += SP_NT) bad |= Q.wflag[(m0 / 32 + cb) * TK + e] != 0;
+        if (__any(bad) && lane == 0) bad_lds[2] = 1;
+    }
+    const int MB = P.Mpad / 32;
+    const int vb[NB] = {tr0 * P.pcols + tc0, tr1 * P.pcols + tc1};
+    for (int s = 0; s < stages; ++s) {
+        const int kc = s / ngv, g = stage_group(s), tap0 = P.gstart[g];
+        if (s) __syncthreads();   // the previous stage's readers are done
+        SplitRange range;
+#pragma unroll
+        for (int i = 0; i < SP_NPX; ++i) {
+            const int e = t + SP_NT * i;
+            if ((e >> 2) >= nvox) break;
+            range.add(px[i]);
+            uint32_t lo[3], hi[3];
+            split2(px[i].x, px[i].y, lo);
+            split2(px[i].z, px[i].w, hi);
+            char* d = lds + slot(e);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) *(uint2*)(d + p * part) = uint2{lo[p], hi[p]};
+        }
+        if (__any(range.exceeded()) && lane == 0) bad_lds[s & 1] = 1;
+        bf16x8 wf[AHEAD][CB][3];
+        auto weights = [&](int tp, bf16x8 (&f)[CB][3]) {
+            const int tap = (int)(Q.taps[tap0 + tp] >> 16);
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) {
+                // (a last block of 64 with 32 channels: the second half reads the first again and is not stored)
+                const int mb = m0 / 32 + cb < MB ? m0 / 32 + cb : MB - 1;
+                const uint16_t* q = Q.wsplit + (((long long)tap * KC + kc) * MB + mb) * (3 * 512) + lane * 8;
+#pragma unroll
+                for (int p = 0; p < 3; ++p) f[cb][p] = *(const bf16x8*)(q + p * 512);
+            }
+        };
+#pragma unroll
+        for (int a = 0; a < AHEAD - 1; ++a) weights(a, wf[a]);
+        if (AHEAD == 1) weights(0, wf[0]);
+        __syncthreads();
+        const bool plain = __builtin_amdgcn_readfirstlane(bad_lds[s & 1] | bad_lds[2]) != 0;
+        if (t == 0) bad_lds[1 - (s & 1)] = 0;   // (next written behind the next stage's first barrier)
+        if (plain) {
+            // raw bits in two halves take the place of the parts; weights come as they are
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < SP_NPX; ++i) {
+                const int e = t + SP_NT * i;
+                if ((e >> 2) >= nvox) break;
+                const uint4 b = __builtin_bit_cast(uint4, px[i]);
+                char* d = lds + slot(e);
+                *(uint2*)d = uint2{b.x >> 16 | (b.y & 0xFFFF0000u), b.z >> 16 | (b.w & 0xFFFF0000u)};
+                *(uint2*)(d + part) = uint2{(b.x & 0xFFFFu) | b.y << 16, (b.z & 0xFFFFu) | b.w << 16};
+            }
+            __syncthreads();
+            if (s + 1 < stages) request(s + 1);
+            if (!active) continue;
+            for (int tp = 0; tp < NTC; ++tp) {
+                const int vo = (int)(Q.taps[tap0 + tp] & 0xFFFFu);
+                const float* wt = Q.w + (long long)(Q.taps[tap0 + tp] >> 16) * Q.w_t;
+#pragma unroll 1
+                for (int i = 0; i < 8; ++i) {
+                    float xv[NB];
+#pragma unroll
+                    for (int r = 0; r < NB; ++r) {
+                        const int v = vb[r] + vo;
+                        const uint16_t* q = (const uint16_t*)(lds + v * 32 + ((half ^ (v >> 3)) & 1) * 16) + i;
+                        xv[r] = __builtin_bit_cast(float, (uint32_t)q[0] << 16 | *(const uint16_t*)((const char*)q + part));
+                    }
+#pragma unroll
+                    for (int cb = 0; cb < CB; ++cb) {
+                        const int m = m0 + 32 * cb + ln, k = kc * SP_CK + 8 * half + i;
+                        const float wv = m < P.M ? wt[m * Q.w_m + k * Q.w_k] : 0.f;
+#pragma unroll
+                        for (int r = 0; r < NB; ++r) acc[r][cb] = mfma2(wv, xv[r], acc[r][cb]);
+                    }
+                }
+            }
+            continue;
+        }
+        if (s + 1 < stages) request(s + 1);
+        if (!active) continue;
+#pragma unroll
+        for (int tp = 0; tp < NTC; ++tp) {
+            if (AHEAD > 1 && tp + AHEAD - 1 < NTC) weights(tp + AHEAD - 1, wf[(tp + AHEAD - 1) % AHEAD]);
+            const int vo = (int)(Q.taps[tap0 + tp] & 0xFFFFu);
+            bf16x8 xf[NB][3];
+#pragma unroll
+            for (int r = 0; r < NB; ++r) {
+                const int v = vb[r] + vo;
+                const char* q = lds + v * 32 + ((half ^ (v >> 3)) & 1) * 16;
+#pragma unroll
+                for (int p = 0; p < 3; ++p) xf[r][p] = *(const bf16x8*)(q + p * part);
+            }
+            // small products first
+            constexpr int PW[6] = {2, 0, 1, 1, 0, 0}, PX[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+            for (int q = 0; q < 6; ++q)
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                    for (int r = 0; r < NB; ++r) acc[r][cb] = mfma16(wf[tp % AHEAD][cb][PW[q]], xf[r][PX[q]], acc[r][cb]);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < NB; ++r) {
+        if (!(r ? ok1 : ok0)) continue;
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) split_store(P, acc[r][cb], n, jd, jh0 + (r ? tr1 : tr0), jw0 + (r ? tc1 : tc0), m0 + 32 * cb, half);
+    }
 }
 
 // The parity classes of a stride-2 data gradient in one launch.  Workgroups are dealt to the 8 XCDs by index modulo
@@ -617,6 +931,35 @@ void wgrad_c4_layout(const Geom& g, WgParams* P) {
     P->S = (int)s;
 }
 
+// Sizes that f32s_gconv_kernel takes (forward and data gradient).  Whole steps of 16 contracted channels, taps that come in
+// groups of 1, 2, 4 or 9 per plane, unit input stride (a strided patch is four times the tile) and at most SP_MAXV voxels of
+// patch (planes of a few columns have more; the general kernel serves those).
+bool split_ok(const Geom& g, int pass) {
+    if (pass == MI3D_PASS_WGRAD || g.kH != 3 || g.kW != 3) return false;
+    const bool dgrad = pass == MI3D_PASS_DGRAD;
+    if ((dgrad ? g.Cout : g.Cin) % SP_CK) return false;
+    if (dgrad ? g.sH != g.sW : (g.sH != 1 || g.sW != 1)) return false;
+    // (the classes of a strided data gradient have 1, 2 or 4 taps per staged patch: with 32 contracted channels they are
+    // over before the staging pays, 64->32 at 9 x 20 x 33 140 -> 155 us; with 64 and more 32->64 at 128^3, N = 2 940 -> 805,
+    // at 9 x 20 x 33 200 -> 157, 128->256 at 32^3, N = 2 829 -> 591, 64->128 at 6 x 10 x 11 263 -> 271)
+    if (g.sH == 2 && g.Cout < 64) return false;
+    const int os = dgrad ? g.sH : 1;
+    const long long JH = ((dgrad ? g.H : g.Ho) + os - 1) / os, JW = ((dgrad ? g.W : g.Wo) + os - 1) / os;
+    for (long long jw = JW > 1 ? JW - 1 : 1; jw <= JW; ++jw) {   // (the parity classes differ by one column)
+        if (jw >= 32) continue;                                   // 8 x 32 or 16 x 16 tiles: 340 voxels at most
+        long long rows = 255 / jw + 2;
+        if (rows > JH) rows = JH;
+        if ((rows + 2) * (jw + 2) > SP_MAXV) return false;
+    }
+    return true;
+}
+size_t split_pack_bytes(const Geom& g, int pass, size_t* flags_at) {
+    const long long K = pass == MI3D_PASS_DGRAD ? g.Cout : g.Cin, M = pass == MI3D_PASS_DGRAD ? g.Cin : g.Cout;
+    const size_t frags = (size_t)g.taps() * (K / SP_CK) * ((M + 31) / 32);
+    *flags_at = frags * 3 * 512 * sizeof(uint16_t);
+    return (*flags_at + frags * sizeof(uint32_t) + 255) & ~(size_t)255;
+}
+
 bool wgrad_magic_ok(const WgParams& P) {
     for (unsigned q = 0; q < (unsigned)(P.prows * P.pcols); ++q)
         if (((q * P.pcols_magic) >> 16) != q / (unsigned)P.pcols) return false;
@@ -646,7 +989,7 @@ bool f32_supported(const Geom& g, int pass) {
 // three passes on the matrix cores).  A call with an added gradient or a two-tensor operand keeps the general kernel.
 static bool f32_head(const Geom& g) { return pointwise_f32_supported(g) && !g.add && !g.hi; }
 
-size_t f32_workspace_bytes(const Geom& g, int pass) {
+size_t f32_min_workspace_bytes(const Geom& g, int pass) {
     if (!f32_supported(g, pass)) return 0;
     size_t b;
     if (pass == MI3D_PASS_WGRAD) {
@@ -663,6 +1006,16 @@ size_t f32_workspace_bytes(const Geom& g, int pass) {
     }
     const size_t h = pointwise_f32_workspace_bytes(g, pass);   // (0 where the head kernels do not apply)
     return b > h ? b : h;
+}
+
+// (the parts of the weights take 1.5 times their room; a call with the smaller workspace gets the fp32 instructions)
+size_t f32_workspace_bytes(const Geom& g, int pass) {
+    size_t b = f32_min_workspace_bytes(g, pass), at;
+    if (f32_supported(g, pass) && split_ok(g, pass)) {
+        const size_t p = split_pack_bytes(g, pass, &at);
+        b = b > p ? b : p;
+    }
+    return b;
 }
 
 bool f32_wgrad_folds_taps(const Geom& g) { return f32_supported(g, MI3D_PASS_WGRAD) && wgrad_c4_ok(g); }
@@ -769,6 +1122,32 @@ static int launch_gconv(GcParams& P, hipStream_t s) {
     return check_launch();
 }
 
+template <int CB>
+static int launch_split_cb(const GsParams& Q, int ntc, unsigned blocks, size_t lds, hipStream_t s) {
+    switch (ntc) {
+        case 1: f32s_gconv_kernel<CB, 1><<<blocks, SP_NT, lds, s>>>(Q); break;
+        case 2: f32s_gconv_kernel<CB, 2><<<blocks, SP_NT, lds, s>>>(Q); break;
+        case 4: f32s_gconv_kernel<CB, 4><<<blocks, SP_NT, lds, s>>>(Q); break;
+        case 9: f32s_gconv_kernel<CB, 9><<<blocks, SP_NT, lds, s>>>(Q); break;
+        default: return MI3D_ERR_UNSUPPORTED;
+    }
+    return check_launch();
+}
+static int launch_split(GsParams& Q, hipStream_t s) {
+    GcParams& P = Q.c;
+    const int CB = gconv_blocks_of_channels(P, (long long)P.N * P.Jd * gconv_row_tiles(P) * gconv_col_tiles(P), P.ntaps);
+    P.JHT = gconv_row_tiles(P);
+    P.JWT = gconv_col_tiles(P);
+    P.MT = (P.Mpad + 32 * CB - 1) / (32 * CB);
+    const long long blocks = (long long)P.N * P.Jd * P.JHT * P.JWT * P.MT;
+    if (blocks <= 0) return MI3D_OK;
+    if (blocks > 0x7fffffffll || P.prows * P.pcols > SP_MAXV) return MI3D_ERR_UNSUPPORTED;
+    for (int k = 0; k < P.ntaps; ++k) Q.taps[k] = (uint32_t)((P.th[k] - P.hmin) * P.pcols + P.tw[k] - P.wmin) | (uint32_t)P.tapidx[k] << 16;
+    const int ntc = P.ngroups ? P.ntaps / P.ngroups : 9;   // (no group: nothing to add, any instance writes the epilogue)
+    const size_t lds = (size_t)P.prows * P.pcols * 96 + 16;
+    return CB == 2 ? launch_split_cb<2>(Q, ntc, (unsigned)blocks, lds, s) : launch_split_cb<1>(Q, ntc, (unsigned)blocks, lds, s);
+}
+
 // all classes of a stride-2 data gradient in one launch (Q.p[0 .. ncls - 1] filled in but for tiles, CK)
 static int launch_gconv_classes(GcMulti& Q, hipStream_t s) {
     if (Q.ncls == 0) return MI3D_OK;
@@ -807,12 +1186,26 @@ static int launch_gconv_classes(GcMulti& Q, hipStream_t s) {
 // forward (in = x, out = y) and data gradient (in = dy, out = dx)
 int f32_conv(const Geom& g, int pass, const void* in, const void* w, void* out, void* ws, size_t ws_bytes, hipStream_t s) {
     if (f32_head(g)) return pointwise_f32_conv(g, pass, in, w, out, ws, ws_bytes, s);
-    if (ws_bytes < f32_workspace_bytes(g, pass)) return MI3D_ERR_WORKSPACE;
+    if (ws_bytes < f32_min_workspace_bytes(g, pass)) return MI3D_ERR_WORKSPACE;
+    const bool split = split_ok(g, pass) && ws_bytes >= f32_workspace_bytes(g, pass);
     const bool dgrad = pass == MI3D_PASS_DGRAD;
     const int T = (int)g.taps();
     const int K = dgrad ? g.Cout : g.Cin, M = dgrad ? g.Cin : g.Cout, Mpad = (M + 31) / 32 * 32;
     const long long total = (long long)T * K * Mpad;
-    f32_pack_kernel<<<(unsigned)((total + 255) / 256), 256, 0, s>>>((const float*)w, (float*)ws, g.Cout, g.Cin, T, Mpad, dgrad ? 1 : 0);
+    GsParams S{};
+    if (split) {
+        size_t at;
+        split_pack_bytes(g, pass, &at);
+        S.wsplit = (const uint16_t*)ws;
+        S.wflag = (const uint32_t*)((const char*)ws + at);
+        S.w = (const float*)w;
+        S.w_m = dgrad ? 1 : (long long)T * g.Cin; S.w_t = g.Cin; S.w_k = dgrad ? (long long)T * g.Cin : 1;
+        S.T = T;
+        const long long frags = (long long)T * (K / SP_CK) * (Mpad / 32);
+        f32s_pack_kernel<<<(unsigned)((frags + 3) / 4), 256, 0, s>>>(S.w, (uint16_t*)ws, (uint32_t*)((char*)ws + at), T, K, M, Mpad / 32, S.w_m, S.w_t, S.w_k);
+    } else {
+        f32_pack_kernel<<<(unsigned)((total + 255) / 256), 256, 0, s>>>((const float*)w, (float*)ws, g.Cout, g.Cin, T, Mpad, dgrad ? 1 : 0);
+    }
     int st = check_launch();
     if (st) return st;
     GcParams B;
@@ -873,12 +1266,17 @@ int f32_conv(const Geom& g, int pass, const void* in, const void* w, void* out, 
                 P.gstart[P.ngroups] = P.ntaps;
                 if (P.ntaps == 0) { hmin = hmax = wmin = wmax = 0; }   // a class no tap reaches: zeros (plus the epilogue)
                 P.hmin = hmin; P.wmin = wmin;
-                gconv_tile_shape(&P, !classes && sD * sH * sW == 1);
+                gconv_tile_shape(&P, !split && !classes && sD * sH * sW == 1);
                 P.prows = (P.TJH - 1) * P.ish + (hmax - hmin) + 1;
                 P.pcols = (P.TJW - 1) * P.isw + (wmax - wmin) + 1;
                 P.wpack = (const float*)ws;
                 if (classes) { Q.p[Q.ncls++] = P; continue; }
-                st = launch_gconv(P, s);
+                if (split) {
+                    S.c = P;
+                    st = launch_split(S, s);
+                } else {
+                    st = launch_gconv(P, s);
+                }
                 if (st) return st;
             }
     return classes ? launch_gconv_classes(Q, s) : MI3D_OK;
@@ -886,7 +1284,7 @@ int f32_conv(const Geom& g, int pass, const void* in, const void* w, void* out, 
 
 int f32_wgrad(const Geom& g, const void* x, const void* dy, float* dw, void* ws, size_t ws_bytes, hipStream_t s) {
     if (f32_head(g)) return pointwise_f32_conv(g, MI3D_PASS_WGRAD, x, dy, dw, ws, ws_bytes, s);
-    if (ws_bytes < f32_workspace_bytes(g, MI3D_PASS_WGRAD)) return MI3D_ERR_WORKSPACE;
+    if (ws_bytes < f32_min_workspace_bytes(g, MI3D_PASS_WGRAD)) return MI3D_ERR_WORKSPACE;
     WgParams P;
     wgrad_layout(g, &P);
     P.x = P.x2 = (const float*)x;

@@ -165,7 +165,8 @@ int embed_k2_conv(const Geom& g, int pass, const void* a, const void* b, void* o
 
 // fp32 MFMA kernels: any kernel extent up to 3 and stride up to 2 (forward, data gradient, weight gradient)
 bool f32_supported(const Geom& g, int pass);
-size_t f32_workspace_bytes(const Geom& g, int pass);
+size_t f32_workspace_bytes(const Geom& g, int pass);       // what the fastest kernel wants
+size_t f32_min_workspace_bytes(const Geom& g, int pass);   // what a call needs at least
 int f32_conv(const Geom& g, int pass, const void* in, const void* w, void* out, void* ws, size_t ws_bytes, hipStream_t s);
 int f32_wgrad(const Geom& g, const void* x, const void* dy, float* dw, void* ws, size_t ws_bytes, hipStream_t s);
 bool f32_wgrad_folds_taps(const Geom& g);   // at most 4 input channels: (tap, channel) pairs as the columns of the MFMA block

@@ -1,0 +1,128 @@
+"""fp32 3x3x3 convolutions whose products come from bf16 matrix instructions (each operand in three parts): edges of the
+tiles and of the dispatch rule against the fp64 oracle, and values the parts cannot hold against the fp32 instructions,
+which a call with the smaller workspace gets."""
+import ctypes
+
+import pytest
+import torch
+
+import synth_inputs as si
+from oracle import conv3d as oc
+from paper_1812_07816_amd import conv3d as mc
+from paper_1812_07816_amd._lib import lib
+from tests import parity
+
+pytestmark = pytest.mark.gpu
+
+# fp32 sums of n terms of random sign: about sqrt(n) half roundings of 2^-24, n = 27 * 320 at most: 6e-6 of the result's
+# root mean square for one standard deviation of the worst operand order; five of those
+TOL = 3e-5
+
+CASES = [
+    # N, D, H, W, Cin, Cout, k, s, p
+    (1, 3, 9, 33, 16, 16, 3, 1, 1),       # one stage deep, one row and column beyond an 8 x 32 tile
+    (1, 2, 17, 48, 48, 33, 3, 1, 1),      # 16 x 16 tiles, one channel beyond a block of 32
+    (2, 3, 7, 31, 32, 80, 3, 1, 0),       # row-major tiles, no padding, last block of 64 half full
+    (1, 3, 5, 12, 64, 5, 3, 1, 2),        # padding 2, few output channels
+    (1, 4, 1, 1, 32, 16, 3, 1, 1),        # one column: planes above and below are zero
+    (1, 2, 200, 1, 32, 16, 3, 1, 1),      # patch of a one-column plane too large: the fp32 instructions
+    (1, 3, 12, 12, 320, 320, 3, 1, 1),    # deepest level
+    (1, 5, 11, 13, 32, 64, 3, 2, 1),      # parity classes of an odd extent
+    (2, 4, 6, 70, 16, 64, 3, 2, 0),       # no padding: classes with one and two taps change places
+    (2, 17, 21, 65, 32, 32, 3, 1, 1),     # weight gradient: one row and column beyond its 4 x 32 patches
+    (1, 9, 30, 31, 64, 96, 3, 1, 0),
+    (3, 5, 15, 28, 96, 64, 3, 1, 2),      # padding 2: dy planes beyond both ends, segments of a few planes
+    (1, 6, 8, 34, 16, 32, (1, 3, 3), 1, (0, 1, 1)),   # one plane per output
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[f"{c[1]}x{c[2]}x{c[3]}-{c[4]}-{c[5]}s{c[7]}" for c in CASES])
+def test_split_products_match_oracle(device, case):
+    N, D, H, W, Cin, Cout, k, s, p = case
+    if isinstance(k, tuple):
+        x = torch.randn((N, D, H, W, Cin), device="cuda")
+        w = torch.randn((Cout, *k, Cin), device="cuda")
+        d = mc.make_desc(N, D, H, W, Cin, Cout, k, s, p, torch.float32)
+        ref = torch.nn.functional.conv3d(x.cpu().double().permute(0, 4, 1, 2, 3), w.cpu().double().permute(0, 4, 1, 2, 3), padding=p)
+        err = mc.conv3d_fwd(d, x, w).cpu().double() - ref.permute(0, 2, 3, 4, 1)
+        assert float(err.abs().max() / ref.square().mean().sqrt()) <= TOL
+        return
+    errs = parity.run_case(97, 10 * CASES.index(case), N, D, H, W, Cin, Cout, k, s, p, bf16=False, full=True)
+    for q in ("fwd", "dgrad", "wgrad"):
+        assert errs[q] <= TOL, (case, q, errs)
+
+
+def _both(d, q, a, w, shape):
+    """The pass with the workspace the query reports and with what the fp32 instructions need."""
+    K, M = (d.Cout, d.Cin) if q == mc.PASS_DGRAD else (d.Cin, d.Cout)
+    small = (27 * K * ((M + 31) // 32 * 32) * 4 + 255) // 256 * 256
+    assert mc.workspace_bytes(d, q) > small
+    f = lib().mi3d_conv3d_dgrad if q == mc.PASS_DGRAD else lib().mi3d_conv3d_fwd
+    outs = []
+    for n in (mc.workspace_bytes(d, q), small):
+        ws, o = torch.zeros(n, dtype=torch.uint8, device="cuda"), torch.empty(shape, device="cuda")
+        assert f(ctypes.byref(d), a.data_ptr(), w.data_ptr(), o.data_ptr(), ws.data_ptr(), n, None) == 0
+        torch.cuda.synchronize()
+        outs.append(o)
+    return outs
+
+
+@pytest.mark.parametrize("q", [0, 1], ids=["fwd", "dgrad"])
+@pytest.mark.parametrize("kind", ["inf", "nan", "large", "tiny", "tiny_w", "inf_w", "scaled"])
+def test_values_without_parts_take_the_fp32_instructions(device, kind, q):
+    torch.manual_seed(5)
+    d = mc.make_desc(1, 3, 10, 40, 32, 48, 3, 1, 1, torch.float32)
+    K, M = (48, 32) if q == mc.PASS_DGRAD else (32, 48)
+    a, w = torch.randn((1, 3, 10, 40, K), device="cuda"), torch.randn((48, 3, 3, 3, 32), device="cuda")
+    if kind == "inf":
+        a[0, 1, 3, 5, 17], a[0, 2, 9, 39, 3] = float("inf"), float("-inf")
+    elif kind == "nan":
+        a[0, 0, 0, 33, 31] = float("nan")
+    elif kind == "large":          # rounds to infinity in bf16; the products stay finite
+        a[0, 1, 2, 3, 4] = 3.4e38
+        w *= 1e-3
+    elif kind == "tiny":           # parts below the normal range
+        a *= 2.0 ** -112
+    elif kind == "tiny_w":
+        w *= 2.0 ** -112
+    elif kind == "inf_w":
+        w[3, 1, 2, 0, 7] = float("inf")
+    else:                          # the ends of what the parts hold
+        a *= 2.0 ** 115
+        w *= 2.0 ** -75
+    got, ref = _both(d, q, a, w, (1, 3, 10, 40, M))
+    for f in (torch.isnan, torch.isposinf, torch.isneginf):
+        assert torch.equal(f(got), f(ref)), kind
+    ok = torch.isfinite(ref)
+    g, r = got[ok].double(), ref[ok].double()
+    rms = r.square().mean().sqrt() if kind != "large" else r.abs().median()
+    assert float(((g - r).abs() / torch.maximum(r.abs(), rms)).max()) <= TOL
+
+
+@pytest.mark.parametrize("kind", ["inf", "nan_dy", "large", "tiny", "scaled"])
+def test_weight_gradient_of_values_without_parts(device, kind):
+    torch.manual_seed(6)
+    N, D, H, W, c = 2, 12, 22, 40, 32
+    d = mc.make_desc(N, D, H, W, c, c, 3, 1, 1, torch.float32)
+    x, dy = torch.randn((N, D, H, W, c), device="cuda"), torch.randn((N, D, H, W, c), device="cuda")
+    if kind == "inf":
+        x[0, 3, 5, 7, 11], x[1, 10, 13, 31, 31] = float("inf"), float("-inf")   # (inside: a border one meets dy's zero padding)
+    elif kind == "nan_dy":
+        dy[1, 1, 1, 33, 2] = float("nan")
+    elif kind == "large":
+        x[0, 6, 9, 9, 4] = 3.4e38
+        dy *= 1e-3
+    elif kind == "tiny":
+        x *= 2.0 ** -112
+    else:
+        x *= 2.0 ** 115
+        dy *= 2.0 ** -75
+    got = mc.conv3d_wgrad(d, x, dy).double().cpu()
+    xr, dyr = (v.double().cpu().permute(0, 4, 1, 2, 3) for v in (x, dy))
+    ref = torch.nn.grad.conv3d_weight(xr, (c, c, 3, 3, 3), dyr, padding=1).permute(0, 2, 3, 4, 1)
+    for f in (torch.isnan, torch.isposinf, torch.isneginf):
+        assert torch.equal(f(got), f(ref)), kind
+    ok = torch.isfinite(ref)
+    g, r = got[ok], ref[ok]
+    rms = r.square().mean().sqrt() if kind != "large" else r.abs().median()
+    assert float(((g - r).abs() / torch.maximum(r.abs(), rms)).max()) <= TOL
