@@ -1011,6 +1011,10 @@ size_t f32_min_workspace_bytes(const Geom& g, int pass) {
 // (the parts of the weights take 1.5 times their room; a call with the smaller workspace gets the fp32 instructions)
 size_t f32_workspace_bytes(const Geom& g, int pass) {
     size_t b = f32_min_workspace_bytes(g, pass), at;
+    if (f32_supported(g, pass) && pass == MI3D_PASS_WGRAD && f32s_wgrad_supported(g)) {
+        const size_t p = f32s_wgrad_workspace_bytes(g);
+        b = b > p ? b : p;
+    }
     if (f32_supported(g, pass) && split_ok(g, pass)) {
         const size_t p = split_pack_bytes(g, pass, &at);
         b = b > p ? b : p;
@@ -1285,6 +1289,7 @@ int f32_conv(const Geom& g, int pass, const void* in, const void* w, void* out, 
 int f32_wgrad(const Geom& g, const void* x, const void* dy, float* dw, void* ws, size_t ws_bytes, hipStream_t s) {
     if (f32_head(g)) return pointwise_f32_conv(g, MI3D_PASS_WGRAD, x, dy, dw, ws, ws_bytes, s);
     if (ws_bytes < f32_min_workspace_bytes(g, MI3D_PASS_WGRAD)) return MI3D_ERR_WORKSPACE;
+    if (f32s_wgrad_supported(g) && ws_bytes >= f32s_wgrad_workspace_bytes(g)) return f32s_wgrad(g, x, dy, dw, ws, ws_bytes, s);
     WgParams P;
     wgrad_layout(g, &P);
     P.x = P.x2 = (const float*)x;

@@ -165,6 +165,9 @@ int embed_k2_conv(const Geom& g, int pass, const void* a, const void* b, void* o
 
 // fp32 MFMA kernels: any kernel extent up to 3 and stride up to 2 (forward, data gradient, weight gradient)
 bool f32_supported(const Geom& g, int pass);
+bool f32s_wgrad_supported(const Geom& g);                  // conv_wgrad_f32s.hip
+size_t f32s_wgrad_workspace_bytes(const Geom& g);
+int f32s_wgrad(const Geom& g, const void* x, const void* dy, float* dw, void* ws, size_t ws_bytes, hipStream_t s);
 size_t f32_workspace_bytes(const Geom& g, int pass);       // what the fastest kernel wants
 size_t f32_min_workspace_bytes(const Geom& g, int pass);   // what a call needs at least
 int f32_conv(const Geom& g, int pass, const void* in, const void* w, void* out, void* ws, size_t ws_bytes, hipStream_t s);

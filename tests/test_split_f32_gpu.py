@@ -29,9 +29,9 @@ CASES = [
     (1, 3, 12, 12, 320, 320, 3, 1, 1),    # deepest level
     (1, 5, 11, 13, 32, 64, 3, 2, 1),      # parity classes of an odd extent
     (2, 4, 6, 70, 16, 64, 3, 2, 0),       # no padding: classes with one and two taps change places
-    (2, 17, 21, 65, 32, 32, 3, 1, 1),     # weight gradient: one row and column beyond its 4 x 32 patches
-    (1, 9, 30, 31, 64, 96, 3, 1, 0),
-    (3, 5, 15, 28, 96, 64, 3, 1, 2),      # padding 2: dy planes beyond both ends, segments of a few planes
+    (2, 49, 41, 65, 32, 32, 3, 1, 1),     # weight gradient: one row and column beyond its 4 x 32 patches
+    (1, 55, 30, 31, 64, 96, 3, 1, 0),
+    (3, 30, 15, 28, 96, 64, 3, 1, 2),     # padding 2: dy planes beyond both ends
     (1, 6, 8, 34, 16, 32, (1, 3, 3), 1, (0, 1, 1)),   # one plane per output
 ]
 
@@ -102,7 +102,7 @@ def test_values_without_parts_take_the_fp32_instructions(device, kind, q):
 @pytest.mark.parametrize("kind", ["inf", "nan_dy", "large", "tiny", "scaled"])
 def test_weight_gradient_of_values_without_parts(device, kind):
     torch.manual_seed(6)
-    N, D, H, W, c = 2, 12, 22, 40, 32
+    N, D, H, W, c = 2, 96, 22, 40, 32
     d = mc.make_desc(N, D, H, W, c, c, 3, 1, 1, torch.float32)
     x, dy = torch.randn((N, D, H, W, c), device="cuda"), torch.randn((N, D, H, W, c), device="cuda")
     if kind == "inf":
