@@ -166,8 +166,11 @@ __global__ void __launch_bounds__(256, 2) c4_fwd_kernel(C4Params P) {
             __builtin_amdgcn_sched_barrier(0);  // keeps the loads here, a whole tile ahead of the LDS write that uses them
 
             // input fragments: lane (voxel n, half h) holds voxels n + 2h and n + 2h + 1 of the row = taps kw 2h, 2h + 1
+            // (kw = 3 has no tap: its voxel lies outside the window and is cleared, a zero weight alone would turn an
+            // infinity or a NaN there into a NaN here)
             bf16x8 xf[3][RH + 2];
             const char* xl = lds + (wave * RH * PITCH + (lane & 31) + 2 * (lane >> 5)) * 8;
+            const bool tap = lane < 32;
 #pragma unroll
             for (int kd = 0; kd < 3; ++kd) {
                 const char* xs = xl + ((od + kd) & (SLOTS - 1)) * PLANE * 8;
@@ -175,7 +178,7 @@ __global__ void __launch_bounds__(256, 2) c4_fwd_kernel(C4Params P) {
                 for (int r = 0; r < RH + 2; ++r) {
                     const uint2 lo = *(const uint2*)(xs + (r * PITCH) * 8);
                     const uint2 hi = *(const uint2*)(xs + (r * PITCH + 1) * 8);
-                    const uint4 v = {lo.x, lo.y, hi.x, hi.y};
+                    const uint4 v = {lo.x, lo.y, tap ? hi.x : 0u, tap ? hi.y : 0u};
                     xf[kd][r] = __builtin_bit_cast(bf16x8, v);
                 }
             }
