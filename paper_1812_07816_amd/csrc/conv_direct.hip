@@ -3,49 +3,17 @@
 // shapes no tuned kernel covers and a slow cross-check for the MFMA kernels.
 // Definitions: forward / data-gradient / weight-gradient of the feature-map
 // layers whose outputs are kept for the backward pass (Section 3.1).
-#include "mi3d_internal.h"
+#include "conv_window.h"
 
 namespace mi3d {
 namespace {
-
-template <typename T> struct Elem;
-template <> struct Elem<float> {
-    static __device__ __forceinline__ float load(const float* p) { return *p; }
-    static __device__ __forceinline__ void store(float* p, float v) { *p = v; }
-};
-template <> struct Elem<uint16_t> {
-    static __device__ __forceinline__ float load(const uint16_t* p) { return bf16_to_f32(*p); }
-    static __device__ __forceinline__ void store(uint16_t* p, float v) { *p = f32_to_bf16_rne(v); }
-};
 
 template <typename T>
 __global__ void __launch_bounds__(256) fwd_kernel(Geom g, const T* __restrict__ x, const T* __restrict__ w, T* __restrict__ y) {
     long long total = g.out_voxels() * g.Cout;
     long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
     if (idx >= total) return;
-    int co = (int)(idx % g.Cout);
-    long long v = idx / g.Cout;
-    int ow = (int)(v % g.Wo); v /= g.Wo;
-    int oh = (int)(v % g.Ho); v /= g.Ho;
-    int od = (int)(v % g.Do);
-    int n = (int)(v / g.Do);
-    float acc = 0.f;
-    for (int kd = 0; kd < g.kD; ++kd) {
-        int id = od * g.sD - g.pD + kd;
-        if (id < 0 || id >= g.D) continue;
-        for (int kh = 0; kh < g.kH; ++kh) {
-            int ih = oh * g.sH - g.pH + kh;
-            if (ih < 0 || ih >= g.H) continue;
-            for (int kw = 0; kw < g.kW; ++kw) {
-                int iw = ow * g.sW - g.pW + kw;
-                if (iw < 0 || iw >= g.W) continue;
-                const T* xp = x + ((((long long)n * g.D + id) * g.H + ih) * g.W + iw) * g.Cin;
-                const T* wp = w + ((((long long)co * g.kD + kd) * g.kH + kh) * g.kW + kw) * g.Cin;
-                for (int ci = 0; ci < g.Cin; ++ci) acc = fmaf(Elem<T>::load(xp + ci), Elem<T>::load(wp + ci), acc);
-            }
-        }
-    }
-    Elem<T>::store(y + idx, acc);
+    Elem<T>::store(y + idx, fwd_sum(g, x, w, idx));
 }
 
 template <typename T>
@@ -53,36 +21,7 @@ __global__ void __launch_bounds__(256) dgrad_kernel(Geom g, const T* __restrict_
     long long total = g.in_voxels() * g.Cin;
     long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
     if (idx >= total) return;
-    int ci = (int)(idx % g.Cin);
-    long long v = idx / g.Cin;
-    int iw = (int)(v % g.W); v /= g.W;
-    int ih = (int)(v % g.H); v /= g.H;
-    int id = (int)(v % g.D);
-    int n = (int)(v / g.D);
-    float acc = 0.f;
-    for (int kd = 0; kd < g.kD; ++kd) {
-        int nd = id + g.pD - kd;
-        if (nd < 0 || nd % g.sD) continue;
-        int od = nd / g.sD;
-        if (od >= g.Do) continue;
-        for (int kh = 0; kh < g.kH; ++kh) {
-            int nh = ih + g.pH - kh;
-            if (nh < 0 || nh % g.sH) continue;
-            int oh = nh / g.sH;
-            if (oh >= g.Ho) continue;
-            for (int kw = 0; kw < g.kW; ++kw) {
-                int nw = iw + g.pW - kw;
-                if (nw < 0 || nw % g.sW) continue;
-                int ow = nw / g.sW;
-                if (ow >= g.Wo) continue;
-                const T* gp = dy + ((((long long)n * g.Do + od) * g.Ho + oh) * g.Wo + ow) * g.Cout;
-                const T* wp = w + (((long long)kd * g.kH + kh) * g.kW + kw) * g.Cin + ci;
-                long long wstride = g.taps() * g.Cin;
-                for (int co = 0; co < g.Cout; ++co) acc = fmaf(Elem<T>::load(gp + co), Elem<T>::load(wp + co * wstride), acc);
-            }
-        }
-    }
-    Elem<T>::store(dx + idx, acc);
+    Elem<T>::store(dx + idx, dgrad_sum(g, dy, w, idx));
 }
 
 // Stage 1 of wgrad: block (pair-block, tap, chunk); each thread owns one
@@ -101,18 +40,7 @@ __global__ void __launch_bounds__(256) wgrad_partial_kernel(Geom g, const T* __r
     long long P = g.out_voxels();
     if (v1 > P) v1 = P;
     float acc = 0.f;
-    for (long long v = v0; v < v1; ++v) {
-        long long r = v;
-        int ow = (int)(r % g.Wo); r /= g.Wo;
-        int oh = (int)(r % g.Ho); r /= g.Ho;
-        int od = (int)(r % g.Do);
-        int n = (int)(r / g.Do);
-        int id = od * g.sD - g.pD + kd, ih = oh * g.sH - g.pH + kh, iw = ow * g.sW - g.pW + kw;
-        if (id < 0 || id >= g.D || ih < 0 || ih >= g.H || iw < 0 || iw >= g.W) continue;
-        float a = Elem<T>::load(dy + v * g.Cout + co);
-        float b = Elem<T>::load(x + ((((long long)n * g.D + id) * g.H + ih) * g.W + iw) * g.Cin + ci);
-        acc = fmaf(a, b, acc);
-    }
+    for (long long v = v0; v < v1; ++v) acc = wgrad_add(g, x, dy, co, kd, kh, kw, ci, v, acc);
     part[(long long)chunk * g.w_elems() + ((long long)co * g.taps() + t) * g.Cin + ci] = acc;
 }
 

@@ -7,7 +7,7 @@
 //     between), after which dx and dw are exactly the stride-1 gradients.
 // They trade extra MFMA work and one extra pass over a tensor for not falling
 // back to the plain kernels; dedicated kernels replace them where it matters.
-#include "mi3d_internal.h"
+#include "conv_window.h"
 
 namespace mi3d {
 namespace {
@@ -15,7 +15,8 @@ namespace {
 // Zero-padding of channel rows: dst[v][0..CP) = src[v][0..C) followed by zeros for v < rows, all zeros for the rows up to
 // rows_p.  Two independent jobs share a launch (the activations and the weights of a pass): these passes take a few
 // microseconds each, about what a launch costs.  One thread per 8 channels of dst; rows whose length is a multiple of 8
-// are read 16 bytes at a time.
+// are read 16 bytes at a time.  wflag (null: none): one word per block of the job `weights` (0 or 1), 1 where the block
+// met an infinity or a NaN.
 struct PadJob {
     const uint16_t* src;
     uint16_t* dst;
@@ -23,51 +24,155 @@ struct PadJob {
     int C, CP;
     __host__ __device__ long long threads() const { return rows_p * (CP / 8); }
 };
-__global__ void __launch_bounds__(256) pad_channels_kernel(PadJob a, PadJob b) {
+__device__ __forceinline__ bool bf16_nonfinite(uint32_t v) { return (v & 0x7F80u) == 0x7F80u; }
+__device__ __forceinline__ bool pair_nonfinite(uint32_t v) { return bf16_nonfinite(v) | bf16_nonfinite(v >> 16); }
+__global__ void __launch_bounds__(256) pad_channels_kernel(PadJob a, PadJob b, uint32_t* __restrict__ wflag, int weights) {
     long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
     const bool second = idx >= a.threads();
     if (second) idx -= a.threads();
     const PadJob& J = second ? b : a;
-    if (idx >= J.threads()) return;
-    const int per = J.CP / 8;
-    const long long v = idx / per;
-    const int c0 = (int)(idx - v * per) * 8;
     uint4 out = {0, 0, 0, 0};
-    if (v < J.rows) {
-        const uint16_t* src = J.src + v * J.C + c0;
-        if (J.C % 8 == 0) {
-            if (c0 < J.C) out = *(const uint4*)src;
-        } else {
-            uint32_t o[4] = {0, 0, 0, 0};
+    if (idx < J.threads()) {
+        const int per = J.CP / 8;
+        const long long v = idx / per;
+        const int c0 = (int)(idx - v * per) * 8;
+        if (v < J.rows) {
+            const uint16_t* src = J.src + v * J.C + c0;
+            if (J.C % 8 == 0) {
+                if (c0 < J.C) out = *(const uint4*)src;
+            } else {
+                uint32_t o[4] = {0, 0, 0, 0};
 #pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (c0 + j < J.C) o[j >> 1] |= (uint32_t)src[j] << (16 * (j & 1));
-            out = uint4{o[0], o[1], o[2], o[3]};
+                for (int j = 0; j < 8; ++j)
+                    if (c0 + j < J.C) o[j >> 1] |= (uint32_t)src[j] << (16 * (j & 1));
+                out = uint4{o[0], o[1], o[2], o[3]};
+            }
         }
+        *(uint4*)(J.dst + v * J.CP + c0) = out;
     }
-    *(uint4*)(J.dst + v * J.CP + c0) = out;
+    if (!wflag) return;
+    const int first = weights ? (int)(a.threads() / 256) : 0;   // block in which the weights begin
+    if ((int)blockIdx.x < first) return;
+    const bool bad = second == (weights == 1) && (pair_nonfinite(out.x) | pair_nonfinite(out.y) | pair_nonfinite(out.z) | pair_nonfinite(out.w));
+    const int any = __syncthreads_or(bad);
+    if (threadIdx.x == 0) wflag[blockIdx.x - first] = any ? 1u : 0u;
 }
 // the same with rows padded to 4 channels (inputs with fewer than 4 channels): one thread per row
-__global__ void __launch_bounds__(256) pad_to4_kernel(const uint16_t* __restrict__ src, uint16_t* __restrict__ dst, long long rows, long long rows_p, int C) {
+__global__ void __launch_bounds__(256) pad_to4_kernel(const uint16_t* __restrict__ src, uint16_t* __restrict__ dst, long long rows, long long rows_p, int C,
+                                                      uint32_t* __restrict__ wflag) {
     const long long v = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (v >= rows_p) return;
     uint32_t o[2] = {0, 0};
     if (v < rows)
         for (int j = 0; j < C; ++j) o[j >> 1] |= (uint32_t)src[v * C + j] << (16 * (j & 1));
-    *(uint2*)(dst + v * 4) = uint2{o[0], o[1]};
+    if (v < rows_p) *(uint2*)(dst + v * 4) = uint2{o[0], o[1]};
+    if (!wflag) return;
+    const int any = __syncthreads_or(pair_nonfinite(o[0]) | pair_nonfinite(o[1]));
+    if (threadIdx.x == 0) wflag[blockIdx.x] = any ? 1u : 0u;
 }
 
-// dst[v][0..C) = src[v][0..C) of CP-channel rows (T = uint16_t or float), V elements per thread (16 bytes, or one where C
-// is not a multiple of that)
-template <typename T, int V>
-__global__ void __launch_bounds__(256) slice_channels_kernel(const T* __restrict__ src, T* __restrict__ dst, long long voxels, int C, int CP) {
+// ---- results of the padded layer ----
+// The matrix-core kernels add zeros where a window or a patch leaves the volume, and 0 x inf is NaN: a NaN of theirs need
+// not be one.  Whatever comes out as NaN is formed again as the sum over its window alone; other values cannot have met
+// such a zero.  Looking for them costs nothing where results are sliced and a launch where they are not (48 -> 48 at
+// 37 x 50 x 61 222.9 -> 223.9 us, 40 -> 96 forward at 64^3 126 -> 130); with nothing but NaN in all operands a pass costs
+// about what the plain kernels take (48 -> 48 weight gradient 43 ms).
+
+// y or dx, channels [0, C) of CP-channel rows; V elements per thread (16 bytes, or one where C is not a multiple of 8)
+__device__ __forceinline__ uint16_t exact_bf16(const Geom& g, int pass, const uint16_t* in, const uint16_t* w, long long e) {
+    return f32_to_bf16_rne(pass == MI3D_PASS_FWD ? fwd_sum<uint16_t, true>(g, in, w, e) : dgrad_sum<uint16_t, true>(g, in, w, e));
+}
+__device__ __forceinline__ bool bf16_nan(uint32_t v) { return (v & 0x7FFFu) > 0x7F80u; }
+__device__ __forceinline__ bool pair_nan(uint32_t v) { return bf16_nan(v) | bf16_nan(v >> 16); }
+__device__ __forceinline__ uint32_t exact_pair(const Geom& g, int pass, const uint16_t* in, const uint16_t* w, long long e, uint32_t v) {
+    if (bf16_nan(v)) v = (v & 0xFFFF0000u) | exact_bf16(g, pass, in, w, e);
+    if (bf16_nan(v >> 16)) v = (v & 0xFFFFu) | (uint32_t)exact_bf16(g, pass, in, w, e + 1) << 16;
+    return v;
+}
+template <int V>
+__global__ void __launch_bounds__(256) slice_channels_kernel(Geom g, int pass, const uint16_t* __restrict__ in, const uint16_t* __restrict__ w,
+                                                             const uint16_t* __restrict__ src, uint16_t* __restrict__ dst, long long voxels, int C, int CP) {
     const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
     const int per = C / V;
     if (idx >= voxels * per) return;
     const long long v = idx / per;
     const int c = (int)(idx - v * per) * V;
-    if constexpr (V == 1) dst[v * C + c] = src[v * CP + c];
-    else *(uint4*)(dst + v * C + c) = *(const uint4*)(src + v * CP + c);
+    if constexpr (V == 1) {
+        uint16_t o = src[v * CP + c];
+        if (bf16_nan(o)) o = exact_bf16(g, pass, in, w, idx);
+        dst[idx] = o;
+    } else {
+        uint4 o = *(const uint4*)(src + v * CP + c);
+        if (pair_nan(o.x) | pair_nan(o.y) | pair_nan(o.z) | pair_nan(o.w)) {
+            uint32_t q[4] = {o.x, o.y, o.z, o.w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) q[j] = exact_pair(g, pass, in, w, idx * 8 + 2 * j, q[j]);
+            o = uint4{q[0], q[1], q[2], q[3]};
+        }
+        *(uint4*)(dst + idx * 8) = o;
+    }
+}
+
+// The same in place, for results that need no slicing (a multiple of 4 elements): only where a weight is not finite (flags
+// of the padding kernel; the kernels keep to the window of an activation), or, with flags null, on any NaN.
+__global__ void __launch_bounds__(256) exact_in_place_kernel(Geom g, int pass, const uint16_t* __restrict__ in, const uint16_t* __restrict__ w,
+                                                             uint16_t* __restrict__ out, long long n4, const uint32_t* __restrict__ flags, int nflags) {
+    if (flags) {
+        uint32_t f = 0;
+        for (int i = threadIdx.x; i < nflags; i += 256) f |= flags[i];
+        if (!__syncthreads_or((int)f)) return;
+    }
+    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n4; i += (long long)gridDim.x * 256) {
+        const uint2 o = *(const uint2*)(out + 4 * i);
+        if (pair_nan(o.x) | pair_nan(o.y))
+            *(uint2*)(out + 4 * i) = uint2{exact_pair(g, pass, in, w, 4 * i, o.x), exact_pair(g, pass, in, w, 4 * i + 2, o.y)};
+    }
+}
+
+// dw, V elements per thread.  The NaN of a block are formed again one after the other by all its threads: partial sums
+// over every 256th voxel, added in a fixed order.
+template <int V>
+__global__ void __launch_bounds__(256) slice_dw_kernel(Geom g, const uint16_t* __restrict__ x, const uint16_t* __restrict__ dy, const float* __restrict__ src,
+                                                       float* __restrict__ dst, int CP) {
+    const int t = threadIdx.x;
+    const long long idx = (long long)blockIdx.x * 256 + t, rows = g.taps() * g.Cout;
+    const int C = g.Cin, per = C / V;
+    bool nan = false;
+    if (idx < rows * per) {
+        const long long v = idx / per;
+        const int c = (int)(idx - v * per) * V;
+        if constexpr (V == 1) {
+            const float o = dst[idx] = src[v * CP + c];
+            nan = o != o;
+        } else {
+            const float4 o = *(float4*)(dst + 4 * idx) = *(const float4*)(src + v * CP + c);
+            nan = (o.x != o.x) | (o.y != o.y) | (o.z != o.z) | (o.w != o.w);
+        }
+    }
+    if (!__syncthreads_or(nan)) return;
+    __shared__ float red[256];
+    const long long first = (long long)blockIdx.x * 256 * V, last = first + 256 * V < rows * C ? first + 256 * V : rows * C, vox = g.out_voxels();
+    for (long long e = first; e < last; ++e) {
+        const float now = dst[e];      // (each element is written by this block alone, before the barrier above or at the end of its turn)
+        if (!__syncthreads_or(now != now)) continue;
+        const int ci = (int)(e % C);
+        const long long r = e / C;
+        const int tap = (int)(r % g.taps()), co = (int)(r / g.taps());
+        const int kd = tap / (g.kH * g.kW), kh = tap / g.kW % g.kH, kw = tap % g.kW;
+        float acc = 0.f;
+        for (long long v0 = 0; v0 < vox; v0 += 256 * 64) {
+            const long long v1 = v0 + 256 * 64 < vox ? v0 + 256 * 64 : vox;
+            for (long long v = v0 + t; v < v1; v += 256) acc = wgrad_add(g, x, dy, co, kd, kh, kw, ci, v, acc);
+            if (__syncthreads_or(acc != acc)) break;       // NaN it stays
+        }
+        red[t] = acc;
+        __syncthreads();
+        for (int h = 128; h > 0; h >>= 1) {
+            if (t < h) red[t] += red[t + h];
+            __syncthreads();
+        }
+        if (t == 0) dst[e] = red[0];
+        __syncthreads();
+    }
 }
 
 // up[n][s*od][s*oh][s*ow][:] = dy[n][od][oh][ow][:], zero elsewhere; up has extents (Du,Hu,Wu).
@@ -117,7 +222,9 @@ unsigned blocks_for(long long n) { return (unsigned)((n + 255) / 256); }
 
 // ---- channel counts that no MFMA kernel takes --------------------------------
 // The padded layer: channels rounded up to multiples of 32 (stride 2: the data-gradient kernel walks output channels in
-// chunks of 64), or input channels to 4 where the first-layer kernels then apply.
+// chunks of 64), or input channels to 4 where the first-layer kernels then apply.  2x2x2 layers get multiples of 64: the
+// kernel for them takes those, the embedding into 3x3x3 reads voxels outside the window, times zero, and does 27/8 of the work
+// (24 -> 24 at 30^3, N = 2, padded to 32 / to 64: 28.7 / 18.8, 22.4 / 18.4, 32.4 / 22.2 us for the three passes).
 static Geom padded_geom(const Geom& g, int pass) {
     Geom p = g;
     p.Cout = (g.Cout + 31) / 32 * 32;
@@ -126,21 +233,24 @@ static Geom padded_geom(const Geom& g, int pass) {
         if (pass == MI3D_PASS_FWD ? c4_fwd_supported(p) : pass == MI3D_PASS_DGRAD ? c4_dgrad_supported(p) : c4_wgrad_supported(p)) return p;
     }
     p.Cin = (g.Cin + 31) / 32 * 32;
-    if (g.sD == 2 && p.Cout > 32) p.Cout = (p.Cout + 63) / 64 * 64;
+    if (g.kD == 2 || (g.sD == 2 && p.Cout > 32)) p.Cout = (p.Cout + 63) / 64 * 64;
     return p;
 }
 
-// bytes of the padded operands and result in the workspace: x-shaped, y-shaped, weight-shaped tensors (0: not padded)
+// bytes of the padded operands and result in the workspace: x-shaped, y-shaped, weight-shaped tensors, flags of the
+// weights (0: not needed)
 struct EmbedC {
     Geom p;
-    size_t xb, yb, wb;
+    size_t xb, yb, wb, fb;
 };
+static long long weight_threads(const Geom& p) { return p.taps() * p.Cout * (p.Cin % 8 ? 1 : p.Cin / 8); }   // of the padding kernels
 static EmbedC embed_c_layout(const Geom& g, int pass) {
-    EmbedC e{padded_geom(g, pass), 0, 0, 0};
+    EmbedC e{padded_geom(g, pass), 0, 0, 0, 0};
     const bool ci = e.p.Cin != g.Cin, co = e.p.Cout != g.Cout;
     if (ci) e.xb = align256((size_t)g.in_voxels() * e.p.Cin * 2);
     if (co) e.yb = align256((size_t)g.out_voxels() * e.p.Cout * 2);
     if (ci || co) e.wb = align256((size_t)e.p.w_elems() * (pass == MI3D_PASS_WGRAD ? 4 : 2));
+    if (e.wb && (pass == MI3D_PASS_FWD ? !co : pass == MI3D_PASS_DGRAD && !ci)) e.fb = align256((size_t)(weight_threads(e.p) / 256 + 2) * 4);
     return e;
 }
 
@@ -154,12 +264,7 @@ bool embed_c_supported(const Geom& g, int pass) {
 size_t embed_c_workspace_bytes(const Geom& g, int pass) {
     if (!embed_c_supported(g, pass)) return 0;
     const EmbedC e = embed_c_layout(g, pass);
-    return e.xb + e.yb + e.wb + align256(auto_workspace_bytes(e.p, pass));
-}
-
-static int pad_rows(const uint16_t* src, uint16_t* dst, long long rows, long long rows_p, int C, int CP, hipStream_t s) {
-    pad_to4_kernel<<<blocks_for(rows_p), 256, 0, s>>>(src, dst, rows, rows_p, C);
-    return check_launch();
+    return e.xb + e.yb + e.wb + e.fb + align256(auto_workspace_bytes(e.p, pass));
 }
 
 // Bound: the copies are a pass over each operand and one more launch, the plain kernels do one product at a time per thread.
@@ -173,44 +278,58 @@ int embed_c_conv(const Geom& g, int pass, const void* a, const void* b, void* ou
     uint16_t* xp = (uint16_t*)ws;
     uint16_t* yp = (uint16_t*)((char*)ws + e.xb);
     void* wp = (char*)ws + e.xb + e.yb;
-    void* rest = (char*)wp + e.wb;
-    const size_t rest_bytes = ws_bytes - e.xb - e.yb - e.wb;
+    uint32_t* flags = e.fb ? (uint32_t*)((char*)wp + e.wb) : nullptr;
+    void* rest = (char*)wp + e.wb + e.fb;
+    const size_t rest_bytes = ws_bytes - e.xb - e.yb - e.wb - e.fb;
     const long long T = g.taps();
     int st = MI3D_OK;
     // operands: the activations that are read (x, dy) and the weights, in one launch
     PadJob jobs[2] = {};
-    int n = 0;
-    auto add = [&](const void* src, void* dst, long long rows, long long rows_p, int C, int CP) {
-        if (CP % 8) st = pad_rows((const uint16_t*)src, (uint16_t*)dst, rows, rows_p, C, CP, s);   // (4 channels)
-        else jobs[n++] = PadJob{(const uint16_t*)src, (uint16_t*)dst, rows, rows_p, C, CP};
+    int n = 0, nflags = 0;
+    auto add = [&](const void* src, void* dst, long long rows, long long rows_p, int C, int CP, uint32_t* f) {
+        if (CP % 8 == 0) { jobs[n++] = PadJob{(const uint16_t*)src, (uint16_t*)dst, rows, rows_p, C, CP}; return; }
+        pad_to4_kernel<<<blocks_for(rows_p), 256, 0, s>>>((const uint16_t*)src, (uint16_t*)dst, rows, rows_p, C, f);   // (4 channels)
+        if (f) nflags = (int)blocks_for(rows_p);
+        st = check_launch();
     };
     const void* x = pass == MI3D_PASS_DGRAD ? nullptr : a;
     const void* dy = pass == MI3D_PASS_DGRAD ? a : (pass == MI3D_PASS_WGRAD ? b : nullptr);
-    if (x && e.xb) { add(x, xp, g.in_voxels(), g.in_voxels(), g.Cin, p.Cin); x = xp; }
+    if (x && e.xb) { add(x, xp, g.in_voxels(), g.in_voxels(), g.Cin, p.Cin, nullptr); x = xp; }
     if (st) return st;
-    if (dy && e.yb) { add(dy, yp, g.out_voxels(), g.out_voxels(), g.Cout, p.Cout); dy = yp; }
-    if (pass != MI3D_PASS_WGRAD) add(b, wp, T * g.Cout, T * p.Cout, g.Cin, p.Cin);
+    if (dy && e.yb) { add(dy, yp, g.out_voxels(), g.out_voxels(), g.Cout, p.Cout, nullptr); dy = yp; }
+    if (pass != MI3D_PASS_WGRAD) add(b, wp, T * g.Cout, T * p.Cout, g.Cin, p.Cin, flags);
     if (st) return st;
     if (n) {
-        pad_channels_kernel<<<blocks_for(jobs[0].threads() + (n > 1 ? jobs[1].threads() : 0)), 256, 0, s>>>(jobs[0], jobs[1]);
+        const unsigned blocks = blocks_for(jobs[0].threads() + (n > 1 ? jobs[1].threads() : 0));
+        uint32_t* f = p.Cin % 8 ? nullptr : flags;     // (weights of 4 channels have had their launch)
+        if (f) nflags = (int)blocks - (n > 1 ? (int)(jobs[0].threads() / 256) : 0);
+        pad_channels_kernel<<<blocks, 256, 0, s>>>(jobs[0], jobs[1], f, n - 1);
         if ((st = check_launch())) return st;
     }
     // the padded layer, then the channels that were asked for
     if (pass == MI3D_PASS_WGRAD) {
         if ((st = auto_conv(p, pass, x, dy, wp, rest, rest_bytes, s))) return st;
         const long long rows = T * g.Cout;
-        if (g.Cin % 4 == 0) slice_channels_kernel<float, 4><<<blocks_for(rows * (g.Cin / 4)), 256, 0, s>>>((const float*)wp, (float*)out, rows, g.Cin, p.Cin);
-        else slice_channels_kernel<float, 1><<<blocks_for(rows * g.Cin), 256, 0, s>>>((const float*)wp, (float*)out, rows, g.Cin, p.Cin);
+        if (g.Cin % 4 == 0) slice_dw_kernel<4><<<blocks_for(rows * (g.Cin / 4)), 256, 0, s>>>(g, (const uint16_t*)a, (const uint16_t*)b, (const float*)wp, (float*)out, p.Cin);
+        else slice_dw_kernel<1><<<blocks_for(rows * g.Cin), 256, 0, s>>>(g, (const uint16_t*)a, (const uint16_t*)b, (const float*)wp, (float*)out, p.Cin);
         return check_launch();
     }
     const bool fwd = pass == MI3D_PASS_FWD;
     const int C = fwd ? g.Cout : g.Cin, CP = fwd ? p.Cout : p.Cin;
     uint16_t* padded_out = C != CP ? (fwd ? yp : xp) : (uint16_t*)out;
     if ((st = auto_conv(p, pass, fwd ? x : dy, wp, padded_out, rest, rest_bytes, s))) return st;
-    if (C == CP) return MI3D_OK;
     const long long rows = fwd ? g.out_voxels() : g.in_voxels();
-    if (C % 8 == 0) slice_channels_kernel<uint16_t, 8><<<blocks_for(rows * (C / 8)), 256, 0, s>>>(padded_out, (uint16_t*)out, rows, C, CP);
-    else slice_channels_kernel<uint16_t, 1><<<blocks_for(rows * C), 256, 0, s>>>(padded_out, (uint16_t*)out, rows, C, CP);
+    const uint16_t *in = (const uint16_t*)a, *w = (const uint16_t*)b;
+    if (C == CP) {
+        // (the 3x3x3 embedding of a 2x2x2 layer reads beyond the window; the data gradient of 4 channels adds zero rows)
+        const bool any = (g.kD == 2 && !k2_supported(p, pass)) || C == 4;
+        const long long n4 = rows * C / 4;
+        exact_in_place_kernel<<<(unsigned)(n4 < 256 * 256 ? (n4 + 255) / 256 : 256), 256, 0, s>>>(g, pass, in, w, (uint16_t*)out, n4, any ? nullptr : flags, nflags);
+    } else if (C % 8 == 0) {
+        slice_channels_kernel<8><<<blocks_for(rows * (C / 8)), 256, 0, s>>>(g, pass, in, w, padded_out, (uint16_t*)out, rows, C, CP);
+    } else {
+        slice_channels_kernel<1><<<blocks_for(rows * C), 256, 0, s>>>(g, pass, in, w, padded_out, (uint16_t*)out, rows, C, CP);
+    }
     return check_launch();
 }
 
