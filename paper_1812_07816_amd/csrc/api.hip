@@ -20,6 +20,19 @@ int check_launch() {
     return MI3D_OK;
 }
 
+int cu_count() {
+    static std::atomic<int> known[64] = {};
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+    int cus = known[dev];
+    if (cus == 0) {
+        cus = 256;
+        (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+        known[dev] = cus;
+    }
+    return cus;
+}
+
 int make_geom(const mi3d_conv_desc* d, Geom* g) {
     if (!d) return MI3D_ERR_INVALID_ARG;
     if (d->N <= 0 || d->D <= 0 || d->H <= 0 || d->W <= 0 || d->Cin <= 0 || d->Cout <= 0) return MI3D_ERR_INVALID_ARG;

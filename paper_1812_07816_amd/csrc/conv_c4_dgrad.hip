@@ -304,9 +304,7 @@ int c4_dgrad(const Geom& g, const void* dy, const void* w, void* dx, void* ws, s
     P.HT = (P.Ho + TH - 1) / TH;
     P.WT = (P.Wo + TW - 1) / TW;
     P.units = (long long)P.N * P.HT * P.WT * P.Do;
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    long long nwg = cus;
+    long long nwg = cu_count();
     if (nwg > P.units) nwg = P.units;
     P.nwg = (int)nwg;
     static std::atomic<bool> attr_set{false};   // set once per process; a second thread racing here repeats an idempotent call

@@ -427,8 +427,7 @@ bool dgrad_s2_fuses_skip_sums(const Geom& g) { return dgrad_s2_supported(g) && g
 static void dg2_layout(const Geom& g, long long* units, int* nwg, int* max_seg) {
     const int QD = (g.D + 1) / 2, HT = ((g.H + 1) / 2 + RP - 1) / RP, WT = ((g.W + 1) / 2 + CP - 1) / CP;
     *units = (long long)g.N * (g.Cin / 32) * HT * WT * QD;
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    const int cus = cu_count();
     *nwg = (int)(cus < *units ? cus : *units);
     *max_seg = (int)(((*units + *nwg - 1) / *nwg + QD - 1) / QD) + 1;
 }
@@ -476,8 +475,7 @@ int dgrad_s2(const Geom& g, const void* dy, const void* w, void* dx, void* ws, s
     G.WT = ((g.W + 1) / 2 + CP - 1) / CP;
     G.CiT = g.Cin / 32;
     G.units = (long long)g.N * G.CiT * G.HT * G.WT * G.QD;
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    const int cus = cu_count();
     const long long nwg = cus < G.units ? cus : G.units;
     G.nwg = (int)nwg;
     const size_t lds = (size_t)27 * KK * 1024 + 2 * (size_t)(2 * KK) * SLABV * 16;

@@ -21,6 +21,7 @@
 // (dealt round-robin to its 8 waves) over a range of position tiles; per-workgroup partial sums are added in index
 // order by reduce_partials (bit-reproducible).
 #include "mi3d_internal.h"
+#include "split_f32.h"
 
 namespace mi3d {
 namespace {
@@ -278,7 +279,6 @@ __global__ void __launch_bounds__(64 * NW, 2) f32_gconv_kernel(GcParams P) {
 // A value the split cannot hold (infinities, NaN, magnitudes from 2^126 and below 2^-100 other than zero, whose parts would
 // overflow or lose bits) sends its stage, or its whole tile if it is a weight, through v_mfma_f32_32x32x2_f32 on the
 // values themselves, so that results are those of the fp32 kernel there too.
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 constexpr int SP_NT = 256, SP_CK = 16;
 constexpr int SP_MAXV = 448;                       // staged voxels (bound of the dispatch rule)
 constexpr int SP_NPX = SP_MAXV * (SP_CK / 4) / SP_NT;   // 16-byte pieces of the patch per thread
@@ -293,32 +293,6 @@ struct GsParams {
     uint32_t taps[MAX_TAPS];     // voxel offset in the patch | index in the layer's tap order << 16 (scalar loads have no bytes)
 };
 
-// Magnitudes whose three parts are exact: zero and 2^-100 ... 2^126.  Zero counts as large in the minimum (0 - 1 wraps).
-struct SplitRange {
-    uint32_t most = 0, least = 0xFFFFFFFFu;
-    __device__ __forceinline__ void add(float v) {
-        const uint32_t u = __builtin_bit_cast(uint32_t, v) & 0x7FFFFFFFu;
-        most = u > most ? u : most;
-        least = u - 1 < least ? u - 1 : least;
-    }
-    __device__ __forceinline__ void add(const float4& v) { add(v.x); add(v.y); add(v.z); add(v.w); }
-    __device__ __forceinline__ bool exceeded() const { return (most >= 0x7E800000u) | (least < 0x0D7FFFFFu); }
-};
-__device__ __forceinline__ uint32_t cvt2(float a, float b) {
-    typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
-    typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
-    f32x2 v = {a, b};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-}
-// the three parts of two values, packed
-__device__ __forceinline__ void split2(float x, float y, uint32_t (&o)[3]) {
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-        o[p] = cvt2(x, y);
-        x -= __builtin_bit_cast(float, o[p] << 16);
-        y -= __builtin_bit_cast(float, o[p] & 0xFFFF0000u);
-    }
-}
 __device__ __forceinline__ f32x16 mfma16(bf16x8 a, bf16x8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
 
 // One wave per fragment: 32 output channels x 16 contracted channels of a tap.  grid.x * 4 waves >= T * K / 16 * Mpad / 32.
@@ -841,12 +815,6 @@ __global__ void __launch_bounds__(256, 2) f32_wgrad_c4_kernel(WgParams P) {
         const int co = co0 + 8 * (i >> 2) + 4 * half + (i & 3);
         if (col_ok && co < P.Cout) part[((long long)co * 27 + tap) * P.Cin + ci] = acc[0][i] + acc[1][i];
     }
-}
-
-int cu_count() {
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    return cus;
 }
 
 // one axis of the gather convolution: valid taps of a class and their input offsets

@@ -359,12 +359,6 @@ __global__ void __launch_bounds__(256) ig_sum_kernel(const float* __restrict__ p
     }
 }
 
-int cu_count() {
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    return cus;
-}
-
 // Tile shape and splits of the contraction, by a model of the time: a round of two workgroups per CU takes STEP_US per
 // step, partial sums are written and read at PART_BYTES_PER_US.
 struct IgPlan {

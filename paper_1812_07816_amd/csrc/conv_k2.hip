@@ -351,9 +351,7 @@ static int k2_wgrad_slots(const Geom& g) {
     const int pairs = (g.Cout / WCO) * (g.Cin / WCI);
     const long long vox = (long long)g.N * g.Do * g.Ho * g.Wo;
     const long long stages = (vox + WV - 1) / WV;
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    long long slots = 2ll * cus / pairs;          // two workgroups per CU
+    long long slots = 2ll * cu_count() / pairs;          // two workgroups per CU
     if (slots < 1) slots = 1;
     if (slots > stages) slots = stages;
     return (int)slots;
@@ -425,10 +423,8 @@ int k2_conv(const Geom& g, int pass, const void* a, const void* w, void* out, vo
     else { P.K16 = g.Cout / 16; blocks = g.Cin / 4; G = pick_g(blocks, P.K16, 64); }
     P.NG = blocks / G;
     const long long tiles = (P.vox + 127) / 128;
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     // a multiple of NG workgroups, about one (forward) or two (data gradient) per CU, no more than there are units
-    long long per_group = (long long)(mode == 0 ? cus : 2 * cus) / P.NG;
+    long long per_group = (long long)((mode == 0 ? 1 : 2) * cu_count()) / P.NG;
     if (per_group < 1) per_group = 1;
     if (per_group > tiles) per_group = tiles;
     P.nwg = (int)(per_group * P.NG);

@@ -330,8 +330,7 @@ int s2_fwd(const Geom& g, const void* x, const void* w, void* y, void* ws, size_
     P.HT = (g.Ho + th - 1) / th;
     P.WT = (g.Wo + TW - 1) / TW;
     P.units = (long long)g.N * P.CT * P.HT * P.WT * g.Do;
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    const int cus = cu_count();
     long long nwg = cus < P.units ? cus : P.units;
     P.nwg = (int)nwg;
     P.slope = g.slope;

@@ -676,12 +676,6 @@ static int sp_plane_tiles(int Ho, int Wo, int* wtf, int* htp) {
     return HT * *wtf + *htp;
 }
 
-static int sp_cu_count() {
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    return cus;
-}
-
 // Volumes with fewer (cout tile, patch, plane) units than two per CU, for layers that contract at least 96 channels:
 // units of whole planes leave CUs idle, and patches cover small planes badly.  The implicit GEMM of conv_ig.hip takes
 // them.  Forward / data gradient, this kernel's former 32-channel chunks of work -> implicit GEMM (us): 320->320 at 12^3
@@ -693,7 +687,7 @@ bool few_units(const Geom& g, int pass) {
     const int Do = flip ? g.D : g.Do, Ho = flip ? g.H : g.Ho, Wo = flip ? g.W : g.Wo;
     int wtf, htp;
     const long long units = (long long)g.N * (cout / 32) * sp_plane_tiles(Ho, Wo, &wtf, &htp) * Do;
-    return cin >= 96 && units < 2ll * sp_cu_count();
+    return cin >= 96 && units < 2ll * cu_count();
 }
 
 static size_t sp_part_offset(const Geom& g) { return (((size_t)g.w_elems() * 2 + 255) & ~(size_t)255) + 8192; }
@@ -704,7 +698,7 @@ static void sp_stat_layout(const Geom& g, int pass, long long* units, int* nwg, 
     const int cout = flip ? g.Cin : g.Cout, Do = flip ? g.D : g.Do, Ho = flip ? g.H : g.Ho, Wo = flip ? g.W : g.Wo;
     int wtf, htp;
     *units = (long long)g.N * (cout / 32) * sp_plane_tiles(Ho, Wo, &wtf, &htp) * Do;
-    long long n = sp_cu_count();
+    long long n = cu_count();
     if (n > *units) n = *units;
     *nwg = (int)n;
     const long long per_wg = (*units + n - 1) / n;
@@ -759,7 +753,7 @@ int conv(const Geom& g, int pass, const void* in, const void* w, void* out, void
     P.ref = mask || bstat ? (const uint16_t*)g.ref : nullptr;
     P.stat_slope = bstat ? g.slope : 1.f;
     P.units = (long long)P.N * P.CT * sp_plane_tiles(P.Ho, P.Wo, &P.WTF, &P.HTP) * P.Do;
-    long long nwg = sp_cu_count();
+    long long nwg = cu_count();
     if (nwg > P.units) nwg = P.units;
     P.nwg = (int)nwg;
     const bool stat = pass == MI3D_PASS_FWD && g.stats;
@@ -835,10 +829,8 @@ static bool sp_rows12(const Geom& g, int pass) {
     // the 12-row build takes a last column of patches that is at most half inside the tensor two patch rows at a time
     const int tail = Wo - (Wo - 1) / 32 * 32;
     if (tail <= 16 && r12 >= 24) return true;
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     const long long units16 = (long long)g.N * (cout / 32) * (r16 / 16) * ((Wo + 31) / 32) * Do;
-    return units16 < 12ll * cus;
+    return units16 < 12ll * cu_count();
 }
 
 // statistics (mean, 1 / sqrt(var + eps)), or with means = 1 the plain means of the two sums, from partial sums another

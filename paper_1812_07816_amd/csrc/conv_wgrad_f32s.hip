@@ -21,13 +21,13 @@
 // A value the parts cannot hold (infinities, NaN, magnitudes from 2^126 and below 2^-100 other than zero) sends its step
 // through v_mfma_f32_16x16x4_f32 on operands read straight from memory.
 #include "mi3d_internal.h"
+#include "split_f32.h"
 
 namespace mi3d {
 namespace {
 
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4;
 typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8;
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
 constexpr int TH = 4, TW = 32, XR = TH + 2, XC = TW + 2;
@@ -49,28 +49,6 @@ struct Params {
     long long units;        // per pair: N * HT * WT * D
 };
 
-// Magnitudes whose three parts are exact: zero and 2^-100 ... 2^126.  Zero counts as large in the minimum (0 - 1 wraps).
-struct SplitRange {
-    uint32_t most = 0, least = 0xFFFFFFFFu;
-    __device__ __forceinline__ void add(float v) {
-        const uint32_t u = __builtin_bit_cast(uint32_t, v) & 0x7FFFFFFFu;
-        most = u > most ? u : most;
-        least = u - 1 < least ? u - 1 : least;
-    }
-    __device__ __forceinline__ void add(const float4& v) { add(v.x); add(v.y); add(v.z); add(v.w); }
-    __device__ __forceinline__ bool exceeded() const { return (most >= 0x7E800000u) | (least < 0x0D7FFFFFu); }
-};
-__device__ __forceinline__ void split2(float x, float y, uint32_t (&o)[3]) {
-    typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
-    typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-        f32x2 v = {x, y};
-        o[p] = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-        x -= __builtin_bit_cast(float, o[p] << 16);
-        y -= __builtin_bit_cast(float, o[p] & 0xFFFF0000u);
-    }
-}
 __device__ __forceinline__ bf16x8 tr_frag(const char* p) {   // 32 voxels of this lane group's 16 channels
     typedef __attribute__((address_space(3))) s16x4* lptr;
     s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lptr)(p));
@@ -327,7 +305,7 @@ __global__ void __launch_bounds__(256, 1) f32s_wgrad_kernel(Params P) {
 long long columns(const Geom& g) { return (long long)g.N * ((g.Ho + TH - 1) / TH) * ((g.Wo + TW - 1) / TW); }
 int slots_of(const Geom& g) {
     const long long pairs = (long long)(g.Cin / 32) * (g.Cout / 32), units = columns(g) * g.D;
-    long long slots = (256 + pairs - 1) / pairs;   // one workgroup per CU in total
+    long long slots = (cu_count() + pairs - 1) / pairs;   // one workgroup per CU in total
     if (slots > units) slots = units;
     return (int)(slots < 1 ? 1 : slots);
 }
@@ -344,7 +322,7 @@ bool f32s_wgrad_supported(const Geom& g) {
     // 6 x 20 x 40, 5 each: 114 -> 126; 64->96 at 8 x 24 x 24, N = 2, 2 each: 75 -> 80).
     const double share = (double)g.Ho * g.Wo / ((double)((g.Ho + TH - 1) / TH * TH) * ((g.Wo + TW - 1) / TW * TW));
     const long long pairs = (long long)(g.Cin / 32) * (g.Cout / 32);
-    return share >= 0.6 && columns(g) * g.D * pairs >= 8 * 256;
+    return share >= 0.6 && columns(g) * g.D * pairs >= 8ll * cu_count();
 }
 
 size_t f32s_wgrad_workspace_bytes(const Geom& g) { return (size_t)slots_of(g) * g.w_elems() * sizeof(float); }

@@ -53,6 +53,7 @@ struct Geom {
 int make_geom(const mi3d_conv_desc* d, Geom* g);  // MI3D_OK or error
 void note_hip_error(hipError_t e);
 int check_launch();  // hipGetLastError -> status
+int cu_count();      // compute units of the current device (256 where there is none)
 
 // bf16 helpers (device): storage is the upper 16 bits of the fp32 pattern.
 __device__ __forceinline__ float bf16_to_f32(uint16_t v) { return __uint_as_float((uint32_t)v << 16); }

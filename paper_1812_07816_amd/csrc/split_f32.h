@@ -1,0 +1,39 @@
+// An fp32 number as the exact sum of three bf16 numbers, for products formed by bf16 matrix instructions.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace mi3d {
+
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+
+// Magnitudes whose three parts are exact: zero and 2^-100 ... 2^126.  Zero counts as large in the minimum (0 - 1 wraps).
+struct SplitRange {
+    uint32_t most = 0, least = 0xFFFFFFFFu;
+    __device__ __forceinline__ void add(float v) {
+        const uint32_t u = __builtin_bit_cast(uint32_t, v) & 0x7FFFFFFFu;
+        most = u > most ? u : most;
+        least = u - 1 < least ? u - 1 : least;
+    }
+    __device__ __forceinline__ void add(const float4& v) { add(v.x); add(v.y); add(v.z); add(v.w); }
+    __device__ __forceinline__ bool exceeded() const { return (most >= 0x7E800000u) | (least < 0x0D7FFFFFu); }
+};
+
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+    typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
+    typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
+    f32x2 v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+
+// the three parts of two values, packed
+__device__ __forceinline__ void split2(float x, float y, uint32_t (&o)[3]) {
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        o[p] = pack_bf16(x, y);
+        x -= __builtin_bit_cast(float, o[p] << 16);
+        y -= __builtin_bit_cast(float, o[p] & 0xFFFF0000u);
+    }
+}
+
+}  // namespace mi3d
