@@ -276,9 +276,9 @@ __global__ void __launch_bounds__(64 * NW, 2) f32_gconv_kernel(GcParams P) {
 // neighbouring voxels cover all banks) and read by all taps of the plane.  Weights are packed in fragment order by
 // f32s_pack_kernel and read from there (L1 / L2) one or two taps ahead of their use.
 //
-// A value the split cannot hold (infinities, NaN, magnitudes from 2^126 and below 2^-100 other than zero, whose parts would
-// overflow or lose bits) sends its stage, or its whole tile if it is a weight, through v_mfma_f32_32x32x2_f32 on the
-// values themselves, so that results are those of the fp32 kernel there too.
+// A value outside the range of the split (split_f32.h; infinities and NaN among them) sends its stage, or its whole tile if it
+// is a weight, through v_mfma_f32_32x32x2_f32 on the values themselves: infinities, NaN and overflow come out as they do
+// from the fp32 instructions.
 constexpr int SP_NT = 256, SP_CK = 16;
 constexpr int SP_MAXV = 448;                       // staged voxels (bound of the dispatch rule)
 constexpr int SP_NPX = SP_MAXV * (SP_CK / 4) / SP_NT;   // 16-byte pieces of the patch per thread

@@ -18,8 +18,9 @@
 // conversion is not hidden.  fp32 instructions -> this kernel: 32->32 at 128^3, N = 2 2343 -> 1260 us (99 -> 184 TFLOP/s),
 // 64->64 at 64^3, N = 2 1173 -> 642, 64->32 at 45 x 75 x 91 397 -> 255.
 //
-// A value the parts cannot hold (infinities, NaN, magnitudes from 2^126 and below 2^-100 other than zero) sends its step
-// through v_mfma_f32_16x16x4_f32 on operands read straight from memory.
+// A value outside the range of the split (split_f32.h; infinities and NaN among them) sends its step through
+// v_mfma_f32_16x16x4_f32 on operands read straight from memory, both zero where either lies outside its volume, so that a
+// value at a border meets no zero that is not there.
 #include "mi3d_internal.h"
 #include "split_f32.h"
 
@@ -246,9 +247,9 @@ __global__ void __launch_bounds__(256, 1) f32s_wgrad_kernel(Params P) {
                             for (int e = 0; e < TH * TW / 4; ++e) {   // four columns at a time
                                 const int oh = h0 + e / (TW / 4), ow = w0 + e % (TW / 4) * 4 + g;
                                 const int ih = oh - P.pH + kh, iw = ow - P.pW + kw;
-                                const bool oky = oh < P.Ho && ow < P.Wo, okx = ih >= 0 && ih < P.H && iw >= 0 && iw < P.W;
-                                const float a = oky ? byn[od * dy_plane + ((long long)oh * P.Wo + ow) * P.Cout] : 0.f;
-                                const float b = okx ? bxn[((long long)ih * P.W + iw) * P.xpitch] : 0.f;
+                                const bool ok = oh < P.Ho && ow < P.Wo && ih >= 0 && ih < P.H && iw >= 0 && iw < P.W;
+                                const float a = ok ? byn[od * dy_plane + ((long long)oh * P.Wo + ow) * P.Cout] : 0.f;
+                                const float b = ok ? bxn[((long long)ih * P.W + iw) * P.xpitch] : 0.f;
                                 acc[kd][kh][kw] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc[kd][kh][kw], 0, 0, 0);
                             }
                 }

@@ -7,7 +7,11 @@ namespace mi3d {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 
-// Magnitudes whose three parts are exact: zero and 2^-100 ... 2^126.  Zero counts as large in the minimum (0 - 1 wraps).
+// Magnitudes for which the products of the parts stand for the product: zero and 2^-100 ... 2^45.  Below, the third part loses
+// bits (bf16 ends at 2^-133; the matrix instructions keep subnormal operands and results).  Above, products could overflow:
+// those of the parts have signs of their own, and inf - inf is NaN where the fp32 instruction gives an infinity.  Up to 2^45 a
+// sum of 2^31 products stays below 2^121: nothing formed from parts ever overflows.
+// Zero counts as large in the minimum (0 - 1 wraps).
 struct SplitRange {
     uint32_t most = 0, least = 0xFFFFFFFFu;
     __device__ __forceinline__ void add(float v) {
@@ -16,7 +20,7 @@ struct SplitRange {
         least = u - 1 < least ? u - 1 : least;
     }
     __device__ __forceinline__ void add(const float4& v) { add(v.x); add(v.y); add(v.z); add(v.w); }
-    __device__ __forceinline__ bool exceeded() const { return (most >= 0x7E800000u) | (least < 0x0D7FFFFFu); }
+    __device__ __forceinline__ bool exceeded() const { return (most >= 0x56000000u) | (least < 0x0D7FFFFFu); }
 };
 
 __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {

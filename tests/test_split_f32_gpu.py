@@ -2,6 +2,7 @@
 tiles and of the dispatch rule against the fp64 oracle, and values the parts cannot hold against the fp32 instructions,
 which a call with the smaller workspace gets."""
 import ctypes
+import itertools
 
 import pytest
 import torch
@@ -68,7 +69,7 @@ def _both(d, q, a, w, shape):
 
 
 @pytest.mark.parametrize("q", [0, 1], ids=["fwd", "dgrad"])
-@pytest.mark.parametrize("kind", ["inf", "nan", "large", "tiny", "tiny_w", "inf_w", "scaled"])
+@pytest.mark.parametrize("kind", ["inf", "nan", "large", "tiny", "tiny_w", "inf_w", "scaled", "overflow", "ends", "subnormal"])
 def test_values_without_parts_take_the_fp32_instructions(device, kind, q):
     torch.manual_seed(5)
     d = mc.make_desc(1, 3, 10, 40, 32, 48, 3, 1, 1, torch.float32)
@@ -87,39 +88,88 @@ def test_values_without_parts_take_the_fp32_instructions(device, kind, q):
         w *= 2.0 ** -112
     elif kind == "inf_w":
         w[3, 1, 2, 0, 7] = float("inf")
-    else:                          # the ends of what the parts hold
+    elif kind == "scaled":         # products of ordinary size from large and small values
         a *= 2.0 ** 115
         w *= 2.0 ** -75
+    elif kind == "overflow":       # every product overflows, to an infinity of the output channel's sign
+        a = a.abs().clamp(min=0.1) * 1e21
+        w = w.abs().clamp(min=0.1) * 1e21
+        w[(..., slice(None, None, 2)) if q == mc.PASS_DGRAD else slice(None, None, 2)] *= -1
+    elif kind == "ends":           # the ends of what the parts hold
+        a *= 2.0 ** 42
+        w *= 2.0 ** -80
+    else:                          # products of the small parts are subnormal numbers
+        a *= 2.0 ** -62
+        w *= 2.0 ** -64
     got, ref = _both(d, q, a, w, (1, 3, 10, 40, M))
     for f in (torch.isnan, torch.isposinf, torch.isneginf):
         assert torch.equal(f(got), f(ref)), kind
     ok = torch.isfinite(ref)
+    if kind == "overflow":
+        assert torch.isinf(ref).all()
+        return
     g, r = got[ok].double(), ref[ok].double()
     rms = r.square().mean().sqrt() if kind != "large" else r.abs().median()
     assert float(((g - r).abs() / torch.maximum(r.abs(), rms)).max()) <= TOL
 
 
-@pytest.mark.parametrize("kind", ["inf", "nan_dy", "large", "tiny", "scaled"])
+def _weight_gradient(x, dy):
+    """dw of a 3x3x3 layer with padding 1 in 64 bits, over the window alone: what is not finite is added voxel by voxel."""
+    x, dy = x.double().cpu(), dy.double().cpu()
+    xf, dyf = (torch.where(torch.isfinite(v), v, 0.0).permute(0, 4, 1, 2, 3) for v in (x, dy))
+    ref = torch.nn.grad.conv3d_weight(xf, (dy.shape[-1], x.shape[-1], 3, 3, 3), dyf, padding=1).permute(0, 2, 3, 4, 1).clone()
+    ext = x.shape[1:4]
+    for t in itertools.product(range(3), repeat=3):
+        for n, *i, c in (~torch.isfinite(x)).nonzero().tolist():
+            o = [v + 1 - k for v, k in zip(i, t)]
+            if all(0 <= v < e for v, e in zip(o, ext)):
+                ref[:, t[0], t[1], t[2], c] += x[n, i[0], i[1], i[2], c] * dy[n, o[0], o[1], o[2], :]
+        for n, *o, c in (~torch.isfinite(dy)).nonzero().tolist():
+            i = [v - 1 + k for v, k in zip(o, t)]
+            if all(0 <= v < e for v, e in zip(i, ext)):
+                ref[c, t[0], t[1], t[2], :] += dy[n, o[0], o[1], o[2], c] * x[n, i[0], i[1], i[2], :]
+    return ref
+
+
+@pytest.mark.parametrize("kind", ["inf", "nan_dy", "border", "border_dy", "large", "tiny", "scaled", "overflow", "ends", "subnormal"])
 def test_weight_gradient_of_values_without_parts(device, kind):
+    """Columns that end inside a patch of 32, rows inside one of 4."""
     torch.manual_seed(6)
-    N, D, H, W, c = 2, 96, 22, 40, 32
+    N, D, H, W, c = 2, 96, 22, 60, 32
     d = mc.make_desc(N, D, H, W, c, c, 3, 1, 1, torch.float32)
     x, dy = torch.randn((N, D, H, W, c), device="cuda"), torch.randn((N, D, H, W, c), device="cuda")
     if kind == "inf":
-        x[0, 3, 5, 7, 11], x[1, 10, 13, 31, 31] = float("inf"), float("-inf")   # (inside: a border one meets dy's zero padding)
+        x[0, 3, 5, 7, 11], x[1, 10, 13, 31, 31] = float("inf"), float("-inf")
     elif kind == "nan_dy":
         dy[1, 1, 1, 33, 2] = float("nan")
+    elif kind == "border":
+        x[0, 0, 0, 0, 11], x[1, 95, 21, 59, 31] = float("inf"), float("-inf")
+    elif kind == "border_dy":
+        dy[0, 95, 0, 59, 3], dy[1, 0, 21, 31, 30] = float("inf"), float("nan")
     elif kind == "large":
         x[0, 6, 9, 9, 4] = 3.4e38
         dy *= 1e-3
     elif kind == "tiny":
         x *= 2.0 ** -112
-    else:
+    elif kind == "scaled":
         x *= 2.0 ** 115
         dy *= 2.0 ** -75
+    elif kind == "overflow":
+        x = x.abs().clamp(min=0.1) * 1e21
+        dy = dy.abs().clamp(min=0.1) * 1e21
+        dy[..., ::2] *= -1
+    elif kind == "ends":
+        x *= 2.0 ** 42
+        dy *= 2.0 ** -80
+    else:
+        x *= 2.0 ** -62
+        dy *= 2.0 ** -64
     got = mc.conv3d_wgrad(d, x, dy).double().cpu()
-    xr, dyr = (v.double().cpu().permute(0, 4, 1, 2, 3) for v in (x, dy))
-    ref = torch.nn.grad.conv3d_weight(xr, (c, c, 3, 3, 3), dyr, padding=1).permute(0, 2, 3, 4, 1)
+    if kind == "overflow":
+        sign = torch.tensor([-1.0, 1.0], dtype=torch.float64).repeat(c // 2)
+        assert torch.equal(got, (sign * float("inf"))[:, None, None, None, None].expand_as(got))
+        return
+    ref = _weight_gradient(x, dy)
     for f in (torch.isnan, torch.isposinf, torch.isneginf):
         assert torch.equal(f(got), f(ref)), kind
     ok = torch.isfinite(ref)
