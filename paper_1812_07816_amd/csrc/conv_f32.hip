@@ -259,11 +259,13 @@ __global__ void __launch_bounds__(64 * NW, 2) f32_gconv_kernel(GcParams P) {
 // ---- fp32 products from bf16 matrix instructions -----------------------------------------------------------------------
 // The same gather convolution with each fp32 operand taken apart into three bf16 numbers, v = a + b + c exactly (a the
 // nearest bf16 to v, b to v - a, c the rest: 3 x 8 significant bits and two signs hold the 24 of v).  Of the nine products
-// the six a a', a b', b a', a c', c a', b b' are formed with v_mfma_f32_32x32x16_bf16 and added in fp32; the three left
-// out are below 2^-26 of the product (|b| <= 2^-9 |v|, |c| <= 2^-18 |v|), a quarter of one fp32 rounding.  An accumulator
-// is rounded 6 times per 16 contracted channels instead of 8 to 16 times.  Measured
+// the six a a', a b', b a', a c', c a', b b' are formed with v_mfma_f32_32x32x16_bf16 and added in fp32.  With |b| <= 2^-8 |v|
+// and |c| <= 2^-17 |v| the three left out can reach 2^-24 of the product, one rounding of a single fp32 product (the worst
+// operands, 1 + 2^-8 - 2^-17, are a test); of normal random operands 3.5 % exceed 2^-26, their root mean square is
+// a tenth of 2^-24.  An accumulator
+// is rounded 6 times per 16 contracted channels instead of 8 to 16 times, and that decides.  Measured
 // against 64 bits (2-norm, fp32 instructions -> this kernel): 32->32 at 8 x 48 x 48 5.0e-7 -> 4.3e-7, 320->320 at 5 x 12 x 12
-// 1.5e-6 -> 1.35e-6, 640->32 2.2e-6 -> 2.0e-6.
+// 1.5e-6 -> 1.35e-6, 640->32 2.2e-6 -> 2.0e-6; operands that are all the worst one 6e-8 (0.99 x 2^-24) with either.
 //
 // Bound: the fp32 matrix instructions need 64 cycles for 32x32x2, six bf16 ones for 32x32x16 need 6 x 32: a ceiling 2.7
 // times as high.  Forward pass with its packing launch, fp32 instructions -> this kernel: 32->32 at 128^3, N = 2 2225 -> 1444 us

@@ -1,7 +1,7 @@
 // fp32 weight gradient of 3x3x3 / stride-1 layers with channels in multiples of 32, its products formed by bf16 matrix
 // instructions (v_mfma_f32_16x16x32_bf16): each fp32 operand is taken apart into three bf16 numbers, v = a + b + c exactly,
-// and six of the nine products are added in fp32; the three left out are below 2^-26 of the product.  The five small ones are
-// summed apart and added once, so that an accumulator is rounded twice per 32 positions (the fp32 instructions: 16 times).
+// and six of the nine products are added in fp32; the three left out are at most about 2^-24 of the product
+// (see conv_f32.hip).  The five small ones are summed apart and added once, so that an accumulator is rounded twice per 32 positions (the fp32 instructions: 16 times).
 // Errors against 64 bits (2-norm, fp32 instructions -> this kernel): 32->32 at 40 x 96 x 96,
 // N = 2 5.0e-7 -> 3.8e-7, 64->64 at 24 x 64 x 64 3.6e-7 -> 2.7e-7.
 //

@@ -176,3 +176,20 @@ def test_weight_gradient_of_values_without_parts(device, kind):
     g, r = got[ok], ref[ok]
     rms = r.square().mean().sqrt() if kind != "large" else r.abs().median()
     assert float(((g - r).abs() / torch.maximum(r.abs(), rms)).max()) <= TOL
+
+
+def test_worst_operands_of_the_split(device):
+    """1 + 2^-8 - 2^-17 has parts 1, 2^-8 and -2^-17: the products left out are 2^-24 of the product, all of one sign.  Sums of
+    the rest are multiples of 2^-7.  With 32 channels, and in the weight gradient of 64, whose small products are added
+    apart, every addition is exact and what is left out is the whole error; with 64 the forward sums pass 1024, where six
+    roundings of at most 2^-24 per 16 of the 27 x 64 products come on top."""
+    v, N, D, H, W = 1 + 2.0 ** -8 - 2.0 ** -17, 2, 24, 22, 60
+    one = torch.ones((N, 1, D, H, W), dtype=torch.float64)
+    window = torch.nn.functional.conv3d(one, torch.ones((1, 1, 3, 3, 3), dtype=torch.float64), padding=1).permute(0, 2, 3, 4, 1)
+    overlap = torch.nn.grad.conv3d_weight(one, (1, 1, 3, 3, 3), one, padding=1).permute(0, 2, 3, 4, 1)
+    for c, most in ((32, 1), (64, 1 + 6 * 27 * 4)):
+        d = mc.make_desc(N, D, H, W, c, c, 3, 1, 1, torch.float32)
+        x, w = torch.full((N, D, H, W, c), v, device="cuda"), torch.full((c, 3, 3, 3, c), v, device="cuda")
+        for got, r, m in ((mc.conv3d_fwd(d, x, w), c * v * v * window, most), (mc.conv3d_dgrad(d, x, w), c * v * v * window, most),
+                          (mc.conv3d_wgrad(d, x, x), v * v * overlap, 1)):
+            assert float(((got.double().cpu() - r) / r).abs().max()) <= m * 2.0 ** -24, c
