@@ -278,10 +278,12 @@ __global__ void __launch_bounds__(64 * NW, 2) f32_gconv_kernel(GcParams P) {
 // neighbouring voxels cover all banks) and read by all taps of the plane.  Weights are packed in fragment order by
 // f32s_pack_kernel and read from there (L1 / L2) one or two taps ahead of their use.
 //
-// A value outside the range of the split (split_f32.h; infinities and NaN among them) sends its stage, or its whole tile if it
-// is a weight, through v_mfma_f32_32x32x2_f32 on the values themselves: infinities, NaN and overflow come out as they do
-// from the fp32 instructions.
+// A value outside the range of the split (split_f32.h; infinities and NaN among them) sends its stage (a weight: that stage of
+// all tiles of its channel block) through v_mfma_f32_32x32x2_f32 on the values themselves: infinities, NaN and overflow come
+// out as they do from the fp32 instructions.  Forward pass 64->64 at 64^3, N = 2: 577 us, with one such activation 577, with
+// one such weight (a stage in twelve) 653, with such activations in every stage 1365 (the kernel of the fp32 instructions 1155).
 constexpr int SP_NT = 256, SP_CK = 16;
+constexpr int SP_BITS = 256;                       // stages told apart by their weights' flags
 constexpr int SP_MAXV = 448;                       // staged voxels (bound of the dispatch rule)
 constexpr int SP_NPX = SP_MAXV * (SP_CK / 4) / SP_NT;   // 16-byte pieces of the patch per thread
 
@@ -376,7 +378,7 @@ __global__ void __launch_bounds__(SP_NT, 2) f32s_gconv_kernel(GsParams Q) {
     bool ok0, ok1, active;
     gconv_positions<NB>(P, jht, jwt, wave, ln, jh0, jw0, tr0, tc0, tr1, tc1, ok0, ok1, active);
     const int nvox = P.prows * P.pcols, part = nvox * 32;
-    uint32_t* bad_lds = (uint32_t*)(lds + 3 * part);   // [0], [1]: stage of that parity, [2]: weights
+    uint32_t* bad_lds = (uint32_t*)(lds + 3 * part);   // [0], [1]: patch of the stage of that parity; then a bit per stage's weights
 
     f32x16 acc[NB][CB];
 #pragma unroll
@@ -421,18 +423,21 @@ __global__ void __launch_bounds__(SP_NT, 2) f32s_gconv_kernel(GsParams Q) {
     };
     auto slot = [&](int e) { const int v = e >> 2, q = e & 3; return v * 32 + (((q >> 1) ^ (v >> 3)) & 1) * 16 + (q & 1) * 8; };
 
-    if (t < 3) bad_lds[t] = 0;
+    if (t < 2 + SP_BITS / 32) bad_lds[t] = 0;
     if (stages > 0) request(0);
     __syncthreads();
-    // weights that cannot be split
-    {
-        bool bad = false;
-        const int TK = Q.T * KC;
-        for (int cb = 0; cb < CB; ++cb)
-            if (m0 + 32 * cb < P.Mpad)
-                for (int e = t; e < TK; e += SP_NT) bad |= Q.wflag[(m0 / 32 + cb) * TK + e] != 0;
-        if (__any(bad) && lane == 0) bad_lds[2] = 1;
-    }
+    // stages with weights that cannot be split (stages SP_BITS apart share a bit: one may go the other way needlessly)
+    auto stage_bit = [&](int kc, int g) { return (kc * P.ngroups + g) & (SP_BITS - 1); };
+    const int TK = Q.T * KC;
+    for (int cb = 0; cb < CB; ++cb)
+        if (m0 + 32 * cb < P.Mpad)
+            for (int e = t; e < TK; e += SP_NT)
+                if (Q.wflag[(m0 / 32 + cb) * TK + e] != 0)
+                    for (int k = 0; k < P.ntaps; ++k)
+                        if ((int)(Q.taps[k] >> 16) == e / KC) {
+                            const int bit = stage_bit(e % KC, k / NTC);
+                            atomicOr(&bad_lds[2 + (bit >> 5)], 1u << (bit & 31));
+                        }
     const int MB = P.Mpad / 32;
     const int vb[NB] = {tr0 * P.pcols + tc0, tr1 * P.pcols + tc1};
     for (int s = 0; s < stages; ++s) {
@@ -468,7 +473,8 @@ __global__ void __launch_bounds__(SP_NT, 2) f32s_gconv_kernel(GsParams Q) {
         for (int a = 0; a < AHEAD - 1; ++a) weights(a, wf[a]);
         if (AHEAD == 1) weights(0, wf[0]);
         __syncthreads();
-        const bool plain = __builtin_amdgcn_readfirstlane(bad_lds[s & 1] | bad_lds[2]) != 0;
+        const int bit = stage_bit(kc, g);
+        const bool plain = __builtin_amdgcn_readfirstlane(bad_lds[s & 1] | (bad_lds[2 + (bit >> 5)] >> (bit & 31) & 1)) != 0;
         if (t == 0) bad_lds[1 - (s & 1)] = 0;   // (next written behind the next stage's first barrier)
         if (plain) {
             // raw bits in two halves take the place of the parts; weights come as they are
@@ -1118,7 +1124,7 @@ static int launch_split(GsParams& Q, hipStream_t s) {
     if (blocks > 0x7fffffffll || P.prows * P.pcols > SP_MAXV) return MI3D_ERR_UNSUPPORTED;
     for (int k = 0; k < P.ntaps; ++k) Q.taps[k] = (uint32_t)((P.th[k] - P.hmin) * P.pcols + P.tw[k] - P.wmin) | (uint32_t)P.tapidx[k] << 16;
     const int ntc = P.ngroups ? P.ntaps / P.ngroups : 9;   // (no group: nothing to add, any instance writes the epilogue)
-    const size_t lds = (size_t)P.prows * P.pcols * 96 + 16;
+    const size_t lds = (size_t)P.prows * P.pcols * 96 + 8 + SP_BITS / 8;
     return CB == 2 ? launch_split_cb<2>(Q, ntc, (unsigned)blocks, lds, s) : launch_split_cb<1>(Q, ntc, (unsigned)blocks, lds, s);
 }
 

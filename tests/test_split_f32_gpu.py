@@ -113,6 +113,20 @@ def test_values_without_parts_take_the_fp32_instructions(device, kind, q):
     assert float(((g - r).abs() / torch.maximum(r.abs(), rms)).max()) <= TOL
 
 
+@pytest.mark.parametrize("tap", [(0, 0, 0), (1, 1, 1), (2, 1, 0), (1, 2, 2)])
+def test_weight_without_parts_in_a_class_of_the_strided_data_gradient(device, tap):
+    """Each parity class runs its own taps: the one with the weight must take the fp32 instructions, in its stage."""
+    torch.manual_seed(7)
+    d = mc.make_desc(1, 5, 10, 13, 32, 64, 3, 2, 1, torch.float32)
+    dy, w = torch.randn((1, 3, 5, 7, 64), device="cuda"), torch.randn((64, 3, 3, 3, 32), device="cuda")
+    w[(37, *tap, 9)] = float("inf")
+    got, ref = _both(d, mc.PASS_DGRAD, dy, w, (1, 5, 10, 13, 32))
+    for f in (torch.isnan, torch.isposinf, torch.isneginf):
+        assert torch.equal(f(got), f(ref))
+    ok = torch.isfinite(ref)
+    assert not ok.all() and float((got[ok] - ref[ok]).abs().max() / ref[ok].square().mean().sqrt()) <= TOL
+
+
 def _weight_gradient(x, dy):
     """dw of a 3x3x3 layer with padding 1 in 64 bits, over the window alone: what is not finite is added voxel by voxel."""
     x, dy = x.double().cpu(), dy.double().cpu()
