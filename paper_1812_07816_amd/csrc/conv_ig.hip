@@ -72,8 +72,14 @@ struct IgParams {
     long long out_elems;
     IgClass cls[8];
     uint32_t taps[27];
+    long long slack;              // voxels by which a position can lie before an earlier one of its tile (max_span)
 };
 
+// the bytes of a tensor from byte `at` on (before it or behind its end too), 2^31 at most
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_from(const uint16_t* p, long long at, long long bytes) {
+    const long long left = bytes - at;
+    return __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)p + at), 0, left > 0x7fffffffll ? 0x7fffffff : left < 0 ? 0 : (int)left, 0x00020000);
+}
 // 16 bytes per lane from buffer r at byte offset off (zeros beyond its range) to the wave's 1 KB at l
 __device__ __forceinline__ void load_lds(__amdgpu_buffer_rsrc_t r, char* l, unsigned off) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr)l, 16, (int)off, 0, 0, 0);
@@ -88,7 +94,10 @@ __device__ __forceinline__ uint32_t cvt2(float a, float b) {
 __device__ __forceinline__ float lo_f(uint32_t v) { return __builtin_bit_cast(float, v << 16); }
 __device__ __forceinline__ float hi_f(uint32_t v) { return __builtin_bit_cast(float, v & 0xFFFF0000u); }
 
-template <int WN>   // waves along the positions: 2 (128 x 128) or 4 (64 x 256)
+// WN = waves along the positions: 2 (128 x 128) or 4 (64 x 256).  WIDE: planes too large for 32-bit offsets from a plane to
+// all that a tile and its taps touch (narrow_planes); the buffers move with the tap then, which costs 2 % (48^3 128->256,
+// stride 2, N = 2: 225 -> 231 us for the three passes).
+template <int WN, bool WIDE>
 __global__ void __launch_bounds__(256, 2) ig_kernel(const IgParams P) {
     constexpr int BM = WN == 2 ? 128 : 64, BN = 64 * WN, NA = BM / 32, NB = BN / 32;
     constexpr int A_BYTES = BM * 128, STAGE = (BM + BN) * 128;
@@ -120,15 +129,20 @@ __global__ void __launch_bounds__(256, 2) ig_kernel(const IgParams P) {
 
     // the rows this thread fetches: row 32 i + 8 wave + lane / 8 of either operand, the same 8-channel piece of each
     const int rl = 8 * wave + (lane >> 3), piece = (lane & 7) ^ (lane >> 3) ^ (wave & 1);
-    // 32-bit offsets are relative to the plane two below the first position's (a tile spans few planes)
+    // 32-bit offsets are relative to the plane two below the first position's (a tile spans few planes).  WIDE: to the first
+    // position's own voxel, and a tap moves the buffer (its voxel may lie before or behind the tensor: lanes that would
+    // read there are masked).
     long long base;
     {
         int n, d, h, w;
         decode(pt * BN, n, d, h, w);
-        const long long v = ((long long)n * P.iD + P.is * d - 2) * P.iH * P.iW;
-        base = v > 0 ? v : 0;
+        if (WIDE) {
+            base = (((long long)n * P.iD + P.is * d) * P.iH + P.is * h) * P.iW + P.is * w - P.slack;
+        } else {
+            const long long v = ((long long)n * P.iD + P.is * d - 2) * P.iH * P.iW;
+            base = v > 0 ? v : 0;
+        }
     }
-    const long long base_b = base * P.pitch * 2;
     const int nch = (P.C + BK - 1) / BK, steps = K.ntap * nch;
     const int s0 = (int)((unsigned)(steps * split) / (unsigned)P.splits), s1 = (int)((unsigned)(steps * (split + 1)) / (unsigned)P.splits);
     int tap = s0 / nch, chunk = s0 - tap * nch;   // of the next step to be fetched
@@ -165,7 +179,7 @@ __global__ void __launch_bounds__(256, 2) ig_kernel(const IgParams P) {
         oka[i] = m < P.M;
         rowa[i] = m * P.T * P.C * 2 + piece * 16;
     }
-    const long long left = P.in_bytes - base_b;
+    const long long base_b = base * P.pitch * 2, left = P.in_bytes - base_b;
     const int range = left > 0x7fffffffll ? 0x7fffffff : (int)left;
     __amdgpu_buffer_rsrc_t r_in = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)P.in + base_b), 0, range, 0x00020000);
     __amdgpu_buffer_rsrc_t r_hi = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)P.in_hi + base_b), 0, range, 0x00020000);
@@ -175,7 +189,14 @@ __global__ void __launch_bounds__(256, 2) ig_kernel(const IgParams P) {
         const IgTap a(__builtin_amdgcn_readlane(tapv, tap));
         const int c = chunk * BK + piece * 8;     // this lane's channels
         const unsigned okc = c < P.C;
-        const int ub = ((a.dd * P.iH + a.dh) * P.iW + a.dw) * P.pitch * 2 + chunk * BK * 2;
+        int ub = 0;
+        if (WIDE) {
+            const long long at = (base + (a.dd * P.iH + a.dh) * P.iW + a.dw) * P.pitch * 2 + chunk * (BK * 2);
+            r_in = buffer_from(P.in, at, P.in_bytes);
+            r_hi = buffer_from(P.in_hi, at - P.csplit * 2, P.in_bytes);
+        } else {
+            ub = ((a.dd * P.iH + a.dh) * P.iW + a.dw) * P.pitch * 2 + chunk * BK * 2;
+        }
         const int ua = (a.wt * P.C + chunk * BK) * 2;
         char* l = lds + buf * STAGE + wave * 1024;
 #pragma unroll
@@ -188,7 +209,7 @@ __global__ void __launch_bounds__(256, 2) ig_kernel(const IgParams P) {
             asm volatile("; low half");   // keeps the branches apart: merged, their last loads run in a loop over the resources
         } else {
 #pragma unroll
-            for (int i = 0; i < NB; ++i) load_lds(r_hi, l + i * 4096, okc & (mask[i] >> tap) ? rowb[i] + ub - P.csplit * 2 : OOB);
+            for (int i = 0; i < NB; ++i) load_lds(r_hi, l + i * 4096, okc & (mask[i] >> tap) ? rowb[i] + ub - (WIDE ? 0 : P.csplit * 2) : OOB);
         }
         if (++chunk == nch) { chunk = 0; ++tap; }
     };
@@ -401,6 +422,46 @@ IgPlan make_plan(const Geom& g, int pass) {
     return best;
 }
 
+// The planes that a tile of 256 positions and its taps touch, with room to spare, within 2 GiB
+bool narrow_planes(const Geom& g, int pass) {
+    const bool flip = pass == MI3D_PASS_DGRAD;
+    const long long plane = flip ? (long long)g.Ho * g.Wo * g.Cout * 2 : (long long)g.H * g.W * g.Cin * 2;
+    const int os = flip ? g.sD : 1;
+    const long long rows = flip ? (long long)(g.H > 1 ? g.H / os : 1) * (g.W > 1 ? g.W / os : 1) : (long long)g.Ho * g.Wo;
+    return plane * (16 + 6 * (255 / rows + 2)) < (1ll << 31);
+}
+
+// Bytes from the first to the last voxel at the positions of a tile (256 of them at most), and the voxels by which a position
+// can lie before an earlier one: positions beyond the volume they read from (it is the smaller one where a data gradient
+// has little padding) run into the next row, plane and sample.  A position's voxel itself is at is * (d, h, w).
+long long max_span(const Geom& g, int pass, long long* slack) {
+    const bool flip = pass == MI3D_PASS_DGRAD;
+    const long long is = flip ? 1 : g.sD, os = flip ? g.sD : 1;
+    const long long C = flip ? g.Cout : g.Cin, iD = flip ? g.Do : g.D, iH = flip ? g.Ho : g.H, iW = flip ? g.Wo : g.W, plane = iH * iW;
+    const long long oD = flip ? g.D : g.Do, oH = flip ? g.H : g.Ho, oW = flip ? g.W : g.Wo;
+    long long most = 0, back = 0;
+    for (int c = 0; c < (os == 2 ? 8 : 1); ++c) {
+        const long long jD = (oD - (c >> 2) + os - 1) / os, jH = (oH - (c >> 1 & 1) + os - 1) / os, jW = (oW - (c & 1) + os - 1) / os;
+        if (jD <= 0 || jH <= 0 || jW <= 0) continue;
+        const long long xD = is * (jD - 1) - (iD - 1), xH = is * (jH - 1) - (iH - 1), xW = is * (jW - 1) - (iW - 1);   // beyond the volume
+        const long long b = (g.N > 1 && xD > 0 ? (xD + 1) * plane : 0) + (xH > 0 ? (xH + 1) * iW : 0) + (xW > 0 ? xW + 1 : 0);
+        if (b > back) back = b;
+        // planes from a plane of positions to the next one, in the same sample or across its end
+        const long long across = iD - is * (jD - 1), step = g.N > 1 && across > is ? across : is, rows = jH * jW;
+        long long v;
+        if (rows >= 256) {   // at most one change of plane, with the end of one plane and the beginning of the next
+            const long long tail = iH - is * jH > 0 ? iH - is * jH : 0;
+            v = (g.N * jD > 1 ? (step - 1) * plane : 0) + (tail + is * (2 * (255 / jW) + 4)) * iW;
+        } else {
+            const long long extent = is * (jH - 1) * iW + is * (jW - 1) + 1;
+            v = (254 / rows + 1) * step * plane + (extent > plane ? extent : plane);
+        }
+        if (v > most) most = v;
+    }
+    if (slack) *slack = back;
+    return (most + back) * C * 2 + 256;
+}
+
 size_t weight_bytes(const Geom& g) { return ((size_t)g.w_elems() * 2 + 255) & ~(size_t)255; }
 
 }  // namespace
@@ -412,11 +473,8 @@ bool ig_supported(const Geom& g, int pass) {
     if (pass == MI3D_PASS_DGRAD && g.sD == 2 && (g.pD != g.pH || g.pD != g.pW)) return false;
     const bool flip = pass == MI3D_PASS_DGRAD;
     if ((flip ? g.H * (long long)g.W : g.Ho * (long long)g.Wo) >= (1ll << 31) || g.w_elems() * 2 >= (1ll << 31)) return false;
-    // 32-bit offsets inside the planes that a tile of 256 positions and its taps touch
-    const long long plane = flip ? (long long)g.Ho * g.Wo * g.Cout * 2 : (long long)g.H * g.W * g.Cin * 2;
-    const int os = flip ? g.sD : 1;
-    const long long rows = flip ? (long long)(g.H > 1 ? g.H / os : 1) * (g.W > 1 ? g.W / os : 1) : (long long)g.Ho * g.Wo;
-    if (plane * (16 + 6 * (255 / rows + 2)) >= (1ll << 31)) return false;
+    // (stride-1 layers have the plane kernels for larger planes)
+    if (!narrow_planes(g, pass) && (g.sD == 1 || max_span(g, pass, nullptr) >= (1ll << 31))) return false;
     return g.in_voxels() < (1ll << 31) - 1024 && g.out_voxels() < (1ll << 31) - 1024 && make_plan(g, pass).splits > 0;
 }
 
@@ -453,6 +511,7 @@ int ig_conv(const Geom& g, int pass, const void* in, const void* w, void* out, v
     if (g.hi && !flip) { P.in_hi = (const uint16_t*)g.hi; P.csplit = P.pitch = P.C / 2; }
     if (g.hi && flip) P.out_hi = (uint16_t*)g.hi;
     P.in_bytes = (long long)g.N * P.iD * P.iH * P.iW * P.pitch * 2;
+    max_span(g, pass, &P.slack);
     const int bn = 64 * plan.wn, pads[3] = {g.pD, g.pH, g.pW};
     int tile = 0, ntap = 0;
     for (int q = 0; q < plan.ncls; ++q) {
@@ -492,13 +551,20 @@ int ig_conv(const Geom& g, int pass, const void* in, const void* w, void* out, v
     const size_t lds2 = 2 * 256 * 128, lds4 = 2 * 320 * 128;
     static std::atomic<bool> attr_set{false};   // set once per process; a second thread racing here repeats an idempotent call
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void*)ig_kernel<2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds2);
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)ig_kernel<4>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds4);
+        hipError_t e = hipSuccess;
+        for (const void* f : {(const void*)ig_kernel<2, false>, (const void*)ig_kernel<2, true>})
+            if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds2);
+        for (const void* f : {(const void*)ig_kernel<4, false>, (const void*)ig_kernel<4, true>})
+            if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds4);
         if (e != hipSuccess) { note_hip_error(e); return MI3D_ERR_HIP; }
         attr_set = true;
     }
-    if (plan.wn == 2) ig_kernel<2><<<(unsigned)(plan.tiles * plan.splits), 256, lds2, s>>>(P);
-    else ig_kernel<4><<<(unsigned)(plan.tiles * plan.splits), 256, lds4, s>>>(P);
+    const unsigned grid = (unsigned)(plan.tiles * plan.splits);
+    const bool wide = !narrow_planes(g, pass);
+    if (plan.wn == 2 && !wide) ig_kernel<2, false><<<grid, 256, lds2, s>>>(P);
+    else if (plan.wn == 2) ig_kernel<2, true><<<grid, 256, lds2, s>>>(P);
+    else if (!wide) ig_kernel<4, false><<<grid, 256, lds4, s>>>(P);
+    else ig_kernel<4, true><<<grid, 256, lds4, s>>>(P);
     st = check_launch();
     if (st || plan.splits == 1) return st;
     const long long n = P.out_elems;

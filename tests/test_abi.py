@@ -77,3 +77,14 @@ def test_largest_sizes_are_routed_by_their_plane_size_or_refused():
     a = ctypes.c_int()
     huge = mc.make_desc(64, 4096, 4096, 4096, 32, 32, 3, 1, 1, bf)   # 2^47 elements
     assert _lib.lib().mi3d_conv3d_out_dims(ctypes.byref(huge), ctypes.byref(a), ctypes.byref(a), ctypes.byref(a)) == -2
+
+
+def test_strided_layers_keep_their_kernels_on_large_planes():
+    """Up to the 2 GiB a plane that the tiled kernels address (64 channels: 4000 x 4000 voxels)."""
+    import torch
+    from paper_1812_07816_amd import conv3d as mc
+    for hw in (700, 800, 1200, 2000, 4000):
+        d = mc.make_desc(1, 8, hw, hw, 64, 128, 3, 2, 1, torch.bfloat16)
+        assert [mc.kernel_name(d, q) for q in range(2)] == ["mfma_stride2_plane_stream", "mfma_dgrad_stride2_parity"], hw
+    d = mc.make_desc(2, 9, 1200, 1200, 128, 256, 3, 2, 0, torch.bfloat16)
+    assert [mc.kernel_name(d, q) for q in range(2)] == ["mfma_stride2_plane_stream", "mfma_dgrad_stride2_parity"]

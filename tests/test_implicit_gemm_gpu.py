@@ -21,6 +21,9 @@ CASES = [
     (1, 1, 5, 1, 64, 128, 2, 1),       # extents of one: six parity classes without a voxel
     (1, 11, 13, 12, 96, 128, 2, 0),    # stride 2 without padding: the classes' taps are the other way round
     (1, 33, 31, 35, 64, 192, 2, 1),    # whole contractions (no partial sums)
+    (3, 4, 5, 40, 96, 96, 1, 0),       # data gradient at positions beyond dy in rows, planes and samples of one tile
+    (2, 6, 20, 21, 96, 128, 2, 0),     # tiles that end one sample and begin the next, whose planes lie four on
+    (2, 5, 24, 23, 128, 128, 1, 0),
 ]
 
 
@@ -46,3 +49,15 @@ def test_halves_that_meet_inside_a_step_give_the_same_bits(device, case):
     dlo, dhi = torch.empty_like(lo), torch.empty_like(hi)
     mc.conv3d_dgrad_pair(desc, dy, w, dlo, dhi)
     assert torch.equal(torch.cat([dlo, dhi], dim=-1), mc.conv3d_dgrad(desc, dy, w))
+
+
+@pytest.mark.parametrize("case", [(1, 5, 800, 790, 64, 256, 1), (2, 4, 810, 800, 64, 256, 0)])
+def test_planes_of_many_voxels(device, case):
+    """Planes of 81 MB and more: the buffers move with the tap.  A tile ends one plane and begins the next, or (without
+    padding) ends a sample whose last plane no position reads."""
+    N, D, H, W, Cin, Cout, p = case
+    desc = mc.make_desc(N, D, H, W, Cin, Cout, 3, 2, p, torch.bfloat16)
+    assert [mc.kernel_name(desc, q) for q in (0, 1)] == ["mfma_stride2_plane_stream", "mfma_dgrad_stride2_parity"]
+    errs = parity.run_case(95, 900 + p, N, D, H, W, Cin, Cout, 3, 2, p, bf16=True, full=False, n_samples=20000, passes=("fwd", "dgrad"))
+    for q, v in errs.items():
+        assert v <= parity.TOL["bf16"], (case, q, v)
