@@ -77,9 +77,17 @@ typedef struct {
 
 int mi3d_conv3d_out_dims(const mi3d_conv_desc *desc, int *Do, int *Ho, int *Wo);
 
-/* Bytes of device scratch the given pass needs for this geometry (may be 0).
- * Returns 0 for an invalid descriptor as well; the pass itself reports it. */
+/* Bytes of device scratch that the fastest kernel of the given pass wants for this geometry (may be 0).
+ * Returns 0 for an invalid descriptor as well; the pass itself reports it.
+ *
+ * A call with less, down to mi3d_conv3d_min_workspace_bytes, is served too, by a slower kernel: fp32 layers by the fp32
+ * matrix instructions, deep bf16 layers with a contraction in fewer parts, channel counts that are not multiples of 32 by
+ * the plain kernels (150 times slower on large volumes).  The sums are then formed in another order, so the bits of a
+ * result depend on the size of the workspace; with the same size repeated calls give identical bits.  Below the minimum
+ * a call returns MI3D_ERR_WORKSPACE and launches nothing.  The entry points with statistics or sums
+ * (mi3d_conv3d_fwd_stats, mi3d_conv3d_dgrad_insums) need the full size. */
 size_t mi3d_conv3d_workspace_bytes(const mi3d_conv_desc *desc, int pass);
+size_t mi3d_conv3d_min_workspace_bytes(const mi3d_conv_desc *desc, int pass);
 
 /* y[n,o,co] = sum_{t,ci} x[n, o*s - p + t, ci] * w[co,t,ci]     (feature map of Section 3.1)
  * x: N*D*H*W*Cin elements, w: Cout*kD*kH*kW*Cin, y: N*Do*Ho*Wo*Cout (fully overwritten). */
@@ -100,13 +108,14 @@ int mi3d_conv3d_wgrad(const mi3d_conv_desc *desc, const void *x, const void *dy,
                       void *ws, size_t ws_bytes, void *stream);
 
 /* mi3d_conv3d_wgrad for callers that cannot allocate device memory or pass a workspace: code under HIP graph
- * capture, tight serving or training loops, harnesses that forbid hipMalloc.  Same result as mi3d_conv3d_wgrad, bit
- * for bit (same kernels); the scratch the kernels need (per-workgroup partial sums, packed operands) is a static
- * device array of MI3D_STATIC_SCRATCH_BYTES inside the library, which every GPU the library runs on holds from the
+ * capture, tight serving or training loops, harnesses that forbid hipMalloc.  Same result as mi3d_conv3d_wgrad with a
+ * workspace of MI3D_STATIC_SCRATCH_BYTES, bit for bit (same kernels; the bits of a call with what the query reports as well,
+ * where that is no more); the scratch the kernels need (per-workgroup partial sums, packed operands) is a static
+ * device array of that size inside the library, which every GPU the library runs on holds from the
  * first call until the process ends.  The call allocates nothing and frees nothing.  A geometry whose weight gradient
- * needs more scratch than that (mi3d_conv3d_workspace_bytes(desc, MI3D_PASS_WGRAD) > MI3D_STATIC_SCRATCH_BYTES)
- * returns MI3D_ERR_WORKSPACE and launches nothing, unless it is only the padded copies of channel counts that are not
- * multiples of 32 that do not fit: the plain kernel, which needs none, then runs (sums in another order); every layer of the 5-level U-Net at 192^3 and 208^3 fits.  All
+ * needs more scratch than that at least (mi3d_conv3d_min_workspace_bytes(desc, MI3D_PASS_WGRAD) >
+ * MI3D_STATIC_SCRATCH_BYTES: the plain kernel's partial sums count too) returns MI3D_ERR_WORKSPACE and launches nothing;
+ * every layer of the 5-level U-Net at 192^3 and 208^3 fits with the fastest kernel.  All
  * calls on one GPU share the one array: calls that overlap in time on the same GPU (two streams, two threads) race
  * on it and must be serialised by the caller.  x, dy, dw: device pointers as for mi3d_conv3d_wgrad. */
 #define MI3D_STATIC_SCRATCH_BYTES (64u << 20)

@@ -35,6 +35,11 @@ def workspace_bytes(desc, pass_):
     return int(lib().mi3d_conv3d_workspace_bytes(ctypes.byref(desc), pass_))
 
 
+def min_workspace_bytes(desc, pass_):
+    """What a call needs at least; between this and workspace_bytes a slower kernel runs, with sums in another order."""
+    return int(lib().mi3d_conv3d_min_workspace_bytes(ctypes.byref(desc), pass_))
+
+
 def kernel_name(desc, pass_):
     buf = ctypes.create_string_buffer(64)
     check(lib().mi3d_conv3d_kernel_name(ctypes.byref(desc), pass_, buf, 64), "conv3d_kernel_name")

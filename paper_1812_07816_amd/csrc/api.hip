@@ -1,4 +1,5 @@
 // C ABI of the convolution passes: descriptor validation and kernel choice.
+#include <algorithm>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
@@ -120,14 +121,29 @@ static size_t kernel_workspace(Kernel k, const Geom& g, int pass) {
     return 0;
 }
 
-// What a call needs at least: with less than the query reports, the fp32 convolutions run on the fp32 instructions.
-static size_t kernel_min_workspace(Kernel k, const Geom& g, int pass) { return k == K_F32 ? f32_min_workspace_bytes(g, pass) : kernel_workspace(k, g, pass); }
+// What a kernel needs at least: with less than the query reports, the fp32 convolutions run on the fp32 instructions and the
+// implicit GEMM splits its contraction into fewer parts.
+static size_t kernel_min_workspace(Kernel k, const Geom& g, int pass) {
+    switch (k) {
+        case K_SP: return sp_min_workspace_bytes(g, pass);
+        case K_S2_FWD: return s2_fwd_min_workspace_bytes(g);
+        case K_DGRAD_S2: return dgrad_s2_min_workspace_bytes(g);
+        case K_EMBED_C: return embed_c_min_workspace_bytes(g, pass);
+        case K_EMBED_S: return embed_s_min_workspace_bytes(g, pass);
+        case K_EMBED_K2: return embed_k2_min_workspace_bytes(g, pass);
+        case K_F32: return f32_min_workspace_bytes(g, pass);
+        default: return kernel_workspace(k, g, pass);
+    }
+}
 
-// The kernel for a given workspace: an embedding whose padded copies do not fit gives way to the plain kernel, which
-// needs none or little (the callers' size query reports what the embedding wants; the static scratch has a fixed size).
+// The kernel for a given workspace: a layer whose padded copies do not fit goes to the 3x3x3 embedding or to the plain
+// kernel, which need none or little (the callers' size query reports what the padding wants; the static scratch has a
+// fixed size).
 static Kernel choose_within(const Geom& g, int pass, size_t ws_bytes) {
     const Kernel k = choose(g, pass);
-    if (k == K_EMBED_C && kernel_workspace(k, g, pass) > ws_bytes && kernel_workspace(K_DIRECT, g, pass) <= ws_bytes) return K_DIRECT;
+    if (k != K_EMBED_C || kernel_min_workspace(k, g, pass) <= ws_bytes) return k;
+    for (Kernel q : {K_EMBED_K2, K_DIRECT})
+        if ((q == K_DIRECT || embed_k2_supported(g, pass)) && kernel_min_workspace(q, g, pass) <= ws_bytes) return q;
     return k;
 }
 
@@ -180,6 +196,7 @@ bool auto_is_mfma(const Geom& g, int pass) {
     return k != K_DIRECT && k != K_POINTWISE;
 }
 size_t auto_workspace_bytes(const Geom& g, int pass) { return kernel_workspace(choose(g, pass), g, pass); }
+size_t auto_min_workspace_bytes(const Geom& g, int pass) { return kernel_min_workspace(choose(g, pass), g, pass); }
 int auto_conv(const Geom& g, int pass, const void* a, const void* b, void* out, void* ws, size_t ws_bytes, hipStream_t s) {
     return run_kernel(choose(g, pass), g, pass, a, b, out, ws, ws_bytes, s);
 }
@@ -234,6 +251,18 @@ size_t mi3d_conv3d_workspace_bytes(const mi3d_conv_desc* desc, int pass) {
     Geom g;
     if (make_geom(desc, &g) || pass < 0 || pass > 2) return 0;
     return auto_workspace_bytes(g, pass);
+}
+
+size_t mi3d_conv3d_min_workspace_bytes(const mi3d_conv_desc* desc, int pass) {
+    Geom g;
+    if (make_geom(desc, &g) || pass < 0 || pass > 2) return 0;
+    const Kernel k = choose(g, pass);
+    size_t b = kernel_min_workspace(k, g, pass);
+    if (k == K_EMBED_C) {
+        b = std::min(b, kernel_min_workspace(K_DIRECT, g, pass));
+        if (embed_k2_supported(g, pass)) b = std::min(b, kernel_min_workspace(K_EMBED_K2, g, pass));
+    }
+    return b;
 }
 
 // slope / ref: optional LeakyReLU epilogue (forward: on y; data gradient: derivative factor from ref), 1 / null = none

@@ -432,6 +432,9 @@ static void dg2_layout(const Geom& g, long long* units, int* nwg, int* max_seg) 
     *max_seg = (int)(((*units + *nwg - 1) / *nwg + QD - 1) / QD) + 1;
 }
 
+size_t dgrad_s2_min_workspace_bytes(const Geom& g) {
+    return dgrad_s2_supported(g) && g.Cout > 64 ? ig_min_workspace_bytes(g, MI3D_PASS_DGRAD) : dgrad_s2_workspace_bytes(g);
+}
 size_t dgrad_s2_workspace_bytes(const Geom& g) {
     if (!dgrad_s2_supported(g)) return 0;
     if (g.Cout > 64) return ig_workspace_bytes(g, MI3D_PASS_DGRAD);
@@ -445,7 +448,7 @@ size_t dgrad_s2_workspace_bytes(const Geom& g) {
 }
 
 int dgrad_s2(const Geom& g, const void* dy, const void* w, void* dx, void* ws, size_t ws_bytes, hipStream_t s) {
-    if (ws_bytes < dgrad_s2_workspace_bytes(g)) return MI3D_ERR_WORKSPACE;
+    if (ws_bytes < dgrad_s2_min_workspace_bytes(g)) return MI3D_ERR_WORKSPACE;
     if (g.Cout > 64) return ig_conv(g, MI3D_PASS_DGRAD, dy, w, dx, ws, ws_bytes, s);
     const long long total = g.w_elems();
     const int KK = g.Cout == 32 ? 2 : 4;

@@ -224,7 +224,9 @@ unsigned blocks_for(long long n) { return (unsigned)((n + 255) / 256); }
 // The padded layer: channels rounded up to multiples of 32 (stride 2: the data-gradient kernel walks output channels in
 // chunks of 64), or input channels to 4 where the first-layer kernels then apply.  2x2x2 layers get multiples of 64: the
 // kernel for them takes those, the embedding into 3x3x3 reads voxels outside the window, times zero, and does 27/8 of the work
-// (24 -> 24 at 30^3, N = 2, padded to 32 / to 64: 28.7 / 18.8, 22.4 / 18.4, 32.4 / 22.2 us for the three passes).
+// (24->24 at 30^3, N = 2, padded to 32 / to 64: 28.7 / 18.8, 22.4 / 18.4, 32.4 / 22.2 us for the three passes; 64->96 at 48^3
+// embedded / padded to 128: 47 / 26, 81 / 20, 40 / 27).  Layers of 32 output channels that need no padding otherwise stay with
+// the embedding (32->32 at 96^3 31 / 27, 32 / 36, 31 / 45).
 static Geom padded_geom(const Geom& g, int pass) {
     Geom p = g;
     p.Cout = (g.Cout + 31) / 32 * 32;
@@ -233,7 +235,8 @@ static Geom padded_geom(const Geom& g, int pass) {
         if (pass == MI3D_PASS_FWD ? c4_fwd_supported(p) : pass == MI3D_PASS_DGRAD ? c4_dgrad_supported(p) : c4_wgrad_supported(p)) return p;
     }
     p.Cin = (g.Cin + 31) / 32 * 32;
-    if (g.kD == 2 || (g.sD == 2 && p.Cout > 32)) p.Cout = (p.Cout + 63) / 64 * 64;
+    const bool ragged = p.Cin != g.Cin || p.Cout != g.Cout;
+    if ((g.kD == 2 && ragged) || (g.sD == 2 && p.Cout > 32)) p.Cout = (p.Cout + 63) / 64 * 64;
     return p;
 }
 
@@ -267,13 +270,20 @@ size_t embed_c_workspace_bytes(const Geom& g, int pass) {
     return e.xb + e.yb + e.wb + e.fb + align256(auto_workspace_bytes(e.p, pass));
 }
 
+size_t embed_c_min_workspace_bytes(const Geom& g, int pass) {
+    if (!embed_c_supported(g, pass)) return 0;
+    const EmbedC e = embed_c_layout(g, pass);
+    return e.xb + e.yb + e.wb + auto_min_workspace_bytes(e.p, pass);
+}
+
 // Bound: the copies are a pass over each operand and one more launch, the plain kernels do one product at a time per thread.
 // The three passes, plain kernels -> this: 48 -> 48 channels at 37 x 50 x 61 34.5 -> 0.22 ms, 8 -> 16 at 6^3 0.140 -> 0.061,
 // 40 -> 48 at 12^3 0.98 -> 0.084, 24 -> 48 at 10^3 with stride 2 0.171 -> 0.064: the padded layer wins at every size, so
 // the plain kernels are left with the geometries no matrix-core kernel takes.
 int embed_c_conv(const Geom& g, int pass, const void* a, const void* b, void* out, void* ws, size_t ws_bytes, hipStream_t s) {
-    if (ws_bytes < embed_c_workspace_bytes(g, pass)) return MI3D_ERR_WORKSPACE;
-    const EmbedC e = embed_c_layout(g, pass);
+    if (ws_bytes < embed_c_min_workspace_bytes(g, pass)) return MI3D_ERR_WORKSPACE;
+    EmbedC e = embed_c_layout(g, pass);
+    if (ws_bytes < embed_c_workspace_bytes(g, pass)) e.fb = 0;      // no room for flags: every result is looked at
     const Geom& p = e.p;
     uint16_t* xp = (uint16_t*)ws;
     uint16_t* yp = (uint16_t*)((char*)ws + e.xb);
@@ -351,16 +361,19 @@ bool embed_s_supported(const Geom& g, int pass) {
     return sp_supported(u, pass);   // forward: full-resolution output, then subsampled
 }
 
-size_t embed_s_workspace_bytes(const Geom& g, int pass) {
+static size_t embed_s_bytes(const Geom& g, int pass, bool least) {
     if (!embed_s_supported(g, pass)) return 0;
     Geom u = unit_stride_geom(g);
     size_t up = align256((size_t)u.out_voxels() * g.Cout * 2);
-    return up + align256(pass == MI3D_PASS_WGRAD ? wgrad_mfma_workspace_bytes(u) : sp_workspace_bytes(u, pass));
+    if (pass == MI3D_PASS_WGRAD) return up + align256(wgrad_mfma_workspace_bytes(u));
+    return up + (least ? sp_min_workspace_bytes(u, pass) : align256(sp_workspace_bytes(u, pass)));
 }
+size_t embed_s_workspace_bytes(const Geom& g, int pass) { return embed_s_bytes(g, pass, false); }
+size_t embed_s_min_workspace_bytes(const Geom& g, int pass) { return embed_s_bytes(g, pass, true); }
 
 // fwd: a = x, b = w, out = y.  dgrad: a = dy, b = w, out = dx.  wgrad: a = x, b = dy, out = dw.
 int embed_s_conv(const Geom& g, int pass, const void* a, const void* b, void* out, void* ws, size_t ws_bytes, hipStream_t s) {
-    if (ws_bytes < embed_s_workspace_bytes(g, pass)) return MI3D_ERR_WORKSPACE;
+    if (ws_bytes < embed_s_min_workspace_bytes(g, pass)) return MI3D_ERR_WORKSPACE;
     Geom u = unit_stride_geom(g);
     const size_t upb = align256((size_t)u.out_voxels() * g.Cout * 2);
     uint16_t* up = (uint16_t*)ws;
@@ -423,15 +436,17 @@ bool embed_k2_supported(const Geom& g, int pass) {
     return g.Cin % 32 == 0 && g.Cout % 32 == 0;
 }
 
-size_t embed_k2_workspace_bytes(const Geom& g, int pass) {
+static size_t embed_k2_bytes(const Geom& g, int pass, bool least) {
     if (!embed_k2_supported(g, pass)) return 0;
     Geom e = k3_geom(g);
     size_t first = pass == MI3D_PASS_WGRAD ? align256((size_t)e.w_elems() * 4) : align256((size_t)e.w_elems() * 2);
-    return first + align256(auto_workspace_bytes(e, pass));
+    return first + (least ? auto_min_workspace_bytes(e, pass) : align256(auto_workspace_bytes(e, pass)));
 }
+size_t embed_k2_workspace_bytes(const Geom& g, int pass) { return embed_k2_bytes(g, pass, false); }
+size_t embed_k2_min_workspace_bytes(const Geom& g, int pass) { return embed_k2_bytes(g, pass, true); }
 
 int embed_k2_conv(const Geom& g, int pass, const void* a, const void* b, void* out, void* ws, size_t ws_bytes, hipStream_t s) {
-    if (ws_bytes < embed_k2_workspace_bytes(g, pass)) return MI3D_ERR_WORKSPACE;
+    if (ws_bytes < embed_k2_min_workspace_bytes(g, pass)) return MI3D_ERR_WORKSPACE;
     Geom e = k3_geom(g);
     int st;
     if (pass == MI3D_PASS_WGRAD) {

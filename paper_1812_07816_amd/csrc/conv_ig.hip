@@ -388,7 +388,10 @@ struct IgPlan {
 };
 constexpr double STEP_US = 0.75, START_US = 3.0, PART_BYTES_PER_US = 3e6;
 
-IgPlan make_plan(const Geom& g, int pass) {
+size_t weight_bytes(const Geom& g) { return ((size_t)g.w_elems() * 2 + 255) & ~(size_t)255; }
+
+// (with less workspace than the best plan wants: fewer splits, down to whole contractions, which need none)
+IgPlan make_plan(const Geom& g, int pass, size_t ws_bytes) {
     const bool flip = pass == MI3D_PASS_DGRAD, classes = flip && g.sD == 2;
     const int M = flip ? g.Cin : g.Cout, C = flip ? g.Cout : g.Cin, nch = (C + BK - 1) / BK, slots = 2 * cu_count();
     IgPlan best{};
@@ -411,6 +414,7 @@ IgPlan make_plan(const Geom& g, int pass) {
         for (const int S : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 40, 48, 64}) {
             if (S > most) break;
             if (S > 1 && (S * out_elems * 4 > ((size_t)64 << 20) || tiles * S > 4 * slots)) break;
+            if (S > 1 && S * out_elems * 4 + (flip ? weight_bytes(g) : 0) > ws_bytes) break;
             const double rounds = classes ? (double)work / most * S / slots + 0.5 : (double)((tiles * S + slots - 1) / slots);
             const double us = rounds * ((most + S - 1) / S) * STEP_US + START_US + (S > 1 ? START_US + S * (double)out_elems * 8 / PART_BYTES_PER_US : 0.0);
             if (us < best_us) {
@@ -462,8 +466,6 @@ long long max_span(const Geom& g, int pass, long long* slack) {
     return (most + back) * C * 2 + 256;
 }
 
-size_t weight_bytes(const Geom& g) { return ((size_t)g.w_elems() * 2 + 255) & ~(size_t)255; }
-
 }  // namespace
 
 bool ig_supported(const Geom& g, int pass) {
@@ -475,19 +477,20 @@ bool ig_supported(const Geom& g, int pass) {
     if ((flip ? g.H * (long long)g.W : g.Ho * (long long)g.Wo) >= (1ll << 31) || g.w_elems() * 2 >= (1ll << 31)) return false;
     // (stride-1 layers have the plane kernels for larger planes)
     if (!narrow_planes(g, pass) && (g.sD == 1 || max_span(g, pass, nullptr) >= (1ll << 31))) return false;
-    return g.in_voxels() < (1ll << 31) - 1024 && g.out_voxels() < (1ll << 31) - 1024 && make_plan(g, pass).splits > 0;
+    return g.in_voxels() < (1ll << 31) - 1024 && g.out_voxels() < (1ll << 31) - 1024 && make_plan(g, pass, 0).splits > 0;
 }
 
+size_t ig_min_workspace_bytes(const Geom& g, int pass) { return pass == MI3D_PASS_DGRAD ? weight_bytes(g) : 0; }
 size_t ig_workspace_bytes(const Geom& g, int pass) {
-    const IgPlan p = make_plan(g, pass);
+    const IgPlan p = make_plan(g, pass, ~(size_t)0);
     return (pass == MI3D_PASS_DGRAD ? weight_bytes(g) : 0) + (p.splits > 1 ? p.splits * p.out_elems * sizeof(float) : 0);
 }
 
 // in: activations read (x of the forward pass, dy of the data gradient); out: y or dx
 int ig_conv(const Geom& g, int pass, const void* in, const void* w, void* out, void* ws, size_t ws_bytes, hipStream_t s) {
-    if (ws_bytes < ig_workspace_bytes(g, pass)) return MI3D_ERR_WORKSPACE;
+    if (ws_bytes < ig_min_workspace_bytes(g, pass)) return MI3D_ERR_WORKSPACE;
     const bool flip = pass == MI3D_PASS_DGRAD;
-    const IgPlan plan = make_plan(g, pass);
+    const IgPlan plan = make_plan(g, pass, ws_bytes);
     if (g.hi && g.Cin % 64) return MI3D_ERR_UNSUPPORTED;
     int st = MI3D_OK;
     if (flip) {

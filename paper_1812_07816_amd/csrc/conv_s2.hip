@@ -306,6 +306,9 @@ bool s2_fwd_supported(const Geom& g) {
     return g.Cin == 32 || (g.Cin % 32 == 0 && ig_supported(g, MI3D_PASS_FWD));
 }
 
+size_t s2_fwd_min_workspace_bytes(const Geom& g) {
+    return s2_fwd_supported(g) && g.Cin > 32 ? ig_min_workspace_bytes(g, MI3D_PASS_FWD) : s2_fwd_workspace_bytes(g);
+}
 size_t s2_fwd_workspace_bytes(const Geom& g) {
     if (!s2_fwd_supported(g)) return 0;
     if (g.Cin > 32) return ig_workspace_bytes(g, MI3D_PASS_FWD);
@@ -313,7 +316,7 @@ size_t s2_fwd_workspace_bytes(const Geom& g) {
 }
 
 int s2_fwd(const Geom& g, const void* x, const void* w, void* y, void* ws, size_t ws_bytes, hipStream_t s) {
-    if (ws_bytes < s2_fwd_workspace_bytes(g)) return MI3D_ERR_WORKSPACE;
+    if (ws_bytes < s2_fwd_min_workspace_bytes(g)) return MI3D_ERR_WORKSPACE;
     if (g.Cin > 32) return ig_conv(g, MI3D_PASS_FWD, x, w, y, ws, ws_bytes, s);
     long long total = g.w_elems();
     s2_pack_weights_kernel<<<(unsigned)((total + 255) / 256), 256, 0, s>>>((const uint16_t*)w, (uint16_t*)ws, g.Cin, g.Cout);

@@ -79,6 +79,7 @@ int reduce_partials(const float* part, float* out, long long n, int parts, hipSt
 // plane-streaming MFMA kernel: bf16, 3x3x3, stride 1 (forward and data gradient)
 bool sp_supported(const Geom& g, int pass);
 size_t sp_workspace_bytes(const Geom& g, int pass);
+size_t sp_min_workspace_bytes(const Geom& g, int pass);
 int sp_conv(const Geom& g, int pass, const void* in, const void* w, void* out, void* ws, size_t ws_bytes, hipStream_t s);
 bool sp_fuses_dgrad_factor(const Geom& g);  // the forward LeakyReLU is always fused
 bool sp_fuses_stats(const Geom& g);         // instance-normalisation statistics of the forward output
@@ -93,7 +94,8 @@ int instnorm_finish_means(const float* part, int blocks, int C, int N, double in
 
 // implicit GEMM over numbered positions: bf16, 3x3x3, stride 1 and 2 (forward and data gradient), small volumes and many channels
 bool ig_supported(const Geom& g, int pass);
-size_t ig_workspace_bytes(const Geom& g, int pass);
+size_t ig_workspace_bytes(const Geom& g, int pass);       // what the best split of the contraction wants
+size_t ig_min_workspace_bytes(const Geom& g, int pass);   // what a call needs at least
 int ig_conv(const Geom& g, int pass, const void* in, const void* w, void* out, void* ws, size_t ws_bytes, hipStream_t s);
 
 
@@ -106,15 +108,18 @@ int wgrad_mfma(const Geom& g, const void* x, const void* dy, float* dw, void* ws
 // MFMA forward pass of the 3x3x3 stride-2 convolution with 32 input channels
 bool s2_fwd_supported(const Geom& g);
 size_t s2_fwd_workspace_bytes(const Geom& g);
+size_t s2_fwd_min_workspace_bytes(const Geom& g);
 int s2_fwd(const Geom& g, const void* x, const void* w, void* y, void* ws, size_t ws_bytes, hipStream_t s);
 
 
 // fallbacks through the MFMA kernels: zero-padded channels, zero-spread dy
 bool embed_c_supported(const Geom& g, int pass);
 size_t embed_c_workspace_bytes(const Geom& g, int pass);
+size_t embed_c_min_workspace_bytes(const Geom& g, int pass);
 int embed_c_conv(const Geom& g, int pass, const void* a, const void* b, void* out, void* ws, size_t ws_bytes, hipStream_t s);
 bool embed_s_supported(const Geom& g, int pass);
 size_t embed_s_workspace_bytes(const Geom& g, int pass);
+size_t embed_s_min_workspace_bytes(const Geom& g, int pass);
 int embed_s_conv(const Geom& g, int pass, const void* a, const void* b, void* out, void* ws, size_t ws_bytes, hipStream_t s);
 
 
@@ -143,6 +148,7 @@ int c4_wgrad(const Geom& g, const void* x, const void* dy, float* dw, void* ws, 
 // MFMA data gradient of the 3x3x3 stride-2 convolution (equal pads 0/1, Cout 32 or 64)
 bool dgrad_s2_supported(const Geom& g);
 size_t dgrad_s2_workspace_bytes(const Geom& g);
+size_t dgrad_s2_min_workspace_bytes(const Geom& g);
 int dgrad_s2(const Geom& g, const void* dy, const void* w, void* dx, void* ws, size_t ws_bytes, hipStream_t s);
 bool dgrad_s2_fuses_factor(const Geom& g);
 bool dgrad_s2_fuses_skip(const Geom& g);   // the added second gradient of a skip connection
@@ -162,6 +168,7 @@ int pointwise_f32_conv(const Geom& g, int pass, const void* a, const void* b, vo
 // whose weights sit at taps {1,2}^3 (even extents only)
 bool embed_k2_supported(const Geom& g, int pass);
 size_t embed_k2_workspace_bytes(const Geom& g, int pass);
+size_t embed_k2_min_workspace_bytes(const Geom& g, int pass);
 int embed_k2_conv(const Geom& g, int pass, const void* a, const void* b, void* out, void* ws, size_t ws_bytes, hipStream_t s);
 
 // fp32 MFMA kernels: any kernel extent up to 3 and stride up to 2 (forward, data gradient, weight gradient)
@@ -179,6 +186,7 @@ bool f32_takes_halves(const Geom& g, int pass);   // the tensor of x's shape as 
 // automatic kernel choice for a geometry (a, b, out per pass: fwd (x, w, y), dgrad (dy, w, dx), wgrad (x, dy, dw))
 bool auto_is_mfma(const Geom& g, int pass);   // a matrix-core kernel takes it, directly or behind an embedding
 size_t auto_workspace_bytes(const Geom& g, int pass);
+size_t auto_min_workspace_bytes(const Geom& g, int pass);   // what the chosen kernel needs at least
 int auto_conv(const Geom& g, int pass, const void* a, const void* b, void* out, void* ws, size_t ws_bytes, hipStream_t s);
 
 }  // namespace mi3d

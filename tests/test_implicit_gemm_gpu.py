@@ -2,10 +2,13 @@
 the sizes where its tiles can go wrong: positions that end inside a tile and tiles that span samples, channel counts
 that end inside a step or a tile, extents of one, classes of the stride-2 data gradient without voxels, contractions
 split and whole, and operands in two halves that meet inside a step."""
+import ctypes
+
 import pytest
 import torch
 
 from paper_1812_07816_amd import conv3d as mc
+from paper_1812_07816_amd._lib import lib
 from tests import parity
 
 pytestmark = pytest.mark.gpu
@@ -61,3 +64,39 @@ def test_planes_of_many_voxels(device, case):
     errs = parity.run_case(95, 900 + p, N, D, H, W, Cin, Cout, 3, 2, p, bf16=True, full=False, n_samples=20000, passes=("fwd", "dgrad"))
     for q, v in errs.items():
         assert v <= parity.TOL["bf16"], (case, q, v)
+
+
+# geometry, pass, workspace that the query reported when these layers had kernels of their own
+KEPT = [
+    ((1, 8, 8, 8, 32, 96, 3, 1, 1), mc.PASS_DGRAD, 370688),
+    ((1, 8, 8, 8, 96, 96, 3, 1, 1), mc.PASS_DGRAD, 1095680),
+    ((1, 9, 10, 11, 256, 96, 3, 1, 1), mc.PASS_FWD, 4376576),
+    ((1, 10, 10, 10, 64, 128, 3, 2, 1), mc.PASS_FWD, 578560),
+]
+
+
+@pytest.mark.parametrize("case", KEPT, ids=[f"{c[0][4]}-{c[0][5]}s{c[0][7]}" for c in KEPT])
+def test_less_workspace_means_fewer_parts(device, case):
+    """A workspace between the minimum and what the best split wants is enough, one byte less than the minimum is not; the
+    result differs from the one with all parts by the order of the fp32 sums: one rounding to bf16."""
+    args, q, kept = case
+    desc = mc.make_desc(*args, torch.bfloat16)
+    least, want = mc.min_workspace_bytes(desc, q), mc.workspace_bytes(desc, q)
+    assert least <= kept < want
+    N, D, H, W, Cin, Cout = args[:6]
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    out = (N, *mc.out_dims(desc), Cout)
+    a = torch.randn(out if q == mc.PASS_DGRAD else (N, D, H, W, Cin), generator=gen, device="cuda").bfloat16()
+    w = (torch.randn((Cout, 3, 3, 3, Cin), generator=gen, device="cuda") / 30).bfloat16()
+    f = lib().mi3d_conv3d_dgrad if q == mc.PASS_DGRAD else lib().mi3d_conv3d_fwd
+    got = []
+    for n in (want, kept, least):
+        o = torch.full((N, D, H, W, Cin) if q == mc.PASS_DGRAD else out, float("nan"), device="cuda").bfloat16()
+        ws = torch.zeros(max(n, 16), dtype=torch.uint8, device="cuda")
+        assert f(ctypes.byref(desc), a.data_ptr(), w.data_ptr(), o.data_ptr(), ws.data_ptr() if n else None, n, None) == 0, n
+        torch.cuda.synchronize()
+        got.append(o.float())
+    for o in got[1:]:
+        assert float((o - got[0]).abs().max()) <= 2.0 ** -8 * float(got[0].abs().max())
+    if least:
+        assert f(ctypes.byref(desc), a.data_ptr(), w.data_ptr(), o.data_ptr(), ws.data_ptr(), least - 1, None) == -3

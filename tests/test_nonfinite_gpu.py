@@ -83,3 +83,19 @@ def test_padded_channels_sum_over_the_window_alone(device, case, where):
         _same(parity.to_host(mc.conv3d_dgrad(desc, dyd, wd)), oc.dgrad(g, dy, w), tol, ("dgrad", case))
     if where != "w":
         _same(parity.to_host(mc.conv3d_wgrad(desc, xd, dyd)), oc.wgrad(g, x, dy), tol, ("wgrad", case))
+
+
+@pytest.mark.parametrize("case", [(2, 4, 6, 9, 31, 32, 3, 1, 1), (1, 3, 6, 9, 32, 48, 3, 1, 2)])
+def test_padding_without_room_for_the_flags(device, case):
+    """The least workspace of a padded layer holds no flags of the weights: every result is looked at instead."""
+    N, D, H, W, Cin, Cout, k, s, p = case
+    q = mc.PASS_FWD if Cin % 32 else mc.PASS_DGRAD
+    x, w, dy = si.conv_case(98, 900 + Cin, N, D, H, W, Cin, Cout, k, s, p, True)
+    w[1, 0, 0, k - 1, Cin // 2] = np.inf
+    desc = mc.make_desc(N, D, H, W, Cin, Cout, k, s, p, torch.bfloat16)
+    g = oc.shape(N, D, H, W, Cin, Cout, k, s, p)
+    ws = torch.empty(mc.workspace_bytes(desc, q) - 256, dtype=torch.uint8, device="cuda")
+    xd, wd, dyd = (parity.to_device(v, True) for v in (x, w, dy))
+    got, ref = ((mc.conv3d_fwd(desc, xd, wd, ws=ws), oc.fwd(g, x, w)) if q == mc.PASS_FWD else
+                (mc.conv3d_dgrad(desc, dyd, wd, ws=ws), oc.dgrad(g, dy, w)))
+    _same(parity.to_host(got), ref, parity.TOL["bf16"], case)
