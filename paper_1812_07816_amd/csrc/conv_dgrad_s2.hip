@@ -408,13 +408,15 @@ __global__ void __launch_bounds__(256) dgrad_s2_pack_kernel(const uint16_t* __re
 
 static size_t dg2_stat_offset(const Geom& g) { return (((size_t)g.w_elems() * 2 + 255) & ~(size_t)255) + 8192; }
 
+// Above 64 output channels the implicit GEMM takes multiples of 32, the last step of a tap half full (data gradients, padded
+// to multiples of 64 / as they are: 32->96 at 48^3 31.5 / 25.0 us, 96->96 35.4 / 27.6, 64->160 at 24^3, N = 2 34.1 / 29.5).
 bool dgrad_s2_supported(const Geom& g) {
     if (g.dtype != MI3D_BF16 || g.kD != 3 || g.kH != 3 || g.kW != 3) return false;
     if (g.sD != 2 || g.sH != 2 || g.sW != 2) return false;
     if (g.pD != g.pH || g.pD != g.pW || g.pD > 1) return false;
     if (!g.planes_fit_32bit()) return false;
     if (g.Cin % 32) return false;
-    return g.Cout == 32 || g.Cout == 64 || (g.Cout % 64 == 0 && ig_supported(g, MI3D_PASS_DGRAD));
+    return g.Cout == 32 || g.Cout == 64 || (g.Cout % 32 == 0 && ig_supported(g, MI3D_PASS_DGRAD));
 }
 
 // the implicit GEMM applies the optional derivative factor of the geometry

@@ -221,12 +221,11 @@ unsigned blocks_for(long long n) { return (unsigned)((n + 255) / 256); }
 }  // namespace
 
 // ---- channel counts that no MFMA kernel takes --------------------------------
-// The padded layer: channels rounded up to multiples of 32 (stride 2: the data-gradient kernel walks output channels in
-// chunks of 64), or input channels to 4 where the first-layer kernels then apply.  2x2x2 layers get multiples of 64: the
-// kernel for them takes those, the embedding into 3x3x3 reads voxels outside the window, times zero, and does 27/8 of the work
-// (24->24 at 30^3, N = 2, padded to 32 / to 64: 28.7 / 18.8, 22.4 / 18.4, 32.4 / 22.2 us for the three passes; 64->96 at 48^3
-// embedded / padded to 128: 47 / 26, 81 / 20, 40 / 27).  Layers of 32 output channels that need no padding otherwise stay with
-// the embedding (32->32 at 96^3 31 / 27, 32 / 36, 31 / 45).
+// The padded layer: channels rounded up to multiples of 32, or input channels to 4 where the first-layer kernels then apply.
+// 2x2x2 layers get multiples of 64: the kernel for them takes those, the embedding into 3x3x3 reads voxels outside the
+// window, times zero, and does 27/8 of the work (24->24 at 30^3, N = 2, padded to 32 / to 64: 28.7 / 18.8, 22.4 / 18.4, 32.4 / 22.2 us
+// for the three passes; 64->96 at 48^3 embedded / padded to 128: 47 / 26, 81 / 20, 40 / 27).  Layers of 32 output channels that
+// need no padding otherwise stay with the embedding (32->32 at 96^3 31 / 27, 32 / 36, 31 / 45).
 static Geom padded_geom(const Geom& g, int pass) {
     Geom p = g;
     p.Cout = (g.Cout + 31) / 32 * 32;
@@ -236,7 +235,7 @@ static Geom padded_geom(const Geom& g, int pass) {
     }
     p.Cin = (g.Cin + 31) / 32 * 32;
     const bool ragged = p.Cin != g.Cin || p.Cout != g.Cout;
-    if ((g.kD == 2 && ragged) || (g.sD == 2 && p.Cout > 32)) p.Cout = (p.Cout + 63) / 64 * 64;
+    if (g.kD == 2 && (ragged || p.Cout > 32)) p.Cout = (p.Cout + 63) / 64 * 64;
     return p;
 }
 

@@ -25,9 +25,9 @@ CASES = [
     (1, 6, 19, 37, 3, 32, 3, 1, 1, (PAD,) * 3),          # padded to 4: first-layer kernels
     (2, 5, 9, 35, 1, 40, 3, 1, 1, (PAD,) * 3),
     (1, 4, 5, 34, 4, 8, 3, 1, 1, (PAD,) * 3),            # 4 input channels as they are
-    (1, 7, 9, 13, 24, 72, 3, 2, 1, (PAD,) * 3),          # stride 2: output channels in 64s
+    (1, 7, 9, 13, 24, 72, 3, 2, 1, (PAD,) * 3),          # stride 2: output channels in 32s, as at stride 1
     (2, 8, 6, 10, 48, 96, 3, 2, 0, (PAD,) * 3),
-    (1, 6, 8, 10, 32, 96, 3, 2, 1, ("mfma_stride2_plane_stream", PAD, "mfma_wgrad_stride2")),
+    (1, 6, 8, 10, 32, 96, 3, 2, 1, ("mfma_stride2_plane_stream", "mfma_dgrad_stride2_parity", "mfma_wgrad_stride2")),
     (1, 4, 6, 8, 24, 48, 2, 2, 0, (PAD,) * 3),           # up-sampling layer
     (1, 1, 1, 1, 5, 7, 3, 1, 1, (PAD,) * 3),             # one voxel
     (1, 4, 4, 4, 40, 5, 1, 1, 0, ("direct",) * 3),       # 1x1x1: no kernel behind the padding
