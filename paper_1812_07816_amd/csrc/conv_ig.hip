@@ -390,26 +390,37 @@ constexpr double STEP_US = 0.75, START_US = 3.0, PART_BYTES_PER_US = 3e6;
 
 size_t weight_bytes(const Geom& g) { return ((size_t)g.w_elems() * 2 + 255) & ~(size_t)255; }
 
+// Tiles of all classes for tiles of bm x bn, the steps of all of them, and of the longest
+long long count_tiles(const Geom& g, int pass, int bm, int bn, long long* work, int* most) {
+    const bool flip = pass == MI3D_PASS_DGRAD, classes = flip && g.sD == 2;
+    const int M = flip ? g.Cin : g.Cout, C = flip ? g.Cout : g.Cin, nch = (C + BK - 1) / BK, MT = (M + bm - 1) / bm;
+    long long tiles = 0;
+    *work = 0; *most = 0;
+    for (int c = 0; c < (classes ? 8 : 1); ++c) {
+        const int a = c >> 2, b = c >> 1 & 1, d = c & 1;
+        const long long J = classes ? (long long)g.N * ((g.D - a + 1) / 2) * ((g.H - b + 1) / 2) * ((g.W - d + 1) / 2) : (flip ? g.in_voxels() : g.out_voxels());
+        const int ntap = classes ? (g.pD ? (1 << (a + b + d)) : (1 << (3 - a - b - d))) : 27;
+        const long long n = (J + bn - 1) / bn * MT;
+        tiles += n;
+        *work += n * ntap * nch;
+        if (J && ntap * nch > *most) *most = ntap * nch;
+    }
+    return tiles;
+}
+constexpr long long MAX_TILES = 1ll << 26;   // (of a grid; no volume whose planes are this small has more)
+
 // (with less workspace than the best plan wants: fewer splits, down to whole contractions, which need none)
 IgPlan make_plan(const Geom& g, int pass, size_t ws_bytes) {
     const bool flip = pass == MI3D_PASS_DGRAD, classes = flip && g.sD == 2;
-    const int M = flip ? g.Cin : g.Cout, C = flip ? g.Cout : g.Cin, nch = (C + BK - 1) / BK, slots = 2 * cu_count();
+    const int M = flip ? g.Cin : g.Cout, slots = 2 * cu_count();
     IgPlan best{};
     double best_us = 1e30;
     for (int wn = 2; wn <= 4; wn += 2) {
-        const int bm = wn == 2 ? 128 : 64, bn = 64 * wn, MT = (M + bm - 1) / bm;
-        long long tiles = 0, work = 0;   // work in tile steps
-        int most = 0;
-        for (int c = 0; c < (classes ? 8 : 1); ++c) {
-            const int a = c >> 2, b = c >> 1 & 1, d = c & 1;
-            const long long J = classes ? (long long)g.N * ((g.D - a + 1) / 2) * ((g.H - b + 1) / 2) * ((g.W - d + 1) / 2) : (flip ? g.in_voxels() : g.out_voxels());
-            const int ntap = classes ? (g.pD ? (1 << (a + b + d)) : (1 << (3 - a - b - d))) : 27;
-            const long long n = (J + bn - 1) / bn * MT;
-            tiles += n;
-            work += n * ntap * nch;
-            if (J && ntap * nch > most) most = ntap * nch;
-        }
-        if (tiles > (1ll << 26)) continue;   // (a grid of 2^26 workgroups at most; no such volume has planes this small)
+        const int bm = wn == 2 ? 128 : 64, MT = (M + bm - 1) / bm;
+        long long work;          // in tile steps
+        int most;
+        const long long tiles = count_tiles(g, pass, bm, 64 * wn, &work, &most);
+        if (tiles > MAX_TILES) continue;
         const size_t out_elems = (size_t)(flip ? g.in_voxels() * g.Cin : g.out_voxels() * g.Cout);
         for (const int S : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 40, 48, 64}) {
             if (S > most) break;
@@ -477,7 +488,10 @@ bool ig_supported(const Geom& g, int pass) {
     if ((flip ? g.H * (long long)g.W : g.Ho * (long long)g.Wo) >= (1ll << 31) || g.w_elems() * 2 >= (1ll << 31)) return false;
     // (stride-1 layers have the plane kernels for larger planes)
     if (!narrow_planes(g, pass) && (g.sD == 1 || max_span(g, pass, nullptr) >= (1ll << 31))) return false;
-    return g.in_voxels() < (1ll << 31) - 1024 && g.out_voxels() < (1ll << 31) - 1024 && make_plan(g, pass, 0).splits > 0;
+    long long work;
+    int most;
+    return g.in_voxels() < (1ll << 31) - 1024 && g.out_voxels() < (1ll << 31) - 1024 &&
+           (count_tiles(g, pass, 128, 128, &work, &most) <= MAX_TILES || count_tiles(g, pass, 64, 256, &work, &most) <= MAX_TILES);
 }
 
 size_t ig_min_workspace_bytes(const Geom& g, int pass) { return pass == MI3D_PASS_DGRAD ? weight_bytes(g) : 0; }
