@@ -224,8 +224,15 @@ int mi3d_conv3d_fwd_lrelu(const mi3d_conv_desc *desc, const void *x, const void 
 int mi3d_conv3d_dgrad_lrelu(const mi3d_conv_desc *desc, const void *dy, const void *w, const void *a_in, float slope,
                             void *dx, void *ws, size_t ws_bytes, void *stream);
 
-/* Writes the name of the kernel family the dispatcher routes this geometry and pass to (for reports and tests). */
+/* Writes the name of the kernel family the dispatcher routes this geometry and pass to (for reports and tests).  A
+ * family can hold several device kernels: "mfma_plane_stream", "mfma_stride2_plane_stream" and
+ * "mfma_dgrad_stride2_parity" run small volumes and many channels as an implicit GEMM, "mfma_f32_gather" forms its
+ * products with the fp32 or the bf16 matrix instructions. */
 int mi3d_conv3d_kernel_name(const mi3d_conv_desc *desc, int pass, char *buf, size_t buf_len);
+
+/* The device kernel that forms the products of a call with ws_bytes of workspace, with the embeddings that lead to it
+ * ("padded_channels > implicit_gemm_128x128 parts 4").  MI3D_ERR_WORKSPACE where such a call is refused. */
+int mi3d_conv3d_kernel_detail(const mi3d_conv_desc *desc, int pass, size_t ws_bytes, char *buf, size_t buf_len);
 
 /* ------------------------------------------------------------------------
  * Steps of the training step around the convolutions (the network of

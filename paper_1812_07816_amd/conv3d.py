@@ -46,6 +46,14 @@ def kernel_name(desc, pass_):
     return buf.value.decode()
 
 
+def kernel_detail(desc, pass_, ws_bytes=None):
+    """The device kernel that forms the products of a call with this much workspace (default: what workspace_bytes reports)."""
+    buf = ctypes.create_string_buffer(128)
+    n = workspace_bytes(desc, pass_) if ws_bytes is None else int(ws_bytes)
+    check(lib().mi3d_conv3d_kernel_detail(ctypes.byref(desc), pass_, n, buf, 128), "conv3d_kernel_detail")
+    return buf.value.decode()
+
+
 def _stream():
     return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
 

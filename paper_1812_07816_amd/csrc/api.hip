@@ -3,6 +3,7 @@
 #include <cstdio>
 #include <cstring>
 #include <mutex>
+#include <string>
 
 #include "mi3d_internal.h"
 
@@ -174,6 +175,32 @@ static int run_kernel(Kernel k, const Geom& g, int pass, const void* a, const vo
     return MI3D_ERR_UNSUPPORTED;
 }
 
+// The device kernel that forms the products, behind the embeddings that lead to it
+static std::string describe(Kernel k, const Geom& g, int pass, size_t ws_bytes) {
+    size_t rest;
+    auto behind = [&](const char* how, const Geom& p) { return std::string(how) + " > " + describe(choose(p, pass), p, pass, rest); };
+    switch (k) {
+        case K_EMBED_C: { const Geom p = embed_c_inner(g, pass, ws_bytes, &rest); return behind("padded_channels", p); }
+        case K_EMBED_S: {
+            const Geom p = embed_s_inner(g, ws_bytes, &rest);
+            return std::string("unit_stride > ") + describe(pass == MI3D_PASS_WGRAD ? K_WGRAD_MFMA : K_SP, p, pass, rest);
+        }
+        case K_EMBED_K2: { const Geom p = embed_k2_inner(g, pass, ws_bytes, &rest); return behind("k3s2", p); }
+        case K_SP: if (!sp_uses_ig(g, pass)) return "plane_stream"; break;
+        case K_S2_FWD: if (g.Cin == 32) return "stride2_plane_stream"; break;
+        case K_DGRAD_S2: if (g.Cout <= 64) return "dgrad_stride2_parity"; break;
+        case K_F32:
+            if (pointwise_f32_supported(g)) return "f32_pointwise_head";
+            if (f32_uses_parts(g, pass, ws_bytes)) return pass == MI3D_PASS_WGRAD ? "f32_wgrad_from_bf16_parts" : "f32_gather_from_bf16_parts";
+            if (pass == MI3D_PASS_WGRAD) return f32_wgrad_folds_taps(g) ? "f32_wgrad_folded_taps" : "f32_wgrad";
+            return "f32_gather";
+        default: return kernel_name(k);
+    }
+    char buf[64];
+    ig_describe(g, pass, ws_bytes, buf, sizeof(buf));
+    return buf;
+}
+
 // Kernels that apply the optional epilogue of the geometry themselves (the others are followed by one elementwise pass)
 static bool fuses_epilogue(Kernel k, const Geom& g, int pass) {
     if (k == K_F32) return pass != MI3D_PASS_WGRAD;
@@ -244,6 +271,17 @@ int mi3d_conv3d_kernel_name(const mi3d_conv_desc* desc, int pass, char* buf, siz
     if (k == K_F32 && pointwise_f32_supported(g)) name = "valu_pointwise_head_f32";
     else if (k == K_F32 && pass == MI3D_PASS_WGRAD && f32_wgrad_folds_taps(g)) name = "mfma_f32_wgrad_cin4_folded_taps";
     snprintf(buf, buf_len, "%s", name);
+    return MI3D_OK;
+}
+
+int mi3d_conv3d_kernel_detail(const mi3d_conv_desc* desc, int pass, size_t ws_bytes, char* buf, size_t buf_len) {
+    Geom g;
+    int st = make_geom(desc, &g);
+    if (st) return st;
+    if (!buf || buf_len == 0 || pass < 0 || pass > 2) return MI3D_ERR_INVALID_ARG;
+    const Kernel k = choose_within(g, pass, ws_bytes);
+    if (ws_bytes < kernel_min_workspace(k, g, pass)) return MI3D_ERR_WORKSPACE;
+    snprintf(buf, buf_len, "%s", describe(k, g, pass, ws_bytes).c_str());
     return MI3D_OK;
 }
 

@@ -275,6 +275,13 @@ size_t embed_c_min_workspace_bytes(const Geom& g, int pass) {
     return e.xb + e.yb + e.wb + auto_min_workspace_bytes(e.p, pass);
 }
 
+Geom embed_c_inner(const Geom& g, int pass, size_t ws_bytes, size_t* rest) {
+    EmbedC e = embed_c_layout(g, pass);
+    if (ws_bytes < embed_c_workspace_bytes(g, pass)) e.fb = 0;
+    *rest = ws_bytes - e.xb - e.yb - e.wb - e.fb;
+    return e.p;
+}
+
 // Bound: the copies are a pass over each operand and one more launch, the plain kernels do one product at a time per thread.
 // The three passes, plain kernels -> this: 48 -> 48 channels at 37 x 50 x 61 34.5 -> 0.22 ms, 8 -> 16 at 6^3 0.140 -> 0.061,
 // 40 -> 48 at 12^3 0.98 -> 0.084, 24 -> 48 at 10^3 with stride 2 0.171 -> 0.064: the padded layer wins at every size, so
@@ -370,6 +377,12 @@ static size_t embed_s_bytes(const Geom& g, int pass, bool least) {
 size_t embed_s_workspace_bytes(const Geom& g, int pass) { return embed_s_bytes(g, pass, false); }
 size_t embed_s_min_workspace_bytes(const Geom& g, int pass) { return embed_s_bytes(g, pass, true); }
 
+Geom embed_s_inner(const Geom& g, size_t ws_bytes, size_t* rest) {
+    const Geom u = unit_stride_geom(g);
+    *rest = ws_bytes - align256((size_t)u.out_voxels() * g.Cout * 2);
+    return u;
+}
+
 // fwd: a = x, b = w, out = y.  dgrad: a = dy, b = w, out = dx.  wgrad: a = x, b = dy, out = dw.
 int embed_s_conv(const Geom& g, int pass, const void* a, const void* b, void* out, void* ws, size_t ws_bytes, hipStream_t s) {
     if (ws_bytes < embed_s_min_workspace_bytes(g, pass)) return MI3D_ERR_WORKSPACE;
@@ -443,6 +456,12 @@ static size_t embed_k2_bytes(const Geom& g, int pass, bool least) {
 }
 size_t embed_k2_workspace_bytes(const Geom& g, int pass) { return embed_k2_bytes(g, pass, false); }
 size_t embed_k2_min_workspace_bytes(const Geom& g, int pass) { return embed_k2_bytes(g, pass, true); }
+
+Geom embed_k2_inner(const Geom& g, int pass, size_t ws_bytes, size_t* rest) {
+    const Geom e = k3_geom(g);
+    *rest = ws_bytes - align256((size_t)e.w_elems() * (pass == MI3D_PASS_WGRAD ? 4 : 2));
+    return e;
+}
 
 int embed_k2_conv(const Geom& g, int pass, const void* a, const void* b, void* out, void* ws, size_t ws_bytes, hipStream_t s) {
     if (ws_bytes < embed_k2_min_workspace_bytes(g, pass)) return MI3D_ERR_WORKSPACE;

@@ -998,6 +998,12 @@ size_t f32_workspace_bytes(const Geom& g, int pass) {
     return b;
 }
 
+bool f32_uses_parts(const Geom& g, int pass, size_t ws_bytes) {
+    if (!f32_supported(g, pass) || f32_head(g)) return false;
+    if (pass == MI3D_PASS_WGRAD) return f32s_wgrad_supported(g) && ws_bytes >= f32s_wgrad_workspace_bytes(g);
+    return split_ok(g, pass) && ws_bytes >= f32_workspace_bytes(g, pass);
+}
+
 bool f32_wgrad_folds_taps(const Geom& g) { return f32_supported(g, MI3D_PASS_WGRAD) && wgrad_c4_ok(g); }
 
 bool f32_takes_halves(const Geom& g, int pass) {   // virtual concatenation: halves of Cin in multiples of 32 channels
@@ -1167,7 +1173,7 @@ static int launch_gconv_classes(GcMulti& Q, hipStream_t s) {
 int f32_conv(const Geom& g, int pass, const void* in, const void* w, void* out, void* ws, size_t ws_bytes, hipStream_t s) {
     if (f32_head(g)) return pointwise_f32_conv(g, pass, in, w, out, ws, ws_bytes, s);
     if (ws_bytes < f32_min_workspace_bytes(g, pass)) return MI3D_ERR_WORKSPACE;
-    const bool split = split_ok(g, pass) && ws_bytes >= f32_workspace_bytes(g, pass);
+    const bool split = f32_uses_parts(g, pass, ws_bytes);
     const bool dgrad = pass == MI3D_PASS_DGRAD;
     const int T = (int)g.taps();
     const int K = dgrad ? g.Cout : g.Cin, M = dgrad ? g.Cin : g.Cout, Mpad = (M + 31) / 32 * 32;
@@ -1265,7 +1271,7 @@ int f32_conv(const Geom& g, int pass, const void* in, const void* w, void* out, 
 int f32_wgrad(const Geom& g, const void* x, const void* dy, float* dw, void* ws, size_t ws_bytes, hipStream_t s) {
     if (f32_head(g)) return pointwise_f32_conv(g, MI3D_PASS_WGRAD, x, dy, dw, ws, ws_bytes, s);
     if (ws_bytes < f32_min_workspace_bytes(g, MI3D_PASS_WGRAD)) return MI3D_ERR_WORKSPACE;
-    if (f32s_wgrad_supported(g) && ws_bytes >= f32s_wgrad_workspace_bytes(g)) return f32s_wgrad(g, x, dy, dw, ws, ws_bytes, s);
+    if (f32_uses_parts(g, MI3D_PASS_WGRAD, ws_bytes)) return f32s_wgrad(g, x, dy, dw, ws, ws_bytes, s);
     WgParams P;
     wgrad_layout(g, &P);
     P.x = P.x2 = (const float*)x;

@@ -17,6 +17,8 @@
 // weights' way from HBM and the launches.  Forward / data gradient with their packing and summing launches, former
 // chunked kernels -> this one: 128->256 at 48^3, stride 2, N = 2 112 / 301 -> 62 / 70 us (794 / 698 TFLOP/s), 64->128 at
 // 96^3, stride 2, N = 2 260 / 551 -> 142 / 204, 320->320 at 12^3 74 / 74 -> 32 / 37, 256->256 at 24^3 101 / 101 -> 69 / 72.
+#include <cstdio>
+
 #include "mi3d_internal.h"
 
 namespace mi3d {
@@ -498,6 +500,11 @@ size_t ig_min_workspace_bytes(const Geom& g, int pass) { return pass == MI3D_PAS
 size_t ig_workspace_bytes(const Geom& g, int pass) {
     const IgPlan p = make_plan(g, pass, ~(size_t)0);
     return (pass == MI3D_PASS_DGRAD ? weight_bytes(g) : 0) + (p.splits > 1 ? p.splits * p.out_elems * sizeof(float) : 0);
+}
+
+void ig_describe(const Geom& g, int pass, size_t ws_bytes, char* buf, size_t len) {
+    const IgPlan p = make_plan(g, pass, ws_bytes);
+    snprintf(buf, len, "implicit_gemm_%s%s parts %d", p.wn == 2 ? "128x128" : "64x256", narrow_planes(g, pass) ? "" : "_wide", p.splits);
 }
 
 // in: activations read (x of the forward pass, dy of the data gradient); out: y or dx

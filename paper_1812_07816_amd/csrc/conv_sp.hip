@@ -850,8 +850,9 @@ static bool sp_small(const Geom& g, int pass) {
 bool sp_fuses_stats(const Geom& g) { return th16::supported(g, MI3D_PASS_FWD) && !sp_small(g, MI3D_PASS_FWD); }
 // the data gradient that also delivers the sums of the instance-normalisation backward pass of the layer below
 bool sp_fuses_bwd_sums(const Geom& g) { return th16::supported(g, MI3D_PASS_DGRAD) && !sp_small(g, MI3D_PASS_DGRAD); }
+bool sp_uses_ig(const Geom& g, int pass) { return th16::supported(g, pass) && sp_small(g, pass); }
 size_t sp_min_workspace_bytes(const Geom& g, int pass) {
-    return th16::supported(g, pass) && sp_small(g, pass) ? ig_min_workspace_bytes(g, pass) : sp_workspace_bytes(g, pass);
+    return sp_uses_ig(g, pass) ? ig_min_workspace_bytes(g, pass) : sp_workspace_bytes(g, pass);
 }
 size_t sp_workspace_bytes(const Geom& g, int pass) {
     if (!th16::supported(g, pass)) return 0;

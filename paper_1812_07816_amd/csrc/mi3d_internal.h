@@ -80,6 +80,7 @@ int reduce_partials(const float* part, float* out, long long n, int parts, hipSt
 bool sp_supported(const Geom& g, int pass);
 size_t sp_workspace_bytes(const Geom& g, int pass);
 size_t sp_min_workspace_bytes(const Geom& g, int pass);
+bool sp_uses_ig(const Geom& g, int pass);   // volumes too small for whole planes as units of work
 int sp_conv(const Geom& g, int pass, const void* in, const void* w, void* out, void* ws, size_t ws_bytes, hipStream_t s);
 bool sp_fuses_dgrad_factor(const Geom& g);  // the forward LeakyReLU is always fused
 bool sp_fuses_stats(const Geom& g);         // instance-normalisation statistics of the forward output
@@ -96,6 +97,7 @@ int instnorm_finish_means(const float* part, int blocks, int C, int N, double in
 bool ig_supported(const Geom& g, int pass);
 size_t ig_workspace_bytes(const Geom& g, int pass);       // what the best split of the contraction wants
 size_t ig_min_workspace_bytes(const Geom& g, int pass);   // what a call needs at least
+void ig_describe(const Geom& g, int pass, size_t ws_bytes, char* buf, size_t len);   // tile and parts of the contraction
 int ig_conv(const Geom& g, int pass, const void* in, const void* w, void* out, void* ws, size_t ws_bytes, hipStream_t s);
 
 
@@ -116,10 +118,12 @@ int s2_fwd(const Geom& g, const void* x, const void* w, void* y, void* ws, size_
 bool embed_c_supported(const Geom& g, int pass);
 size_t embed_c_workspace_bytes(const Geom& g, int pass);
 size_t embed_c_min_workspace_bytes(const Geom& g, int pass);
+Geom embed_c_inner(const Geom& g, int pass, size_t ws_bytes, size_t* rest);   // the layer behind the padding and the workspace left for it
 int embed_c_conv(const Geom& g, int pass, const void* a, const void* b, void* out, void* ws, size_t ws_bytes, hipStream_t s);
 bool embed_s_supported(const Geom& g, int pass);
 size_t embed_s_workspace_bytes(const Geom& g, int pass);
 size_t embed_s_min_workspace_bytes(const Geom& g, int pass);
+Geom embed_s_inner(const Geom& g, size_t ws_bytes, size_t* rest);
 int embed_s_conv(const Geom& g, int pass, const void* a, const void* b, void* out, void* ws, size_t ws_bytes, hipStream_t s);
 
 
@@ -169,6 +173,7 @@ int pointwise_f32_conv(const Geom& g, int pass, const void* a, const void* b, vo
 bool embed_k2_supported(const Geom& g, int pass);
 size_t embed_k2_workspace_bytes(const Geom& g, int pass);
 size_t embed_k2_min_workspace_bytes(const Geom& g, int pass);
+Geom embed_k2_inner(const Geom& g, int pass, size_t ws_bytes, size_t* rest);
 int embed_k2_conv(const Geom& g, int pass, const void* a, const void* b, void* out, void* ws, size_t ws_bytes, hipStream_t s);
 
 // fp32 MFMA kernels: any kernel extent up to 3 and stride up to 2 (forward, data gradient, weight gradient)
@@ -180,6 +185,7 @@ size_t f32_workspace_bytes(const Geom& g, int pass);       // what the fastest k
 size_t f32_min_workspace_bytes(const Geom& g, int pass);   // what a call needs at least
 int f32_conv(const Geom& g, int pass, const void* in, const void* w, void* out, void* ws, size_t ws_bytes, hipStream_t s);
 int f32_wgrad(const Geom& g, const void* x, const void* dy, float* dw, void* ws, size_t ws_bytes, hipStream_t s);
+bool f32_uses_parts(const Geom& g, int pass, size_t ws_bytes);   // products from bf16 matrix instructions
 bool f32_wgrad_folds_taps(const Geom& g);   // at most 4 input channels: (tap, channel) pairs as the columns of the MFMA block
 bool f32_takes_halves(const Geom& g, int pass);   // the tensor of x's shape as two halves along the channels
 

@@ -88,3 +88,21 @@ def test_strided_layers_keep_their_kernels_on_large_planes():
         assert [mc.kernel_name(d, q) for q in range(2)] == ["mfma_stride2_plane_stream", "mfma_dgrad_stride2_parity"], hw
     d = mc.make_desc(2, 9, 1200, 1200, 128, 256, 3, 2, 0, torch.bfloat16)
     assert [mc.kernel_name(d, q) for q in range(2)] == ["mfma_stride2_plane_stream", "mfma_dgrad_stride2_parity"]
+
+
+def test_kernel_detail_names_what_runs_and_refuses_what_a_call_refuses():
+    import torch
+    from paper_1812_07816_amd import conv3d as mc
+    d = mc.make_desc(1, 12, 12, 12, 320, 320, 3, 1, 1, torch.bfloat16)
+    assert mc.kernel_detail(d, 0).startswith("implicit_gemm") and mc.kernel_detail(d, 0, 0).endswith("parts 1")
+    d = mc.make_desc(1, 8, 8, 8, 40, 48, 3, 1, 1, torch.bfloat16)
+    assert mc.kernel_detail(d, 0) == "padded_channels > plane_stream" and mc.kernel_detail(d, 0, 0) == "direct"
+    d = mc.make_desc(1, 64, 64, 64, 64, 64, 3, 1, 1, torch.float32)
+    least = mc.min_workspace_bytes(d, 1)
+    assert mc.kernel_detail(d, 1) == "f32_gather_from_bf16_parts" and mc.kernel_detail(d, 1, least) == "f32_gather"
+    buf = ctypes.create_string_buffer(64)
+    l = _lib.lib()
+    assert l.mi3d_conv3d_kernel_detail(ctypes.byref(d), 1, least - 1, buf, 64) == -3
+    assert l.mi3d_conv3d_kernel_detail(ctypes.byref(d), 3, least, buf, 64) == -1
+    assert l.mi3d_conv3d_kernel_detail(ctypes.byref(d), 1, least, None, 0) == -1
+    assert l.mi3d_conv3d_kernel_detail(None, 1, least, buf, 64) == -1

@@ -20,35 +20,36 @@ pytestmark = pytest.mark.gpu
 TOL = 3e-5
 
 CASES = [
-    # N, D, H, W, Cin, Cout, k, s, p
-    (1, 3, 9, 33, 16, 16, 3, 1, 1),       # one stage deep, one row and column beyond an 8 x 32 tile
-    (1, 2, 17, 48, 48, 33, 3, 1, 1),      # 16 x 16 tiles, one channel beyond a block of 32
-    (2, 3, 7, 31, 32, 80, 3, 1, 0),       # row-major tiles, no padding, last block of 64 half full
-    (1, 3, 5, 12, 64, 5, 3, 1, 2),        # padding 2, few output channels
-    (1, 4, 1, 1, 32, 16, 3, 1, 1),        # one column: planes above and below are zero
-    (1, 2, 200, 1, 32, 16, 3, 1, 1),      # patch of a one-column plane too large: the fp32 instructions
-    (1, 3, 12, 12, 320, 320, 3, 1, 1),    # deepest level
-    (1, 5, 11, 13, 32, 64, 3, 2, 1),      # parity classes of an odd extent
-    (2, 4, 6, 70, 16, 64, 3, 2, 0),       # no padding: classes with one and two taps change places
-    (2, 49, 41, 65, 32, 32, 3, 1, 1),     # weight gradient: one row and column beyond its 4 x 32 patches
-    (1, 55, 30, 31, 64, 96, 3, 1, 0),
-    (3, 30, 15, 28, 96, 64, 3, 1, 2),     # padding 2: dy planes beyond both ends
-    (1, 6, 8, 34, 16, 32, (1, 3, 3), 1, (0, 1, 1)),   # one plane per output
+    # N, D, H, W, Cin, Cout, k, s, p; passes whose products come from bf16 parts
+    ((1, 3, 9, 33, 16, 16, 3, 1, 1), "01"),       # one stage deep, one row and column beyond an 8 x 32 tile
+    ((1, 2, 17, 48, 48, 33, 3, 1, 1), "0"),      # 16 x 16 tiles, one channel beyond a block of 32
+    ((2, 3, 7, 31, 32, 80, 3, 1, 0), "01"),       # row-major tiles, no padding, last block of 64 half full
+    ((1, 3, 5, 12, 64, 5, 3, 1, 2), "0"),        # padding 2, few output channels
+    ((1, 4, 1, 1, 32, 16, 3, 1, 1), "01"),        # one column: planes above and below are zero
+    ((1, 2, 200, 1, 32, 16, 3, 1, 1), ""),      # patch of a one-column plane too large: the fp32 instructions
+    ((1, 3, 12, 12, 320, 320, 3, 1, 1), "01"),    # deepest level
+    ((1, 5, 11, 13, 32, 64, 3, 2, 1), "1"),      # parity classes of an odd extent
+    ((2, 4, 6, 70, 16, 64, 3, 2, 0), "1"),       # no padding: classes with one and two taps change places
+    ((2, 49, 41, 65, 32, 32, 3, 1, 1), "012"),     # weight gradient: one row and column beyond its 4 x 32 patches
+    ((1, 55, 30, 31, 64, 96, 3, 1, 0), "012"),
+    ((3, 30, 15, 28, 96, 64, 3, 1, 2), "012"),     # padding 2: dy planes beyond both ends
+    ((1, 6, 8, 34, 16, 32, (1, 3, 3), 1, (0, 1, 1)), "01"),   # one plane per output
 ]
 
 
-@pytest.mark.parametrize("case", CASES, ids=[f"{c[1]}x{c[2]}x{c[3]}-{c[4]}-{c[5]}s{c[7]}" for c in CASES])
-def test_split_products_match_oracle(device, case):
+@pytest.mark.parametrize("case, parts", CASES, ids=[f"{c[1]}x{c[2]}x{c[3]}-{c[4]}-{c[5]}s{c[7]}" for c, _ in CASES])
+def test_split_products_match_oracle(device, case, parts):
     N, D, H, W, Cin, Cout, k, s, p = case
+    d = mc.make_desc(N, D, H, W, Cin, Cout, k, s, p, torch.float32)
+    assert "".join(str(q) for q in range(3) if mc.kernel_detail(d, q).endswith("from_bf16_parts")) == parts
     if isinstance(k, tuple):
         x = torch.randn((N, D, H, W, Cin), device="cuda")
         w = torch.randn((Cout, *k, Cin), device="cuda")
-        d = mc.make_desc(N, D, H, W, Cin, Cout, k, s, p, torch.float32)
         ref = torch.nn.functional.conv3d(x.cpu().double().permute(0, 4, 1, 2, 3), w.cpu().double().permute(0, 4, 1, 2, 3), padding=p)
         err = mc.conv3d_fwd(d, x, w).cpu().double() - ref.permute(0, 2, 3, 4, 1)
         assert float(err.abs().max() / ref.square().mean().sqrt()) <= TOL
         return
-    errs = parity.run_case(97, 10 * CASES.index(case), N, D, H, W, Cin, Cout, k, s, p, bf16=False, full=True)
+    errs = parity.run_case(97, 10 * CASES.index((case, parts)), N, D, H, W, Cin, Cout, k, s, p, bf16=False, full=True)
     for q in ("fwd", "dgrad", "wgrad"):
         assert errs[q] <= TOL, (case, q, errs)
 
@@ -58,6 +59,7 @@ def _both(d, q, a, w, shape):
     K, M = (d.Cout, d.Cin) if q == mc.PASS_DGRAD else (d.Cin, d.Cout)
     small = (27 * K * ((M + 31) // 32 * 32) * 4 + 255) // 256 * 256
     assert mc.workspace_bytes(d, q) > small
+    assert (mc.kernel_detail(d, q), mc.kernel_detail(d, q, small)) == ("f32_gather_from_bf16_parts", "f32_gather")
     f = lib().mi3d_conv3d_dgrad if q == mc.PASS_DGRAD else lib().mi3d_conv3d_fwd
     outs = []
     for n in (mc.workspace_bytes(d, q), small):
@@ -151,6 +153,7 @@ def test_weight_gradient_of_values_without_parts(device, kind):
     torch.manual_seed(6)
     N, D, H, W, c = 2, 96, 22, 60, 32
     d = mc.make_desc(N, D, H, W, c, c, 3, 1, 1, torch.float32)
+    assert mc.kernel_detail(d, mc.PASS_WGRAD) == "f32_wgrad_from_bf16_parts"
     x, dy = torch.randn((N, D, H, W, c), device="cuda"), torch.randn((N, D, H, W, c), device="cuda")
     if kind == "inf":
         x[0, 3, 5, 7, 11], x[1, 10, 13, 31, 31] = float("inf"), float("-inf")
@@ -203,6 +206,7 @@ def test_worst_operands_of_the_split(device):
     overlap = torch.nn.grad.conv3d_weight(one, (1, 1, 3, 3, 3), one, padding=1).permute(0, 2, 3, 4, 1)
     for c, most in ((32, 1), (64, 1 + 6 * 27 * 4)):
         d = mc.make_desc(N, D, H, W, c, c, 3, 1, 1, torch.float32)
+        assert (mc.kernel_detail(d, mc.PASS_WGRAD) == "f32_wgrad_from_bf16_parts") == (c == 64)
         x, w = torch.full((N, D, H, W, c), v, device="cuda"), torch.full((c, 3, 3, 3, c), v, device="cuda")
         for got, r, m in ((mc.conv3d_fwd(d, x, w), c * v * v * window, most), (mc.conv3d_dgrad(d, x, w), c * v * v * window, most),
                           (mc.conv3d_wgrad(d, x, x), v * v * overlap, 1)):
