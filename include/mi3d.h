@@ -484,6 +484,12 @@ int mi3d_swap_set_arena(mi3d_swap_engine *e, void *dev_arena, size_t arena_bytes
 /* Changes budget_bytes of the configuration (a caller that measures its real footprint tightens the planner's budget by
  * what the measurement exceeds the budget it was given).  Invalidates the plan. */
 int mi3d_swap_set_budget(mi3d_swap_engine *e, size_t budget_bytes);
+/* Bytes that the static placement of the next mi3d_swap_plan should keep to (0, the default: as many as the modelled
+ * copies ask for).  A tensor's place is kept from others until its copy to the host is modelled to have finished; under
+ * a limit that time is cut, evenly for all tensors, as far as needed: whoever takes a place too early makes the compute
+ * stream wait for the copy.  mi3d_swap_static_arena_bytes tells what came out; it can exceed the limit where tensors
+ * that are needed together do. */
+int mi3d_swap_set_arena_limit(mi3d_swap_engine *e, size_t bytes);
 int mi3d_swap_static_arena_bytes(mi3d_swap_engine *e, uint64_t *bytes);
 int mi3d_swap_alloc_tensor(mi3d_swap_engine *e, int id, void *stream, void **dev_ptr);
 /* Offset of stay 0 or 1 of tensor `id` in the static placement (stay 1 only for tensors that leave the device). */

@@ -111,6 +111,7 @@ SIGNATURES = {
     "mi3d_swap_free": (_i, [_vp, _vp, _vp]),
     "mi3d_swap_set_arena": (_i, [_vp, _vp, _sz]),
     "mi3d_swap_set_budget": (_i, [_vp, _sz]),
+    "mi3d_swap_set_arena_limit": (_i, [_vp, _sz]),
     "mi3d_swap_planned_offset": (_i, [_vp, _i, _i, ctypes.POINTER(ctypes.c_uint64)]),
     "mi3d_swap_static_arena_bytes": (_i, [_vp, ctypes.POINTER(ctypes.c_uint64)]),
     "mi3d_swap_alloc_tensor": (_i, [_vp, _i, _vp, ctypes.POINTER(_vp)]),

@@ -95,6 +95,7 @@ struct mi3d_swap_engine {
     std::vector<float> op_ms;   // measured op durations (optional): swap-ins are then scheduled by time
     float link_gbs = 0.f;
     int eviction = MI3D_EVICT_SWAP;
+    size_t arena_limit = 0;   // extent the static placement should keep to (0 = none)
     int n_fwd_ops = 0, n_ops = 0;
     bool have_plan = false;
     PlanResult plan_res;
@@ -374,6 +375,7 @@ int mi3d_swap_plan(mi3d_swap_engine* e) {
     p.exclude_tags = e->cfg.exclude_tags;
     p.include_tags = e->cfg.include_tags;
     p.eviction = e->eviction;
+    p.arena_bytes = e->arena_limit;
     p.n_fwd_ops = e->n_fwd_ops;
     p.n_ops = std::max<int>(e->n_ops, (int)e->transient.size());
     int st = plan_swaps(ts, e->transient, p, &e->plan_res);
@@ -517,6 +519,13 @@ int mi3d_swap_alloc(mi3d_swap_engine* e, size_t bytes, void* stream, void** dev_
 int mi3d_swap_set_budget(mi3d_swap_engine* e, size_t budget_bytes) {
     if (!e) return MI3D_ERR_INVALID_ARG;
     e->cfg.budget_bytes = budget_bytes;
+    e->have_plan = false;
+    return MI3D_OK;
+}
+
+int mi3d_swap_set_arena_limit(mi3d_swap_engine* e, size_t bytes) {
+    if (!e) return MI3D_ERR_INVALID_ARG;
+    e->arena_limit = bytes;
     e->have_plan = false;
     return MI3D_OK;
 }

@@ -94,7 +94,7 @@ static void apply_deps(std::vector<PlanTensor>& ts, const PlanParams& p) {
     for (PlanTensor& t : ts) t.prefetch_op = prefetch_by_ops(t, p);
 }
 
-uint64_t place_static(std::vector<PlanTensor>& ts, const PlanParams& p) {
+uint64_t place_static(std::vector<PlanTensor>& ts, const PlanParams& p, int grace) {
     int n_ops = p.n_ops;
     for (const PlanTensor& t : ts) n_ops = std::max(n_ops, t.bwd_last_use_op + 1);
     const bool timed = p.op_ms && !p.op_ms->empty() && p.link_gbs > 0.f;
@@ -112,12 +112,12 @@ uint64_t place_static(std::vector<PlanTensor>& ts, const PlanParams& p) {
         const PlanTensor& t = ts[i];
         fwd_end[i] = t.last_fwd_use_op;
         if (!t.planned) continue;
-        if (!timed) { fwd_end[i] = std::min(t.last_fwd_use_op + 1, std::max(t.prefetch_op - 1, t.last_fwd_use_op)); continue; }
+        if (!timed) { fwd_end[i] = std::min(t.last_fwd_use_op + std::min(grace, 1), std::max(t.prefetch_op - 1, t.last_fwd_use_op)); continue; }
         const double begin = std::max(start[std::min(t.produce_op + 1, n_ops)], link_free);
         const double finish = begin + (double)t.bytes / ((double)p.link_gbs * 1e6) * 1.15 + 0.05;
         link_free = finish;
         int e = t.last_fwd_use_op;
-        while (e + 1 < t.prefetch_op && start[e + 1] < finish) ++e;   // ops that start while the copy still reads the block
+        while (e + 1 < t.prefetch_op && start[e + 1] < finish && e - t.last_fwd_use_op < grace) ++e;   // ops that start while the copy still reads the block
         fwd_end[i] = e;
     }
     struct Stay { int tensor, which, from, to; size_t size, off; };
@@ -159,6 +159,22 @@ uint64_t place_static(std::vector<PlanTensor>& ts, const PlanParams& p) {
     }
     for (const Stay& s : stays) ts[s.tensor].arena_off[s.which] = s.off;
     return extent;
+}
+
+uint64_t place_within(std::vector<PlanTensor>& ts, const PlanParams& p) {
+    int n_ops = p.n_ops;
+    for (const PlanTensor& t : ts) n_ops = std::max(n_ops, t.bwd_last_use_op + 1);
+    uint64_t extent = place_static(ts, p, n_ops);
+    if (p.arena_bytes == 0 || extent <= p.arena_bytes) return extent;
+    int least = n_ops;
+    for (int grace = n_ops - 1; grace >= 0; --grace) {
+        const uint64_t e = place_static(ts, p, grace);
+        if (e >= extent) continue;
+        extent = e;
+        least = grace;
+        if (e <= p.arena_bytes) return e;
+    }
+    return place_static(ts, p, least);
 }
 
 int plan_swaps(std::vector<PlanTensor>& ts, const std::vector<size_t>& transient, const PlanParams& p, PlanResult* res) {
@@ -352,7 +368,7 @@ int plan_swaps(std::vector<PlanTensor>& ts, const std::vector<size_t>& transient
             res->recompute_ms += t.recompute_ms;
         }
     res->planned_peak = peak(ts, transient, n_ops, false, nullptr);
-    res->static_arena_bytes = place_static(ts, p);
+    res->static_arena_bytes = place_within(ts, p);
     if (p.host_pool_bytes && off > p.host_pool_bytes) return MI3D_ERR_HOST_POOL;
     if (res->planned_peak > p.budget_bytes) return MI3D_ERR_OVER_BUDGET;
     return MI3D_OK;

@@ -45,6 +45,7 @@ struct PlanParams {
     const std::vector<float>* op_ms = nullptr;
     float link_gbs = 0.f;
     int eviction = 0;            // MI3D_EVICT_SWAP / _RECOMPUTE / _HYBRID
+    size_t arena_bytes = 0;      // extent the static placement should keep to (0 = none; see place_within)
 };
 
 struct PlanResult {
@@ -68,8 +69,13 @@ uint64_t plan_bytes_at(const std::vector<PlanTensor>& ts, const std::vector<size
 // fixed offset, largest tensors first, each at the lowest offset where it overlaps no stay already placed that it shares an
 // op with.  The first stay of a swapped tensor lasts until its copy to the host has finished: with op times that is
 // modelled (the copies leave one after the other in production order at the link rate), else one op of grace is added.
-// Sizes count in units of 256 bytes.  Fills arena_off and returns the extent of the arena.
-uint64_t place_static(std::vector<PlanTensor>& ts, const PlanParams& p);
+// The copy is waited for `grace` ops at most: a stay that takes a place whose copy is still under way makes the compute
+// stream wait.  Sizes count in units of 256 bytes.  Fills arena_off and returns the extent of the arena.
+uint64_t place_static(std::vector<PlanTensor>& ts, const PlanParams& p, int grace);
+// place_static with the largest grace whose extent keeps to p.arena_bytes (the smallest extent where none does).  Where the
+// link is slower than the forward pass the copies queue up, and with their full time the first stays of the tensors
+// that leave last reach the end of the forward pass: the more is swapped, the larger the arena.
+uint64_t place_within(std::vector<PlanTensor>& ts, const PlanParams& p);
 
 // Fills planned / prefetch_op / host_offset.  Returns 0, MI3D_ERR_OVER_BUDGET
 // or MI3D_ERR_HOST_POOL (the plan is filled in either way), or

@@ -111,6 +111,10 @@ class SwapEngine:
     def set_budget(self, budget_bytes):
         check(lib().mi3d_swap_set_budget(self._h, int(budget_bytes)), "swap_set_budget")
 
+    def set_arena_limit(self, bytes):
+        """Extent that the next plan's static placement should keep to (0: none)."""
+        check(lib().mi3d_swap_set_arena_limit(self._h, int(bytes)), "swap_set_arena_limit")
+
     def static_arena_bytes(self):
         b = ctypes.c_uint64()
         check(lib().mi3d_swap_static_arena_bytes(self._h, ctypes.byref(b)), "swap_static_arena_bytes")

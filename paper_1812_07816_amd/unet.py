@@ -619,6 +619,10 @@ class UNetStep:
             self._calibrate_once(link_gbs)
 
     def _calibrate_once(self, link_gbs):
+        self._measure_op_times(link_gbs)
+        self._read_plan(self.engine.plan(allow_over_budget=True))
+
+    def _measure_op_times(self, link_gbs):
         self.run(update=False)
         tl = []
         self._wait_events = []
@@ -632,13 +636,16 @@ class UNetStep:
         assert len(ms) == self.n_ops
         for op_index, e0, e1 in waits:
             ms[op_index] = max(ms[op_index] - e0.elapsed_time(e1), 0.0)
-        e = self.engine
         # a re-computation costs what the forward op took; the backward ops that ran one under the current plan are
         # charged without it (the planner adds the cost of the re-computations it chooses itself)
         for s in self.saved:
             if self.recomputed[s.id]:
-                b = e.first_use_op(s.id)
+                b = self.engine.first_use_op(s.id)
                 ms[b] = max(ms[b] - ms[s.produce], 0.0)
+        self._set_op_times(ms, link_gbs)
+
+    def _set_op_times(self, ms, link_gbs):
+        e = self.engine
         e.set_op_times(ms, link_gbs)
         for f, op in enumerate(self.ops):
             if op["kind"] in ("conv", "head"):
@@ -646,41 +653,72 @@ class UNetStep:
                     e.set_recompute(op["out"].id, ms[f], op["src"].id, op["src2"].id)
                 else:
                     e.set_recompute(op["out"].id, ms[f], op["src"].id)
-        self._read_plan(e.plan(allow_over_budget=True))
         self.op_ms = ms
 
-    def fit_budget(self, rounds=6):
-        """Makes the step's measured device footprint meet its budget: runs a step, reads the peak of the torch
-        allocator (arena, gradients, weights, workspaces, labels: every device byte this process holds) and, where
-        that exceeds the budget, takes the excess off the planner's budget and plans again.  Returns the measured
-        peak of the last step (bytes)."""
+    def _plan_within(self, limit):
+        """Plans for an arena of at most `limit` bytes: tries planner budgets from the unswapped peak down to what evicting
+        everything leaves, and takes the plan that exposes least of its copies and re-computes least (by the planner's
+        op times; without them the one that moves least), or the smallest arena where none keeps to the limit."""
+        e = self.engine
+        e.set_arena_limit(max(int(limit), 1))
+        e.set_budget(1)
+        e.plan(allow_over_budget=True)
+        st = e.stats()
+        low, high = st["planned_peak_bytes"], st["unswapped_peak_bytes"]
+        ms = getattr(self, "op_ms", None)
+        room = 0.9 * min(sum(ms[:self.n_fwd]), sum(ms[self.n_fwd:])) if ms else 0.0
+        link = getattr(self, "link_gbs", None) or 50.0
+
+        def key(budget):
+            e.set_budget(budget)
+            e.plan(allow_over_budget=True)
+            copy_ms = sum(s.bytes for s in self.saved if e.is_planned(s.id)) / (link * 1e6)
+            over = max(e.static_arena_bytes() - int(limit), 0)
+            return over, max(copy_ms - room, 0.0) + e.stats()["recompute_ms"], copy_ms, -budget
+
+        n = 64
+        best = min(key(b) for b in [1] + [low + (high - low) * k // n for k in range(n + 1)])
+        e.set_budget(-best[3])
+        self._read_plan(e.plan(allow_over_budget=True))
+        return -best[3]
+
+    def fit_budget(self, rounds=3):
+        """Makes the step's measured device footprint meet its budget: runs a step and reads the peak of the torch
+        allocator (arena, gradients, weights, workspaces, labels: every device byte this process holds).  What is held
+        besides the arena does not depend on the plan, so where the peak exceeds the budget the excess bounds the
+        arena: the step is planned for an arena of that size, its op durations are measured under the new plan and it
+        is planned and measured again.  The first plan whose measured peak is within the budget is kept, the one with
+        the smallest peak where none is.  Returns the measured peak under that plan (bytes)."""
         if self.engine is None:
             return None
-        internal = self.budget
-        peak = None
+        budget, best = self.budget, None
         self.fit_log = []     # per round: planner budget, plan status, tensors swapped, re-computed, measured peak
-        for r in range(rounds + 4):
+        limit = 0
+        for r in range(rounds + 1):
             torch.cuda.synchronize()
             torch.cuda.reset_peak_memory_stats()
             self.run(update=False)
             torch.cuda.synchronize()
             peak = torch.cuda.max_memory_allocated()
-            self.fit_log.append((internal, self.plan_status, sum(self.planned), sum(self.recomputed), peak))
-            if peak <= self.budget or self.budget >= (1 << 60):
+            self.fit_log.append((budget, self.plan_status, sum(self.planned), sum(self.recomputed), peak))
+            if best is None or peak < best[0]:
+                best = (peak, budget, limit, getattr(self, "op_ms", None))
+            if peak <= self.budget or self.budget >= (1 << 60) or r == rounds:
                 break
-            # the planner's model has to come down by what the measurement exceeds the budget (the model knows nothing
-            # of what else the process holds, so the correction is relative to the model's own peak)
-            modelled = self.engine.stats()["planned_peak_bytes"]
-            internal = min(internal, modelled) - (peak - self.budget) - (4 << 20)
-            if internal <= 0:
+            if r > 1 and peak >= self.fit_log[-2][4]:     # the arena does not get any smaller
                 break
-            self.engine.set_budget(internal)
+            limit = self.budget - (peak - self.arena.numel()) - (4 << 20)
+            budget = self._plan_within(limit)
+            if getattr(self, "link_gbs", None):
+                self._measure_op_times(self.link_gbs)      # other tensors wait now
+                budget = self._plan_within(limit)
+        if peak != best[0]:
+            peak, budget, limit, ms = best
+            if ms is not None:
+                self._set_op_times(ms, self.link_gbs)
+            self.engine.set_arena_limit(max(int(limit), 0))
+            self.engine.set_budget(budget)
             self._read_plan(self.engine.plan(allow_over_budget=True))
-            # op durations under the new plan (other tensors wait now); the last rounds keep the op durations they
-            # have, so that the plan only moves with the budget (a re-measured time line can move a swap-in by an op
-            # and the footprint by some MB, which kept one run from settling within 0.1 % of its budget)
-            if getattr(self, "link_gbs", None) and r < rounds:
-                self._calibrate_once(self.link_gbs)
         self.measured_peak_bytes = peak
         return peak
 

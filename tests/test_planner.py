@@ -479,3 +479,62 @@ def test_static_placement_reuses_the_space_of_swapped_tensors():
     e2 = make(ts, n_fwd, n_ops, budget_bytes=1 << 40)
     e2.plan()
     assert e2.stats()["static_arena_bytes"] == 10 * 4096     # nothing leaves: everything side by side
+
+
+def _timed_chain(n, size, link_gbs, **kw):
+    """Equal tensors, ops of a millisecond, copies of four: the swap-outs queue up behind the forward pass."""
+    n_fwd, n_ops, ts = chain(n, [size] * n)
+    e = make(ts, n_fwd, n_ops, lookahead=1, **kw)
+    e.set_op_times([1.0] * n_ops, link_gbs)
+    return n_fwd, n_ops, ts, e
+
+
+def test_arena_limit_cuts_the_time_that_places_are_kept_for_copies():
+    size = 1 << 20
+    link = size / 1e6 / 4.0 * 1.15
+    n_fwd, n_ops, ts, e = _timed_chain(12, size, link, budget_bytes=3 * size)
+    e.plan(allow_over_budget=True)
+    kept = e.static_arena_bytes()
+    assert kept >= 10 * size                     # nearly every copy is still under way when the forward pass ends
+    offsets = [e.planned_offset(t[0], 0) for t in ts]
+    e.set_arena_limit(kept)                      # a limit that is met changes nothing
+    e.plan(allow_over_budget=True)
+    assert e.static_arena_bytes() == kept and [e.planned_offset(t[0], 0) for t in ts] == offsets
+    before = kept
+    for limit in (9, 7, 5, 3):
+        e.set_arena_limit(limit * size)
+        e.plan(allow_over_budget=True)
+        got = e.static_arena_bytes()
+        assert got <= limit * size and got <= before, limit
+        before = got
+        # tensors that are needed together still have places of their own
+        stays = [(p, lf, e.planned_offset(i, 0)) for i, _, p, lf, _, _, _ in ts]
+        stays += [(e.prefetch_op(i), bl, e.planned_offset(i, 1)) for i, _, _, _, _, bl, _ in ts if e.is_planned(i)]
+        stays += [(p, bl, e.planned_offset(i, 0)) for i, _, p, _, _, bl, _ in ts if not e.is_planned(i)]
+        for a in range(len(stays)):
+            for b in range(a + 1, len(stays)):
+                (fa, ta, oa), (fb, tb, ob) = stays[a], stays[b]
+                if fa <= tb and fb <= ta and (oa, fa) != (ob, fb):
+                    assert oa + size <= ob or ob + size <= oa
+    e.set_arena_limit(1)                         # cannot be met: the smallest there is
+    e.plan(allow_over_budget=True)
+    assert e.static_arena_bytes() == before
+    e.set_arena_limit(0)
+    e.plan(allow_over_budget=True)
+    assert e.static_arena_bytes() == kept
+
+
+def test_lower_budgets_shrink_the_arena_under_a_limit():
+    """Without the limit the arena stays as it is however much is swapped: with every further tensor that leaves, the copies
+    queue up longer."""
+    size = 1 << 20
+    link = size / 1e6 / 4.0 * 1.15
+    extents = {}
+    for limit in (0, 6):
+        for budget in (9, 7, 5, 3, 1):
+            _, _, _, e = _timed_chain(12, size, link, budget_bytes=budget * size)
+            e.set_arena_limit(limit * size)
+            e.plan(allow_over_budget=True)
+            extents[limit, budget] = e.static_arena_bytes() // size
+    assert [extents[0, b] for b in (9, 7, 5, 3, 1)] == [10] * 5
+    assert [extents[6, b] for b in (9, 7, 5, 3, 1)] == [9, 7, 6, 6, 6]

@@ -334,6 +334,43 @@ def test_measured_device_footprint_meets_the_budget(unet):
     st.close()
 
 
+def test_footprint_meets_the_budget_on_a_link_slower_than_the_forward_pass(unet):
+    """A link of 2 GB/s in the planner's model: the copies out last beyond the forward pass, and places kept until they end
+    would hold everything at once, the more the more is swapped.  The budget comes first; one that nothing meets is
+    answered with the smallest footprint measured, not with the last."""
+    N, vol = 2, 32
+    _, _, ws, xd, ld = _inputs(N, vol, CH, 5)
+    plain = unet.UNetStep(N, vol, CH, ws, xd, ld, swap=False)
+    plain.run(update=False)
+    torch.cuda.synchronize()
+    ref = plain.dw32.clone()
+    del plain
+    torch.cuda.empty_cache()
+    held = torch.cuda.memory_allocated()
+    probe = unet.UNetStep(N, vol, CH, ws, xd, ld, swap=True)
+    free_peak = probe.fit_budget() - held
+    fixed = probe._transient(0)
+    probe.close()
+    del probe
+    torch.cuda.empty_cache()
+    for share, met in ((0.15, True), (0.9, False)):
+        budget = int(free_peak - share * (free_peak - fixed))
+        st = unet.UNetStep(N, vol, CH, ws, xd, ld, swap=True, budget_bytes=budget + held, lookahead=1)
+        st.calibrate(link_gbs=2.0)
+        peak = st.fit_budget()
+        assert (peak - held <= budget) == met, (peak - held, budget, st.fit_log)
+        assert peak == min(row[4] for row in st.fit_log)
+        torch.cuda.synchronize()
+        torch.cuda.reset_peak_memory_stats()
+        st.run(update=False)
+        torch.cuda.synchronize()
+        assert torch.cuda.max_memory_allocated() == peak       # the plan that is kept is the one that was measured
+        assert torch.equal(st.dw32, ref) and st.engine.stats()["n_arena_overflow"] == 0
+        st.close()
+        del st
+        torch.cuda.empty_cache()
+
+
 def test_recomputed_and_hybrid_steps_are_bit_identical(unet):
     """Section 5: dropped tensors are produced again by their convolution at their first backward use; the kernels
     are deterministic, so the gradients are those of the plain step bit for bit."""
