@@ -681,6 +681,10 @@ static int sp_plane_tiles(int Ho, int Wo, int* wtf, int* htp) {
 // them.  Forward / data gradient, this kernel's former 32-channel chunks of work -> implicit GEMM (us): 320->320 at 12^3
 // 74 / 74 -> 32 / 37, 256->256 at 16^3 66 / 66 -> 35 / 38, 256->256 at 24^3 101 / 101 -> 69 / 72, 512->256 at 24^3 forward
 // 180 -> 117; with more units it is no faster than this kernel (256->256 at 24^3, N = 2: 144 / 144 with either).
+// The line at 96 channels is that of the chunks this replaced.  Below it, this kernel -> implicit GEMM forward: 32->32 at 32^3,
+// N = 2 18.6 -> 34.9, at 48^3 21.3 -> 49.3, at 16^3, N = 2 17.1 -> 15.7: 32 channels belong here.  With 64 there is no single
+// answer: 64->64 at 8^3 25.0 -> 12.8, at 16^3, N = 2 28.4 -> 16.5, at 24^3 25.8 -> 21.8, at 40^3 44.2 -> 36.3, but at 32^3, N = 2 34.2 -> 35.6,
+// 64->32 there 29.8 -> 31.1; those volumes take the implicit GEMM only once a rule on rounds of the grid tells them apart.
 bool few_units(const Geom& g, int pass) {
     const bool flip = pass == MI3D_PASS_DGRAD;
     const int cin = flip ? g.Cout : g.Cin, cout = flip ? g.Cin : g.Cout;
