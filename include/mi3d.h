@@ -177,7 +177,7 @@ int mi3d_conv3d_dgrad_skip(const mi3d_conv_desc *desc, const void *dy, const voi
  * x_hi is not null: x then is the low half), and stats[n][c] = (mean, 1 / sqrt(var + eps)) of the stored bf16 values of
  * y over the voxels of sample n, biased variance, as mi3d_instnorm_stats computes them in a pass of its own (same
  * values up to the order of the fp32 partial sums; the order is fixed, so repeated calls give identical bits).
- * stats: N * Cout * 2 floats, device.  Only the unchunked bf16 3x3x3 stride-1 MFMA forward kernels (and the 4-channel
+ * stats: N * Cout * 2 floats, device.  Only the bf16 3x3x3 stride-1 plane-streaming forward kernels (and the 4-channel
  * first-layer kernel with 32 output channels) do this
  * (mi3d_conv3d_fwd_stats_supported tells, 1 / 0); other geometries return MI3D_ERR_UNSUPPORTED and the caller runs
  * the two passes.  Workspace as for mi3d_conv3d_fwd. */
@@ -193,8 +193,8 @@ int mi3d_conv3d_fwd_stats(const mi3d_conv_desc *desc, const void *x, const void 
  *   sums[n][c] = (mean over the voxels of g, mean over the voxels of g * xhat),
  * which is what mi3d_instnorm_lrelu_bwd computes in a reduction pass of its own (same values up to the order of the
  * fp32 partial sums; the order is fixed).  mi3d_instnorm_lrelu_bwd_sums then finishes the backward pass without that
- * reduction.  sums: N * Cin * 2 floats, device; 0 < slope <= 1.  Without add: the unchunked bf16 3x3x3 stride-1 MFMA
- * data-gradient kernels and the 1x1x1 head kernel do this; with add: the unchunked 3x3x3 stride-2 kernel (Cout = 64)
+ * reduction.  sums: N * Cin * 2 floats, device; 0 < slope <= 1.  Without add: the bf16 3x3x3 stride-1 plane-streaming
+ * data-gradient kernels and the 1x1x1 head kernel do this; with add: the 3x3x3 stride-2 kernel (Cout = 64)
  * (mi3d_conv3d_dgrad_insums_supported tells, 1 / 0); other geometries return MI3D_ERR_UNSUPPORTED and the caller runs
  * mi3d_conv3d_dgrad or mi3d_conv3d_dgrad_skip and mi3d_instnorm_lrelu_bwd.  Workspace as for mi3d_conv3d_dgrad; add and
  * a_in must not overlap dx. */

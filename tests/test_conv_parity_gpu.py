@@ -225,7 +225,7 @@ def test_batch2_192_level0_sampled(device):
 
 # ---- config 5's own shapes: batch 2 at full size.  The dispatcher counts work units, so several layers take another
 # kernel variant (or another unit mapping of the same one) at N = 2 than at N = 1: the 24^3 layers run the
-# streamed-weight plane kernel instead of the chunked one, and every persistent kernel deals twice the units.
+# streamed-weight plane kernel instead of the implicit GEMM, and every persistent kernel deals twice the units.
 N2_LAYERS = [
     # name, vol, Cin, Cout, k, s, p, kernels (fwd, dgrad, wgrad)
     ("enc0.conv1", 192, 4, 32, 3, 1, 1, ("mfma_cin4_folded_taps", "mfma_dgrad_cin4_folded_taps", "mfma_wgrad_cin4_folded_taps")),

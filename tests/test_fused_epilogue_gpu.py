@@ -2,7 +2,7 @@
 conv3d_fwd_lrelu (y = lrelu(conv(x, w))) and conv3d_dgrad_lrelu (dx = dgrad(dy, w) * lrelu'(a_in)).
 The oracle side is the fp64 convolution followed by the network's LeakyReLU (Section 4.1) written out with
 numpy; tolerance as for the plain bf16 passes.  The geometries cover every kernel that applies the epilogue
-itself (stride-1 plane streaming with 1, 2 and more input-channel chunks, the chunked variants, the stride-2
+itself (stride-1 plane streaming with 1, 2 and more input-channel chunks, the implicit GEMM, the stride-2
 forward kernels, the 4-channel first layer) and ones that fall back to a separate elementwise pass."""
 import numpy as np
 import pytest
@@ -21,12 +21,12 @@ CASES = [
     (1, 10, 20, 40, 32, 32, 3, 1, 1),     # plane streaming, one chunk
     (1, 8, 16, 32, 64, 32, 3, 1, 1),      # two chunks (forward) / one chunk, two cout tiles (data gradient)
     (1, 65, 65, 66, 128, 32, 3, 1, 1),    # streamed weights (enough units to fill the chip without chunking); sampled
-    (1, 6, 6, 12, 128, 64, 3, 1, 1),      # chunked variant, forward
-    (1, 4, 6, 12, 64, 128, 3, 1, 1),      # chunked variant, data gradient
+    (1, 6, 6, 12, 128, 64, 3, 1, 1),      # implicit GEMM, forward
+    (1, 4, 6, 12, 64, 128, 3, 1, 1),      # implicit GEMM, data gradient
     (1, 4, 4, 6, 320, 320, 3, 1, 1),
     (2, 12, 20, 36, 4, 32, 3, 1, 1),      # first layer
     (1, 12, 14, 34, 32, 64, 3, 2, 1),     # stride 2, one chunk
-    (1, 12, 12, 12, 64, 128, 3, 2, 1),    # stride 2, chunked forward and chunked data gradient
+    (1, 12, 12, 12, 64, 128, 3, 2, 1),    # stride 2, implicit GEMM both ways
     (1, 9, 21, 37, 32, 32, 3, 2, 1),
     (1, 8, 8, 16, 32, 64, 2, 2, 0),       # up-sampling geometry: separate elementwise pass
     (2, 9, 10, 37, 8, 8, 3, 1, 1),        # operand embedding: separate elementwise pass
@@ -74,7 +74,7 @@ SKIP_CASES = [
     (1, 12, 14, 34, 32, 64, 3, 2, 1),     # stride-2 data gradient, sum and factor in the store path; ragged patch tails
     (1, 11, 13, 35, 32, 64, 3, 2, 1),     # odd extents: the last plane, row and column pair are half outside
     (1, 8, 10, 12, 32, 64, 3, 2, 0),      # no padding
-    (1, 12, 12, 12, 64, 128, 3, 2, 1),    # chunked data gradient: sum and factor while the chunks are added
+    (1, 12, 12, 12, 64, 128, 3, 2, 1),    # implicit GEMM, data gradient: sum and factor in its store path
     (1, 4, 6, 6, 256, 320, 3, 2, 1),
     (1, 9, 21, 37, 32, 32, 3, 2, 1),      # Cout 32: two passes
     (1, 8, 16, 32, 32, 32, 3, 1, 1),      # stride 1: two passes

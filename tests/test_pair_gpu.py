@@ -23,7 +23,7 @@ CASES = [
     (1, 6, 20, 40, 64, 32, 1),      # two resident weight chunks forward; one-chunk data gradient, two cout tiles
     (2, 5, 18, 34, 128, 64, 1),     # streamed weights forward; ragged patch tails
     (1, 7, 16, 32, 64, 64, 1),
-    (1, 12, 12, 12, 256, 128, 1),   # few units: chunked variants with fp32 partial sums in both passes
+    (1, 12, 12, 12, 256, 128, 1),   # few units: implicit GEMM with fp32 partial sums in both passes
     (1, 6, 10, 12, 512, 256, 1),
     (1, 5, 17, 33, 64, 32, 0),      # no padding
 ]
@@ -96,7 +96,7 @@ STATS_CASES = [
     (2, 6, 20, 40, 32, 32, 1, False),    # one chunk; two samples
     (1, 9, 17, 33, 32, 64, 1, False),    # two cout tiles, ragged patches
     (2, 5, 18, 34, 64, 32, 1, True),     # two resident chunks, halves
-    (2, 33, 33, 66, 128, 32, 1, True),   # streamed weights (enough units to stay unchunked), halves
+    (2, 33, 33, 66, 128, 32, 1, True),   # streamed weights (enough units for the plane kernel), halves
     (3, 4, 9, 70, 64, 96, 2, False),     # three samples, pad 2, three cout tiles
     (2, 12, 20, 36, 4, 32, 1, False),    # first layer (4 input channels): one segment per workgroup
     (1, 5, 19, 45, 4, 32, 0, False),
@@ -142,7 +142,7 @@ def test_forward_statistics_match_the_separate_pass_and_the_oracle(device, case)
 
 def test_forward_statistics_are_refused_where_the_kernel_cannot_produce_them(device):
     bf = torch.bfloat16
-    for args in ((1, 12, 12, 12, 320, 320, 3, 1, 1),   # chunked variant
+    for args in ((1, 12, 12, 12, 320, 320, 3, 1, 1),   # implicit GEMM
                  (1, 8, 8, 8, 32, 64, 3, 2, 1),        # stride 2
                  (1, 8, 8, 8, 4, 64, 3, 1, 1)):        # first layer with more than one block of output channels
         d = mc.make_desc(*args, bf)
@@ -159,7 +159,7 @@ BSUM_CASES = [
     (2, 6, 20, 40, 32, 32, 1),     # one chunk; two samples
     (1, 9, 17, 33, 64, 32, 1),     # one chunk contracted, two tiles of output channels, ragged patches
     (2, 5, 18, 34, 64, 64, 1),     # two resident chunks
-    (2, 33, 33, 66, 32, 128, 1),   # streamed weights (enough units to stay unchunked)
+    (2, 33, 33, 66, 32, 128, 1),   # streamed weights (enough units for the plane kernel)
     (3, 4, 9, 70, 96, 64, 2),      # three samples, pad 2, three tiles of output channels
 ]
 
@@ -235,7 +235,7 @@ def test_head_data_gradient_with_the_sums_of_the_normalisation_backward_pass(dev
 
 def test_backward_sums_are_refused_where_the_kernel_cannot_produce_them(device):
     bf = torch.bfloat16
-    for args in ((1, 12, 12, 12, 320, 320, 3, 1, 1),   # chunked variant
+    for args in ((1, 12, 12, 12, 320, 320, 3, 1, 1),   # implicit GEMM
                  (1, 8, 8, 8, 32, 64, 3, 2, 1),        # stride 2
                  (1, 8, 8, 8, 4, 32, 3, 1, 1)):        # first layer
         d = mc.make_desc(*args, bf)

@@ -69,7 +69,7 @@ def test_random_geometry_matches_oracle(device, case):
 def _tall_cases():
     """3x3x3 stride-1 layers on planes of 10 to 60 rows and 9 to 100 columns: one to five patch rows of 16 or 12 rows,
     last columns of patches that are paired two patch rows at a time (at most 16 columns inside the tensor) or not, few
-    and many units (chunked, streamed and resident weights).  Sampled oracle: every patch seam plus random positions."""
+    and many units (implicit GEMM, streamed and resident weights).  Sampled oracle: every patch seam plus random positions."""
     r = np.random.RandomState(181207817)
     out = []
     for _ in range(16):

@@ -18,7 +18,7 @@ CASES = [
     (1, 2, 2, 1, 320, 320, 3, 1, 1),    # single column, the deepest level's channels
     (1, 1, 1, 1, 32, 64, 3, 2, 1),      # stride 2 on one voxel
     (1, 2, 3, 5, 32, 64, 3, 2, 1),      # stride 2: one output plane, ragged parity classes
-    (2, 1, 4, 2, 64, 128, 3, 2, 1),     # stride 2, chunked channels
+    (2, 1, 4, 2, 64, 128, 3, 2, 1),     # stride 2, many channels
     (1, 3, 3, 3, 32, 32, 3, 2, 0),      # no padding: a single output voxel
     (1, 1, 1, 1, 4, 32, 3, 1, 1),       # first layer on one voxel
     (1, 1, 3, 7, 4, 32, 3, 1, 1),
