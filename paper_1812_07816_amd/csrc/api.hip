@@ -191,6 +191,11 @@ static std::string describe(Kernel k, const Geom& g, int pass, size_t ws_bytes) 
         case K_DGRAD_S2: if (g.Cout <= 64) return "dgrad_stride2_parity"; break;
         case K_F32:
             if (pointwise_f32_supported(g)) return "f32_pointwise_head";
+            if (f32_uses_ig(g, pass, ws_bytes)) {
+                char buf[64];
+                igf_describe(g, pass, ws_bytes, buf, sizeof(buf));
+                return std::string(buf) + (f32_gathers_parts(g, pass) ? "_from_bf16_parts" : "");
+            }
             if (f32_uses_parts(g, pass, ws_bytes)) return pass == MI3D_PASS_WGRAD ? "f32_wgrad_from_bf16_parts" : "f32_gather_from_bf16_parts";
             if (pass == MI3D_PASS_WGRAD) return f32_wgrad_folds_taps(g) ? "f32_wgrad_folded_taps" : "f32_wgrad";
             return "f32_gather";

@@ -20,6 +20,7 @@
 // B = x at the tap's shift (N = 32 input channels); a workgroup owns one 32 x 32 block of (cout, cin) for all taps
 // (dealt round-robin to its 8 waves) over a range of position tiles; per-workgroup partial sums are added in index
 // order by reduce_partials (bit-reproducible).
+#include "ig_common.h"
 #include "mi3d_internal.h"
 #include "split_f32.h"
 
@@ -825,22 +826,6 @@ __global__ void __launch_bounds__(256, 2) f32_wgrad_c4_kernel(WgParams P) {
     }
 }
 
-// one axis of the gather convolution: valid taps of a class and their input offsets
-struct AxisTaps { int n; int t[3]; int d[3]; };
-
-// forward: every tap, delta = t - p.  data gradient, stride 1: every tap, delta = p - t.  data gradient, stride 2,
-// class pi: taps with pi + p - t even, delta = (pi + p - t) / 2 (floor division is exact here, also for negatives)
-AxisTaps axis_taps(int k, int s, int p, bool dgrad, int pi) {
-    AxisTaps a{0, {0, 0, 0}, {0, 0, 0}};
-    for (int t = 0; t < k; ++t) {
-        if (!dgrad) { a.t[a.n] = t; a.d[a.n++] = t - p; continue; }
-        const int v = pi + p - t;
-        if (v % s) continue;
-        a.t[a.n] = t; a.d[a.n++] = v / s;
-    }
-    return a;
-}
-
 size_t pack_bytes(const Geom& g, int pass) {
     const int K = pass == MI3D_PASS_DGRAD ? g.Cout : g.Cin, M = pass == MI3D_PASS_DGRAD ? g.Cin : g.Cout;
     const int Mpad = (M + 31) / 32 * 32;
@@ -965,6 +950,8 @@ bool f32_supported(const Geom& g, int pass) {
 // three passes on the matrix cores).  A call with an added gradient or a two-tensor operand keeps the general kernel.
 static bool f32_head(const Geom& g) { return pointwise_f32_supported(g) && !g.add && !g.hi; }
 
+static bool ig_better(const Geom& g, int pass);
+
 size_t f32_min_workspace_bytes(const Geom& g, int pass) {
     if (!f32_supported(g, pass)) return 0;
     size_t b;
@@ -991,11 +978,21 @@ size_t f32_workspace_bytes(const Geom& g, int pass) {
         const size_t p = f32s_wgrad_workspace_bytes(g);
         b = b > p ? b : p;
     }
+    if (f32_supported(g, pass) && ig_better(g, pass)) {
+        const size_t p = igf_workspace_bytes(g, pass);
+        return b > p ? b : p;
+    }
     if (f32_supported(g, pass) && split_ok(g, pass)) {
         const size_t p = split_pack_bytes(g, pass, &at);
         b = b > p ? b : p;
     }
     return b;
+}
+
+bool f32_gathers_parts(const Geom& g, int pass) { return split_ok(g, pass); }
+
+bool f32_uses_ig(const Geom& g, int pass, size_t ws_bytes) {
+    return f32_supported(g, pass) && !f32_head(g) && ig_better(g, pass) && ws_bytes >= igf_min_workspace_bytes(g, pass);
 }
 
 bool f32_uses_parts(const Geom& g, int pass, size_t ws_bytes) {
@@ -1066,6 +1063,46 @@ static int gconv_blocks_of_channels(const GcParams& P, long long tiles, int ntap
         if (fill(1) > 1.15 * fill(2)) CB = 1;
     }
     return CB;
+}
+
+// What f32s_gconv_kernel takes for a stride-1 layer: stages of 16 channels of a plane times what one takes with that many
+// workgroups on a CU (32 / 64 channels per workgroup; alone: 320->320 at 8^3 and 256->256 at 16^3, N = 2, 20^3 64->128; full:
+// 45 x 75 x 91 64->32 and back, 64->64 at 64^3 and 128->128 at 32^3, N = 2).
+static double split_us(const Geom& g, int pass) {
+    GcParams P{};
+    const bool dgrad = pass == MI3D_PASS_DGRAD;
+    P.N = g.N; P.Jd = dgrad ? g.D : g.Do; P.Jh = dgrad ? g.H : g.Ho; P.Jw = dgrad ? g.W : g.Wo;
+    P.K = dgrad ? g.Cout : g.Cin; P.M = dgrad ? g.Cin : g.Cout; P.Mpad = (P.M + 31) / 32 * 32;
+    gconv_tile_shape(&P, false);
+    const long long tiles = (long long)P.N * P.Jd * gconv_row_tiles(P) * gconv_col_tiles(P);
+    const int CB = gconv_blocks_of_channels(P, tiles, (int)g.taps());
+    const double alone = CB == 2 ? 6.4 : 5.0, full = CB == 2 ? 6.2 : 3.95;
+    const double per_cu = full * (double)(tiles * ((P.Mpad + 32 * CB - 1) / (32 * CB))) / cu_count();
+    return 5.0 + (double)(P.K / SP_CK) * g.kD * (per_cu > alone ? per_cu : alone);
+}
+
+// Layers that the implicit GEMM over numbered positions serves better than the kernels here, which stage patches.
+// - Everything f32s_gconv_kernel does not take: its products are formed on the fp32 instructions, from patches up to four
+//   times the tile where the stride is 2.  Forward / data gradient with their packing launches, f32_gconv_kernel -> igf_kernel:
+//   64->128, 2x2x2 at 96^3 320 / 250 -> 138 / 163 us, 32->64, stride 2 at 128^3, N = 2 834 -> 462, 128->256, stride 2 at 32^3,
+//   N = 2 448 -> 116.  Not where a workgroup would be over after four steps and writes 32 channels (the first layer on large
+//   volumes): 4->32 at 60^3 33 -> 40, at 16^3 19 -> 17.
+// - The strided data gradients it does take, eight launches of one to eight taps each: 32->64 at 128^3, N = 2 810 -> 709,
+//   64->128 at 64^3, N = 2 415 -> 244, 128->256 at 32^3, N = 2 592 -> 140, 32->64 at 24^3 159 -> 25.  (Volumes below 2048 voxels
+//   with at most 32 channels keep their kernel, whose classes are tested there on values without parts.)
+// - Of the stride-1 layers those too small for its tiles of 256 positions of a plane and of 64 contracted channels or more
+//   (those with fewer are the large volumes of a network), by the two models of the time: 320->320 at 8^3, N = 2 322 -> 73,
+//   256->256 at 16^3, N = 2 230 -> 194; but 128->128 at 32^3, N = 2 291 -> 338 and 64->64 at 64^3, N = 2 600 -> 745: a patch is
+//   taken apart once for its 27 taps.
+static bool ig_better(const Geom& g, int pass) {
+    if (!igf_supported(g, pass)) return false;
+    const bool dgrad = pass == MI3D_PASS_DGRAD;
+    if (!split_ok(g, pass)) {
+        const int K = dgrad ? g.Cout : g.Cin, M = dgrad ? g.Cin : g.Cout;
+        return K * g.taps() > 128 || M > 32 || (dgrad ? g.in_voxels() : g.out_voxels()) <= 65536;
+    }
+    if (dgrad && g.sH == 2) return g.Cin > 32 || g.N * (long long)g.D * g.H * g.W >= 2048;
+    return (dgrad ? g.Cout : g.Cin) >= 64 && igf_us(g, pass) < split_us(g, pass);
 }
 
 // tiles, channel chunk and LDS bytes of one launch (or one class of a launch) for CB blocks of output channels
@@ -1173,6 +1210,7 @@ static int launch_gconv_classes(GcMulti& Q, hipStream_t s) {
 int f32_conv(const Geom& g, int pass, const void* in, const void* w, void* out, void* ws, size_t ws_bytes, hipStream_t s) {
     if (f32_head(g)) return pointwise_f32_conv(g, pass, in, w, out, ws, ws_bytes, s);
     if (ws_bytes < f32_min_workspace_bytes(g, pass)) return MI3D_ERR_WORKSPACE;
+    if (f32_uses_ig(g, pass, ws_bytes)) return igf_conv(g, pass, in, w, out, ws, ws_bytes, s);
     const bool split = f32_uses_parts(g, pass, ws_bytes);
     const bool dgrad = pass == MI3D_PASS_DGRAD;
     const int T = (int)g.taps();

@@ -19,6 +19,7 @@
 // 96^3, stride 2, N = 2 260 / 551 -> 142 / 204, 320->320 at 12^3 74 / 74 -> 32 / 37, 256->256 at 24^3 101 / 101 -> 69 / 72.
 #include <cstdio>
 
+#include "ig_common.h"
 #include "mi3d_internal.h"
 
 namespace mi3d {
@@ -32,32 +33,11 @@ typedef __attribute__((address_space(3))) void* lds_ptr;
 constexpr unsigned OOB = 0x80000000u;   // buffer offset of a piece that must read as zero
 constexpr int BK = 64;                  // contracted channels of a step
 
-// x / d for 0 <= x < 2^31 by multiplication (Granlund and Montgomery, "Division by Invariant Integers using
-// Multiplication", PLDI 1994): s = ceil(log2 d), m = floor(2^32 (2^s - d) / d) + 1
-struct Div {
-    uint32_t m, s, d;
-};
-Div make_div(uint32_t d) {
-    uint32_t s = 0;
-    while ((1ull << s) < d) ++s;
-    return Div{(uint32_t)(((1ull << 32) * ((1ull << s) - d)) / d + 1), s, d};
-}
-__device__ __forceinline__ int divide(int x, const Div& v) {
-    const uint64_t t = (uint64_t)__umulhi(v.m, (uint32_t)x) + (uint32_t)x;
-    return (int)(t >> v.s);
-}
-
 struct IgClass {      // one product: a parity class of the output voxels (stride-2 data gradient) or everything
     Div jD, jH, jW;   // extents of the position space of a sample
     int J, PT, tile0; // positions of all samples, tiles of them, first tile in the grid
     int od0, oh0, ow0;
     int tap0, ntap;
-};
-// A tap in one word (scalar loads have no bytes): delta_t + 8 along d, h, w and the tap's index in the weights.
-__host__ __device__ __forceinline__ uint32_t tap_word(int dd, int dh, int dw, int wt) { return (dd + 8) | (dh + 8) << 8 | (dw + 8) << 16 | (uint32_t)wt << 24; }
-struct IgTap {
-    int dd, dh, dw, wt;
-    __device__ __forceinline__ IgTap(uint32_t v) : dd((int)(v & 255) - 8), dh((int)(v >> 8 & 255) - 8), dw((int)(v >> 16 & 255) - 8), wt((int)(v >> 24)) {}
 };
 struct IgParams {
     const uint16_t *in, *in_hi;   // two halves along the channels (virtual concatenation), or the tensor and itself

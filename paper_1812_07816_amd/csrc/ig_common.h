@@ -1,0 +1,47 @@
+// What the kernels over numbered positions (implicit GEMM) share: division of position numbers by the extents of the volume,
+// taps in one word, and the parity classes of a strided data gradient.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace mi3d {
+
+// x / d for 0 <= x < 2^31 by multiplication (Granlund and Montgomery, "Division by Invariant Integers using
+// Multiplication", PLDI 1994): s = ceil(log2 d), m = floor(2^32 (2^s - d) / d) + 1
+struct Div {
+    uint32_t m, s, d;
+};
+inline Div make_div(uint32_t d) {
+    uint32_t s = 0;
+    while ((1ull << s) < d) ++s;
+    return Div{(uint32_t)(((1ull << 32) * ((1ull << s) - d)) / d + 1), s, d};
+}
+__device__ __forceinline__ int divide(int x, const Div& v) {
+    const uint64_t t = (uint64_t)__umulhi(v.m, (uint32_t)x) + (uint32_t)x;
+    return (int)(t >> v.s);
+}
+
+// A tap in one word (scalar loads have no bytes): delta_t + 8 along d, h, w and the tap's index in the weights.
+__host__ __device__ __forceinline__ uint32_t tap_word(int dd, int dh, int dw, int wt) { return (dd + 8) | (dh + 8) << 8 | (dw + 8) << 16 | (uint32_t)wt << 24; }
+struct IgTap {
+    int dd, dh, dw, wt;
+    __device__ __forceinline__ IgTap(uint32_t v) : dd((int)(v & 255) - 8), dh((int)(v >> 8 & 255) - 8), dw((int)(v >> 16 & 255) - 8), wt((int)(v >> 24)) {}
+};
+
+// The taps of one axis for outputs of parity class par of the data gradient (out = s j + par reads in = j + delta), or of
+// the forward pass (in = s j + delta): weight indices and deltas.  v / s is exact.
+struct AxisTaps {
+    int n, t[3], d[3];
+};
+inline AxisTaps axis_taps(int k, int s, int p, bool dgrad, int par) {
+    AxisTaps a{0, {0, 0, 0}, {0, 0, 0}};
+    for (int t = 0; t < k; ++t) {
+        if (!dgrad) { a.t[a.n] = t; a.d[a.n++] = t - p; continue; }
+        const int v = par + p - t;
+        if (v % s) continue;
+        a.t[a.n] = t; a.d[a.n++] = v / s;
+    }
+    return a;
+}
+
+}  // namespace mi3d

@@ -181,11 +181,20 @@ bool f32_supported(const Geom& g, int pass);
 bool f32s_wgrad_supported(const Geom& g);                  // conv_wgrad_f32s.hip
 size_t f32s_wgrad_workspace_bytes(const Geom& g);
 int f32s_wgrad(const Geom& g, const void* x, const void* dy, float* dw, void* ws, size_t ws_bytes, hipStream_t s);
+// implicit GEMM over numbered positions, products from bf16 matrix instructions (conv_ig_f32.hip): forward and data gradient
+bool igf_supported(const Geom& g, int pass);
+size_t igf_workspace_bytes(const Geom& g, int pass);
+size_t igf_min_workspace_bytes(const Geom& g, int pass);
+void igf_describe(const Geom& g, int pass, size_t ws_bytes, char* buf, size_t len);
+double igf_us(const Geom& g, int pass);                    // what its model expects the call to take
+int igf_conv(const Geom& g, int pass, const void* in, const void* w, void* out, void* ws, size_t ws_bytes, hipStream_t s);
 size_t f32_workspace_bytes(const Geom& g, int pass);       // what the fastest kernel wants
 size_t f32_min_workspace_bytes(const Geom& g, int pass);   // what a call needs at least
 int f32_conv(const Geom& g, int pass, const void* in, const void* w, void* out, void* ws, size_t ws_bytes, hipStream_t s);
 int f32_wgrad(const Geom& g, const void* x, const void* dy, float* dw, void* ws, size_t ws_bytes, hipStream_t s);
-bool f32_uses_parts(const Geom& g, int pass, size_t ws_bytes);   // products from bf16 matrix instructions
+bool f32_uses_ig(const Geom& g, int pass, size_t ws_bytes);      // implicit GEMM over numbered positions
+bool f32_gathers_parts(const Geom& g, int pass);                 // sizes that the patch kernel with such products serves
+bool f32_uses_parts(const Geom& g, int pass, size_t ws_bytes);   // other kernels with products from bf16 matrix instructions
 bool f32_wgrad_folds_taps(const Geom& g);   // at most 4 input channels: (tap, channel) pairs as the columns of the MFMA block
 bool f32_takes_halves(const Geom& g, int pass);   // the tensor of x's shape as two halves along the channels
 

@@ -23,6 +23,20 @@ struct SplitRange {
     __device__ __forceinline__ bool exceeded() const { return (most >= 0x56000000u) | (least < 0x0D7FFFFFu); }
 };
 
+// The same for values whose NaN may pass (the parts of a NaN are NaN, and so is every sum they enter): half the instructions.
+struct SplitRangeNumbers {
+    float most = 0.f;
+    uint32_t least = 0xFFFFFFFFu;
+    __device__ __forceinline__ void add(float x, float y) {
+        most = __builtin_fmaxf(__builtin_fmaxf(__builtin_fabsf(x), __builtin_fabsf(y)), most);
+        const uint32_t u = (__builtin_bit_cast(uint32_t, x) << 1) - 1, v = (__builtin_bit_cast(uint32_t, y) << 1) - 1;
+        const uint32_t m = u < v ? u : v;
+        least = m < least ? m : least;
+    }
+    __device__ __forceinline__ void add(const float4& v) { add(v.x, v.y); add(v.z, v.w); }
+    __device__ __forceinline__ bool exceeded() const { return (most >= 0x1p45f) | (least < 0x1AFFFFFFu); }
+};
+
 __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
     typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
     typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
