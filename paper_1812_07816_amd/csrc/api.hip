@@ -123,10 +123,12 @@ static size_t kernel_workspace(Kernel k, const Geom& g, int pass) {
 }
 
 // What a kernel needs at least: with less than the query reports, the fp32 convolutions run on the fp32 instructions and the
-// implicit GEMM splits its contraction into fewer parts.
+// implicit GEMM splits its contraction (the weight gradient over numbered positions: those) into fewer parts.
 static size_t kernel_min_workspace(Kernel k, const Geom& g, int pass) {
     switch (k) {
         case K_SP: return sp_min_workspace_bytes(g, pass);
+        case K_WGRAD_MFMA: return wgrad_mfma_min_workspace_bytes(g);
+        case K_WGRAD_S2: return wgrad_s2_min_workspace_bytes(g);
         case K_S2_FWD: return s2_fwd_min_workspace_bytes(g);
         case K_DGRAD_S2: return dgrad_s2_min_workspace_bytes(g);
         case K_EMBED_C: return embed_c_min_workspace_bytes(g, pass);
@@ -178,6 +180,11 @@ static int run_kernel(Kernel k, const Geom& g, int pass, const void* a, const vo
 // The device kernel that forms the products, behind the embeddings that lead to it
 static std::string describe(Kernel k, const Geom& g, int pass, size_t ws_bytes) {
     size_t rest;
+    char buf[64];
+    if (pass == MI3D_PASS_WGRAD && ((k == K_WGRAD_MFMA && wgrad_mfma_uses_igw(g)) || (k == K_WGRAD_S2 && wgrad_s2_uses_igw(g)) || (k == K_F32 && f32_uses_igw(g, ws_bytes)))) {
+        igw_describe(g, ws_bytes, buf, sizeof(buf));
+        return buf;
+    }
     auto behind = [&](const char* how, const Geom& p) { return std::string(how) + " > " + describe(choose(p, pass), p, pass, rest); };
     switch (k) {
         case K_EMBED_C: { const Geom p = embed_c_inner(g, pass, ws_bytes, &rest); return behind("padded_channels", p); }
@@ -192,7 +199,6 @@ static std::string describe(Kernel k, const Geom& g, int pass, size_t ws_bytes) 
         case K_F32:
             if (pointwise_f32_supported(g)) return "f32_pointwise_head";
             if (f32_uses_ig(g, pass, ws_bytes)) {
-                char buf[64];
                 igf_describe(g, pass, ws_bytes, buf, sizeof(buf));
                 return std::string(buf) + (f32_gathers_parts(g, pass) ? "_from_bf16_parts" : "");
             }
@@ -201,7 +207,6 @@ static std::string describe(Kernel k, const Geom& g, int pass, size_t ws_bytes) 
             return "f32_gather";
         default: return kernel_name(k);
     }
-    char buf[64];
     ig_describe(g, pass, ws_bytes, buf, sizeof(buf));
     return buf;
 }

@@ -971,11 +971,32 @@ size_t f32_min_workspace_bytes(const Geom& g, int pass) {
     return b > h ? b : h;
 }
 
+// Weight gradients that the matrix product over numbered positions serves better than the fp32 instructions (which take about 35 us and
+// reach about 70 TFLOP/s of whole 32 x 32 blocks of channels, 45 where taps do not overlap), by its model of the time.  With the launch that adds
+// the partial sums, f32_wgrad_kernel -> igw_f32_kernel: 64->128, 2x2x2 at 96^3 342 -> 120 us, 32->64, stride 2 at 128^3, N = 2 861 -> 684,
+// 128->256, stride 2 at 32^3, N = 2 218 -> 110, 256->256 at 16^3, N = 2 339 -> 213, 128->320 at 11 x 12 x 9 71 -> 43,
+// 32->64 at 13 x 18 x 20 57 -> 21.  Layers with at most
+// four input channels have the kernel that folds the taps (4->32 at 60^3 44 -> 60) but for the smallest volumes (4->8 at
+// 16^3 24 -> 17), and those f32s_wgrad takes stay there (128->128 at 32^3, N = 2 333 -> 394).
+static bool igw_better(const Geom& g, size_t ws_bytes) {
+    Geom q = g;
+    q.hi = nullptr;      // (the sizes decide, not how the call passes its tensors)
+    if (f32s_wgrad_supported(q) || !igw_supported(q) || (g.hi && g.Cin % 64)) return false;
+    if (wgrad_c4_ok(q)) return g.out_voxels() <= 8192;
+    const double blocks = (double)((g.Cin + 31) / 32) * ((g.Cout + 31) / 32) * 1024;
+    const bool apart = g.kD <= g.sD && g.kH <= g.sH && g.kW <= g.sW;
+    return igw_us(q, ws_bytes) < 35.0 + 2.0 * g.out_voxels() * g.taps() * blocks / (apart ? 45e6 : 70e6);
+}
+
 // (the parts of the weights take 1.5 times their room; a call with the smaller workspace gets the fp32 instructions)
 size_t f32_workspace_bytes(const Geom& g, int pass) {
     size_t b = f32_min_workspace_bytes(g, pass), at;
     if (f32_supported(g, pass) && pass == MI3D_PASS_WGRAD && f32s_wgrad_supported(g)) {
         const size_t p = f32s_wgrad_workspace_bytes(g);
+        b = b > p ? b : p;
+    }
+    if (f32_supported(g, pass) && pass == MI3D_PASS_WGRAD && igw_better(g, ~(size_t)0)) {
+        const size_t p = igw_workspace_bytes(g);
         b = b > p ? b : p;
     }
     if (f32_supported(g, pass) && ig_better(g, pass)) {
@@ -988,6 +1009,8 @@ size_t f32_workspace_bytes(const Geom& g, int pass) {
     }
     return b;
 }
+
+bool f32_uses_igw(const Geom& g, size_t ws_bytes) { return f32_supported(g, MI3D_PASS_WGRAD) && !f32_head(g) && igw_better(g, ws_bytes); }
 
 bool f32_gathers_parts(const Geom& g, int pass) { return split_ok(g, pass); }
 
@@ -1309,6 +1332,7 @@ int f32_conv(const Geom& g, int pass, const void* in, const void* w, void* out, 
 int f32_wgrad(const Geom& g, const void* x, const void* dy, float* dw, void* ws, size_t ws_bytes, hipStream_t s) {
     if (f32_head(g)) return pointwise_f32_conv(g, MI3D_PASS_WGRAD, x, dy, dw, ws, ws_bytes, s);
     if (ws_bytes < f32_min_workspace_bytes(g, MI3D_PASS_WGRAD)) return MI3D_ERR_WORKSPACE;
+    if (f32_uses_igw(g, ws_bytes)) return igw_run(g, x, dy, dw, ws, ws_bytes, s);
     if (f32_uses_parts(g, MI3D_PASS_WGRAD, ws_bytes)) return f32s_wgrad(g, x, dy, dw, ws, ws_bytes, s);
     WgParams P;
     wgrad_layout(g, &P);

@@ -20,6 +20,8 @@
 //   MFMAs.  Partial sums go to a per-workgroup slot of the workspace and are
 //   added in slot order by a second kernel, which makes the result
 //   bit-reproducible.
+#include <cmath>
+
 #include "mi3d_internal.h"
 
 // The file is compiled twice: as it is (16-row patches, namespace th16) and from conv_wgrad12.hip with 12-row patches
@@ -402,8 +404,32 @@ static bool wgrad_rows12(const Geom& g) {
 }
 
 bool wgrad_mfma_supported(const Geom& g) { return th16::supported(g); }
-size_t wgrad_mfma_workspace_bytes(const Geom& g) { return wgrad_rows12(g) ? th12::workspace_bytes(g) : th16::workspace_bytes(g); }
+
+// The matrix product over numbered positions where the patches of this kernel are too few, too empty or too many partial
+// sums, by the two models of the time (this kernel: patches a workgroup walks, doubled up where there are more workgroups
+// than CUs, and the way of the partial sums).  With the launch that adds them, this kernel -> igw_kernel: 320->320 at 12^3
+// 51 -> 30 us, at 8^3 41 -> 13, 256->256 at 4^3, N = 2 30 -> 11, 128->128 at 16^3 28 -> 21, at 8^3, N = 2 27 -> 15; but
+// 256->256 at 24^3, N = 2 106 -> 129, 128->128 at 48^3, N = 2 148 -> 222, 64->64 at 37 x 50 x 61 42 -> 63: here an LDS fragment
+// feeds nine products.
+bool wgrad_mfma_uses_igw(const Geom& g) {
+    Geom q = g;
+    q.hi = nullptr;      // (the sizes decide, not how the call passes its tensors)
+    if (!igw_supported(q)) return false;
+    const size_t parts = wgrad_rows12(g) ? th12::workspace_bytes(g) : th16::workspace_bytes(g);
+    const double pairs = (double)(g.Cin / 32) * (g.Cout / 32), slots = (double)parts / (4.0 * g.w_elems());
+    const int rows = wgrad_rows12(g) ? 12 : 16;
+    const double units = (double)g.N * g.D * ((g.Ho + rows - 1) / rows) * ((g.Wo + 31) / 32);
+    const double us = 14.0 + 3.8 * rows / 12 * ceil(units / slots) * (pairs * slots > cu_count() ? 1.5 : 1.0) + (double)parts * 2 / 5e6;
+    return igw_us(q, ~(size_t)0) < 0.9 * us;
+}
+
+size_t wgrad_mfma_workspace_bytes(const Geom& g) {
+    if (wgrad_mfma_uses_igw(g)) return igw_workspace_bytes(g);
+    return wgrad_rows12(g) ? th12::workspace_bytes(g) : th16::workspace_bytes(g);
+}
+size_t wgrad_mfma_min_workspace_bytes(const Geom& g) { return wgrad_mfma_uses_igw(g) ? 0 : wgrad_mfma_workspace_bytes(g); }
 int wgrad_mfma(const Geom& g, const void* x, const void* dy, float* dw, void* ws, size_t ws_bytes, hipStream_t s) {
+    if (wgrad_mfma_uses_igw(g)) return igw_run(g, x, dy, dw, ws, ws_bytes, s);
     return wgrad_rows12(g) ? th12::run(g, x, dy, dw, ws, ws_bytes, s) : th16::run(g, x, dy, dw, ws, ws_bytes, s);
 }
 #endif

@@ -304,12 +304,26 @@ static int wgrad_s2_slots(const Geom& g) {
     return (int)slots;
 }
 
-size_t wgrad_s2_workspace_bytes(const Geom& g) {
-    if (!wgrad_s2_supported(g)) return 0;
-    return (size_t)wgrad_s2_slots(g) * g.w_elems() * sizeof(float);
+// The matrix product over numbered positions where its model expects it to be faster than 25 us and 700 TFLOP/s, about what
+// this kernel reaches at its best (it stages a patch four times the tile for 32 input channels at a time).  With the
+// launch that adds the partial sums, this kernel -> igw_kernel: 64->128 at 96^3, N = 2 169 -> 132 us, 128->256 at 48^3, N = 2 91 -> 66,
+// 256->320 at 24^3, N = 2 101 -> 33, 32->64 at 32^3, N = 2 29 -> 15; but 32->64 at 192^3 153 -> 213 (seven tiles of columns read
+// every position again).
+bool wgrad_s2_uses_igw(const Geom& g) {
+    if (!igw_supported(g)) return false;
+    const double us = 25.0 + 2.0 * g.out_voxels() * 27 * g.Cin * (double)g.Cout / 7e8;
+    return igw_us(g, ~(size_t)0) < us;
 }
 
+size_t wgrad_s2_workspace_bytes(const Geom& g) {
+    if (!wgrad_s2_supported(g)) return 0;
+    if (wgrad_s2_uses_igw(g)) return igw_workspace_bytes(g);
+    return (size_t)wgrad_s2_slots(g) * g.w_elems() * sizeof(float);
+}
+size_t wgrad_s2_min_workspace_bytes(const Geom& g) { return wgrad_s2_supported(g) && wgrad_s2_uses_igw(g) ? 0 : wgrad_s2_workspace_bytes(g); }
+
 int wgrad_s2(const Geom& g, const void* x, const void* dy, float* dw, void* ws, size_t ws_bytes, hipStream_t s) {
+    if (wgrad_s2_uses_igw(g)) return igw_run(g, x, dy, dw, ws, ws_bytes, s);
     if (ws_bytes < wgrad_s2_workspace_bytes(g)) return MI3D_ERR_WORKSPACE;
     Wg2Params P;
     P.x = (const uint16_t*)x; P.dy = (const uint16_t*)dy; P.part = (float*)ws;

@@ -101,9 +101,19 @@ void ig_describe(const Geom& g, int pass, size_t ws_bytes, char* buf, size_t len
 int ig_conv(const Geom& g, int pass, const void* in, const void* w, void* out, void* ws, size_t ws_bytes, hipStream_t s);
 
 
+// weight gradient as a matrix product over numbered positions (bf16, and fp32 with products from bf16 matrix instructions)
+bool igw_supported(const Geom& g);
+double igw_us(const Geom& g, size_t ws_bytes);       // what its model expects a call with this workspace to take (very long: none fits)
+size_t igw_workspace_bytes(const Geom& g);           // what the best split of the positions wants
+void igw_describe(const Geom& g, size_t ws_bytes, char* buf, size_t len);
+int igw_run(const Geom& g, const void* x, const void* dy, float* dw, void* ws, size_t ws_bytes, hipStream_t s);
+
+
 // MFMA weight gradient: bf16, 3x3x3, stride 1, channels in multiples of 32
 bool wgrad_mfma_supported(const Geom& g);
 size_t wgrad_mfma_workspace_bytes(const Geom& g);
+size_t wgrad_mfma_min_workspace_bytes(const Geom& g);
+bool wgrad_mfma_uses_igw(const Geom& g);                // volumes that its patches cover badly or fill the chip with badly
 int wgrad_mfma(const Geom& g, const void* x, const void* dy, float* dw, void* ws, size_t ws_bytes, hipStream_t s);
 
 
@@ -130,6 +140,8 @@ int embed_s_conv(const Geom& g, int pass, const void* a, const void* b, void* ou
 // MFMA weight gradient of the 3x3x3 stride-2 convolution, channels in multiples of 32
 bool wgrad_s2_supported(const Geom& g);
 size_t wgrad_s2_workspace_bytes(const Geom& g);
+size_t wgrad_s2_min_workspace_bytes(const Geom& g);
+bool wgrad_s2_uses_igw(const Geom& g);
 int wgrad_s2(const Geom& g, const void* x, const void* dy, float* dw, void* ws, size_t ws_bytes, hipStream_t s);
 
 
@@ -193,6 +205,7 @@ size_t f32_min_workspace_bytes(const Geom& g, int pass);   // what a call needs 
 int f32_conv(const Geom& g, int pass, const void* in, const void* w, void* out, void* ws, size_t ws_bytes, hipStream_t s);
 int f32_wgrad(const Geom& g, const void* x, const void* dy, float* dw, void* ws, size_t ws_bytes, hipStream_t s);
 bool f32_uses_ig(const Geom& g, int pass, size_t ws_bytes);      // implicit GEMM over numbered positions
+bool f32_uses_igw(const Geom& g, size_t ws_bytes);               // weight gradient over numbered positions
 bool f32_gathers_parts(const Geom& g, int pass);                 // sizes that the patch kernel with such products serves
 bool f32_uses_parts(const Geom& g, int pass, size_t ws_bytes);   // other kernels with products from bf16 matrix instructions
 bool f32_wgrad_folds_taps(const Geom& g);   // at most 4 input channels: (tap, channel) pairs as the columns of the MFMA block

@@ -19,7 +19,8 @@ struct SplitRange {
         most = u > most ? u : most;
         least = u - 1 < least ? u - 1 : least;
     }
-    __device__ __forceinline__ void add(const float4& v) { add(v.x); add(v.y); add(v.z); add(v.w); }
+    __device__ __forceinline__ void add2(float x, float y) { add(x); add(y); }
+    __device__ __forceinline__ void add(const float4& v) { add2(v.x, v.y); add2(v.z, v.w); }
     __device__ __forceinline__ bool exceeded() const { return (most >= 0x56000000u) | (least < 0x0D7FFFFFu); }
 };
 
@@ -27,13 +28,13 @@ struct SplitRange {
 struct SplitRangeNumbers {
     float most = 0.f;
     uint32_t least = 0xFFFFFFFFu;
-    __device__ __forceinline__ void add(float x, float y) {
+    __device__ __forceinline__ void add2(float x, float y) {
         most = __builtin_fmaxf(__builtin_fmaxf(__builtin_fabsf(x), __builtin_fabsf(y)), most);
         const uint32_t u = (__builtin_bit_cast(uint32_t, x) << 1) - 1, v = (__builtin_bit_cast(uint32_t, y) << 1) - 1;
         const uint32_t m = u < v ? u : v;
         least = m < least ? m : least;
     }
-    __device__ __forceinline__ void add(const float4& v) { add(v.x, v.y); add(v.z, v.w); }
+    __device__ __forceinline__ void add(const float4& v) { add2(v.x, v.y); add2(v.z, v.w); }
     __device__ __forceinline__ bool exceeded() const { return (most >= 0x1p45f) | (least < 0x1AFFFFFFu); }
 };
 
