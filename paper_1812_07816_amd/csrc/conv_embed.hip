@@ -112,6 +112,15 @@ __global__ void __launch_bounds__(256) slice_channels_kernel(Geom g, int pass, c
     }
 }
 
+// One word per block of 256 x 8 weights: 1 where the block met an infinity or a NaN (n a multiple of 8)
+__global__ void __launch_bounds__(256) weight_flags_kernel(const uint16_t* __restrict__ w, long long n8, uint32_t* __restrict__ flags) {
+    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+    uint4 v = {0, 0, 0, 0};
+    if (i < n8) v = *(const uint4*)(w + 8 * i);
+    const int any = __syncthreads_or(pair_nonfinite(v.x) | pair_nonfinite(v.y) | pair_nonfinite(v.z) | pair_nonfinite(v.w));
+    if (threadIdx.x == 0) flags[blockIdx.x] = any ? 1u : 0u;
+}
+
 // The same in place, for results that need no slicing (a multiple of 4 elements): only where a weight is not finite (flags
 // of the padding kernel; the kernels keep to the window of an activation), or, with flags null, on any NaN.
 __global__ void __launch_bounds__(256) exact_in_place_kernel(Geom g, int pass, const uint16_t* __restrict__ in, const uint16_t* __restrict__ w,
@@ -128,11 +137,11 @@ __global__ void __launch_bounds__(256) exact_in_place_kernel(Geom g, int pass, c
     }
 }
 
-// dw, V elements per thread.  The NaN of a block are formed again one after the other by all its threads: partial sums
+// dw, V elements per thread (src may be dst: nothing to slice).  The NaN of a block are formed again one after the other by all its threads: partial sums
 // over every 256th voxel, added in a fixed order.
 template <int V>
-__global__ void __launch_bounds__(256) slice_dw_kernel(Geom g, const uint16_t* __restrict__ x, const uint16_t* __restrict__ dy, const float* __restrict__ src,
-                                                       float* __restrict__ dst, int CP) {
+__global__ void __launch_bounds__(256) slice_dw_kernel(Geom g, const uint16_t* __restrict__ x, const uint16_t* __restrict__ dy, const float* src,
+                                                       float* dst, int CP) {
     const int t = threadIdx.x;
     const long long idx = (long long)blockIdx.x * 256 + t, rows = g.taps() * g.Cout;
     const int C = g.Cin, per = C / V;
@@ -275,6 +284,37 @@ size_t embed_c_min_workspace_bytes(const Geom& g, int pass) {
     return e.xb + e.yb + e.wb + auto_min_workspace_bytes(e.p, pass);
 }
 
+// Layers whose channels come in eights and that the kernels over numbered positions take as they are.
+static bool ragged_as_is(const Geom& g, int pass) {
+    if (g.Cin % 8 || g.Cout % 8 || g.kD != 3 || g.kH != 3 || g.kW != 3) return false;
+    if (pass == MI3D_PASS_WGRAD) return igw_supported(g);
+    return ig_takes(g, pass) && g.out_voxels() >= 1024;
+}
+static int weight_flag_words(const Geom& g, int pass) {
+    return pass == MI3D_PASS_FWD ? (int)((g.w_elems() / 8 + 255) / 256) : 27 * ((g.Cin + 63) / 64) * ((g.Cout + 63) / 64);
+}
+
+// The layer as it is; its NaN are formed again like those of a padded one
+static int ragged_conv(const Geom& g, int pass, const void* a, const void* b, void* out, void* ws, size_t ws_bytes, hipStream_t s) {
+    int st;
+    if (pass == MI3D_PASS_WGRAD) {
+        if ((st = igw_run(g, a, b, (float*)out, ws, ws_bytes, s))) return st;
+        slice_dw_kernel<4><<<blocks_for(g.w_elems() / 4), 256, 0, s>>>(g, (const uint16_t*)a, (const uint16_t*)b, (const float*)out, (float*)out, g.Cin);
+        return check_launch();
+    }
+    const int nflags = weight_flag_words(g, pass);
+    const size_t fb = align256((size_t)nflags * 4);
+    uint32_t* flags = ws_bytes >= fb + ig_min_workspace_bytes(g, pass) ? (uint32_t*)ws : nullptr;   // (no room: every result is looked at)
+    if (flags && pass == MI3D_PASS_FWD) {
+        weight_flags_kernel<<<(unsigned)nflags, 256, 0, s>>>((const uint16_t*)b, g.w_elems() / 8, flags);
+        if ((st = check_launch())) return st;
+    }
+    if ((st = ig_conv(g, pass, a, b, out, (char*)ws + (flags ? fb : 0), ws_bytes - (flags ? fb : 0), s, flags))) return st;
+    const long long n4 = (pass == MI3D_PASS_FWD ? g.out_voxels() * g.Cout : g.in_voxels() * g.Cin) / 4;
+    exact_in_place_kernel<<<(unsigned)(n4 < 256 * 256 ? (n4 + 255) / 256 : 256), 256, 0, s>>>(g, pass, (const uint16_t*)a, (const uint16_t*)b, (uint16_t*)out, n4, flags, nflags);
+    return check_launch();
+}
+
 Geom embed_c_inner(const Geom& g, int pass, size_t ws_bytes, size_t* rest) {
     EmbedC e = embed_c_layout(g, pass);
     if (ws_bytes < embed_c_workspace_bytes(g, pass)) e.fb = 0;
@@ -288,6 +328,7 @@ Geom embed_c_inner(const Geom& g, int pass, size_t ws_bytes, size_t* rest) {
 // the plain kernels are left with the geometries no matrix-core kernel takes.
 int embed_c_conv(const Geom& g, int pass, const void* a, const void* b, void* out, void* ws, size_t ws_bytes, hipStream_t s) {
     if (ws_bytes < embed_c_min_workspace_bytes(g, pass)) return MI3D_ERR_WORKSPACE;
+    if (ragged_as_is(g, pass)) return ragged_conv(g, pass, a, b, out, ws, ws_bytes, s);
     EmbedC e = embed_c_layout(g, pass);
     if (ws_bytes < embed_c_workspace_bytes(g, pass)) e.fb = 0;      // no room for flags: every result is looked at
     const Geom& p = e.p;

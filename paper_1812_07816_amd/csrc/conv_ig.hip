@@ -53,6 +53,7 @@ struct IgParams {
     long long in_bytes;           // of one of in / in_hi
     long long out_elems;
     IgClass cls[8];
+    Div Cdiv;                     // contracted channels
     uint32_t taps[27];
     long long slack;              // voxels by which a position can lie before an earlier one of its tile (max_span)
 };
@@ -76,12 +77,15 @@ __device__ __forceinline__ uint32_t cvt2(float a, float b) {
 __device__ __forceinline__ float lo_f(uint32_t v) { return __builtin_bit_cast(float, v << 16); }
 __device__ __forceinline__ float hi_f(uint32_t v) { return __builtin_bit_cast(float, v & 0xFFFF0000u); }
 
-// WN = waves along the positions: 2 (128 x 128) or 4 (64 x 256).  WIDE: planes too large for 32-bit offsets from a plane to
+// WN = waves along the positions, MA = blocks of 32 channels of a wave: 2, 2 (128 x 128), 4, 2 (64 x 256) or 4, 1 (32 x 256).
+// FLAT: the contraction runs over (tap, channel) pairs, 64 of them per step whatever the number of channels; without it a step is
+// 64 channels of one tap, which is the same where the channels come in multiples of 64.  WIDE: planes too large for 32-bit offsets from a plane to
 // all that a tile and its taps touch (narrow_planes); the buffers move with the tap then, which costs 2 % (48^3 128->256,
 // stride 2, N = 2: 225 -> 231 us for the three passes).
-template <int WN, bool WIDE>
+template <int WN, int MA, bool WIDE, bool FLAT>
 __global__ void __launch_bounds__(256, 2) ig_kernel(const IgParams P) {
-    constexpr int BM = WN == 2 ? 128 : 64, BN = 64 * WN, NA = BM / 32, NB = BN / 32;
+    static_assert(!(WIDE && FLAT), "");
+    constexpr int BM = 128 / WN * MA, BN = 64 * WN, NA = BM / 32, NB = BN / 32;
     constexpr int A_BYTES = BM * 128, STAGE = (BM + BN) * 128;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -125,7 +129,7 @@ __global__ void __launch_bounds__(256, 2) ig_kernel(const IgParams P) {
             base = v > 0 ? v : 0;
         }
     }
-    const int nch = (P.C + BK - 1) / BK, steps = K.ntap * nch;
+    const int nch = (P.C + BK - 1) / BK, steps = FLAT ? (K.ntap * P.C + BK - 1) / BK : K.ntap * nch;
     const int s0 = (int)((unsigned)(steps * split) / (unsigned)P.splits), s1 = (int)((unsigned)(steps * (split + 1)) / (unsigned)P.splits);
     int tap = s0 / nch, chunk = s0 - tap * nch;   // of the next step to be fetched
     // lane k keeps tap k: reading it from there costs no memory latency between two steps
@@ -144,7 +148,7 @@ __global__ void __launch_bounds__(256, 2) ig_kernel(const IgParams P) {
             mask[i] = 0;
             dd[i] = j < K.J ? d : -1000000; hh[i] = h; ww[i] = w;
         }
-        for (int k = tap; k * nch < s1; ++k) {
+        for (int k = FLAT ? 0 : tap; FLAT ? k < K.ntap : k * nch < s1; ++k) {
             const IgTap a(__builtin_amdgcn_readlane(tapv, k));
 #pragma unroll
             for (int i = 0; i < NB; ++i) {
@@ -167,7 +171,21 @@ __global__ void __launch_bounds__(256, 2) ig_kernel(const IgParams P) {
     __amdgpu_buffer_rsrc_t r_hi = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)P.in_hi + base_b), 0, range, 0x00020000);
     __amdgpu_buffer_rsrc_t r_w = __builtin_amdgcn_make_buffer_rsrc((void*)P.w, 0, P.M * P.T * P.C * 2, 0x00020000);
 
-    auto fetch = [&](int buf) {
+    auto fetch_flat = [&](int buf, int s) {
+        const int k = s * BK + piece * 8, tp = divide(k, P.Cdiv), c = k - tp * P.C;   // this lane's tap and channels
+        const bool in = tp < K.ntap;
+        const IgTap a((uint32_t)__shfl(tapv, tp & 31));
+        const int ua = (a.wt * P.C + c) * 2 - piece * 16, ub = (((a.dd * P.iH + a.dh) * P.iW + a.dw) * P.pitch + c) * 2 - piece * 16;
+        const uint32_t bit = in ? 1u << (tp & 31) : 0u;
+        char* l = lds + buf * STAGE + wave * 1024;
+#pragma unroll
+        for (int i = 0; i < NA; ++i) load_lds(r_w, l + i * 4096, oka[i] & (in ? 1u : 0u) ? rowa[i] + ua : OOB);
+        l += A_BYTES;
+#pragma unroll
+        for (int i = 0; i < NB; ++i) load_lds(r_in, l + i * 4096, mask[i] & bit ? rowb[i] + ub : OOB);
+    };
+    auto fetch = [&](int buf, int s) {
+        if constexpr (FLAT) return fetch_flat(buf, s);
         const IgTap a(__builtin_amdgcn_readlane(tapv, tap));
         const int c = chunk * BK + piece * 8;     // this lane's channels
         const unsigned okc = c < P.C;
@@ -196,9 +214,9 @@ __global__ void __launch_bounds__(256, 2) ig_kernel(const IgParams P) {
         if (++chunk == nch) { chunk = 0; ++tap; }
     };
 
-    f32x16 acc[2][2];
+    f32x16 acc[MA][2];
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < MA; ++a)
 #pragma unroll
         for (int b = 0; b < 2; ++b)
 #pragma unroll
@@ -211,22 +229,22 @@ __global__ void __launch_bounds__(256, 2) ig_kernel(const IgParams P) {
     for (int k = 0; k < 4; ++k) frag[k] = r32 * 128 + ((2 * k + half) ^ swz) * 16;
 
     if (s0 < s1) {
-        fetch(0);
+        fetch(0, s0);
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
         for (int s = s0; s < s1; ++s) {
             const int buf = (s - s0) & 1;
-            if (s + 1 < s1) fetch(1 - buf);
+            if (s + 1 < s1) fetch(1 - buf, s + 1);
             const char* la = lds + buf * STAGE + wm * 64 * 128;
             const char* lb = lds + buf * STAGE + A_BYTES + wn * 64 * 128;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                bf16x8 fa[2], fb[2];
+                bf16x8 fa[MA], fb[2];
 #pragma unroll
-                for (int a = 0; a < 2; ++a) fa[a] = *(const bf16x8*)(la + a * 4096 + frag[k]);
+                for (int a = 0; a < MA; ++a) fa[a] = *(const bf16x8*)(la + a * 4096 + frag[k]);
 #pragma unroll
                 for (int b = 0; b < 2; ++b) fb[b] = *(const bf16x8*)(lb + b * 4096 + frag[k]);
 #pragma unroll
-                for (int a = 0; a < 2; ++a)
+                for (int a = 0; a < MA; ++a)
 #pragma unroll
                     for (int b = 0; b < 2; ++b) acc[a][b] = mfma(fa[a], fb[b], acc[a][b]);
             }
@@ -243,13 +261,15 @@ __global__ void __launch_bounds__(256, 2) ig_kernel(const IgParams P) {
         decode(j, n, d, h, w);
         const long long vox = (((long long)n * P.oD + P.os * d + K.od0) * P.oH + P.os * h + K.oh0) * P.oW + P.os * w + K.ow0;
 #pragma unroll
-        for (int a = 0; a < 2; ++a) {
+        for (int a = 0; a < MA; ++a) {
             const int m0 = mt * BM + wm * 64 + a * 32;
             if (m0 >= P.M) continue;
+            const int groups = (P.M - m0 - 4 * half + 7) >> 3;     // (channels in fours: a last block may end early)
             if (P.part) {
                 float* p = P.part + (long long)split * P.out_elems + vox * P.M + m0 + 4 * half;
 #pragma unroll
-                for (int g = 0; g < 4; ++g) *(float4*)(p + 8 * g) = float4{acc[a][b][4 * g], acc[a][b][4 * g + 1], acc[a][b][4 * g + 2], acc[a][b][4 * g + 3]};
+                for (int g = 0; g < 4; ++g)
+                    if (g < groups) *(float4*)(p + 8 * g) = float4{acc[a][b][4 * g], acc[a][b][4 * g + 1], acc[a][b][4 * g + 2], acc[a][b][4 * g + 3]};
                 continue;
             }
             const long long e = vox * P.M + m0 + 4 * half;
@@ -257,6 +277,7 @@ __global__ void __launch_bounds__(256, 2) ig_kernel(const IgParams P) {
             uint16_t* o = P.out_hi ? (high ? P.out_hi - (P.M >> 1) : P.out) + vox * (P.M >> 1) + m0 + 4 * half : P.out + e;
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
+                if (g >= groups) break;
                 float v[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) v[i] = acc[a][b][4 * g + i];
@@ -283,16 +304,25 @@ __global__ void __launch_bounds__(256, 2) ig_kernel(const IgParams P) {
 }
 
 // wt[ci][tap][co] = w[co][tap][ci]: the data gradient's weights with the contracted channels contiguous.  64 x 64 blocks
-// through LDS, 16-byte accesses on both sides; block (tap, ci block, co block).
-__global__ void __launch_bounds__(256) ig_transpose_kernel(const uint16_t* __restrict__ w, uint16_t* __restrict__ wt, int T, int Cin, int Cout) {
+// through LDS, 16-byte accesses on both sides; block (tap, ci block, co block).  flags (null: none): one word per block, 1 where it
+// met an infinity or a NaN.
+__device__ __forceinline__ bool odd_bf16(uint32_t v) { return (v & 0x7F80u) == 0x7F80u || (v & 0x7F800000u) == 0x7F800000u; }
+__global__ void __launch_bounds__(256) ig_transpose_kernel(const uint16_t* __restrict__ w, uint16_t* __restrict__ wt, int T, int Cin, int Cout,
+                                                           uint32_t* __restrict__ flags) {
     __shared__ uint16_t tile[64][72];
     const int tap = blockIdx.x, ci0 = blockIdx.y * 64, co0 = blockIdx.z * 64, t = threadIdx.x;
+    bool odd = false;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int r = (t >> 3) + 32 * i, c = (t & 7) * 8;
-        if (co0 + r < Cout && ci0 + c < Cin) *(uint4*)&tile[r][c] = *(const uint4*)(w + ((long long)(co0 + r) * T + tap) * Cin + ci0 + c);
+        if (co0 + r < Cout && ci0 + c < Cin) {
+            const uint4 v = *(const uint4*)(w + ((long long)(co0 + r) * T + tap) * Cin + ci0 + c);
+            *(uint4*)&tile[r][c] = v;
+            odd |= odd_bf16(v.x) | odd_bf16(v.y) | odd_bf16(v.z) | odd_bf16(v.w);
+        }
     }
-    __syncthreads();
+    const int any = __syncthreads_or(odd);
+    if (flags && t == 0) flags[tap + T * (blockIdx.y + gridDim.y * blockIdx.z)] = any ? 1u : 0u;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         // lanes run over ci, so that the column reads of a wave are 2 bytes apart
@@ -365,17 +395,36 @@ __global__ void __launch_bounds__(256) ig_sum_kernel(const float* __restrict__ p
 // Tile shape and splits of the contraction, by a model of the time: a round of two workgroups per CU takes STEP_US per
 // step, partial sums are written and read at PART_BYTES_PER_US.
 struct IgPlan {
-    int wn, splits, MT, ncls, tiles;
+    int v, splits, MT, ncls, tiles;   // v: 0 128 x 128, 1 64 x 256, 2 32 x 256
     size_t out_elems;
 };
-constexpr double STEP_US = 0.75, START_US = 3.0, PART_BYTES_PER_US = 3e6;
+constexpr int BMS[3] = {128, 64, 32}, BNS[3] = {128, 256, 256};
+constexpr double STEP_US[3] = {0.75, 0.75, 0.5}, START_US = 3.0, PART_BYTES_PER_US = 3e6;
 
 size_t weight_bytes(const Geom& g) { return ((size_t)g.w_elems() * 2 + 255) & ~(size_t)255; }
+
+// The planes that a tile of 256 positions and its taps touch, with room to spare, within 2 GiB
+bool narrow_planes(const Geom& g, int pass) {
+    const bool flip = pass == MI3D_PASS_DGRAD;
+    const long long plane = flip ? (long long)g.Ho * g.Wo * g.Cout * 2 : (long long)g.H * g.W * g.Cin * 2;
+    const int os = flip ? g.sD : 1;
+    const long long rows = flip ? (long long)(g.H > 1 ? g.H / os : 1) * (g.W > 1 ? g.W / os : 1) : (long long)g.Ho * g.Wo;
+    return plane * (16 + 6 * (255 / rows + 2)) < (1ll << 31);
+}
+
+// Steps of (tap, channel) pairs: where steps of 64 channels would be partly empty.  48->48 at 37 x 50 x 61: 27 steps -> 21,
+// 16 channels: 27 -> 7.  (Not for the classes of a strided data gradient with channels in multiples of 32, 96 and more: a quarter
+// at most.)
+bool is_flat(const Geom& g, int pass) {
+    const int C = pass == MI3D_PASS_DGRAD ? g.Cout : g.Cin;
+    return C % BK != 0 && (C % 32 != 0 || g.sD == 1) && narrow_planes(g, pass);   // (halves of an input come in 32s: C is a multiple of 64)
+}
 
 // Tiles of all classes for tiles of bm x bn, the steps of all of them, and of the longest
 long long count_tiles(const Geom& g, int pass, int bm, int bn, long long* work, int* most) {
     const bool flip = pass == MI3D_PASS_DGRAD, classes = flip && g.sD == 2;
     const int M = flip ? g.Cin : g.Cout, C = flip ? g.Cout : g.Cin, nch = (C + BK - 1) / BK, MT = (M + bm - 1) / bm;
+    const bool flat = is_flat(g, pass);
     long long tiles = 0;
     *work = 0; *most = 0;
     for (int c = 0; c < (classes ? 8 : 1); ++c) {
@@ -384,8 +433,9 @@ long long count_tiles(const Geom& g, int pass, int bm, int bn, long long* work, 
         const int ntap = classes ? (g.pD ? (1 << (a + b + d)) : (1 << (3 - a - b - d))) : 27;
         const long long n = (J + bn - 1) / bn * MT;
         tiles += n;
-        *work += n * ntap * nch;
-        if (J && ntap * nch > *most) *most = ntap * nch;
+        const int steps = flat ? (ntap * C + BK - 1) / BK : ntap * nch;
+        *work += n * steps;
+        if (J && steps > *most) *most = steps;
     }
     return tiles;
 }
@@ -397,11 +447,13 @@ IgPlan make_plan(const Geom& g, int pass, size_t ws_bytes) {
     const int M = flip ? g.Cin : g.Cout, slots = 2 * cu_count();
     IgPlan best{};
     double best_us = 1e30;
-    for (int wn = 2; wn <= 4; wn += 2) {
-        const int bm = wn == 2 ? 128 : 64, MT = (M + bm - 1) / bm;
+    // (tiles of 32 channels where there are no more and the positions are not few: two tiles of 512 would need more splits)
+    const bool narrow = M <= 32 && (flip ? g.in_voxels() : g.out_voxels()) >= 1024;
+    for (int v = 0; v < (narrow ? 3 : 2); ++v) {
+        const int bm = BMS[v], MT = (M + bm - 1) / bm;
         long long work;          // in tile steps
         int most;
-        const long long tiles = count_tiles(g, pass, bm, 64 * wn, &work, &most);
+        const long long tiles = count_tiles(g, pass, bm, BNS[v], &work, &most);
         if (tiles > MAX_TILES) continue;
         const size_t out_elems = (size_t)(flip ? g.in_voxels() * g.Cin : g.out_voxels() * g.Cout);
         for (const int S : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 40, 48, 64}) {
@@ -409,23 +461,14 @@ IgPlan make_plan(const Geom& g, int pass, size_t ws_bytes) {
             if (S > 1 && (S * out_elems * 4 > ((size_t)64 << 20) || tiles * S > 4 * slots)) break;
             if (S > 1 && S * out_elems * 4 + (flip ? weight_bytes(g) : 0) > ws_bytes) break;
             const double rounds = classes ? (double)work / most * S / slots + 0.5 : (double)((tiles * S + slots - 1) / slots);
-            const double us = rounds * ((most + S - 1) / S) * STEP_US + START_US + (S > 1 ? START_US + S * (double)out_elems * 8 / PART_BYTES_PER_US : 0.0);
+            const double us = rounds * ((most + S - 1) / S) * STEP_US[v] + START_US + (S > 1 ? START_US + S * (double)out_elems * 8 / PART_BYTES_PER_US : 0.0);
             if (us < best_us) {
                 best_us = us;
-                best = IgPlan{wn, S, MT, classes ? 8 : 1, (int)tiles, out_elems};
+                best = IgPlan{v, S, MT, classes ? 8 : 1, (int)tiles, out_elems};
             }
         }
     }
     return best;
-}
-
-// The planes that a tile of 256 positions and its taps touch, with room to spare, within 2 GiB
-bool narrow_planes(const Geom& g, int pass) {
-    const bool flip = pass == MI3D_PASS_DGRAD;
-    const long long plane = flip ? (long long)g.Ho * g.Wo * g.Cout * 2 : (long long)g.H * g.W * g.Cin * 2;
-    const int os = flip ? g.sD : 1;
-    const long long rows = flip ? (long long)(g.H > 1 ? g.H / os : 1) * (g.W > 1 ? g.W / os : 1) : (long long)g.Ho * g.Wo;
-    return plane * (16 + 6 * (255 / rows + 2)) < (1ll << 31);
 }
 
 // Bytes from the first to the last voxel at the positions of a tile (256 of them at most), and the voxels by which a position
@@ -461,9 +504,12 @@ long long max_span(const Geom& g, int pass, long long* slack) {
 
 }  // namespace
 
-bool ig_supported(const Geom& g, int pass) {
+bool ig_supported(const Geom& g, int pass) { return g.Cin % 32 == 0 && g.Cout % 32 == 0 && ig_takes(g, pass); }
+
+// (channels in eights: rows of whole 16-byte pieces)
+bool ig_takes(const Geom& g, int pass) {
     if (g.dtype != MI3D_BF16 || pass == MI3D_PASS_WGRAD || g.kD != 3 || g.kH != 3 || g.kW != 3) return false;
-    if (g.sD != g.sH || g.sD != g.sW || g.sD > 2 || g.Cin % 32 || g.Cout % 32) return false;
+    if (g.sD != g.sH || g.sD != g.sW || g.sD > 2 || g.Cin % 8 || g.Cout % 8) return false;
     if (g.sD == 1 ? (g.pD > 2 || g.pH > 2 || g.pW > 2) : (g.pD > 1 || g.pH > 1 || g.pW > 1)) return false;
     if (pass == MI3D_PASS_DGRAD && g.sD == 2 && (g.pD != g.pH || g.pD != g.pW)) return false;
     const bool flip = pass == MI3D_PASS_DGRAD;
@@ -484,18 +530,19 @@ size_t ig_workspace_bytes(const Geom& g, int pass) {
 
 void ig_describe(const Geom& g, int pass, size_t ws_bytes, char* buf, size_t len) {
     const IgPlan p = make_plan(g, pass, ws_bytes);
-    snprintf(buf, len, "implicit_gemm_%s%s parts %d", p.wn == 2 ? "128x128" : "64x256", narrow_planes(g, pass) ? "" : "_wide", p.splits);
+    snprintf(buf, len, "implicit_gemm_%dx%d%s parts %d", BMS[p.v], BNS[p.v], narrow_planes(g, pass) ? "" : "_wide", p.splits);
 }
 
 // in: activations read (x of the forward pass, dy of the data gradient); out: y or dx
-int ig_conv(const Geom& g, int pass, const void* in, const void* w, void* out, void* ws, size_t ws_bytes, hipStream_t s) {
+// wflags: see ig_transpose_kernel (27 words per 64 x 64 block of channels; the forward pass writes none)
+int ig_conv(const Geom& g, int pass, const void* in, const void* w, void* out, void* ws, size_t ws_bytes, hipStream_t s, uint32_t* wflags) {
     if (ws_bytes < ig_min_workspace_bytes(g, pass)) return MI3D_ERR_WORKSPACE;
     const bool flip = pass == MI3D_PASS_DGRAD;
     const IgPlan plan = make_plan(g, pass, ws_bytes);
     if (g.hi && g.Cin % 64) return MI3D_ERR_UNSUPPORTED;
     int st = MI3D_OK;
     if (flip) {
-        ig_transpose_kernel<<<dim3(27, (g.Cin + 63) / 64, (g.Cout + 63) / 64), 256, 0, s>>>((const uint16_t*)w, (uint16_t*)ws, 27, g.Cin, g.Cout);
+        ig_transpose_kernel<<<dim3(27, (g.Cin + 63) / 64, (g.Cout + 63) / 64), 256, 0, s>>>((const uint16_t*)w, (uint16_t*)ws, 27, g.Cin, g.Cout, wflags);
         if ((st = check_launch())) return st;
     }
     IgParams P{};
@@ -516,7 +563,8 @@ int ig_conv(const Geom& g, int pass, const void* in, const void* w, void* out, v
     if (g.hi && flip) P.out_hi = (uint16_t*)g.hi;
     P.in_bytes = (long long)g.N * P.iD * P.iH * P.iW * P.pitch * 2;
     max_span(g, pass, &P.slack);
-    const int bn = 64 * plan.wn, pads[3] = {g.pD, g.pH, g.pW};
+    P.Cdiv = make_div(P.C);
+    const int bn = BNS[plan.v], pads[3] = {g.pD, g.pH, g.pW};
     int tile = 0, ntap = 0;
     for (int q = 0; q < plan.ncls; ++q) {
         // classes with the most taps first, so that the long workgroups do not start last
@@ -552,23 +600,22 @@ int ig_conv(const Geom& g, int pass, const void* in, const void* w, void* out, v
         }
         K.ntap = ntap - K.tap0;
     }
-    const size_t lds2 = 2 * 256 * 128, lds4 = 2 * 320 * 128;
+    const bool wide = !narrow_planes(g, pass), flat = is_flat(g, pass);
+    typedef void (*Kernel)(IgParams);
+    static const Kernel kernels[3][3] = {{ig_kernel<2, 2, false, false>, ig_kernel<2, 2, true, false>, ig_kernel<2, 2, false, true>},
+                                         {ig_kernel<4, 2, false, false>, ig_kernel<4, 2, true, false>, ig_kernel<4, 2, false, true>},
+                                         {ig_kernel<4, 1, false, false>, ig_kernel<4, 1, true, false>, ig_kernel<4, 1, false, true>}};
+    auto lds = [](int v) { return (size_t)2 * (BMS[v] + BNS[v]) * 128; };
     static std::atomic<bool> attr_set{false};   // set once per process; a second thread racing here repeats an idempotent call
     if (!attr_set) {
-        hipError_t e = hipSuccess;
-        for (const void* f : {(const void*)ig_kernel<2, false>, (const void*)ig_kernel<2, true>})
-            if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds2);
-        for (const void* f : {(const void*)ig_kernel<4, false>, (const void*)ig_kernel<4, true>})
-            if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds4);
-        if (e != hipSuccess) { note_hip_error(e); return MI3D_ERR_HIP; }
+        for (int v = 0; v < 3; ++v)
+            for (Kernel f : kernels[v]) {
+                hipError_t e = hipFuncSetAttribute((const void*)f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds(v));
+                if (e != hipSuccess) { note_hip_error(e); return MI3D_ERR_HIP; }
+            }
         attr_set = true;
     }
-    const unsigned grid = (unsigned)(plan.tiles * plan.splits);
-    const bool wide = !narrow_planes(g, pass);
-    if (plan.wn == 2 && !wide) ig_kernel<2, false><<<grid, 256, lds2, s>>>(P);
-    else if (plan.wn == 2) ig_kernel<2, true><<<grid, 256, lds2, s>>>(P);
-    else if (!wide) ig_kernel<4, false><<<grid, 256, lds4, s>>>(P);
-    else ig_kernel<4, true><<<grid, 256, lds4, s>>>(P);
+    kernels[plan.v][wide ? 1 : flat ? 2 : 0]<<<(unsigned)(plan.tiles * plan.splits), 256, lds(plan.v), s>>>(P);
     st = check_launch();
     if (st || plan.splits == 1) return st;
     const long long n = P.out_elems;

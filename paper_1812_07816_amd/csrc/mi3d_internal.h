@@ -95,10 +95,11 @@ int instnorm_finish_means(const float* part, int blocks, int C, int N, double in
 
 // implicit GEMM over numbered positions: bf16, 3x3x3, stride 1 and 2 (forward and data gradient), small volumes and many channels
 bool ig_supported(const Geom& g, int pass);
+bool ig_takes(const Geom& g, int pass);   // the same with channels in multiples of 8
 size_t ig_workspace_bytes(const Geom& g, int pass);       // what the best split of the contraction wants
 size_t ig_min_workspace_bytes(const Geom& g, int pass);   // what a call needs at least
 void ig_describe(const Geom& g, int pass, size_t ws_bytes, char* buf, size_t len);   // tile and parts of the contraction
-int ig_conv(const Geom& g, int pass, const void* in, const void* w, void* out, void* ws, size_t ws_bytes, hipStream_t s);
+int ig_conv(const Geom& g, int pass, const void* in, const void* w, void* out, void* ws, size_t ws_bytes, hipStream_t s, uint32_t* wflags = nullptr);
 
 
 // weight gradient as a matrix product over numbered positions (bf16, and fp32 with products from bf16 matrix instructions)
