@@ -318,7 +318,7 @@ __global__ void __launch_bounds__(256) ig_transpose_kernel(const uint16_t* __res
         if (co0 + r < Cout && ci0 + c < Cin) {
             const uint4 v = *(const uint4*)(w + ((long long)(co0 + r) * T + tap) * Cin + ci0 + c);
             *(uint4*)&tile[r][c] = v;
-            odd |= odd_bf16(v.x) | odd_bf16(v.y) | odd_bf16(v.z) | odd_bf16(v.w);
+            odd = odd || odd_bf16(v.x) || odd_bf16(v.y) || odd_bf16(v.z) || odd_bf16(v.w);
         }
     }
     const int any = __syncthreads_or(odd);
@@ -514,8 +514,8 @@ bool ig_takes(const Geom& g, int pass) {
     if (pass == MI3D_PASS_DGRAD && g.sD == 2 && (g.pD != g.pH || g.pD != g.pW)) return false;
     const bool flip = pass == MI3D_PASS_DGRAD;
     if ((flip ? g.H * (long long)g.W : g.Ho * (long long)g.Wo) >= (1ll << 31) || g.w_elems() * 2 >= (1ll << 31)) return false;
-    // (stride-1 layers have the plane kernels for larger planes)
-    if (!narrow_planes(g, pass) && (g.sD == 1 || max_span(g, pass, nullptr) >= (1ll << 31))) return false;
+    // (stride-1 layers have the plane kernels for larger planes; ragged channels need steps of (tap, channel) pairs)
+    if (!narrow_planes(g, pass) && (g.sD == 1 || g.Cin % 32 || g.Cout % 32 || max_span(g, pass, nullptr) >= (1ll << 31))) return false;
     long long work;
     int most;
     return g.in_voxels() < (1ll << 31) - 1024 && g.out_voxels() < (1ll << 31) - 1024 &&
