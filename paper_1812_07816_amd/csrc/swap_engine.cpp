@@ -1,10 +1,11 @@
 // Run-time half of the data-swapping engine (Sections 3.1 and 3.3): pinned
-// host pool, one side stream per copy direction, events that order copies
+// host pool, one side stream per copy direction and device, events that order copies
 // against the compute stream, an event-aware device arena, and counters.
 #include <algorithm>
 #include <cstring>
 #include <map>
 #include <memory>
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -138,6 +139,57 @@ namespace {
         }                                     \
     } while (0)
 
+// The copy streams of a device, one per direction, shared by all its engines and destroyed with the last of them.  The
+// runtime deals streams out to a few hardware queues (4): with a pair per engine a third engine's copies came to share the
+// queue of the compute stream, where a copy that waits for an event holds up every kernel behind it (fp32 step at 128^3,
+// N = 2, under a budget, three engines in turn: 40, 40 and 75 ms a pass; sharing: 40 each).  Engines share the link anyway.
+// Whatever waits on these streams waits for work enqueued before it, so engines cannot wait for each other in a circle.
+struct CopyStreams {
+    hipStream_t out = nullptr, in = nullptr;
+    int users = 0;
+};
+std::mutex g_streams_mutex;
+std::map<int, CopyStreams> g_streams;
+
+hipError_t acquire_streams(mi3d_swap_engine* e) {
+    std::lock_guard<std::mutex> lock(g_streams_mutex);
+    CopyStreams& s = g_streams[e->device];
+    if (s.users == 0) {
+        hipError_t err = hipStreamCreateWithFlags(&s.out, hipStreamNonBlocking);
+        if (err != hipSuccess) return err;
+        err = hipStreamCreateWithFlags(&s.in, hipStreamNonBlocking);
+        if (err != hipSuccess) {
+            (void)hipStreamDestroy(s.out);
+            return err;
+        }
+    }
+    ++s.users;
+    e->s_out = s.out;
+    e->s_in = s.in;
+    return hipSuccess;
+}
+
+void release_streams(mi3d_swap_engine* e) {
+    std::lock_guard<std::mutex> lock(g_streams_mutex);
+    CopyStreams& s = g_streams[e->device];
+    if (--s.users) return;
+    (void)hipStreamDestroy(s.out);
+    (void)hipStreamDestroy(s.in);
+}
+
+// All copies of this engine have ended (those of others may still be under way, unless one of its own is waited for)
+int wait_for_copies(mi3d_swap_engine* e) {
+    bool out = e->verify, in = e->verify;      // (a checksum follows its copy's event)
+    for (auto& kv : e->tensors) {
+        const Tensor& t = kv.second;
+        out = out || (t.out.issued && hipEventQuery(t.out.done) != hipSuccess);
+        in = in || (t.in.issued && hipEventQuery(t.in.done) != hipSuccess);
+    }
+    if (out) HIP_TRY(hipStreamSynchronize(e->s_out));
+    if (in) HIP_TRY(hipStreamSynchronize(e->s_in));
+    return MI3D_OK;
+}
+
 int get_event(mi3d_swap_engine* e, bool timed, hipEvent_t* ev) {
     std::vector<hipEvent_t>& pool = timed ? e->free_events_timed : e->free_events_plain;
     if (!pool.empty()) {
@@ -269,15 +321,13 @@ int mi3d_swap_create(const mi3d_swap_config* cfg, mi3d_swap_engine** out) {
         if (err == hipSuccess) err = hipHostMalloc((void**)&e->host_pool, cfg->host_pool_bytes, hipHostMallocDefault);
         // touch every page once: the first DMA into untouched pinned pages runs at a fraction of link speed
         if (err == hipSuccess) memset(e->host_pool, 0, cfg->host_pool_bytes);
-        if (err == hipSuccess) err = hipStreamCreateWithFlags(&e->s_out, hipStreamNonBlocking);
-        if (err == hipSuccess) err = hipStreamCreateWithFlags(&e->s_in, hipStreamNonBlocking);
+        if (err == hipSuccess) err = acquire_streams(e);
         if (err == hipSuccess) err = hipEventCreate(&e->base);
         if (err == hipSuccess) err = hipEventRecord(e->base, e->s_out);
         if (err != hipSuccess) {
             note_hip_error(err);
             if (e->base) (void)hipEventDestroy(e->base);
-            if (e->s_in) (void)hipStreamDestroy(e->s_in);
-            if (e->s_out) (void)hipStreamDestroy(e->s_out);
+            if (e->s_out) release_streams(e);
             if (e->host_pool) (void)hipHostFree(e->host_pool);
             delete e;
             return MI3D_ERR_HIP;
@@ -291,10 +341,7 @@ int mi3d_swap_create(const mi3d_swap_config* cfg, mi3d_swap_engine** out) {
 int mi3d_swap_destroy(mi3d_swap_engine* e) {
     if (!e) return MI3D_ERR_INVALID_ARG;
     int st = MI3D_OK;
-    if (e->live) {
-        if (hipStreamSynchronize(e->s_out) != hipSuccess) st = MI3D_ERR_HIP;
-        if (hipStreamSynchronize(e->s_in) != hipSuccess) st = MI3D_ERR_HIP;
-    }
+    if (e->live) st = wait_for_copies(e);
     // (an engine without a pinned pool still records events when its arena is used)
     e->blocks.clear();  // drops shared events into the free lists
     reset_step_state(e);
@@ -306,8 +353,7 @@ int mi3d_swap_destroy(mi3d_swap_engine* e) {
 #endif
     if (e->live) {
         (void)hipEventDestroy(e->base);
-        (void)hipStreamDestroy(e->s_out);
-        (void)hipStreamDestroy(e->s_in);
+        release_streams(e);
         (void)hipHostFree(e->host_pool);
     }
     delete e;
@@ -744,9 +790,7 @@ int mi3d_checksum64(const void* dev, size_t bytes, uint64_t* value, void* stream
 int mi3d_swap_sync(mi3d_swap_engine* e) {
     if (!e) return MI3D_ERR_INVALID_ARG;
     if (!e->live) return MI3D_OK;
-    HIP_TRY(hipStreamSynchronize(e->s_out));
-    HIP_TRY(hipStreamSynchronize(e->s_in));
-    return MI3D_OK;
+    return wait_for_copies(e);
 }
 
 int mi3d_swap_reset_step(mi3d_swap_engine* e) {
@@ -806,7 +850,7 @@ int mi3d_swap_stats(mi3d_swap_engine* e, mi3d_swap_stats_t* out) {
             iv.emplace_back(t0, t1);
         }
     }
-    for (auto& kv : e->sum_slot) {   // (both side streams are idle here)
+    for (auto& kv : e->sum_slot) {   // (its copies have ended, and the checksums before and behind them)
         Tensor* t = find(e, kv.first);
         if (!t || !t->in.issued) continue;
         out->n_checksummed++;
