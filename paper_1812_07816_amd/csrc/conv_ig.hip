@@ -25,7 +25,6 @@
 namespace mi3d {
 namespace {
 
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef unsigned u32x2 __attribute__((__vector_size__(2 * sizeof(unsigned))));
 typedef __attribute__((address_space(3))) void* lds_ptr;
@@ -78,13 +77,14 @@ __device__ __forceinline__ float lo_f(uint32_t v) { return __builtin_bit_cast(fl
 __device__ __forceinline__ float hi_f(uint32_t v) { return __builtin_bit_cast(float, v & 0xFFFF0000u); }
 
 // WN = waves along the positions, MA = blocks of 32 channels of a wave: 2, 2 (128 x 128), 4, 2 (64 x 256) or 4, 1 (32 x 256).
-// FLAT: the contraction runs over (tap, channel) pairs, 64 of them per step whatever the number of channels; without it a step is
+// TR: the weights are read as they are, w[contracted][T][M] (the data gradient's): rows of the tile's channels per contracted one,
+// which the fragments are read from transposed (ds_read_b64_tr_b16).  FLAT: the contraction runs over (tap, channel) pairs, 64 of them per step whatever the number of channels; without it a step is
 // 64 channels of one tap, which is the same where the channels come in multiples of 64.  WIDE: planes too large for 32-bit offsets from a plane to
 // all that a tile and its taps touch (narrow_planes); the buffers move with the tap then, which costs 2 % (48^3 128->256,
 // stride 2, N = 2: 225 -> 231 us for the three passes).
-template <int WN, int MA, bool WIDE, bool FLAT>
+template <int WN, int MA, bool WIDE, bool FLAT, bool TR = false>
 __global__ void __launch_bounds__(256, 2) ig_kernel(const IgParams P) {
-    static_assert(!(WIDE && FLAT), "");
+    static_assert(!(WIDE && FLAT) && !(TR && (WIDE || FLAT)), "");
     constexpr int BM = 128 / WN * MA, BN = 64 * WN, NA = BM / 32, NB = BN / 32;
     constexpr int A_BYTES = BM * 128, STAGE = (BM + BN) * 128;
     extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -157,10 +157,15 @@ __global__ void __launch_bounds__(256, 2) ig_kernel(const IgParams P) {
             }
         }
     }
+    // TR: this lane's row (contracted channel) and piece of it; all its rows are a multiple of four apart and permuted alike
+    constexpr int RA = BM * 2, LA = 64 / (RA / 16);
+    auto swz_a = [](int row) { return RA == 256 ? 4 * (row & 3) : RA == 128 ? 2 * (row & 2) : 0; };
+    const int ra = wave * LA + lane / (RA / 16), ma = mt * BM + 8 * (lane % (RA / 16) ^ swz_a(ra));
+    const unsigned row_w = (unsigned)(P.T * P.M) * 2, offa = ma < P.M ? (unsigned)ra * row_w + (unsigned)ma * 2 : OOB;
     int rowa[NA];
     unsigned oka[NA];
 #pragma unroll
-    for (int i = 0; i < NA; ++i) {
+    for (int i = 0; i < NA && !TR; ++i) {
         const int m = mt * BM + 32 * i + rl;
         oka[i] = m < P.M;
         rowa[i] = m * P.T * P.C * 2 + piece * 16;
@@ -171,6 +176,7 @@ __global__ void __launch_bounds__(256, 2) ig_kernel(const IgParams P) {
     __amdgpu_buffer_rsrc_t r_hi = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)P.in_hi + base_b), 0, range, 0x00020000);
     __amdgpu_buffer_rsrc_t r_w = __builtin_amdgcn_make_buffer_rsrc((void*)P.w, 0, P.M * P.T * P.C * 2, 0x00020000);
 
+    const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(lds_ptr)lds);
     auto fetch_flat = [&](int buf, int s) {
         const int k = s * BK + piece * 8, tp = divide(k, P.Cdiv), c = k - tp * P.C;   // this lane's tap and channels
         const bool in = tp < K.ntap;
@@ -199,17 +205,27 @@ __global__ void __launch_bounds__(256, 2) ig_kernel(const IgParams P) {
         }
         const int ua = (a.wt * P.C + chunk * BK) * 2;
         char* l = lds + buf * STAGE + wave * 1024;
+        const unsigned la = lds0 + buf * STAGE + wave * 1024;
+        auto to_lds = [&](__amdgpu_buffer_rsrc_t r, int at, unsigned off) {
+            if constexpr (TR) load_lds_asm(r, la + at, off);
+            else load_lds(r, l + at, off);
+        };
+        if constexpr (TR) {   // (contracted channels behind the last one lie behind the end of w)
+            const unsigned u = (unsigned)(chunk * BK) * row_w + (unsigned)(a.wt * P.M) * 2;
 #pragma unroll
-        for (int i = 0; i < NA; ++i) load_lds(r_w, l + i * 4096, oka[i] & okc ? rowa[i] + ua : OOB);
+            for (int i = 0; i < NA; ++i) to_lds(r_w, i * 4096, offa == OOB ? OOB : offa + u + (unsigned)(i * 4 * LA) * row_w);
+        } else {
+#pragma unroll
+            for (int i = 0; i < NA; ++i) to_lds(r_w, i * 4096, oka[i] & okc ? rowa[i] + ua : OOB);
+        }
         // (a step may begin in one half of a virtual concatenation and end in the other: inactive lanes write nothing)
-        l += A_BYTES;
         if (c < P.csplit) {
 #pragma unroll
-            for (int i = 0; i < NB; ++i) load_lds(r_in, l + i * 4096, okc & (mask[i] >> tap) ? rowb[i] + ub : OOB);
+            for (int i = 0; i < NB; ++i) to_lds(r_in, A_BYTES + i * 4096, okc & (mask[i] >> tap) ? rowb[i] + ub : OOB);
             asm volatile("; low half");   // keeps the branches apart: merged, their last loads run in a loop over the resources
         } else {
 #pragma unroll
-            for (int i = 0; i < NB; ++i) load_lds(r_hi, l + i * 4096, okc & (mask[i] >> tap) ? rowb[i] + ub - (WIDE ? 0 : P.csplit * 2) : OOB);
+            for (int i = 0; i < NB; ++i) to_lds(r_hi, A_BYTES + i * 4096, okc & (mask[i] >> tap) ? rowb[i] + ub - (WIDE ? 0 : P.csplit * 2) : OOB);
         }
         if (++chunk == nch) { chunk = 0; ++tap; }
     };
@@ -227,6 +243,17 @@ __global__ void __launch_bounds__(256, 2) ig_kernel(const IgParams P) {
     int frag[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) frag[k] = r32 * 128 + ((2 * k + half) ^ swz) * 16;
+    // TR: a group of 16 lanes reads four rows of 16 channels; groups 0, 1 rows 0 .. 7 of channels 0 .. 15 and 16 .. 31 of a block of 32,
+    // groups 2, 3 rows 8 .. 15
+    int fraga[MA];
+    if constexpr (TR) {
+        const int g = lane >> 4, row = 8 * (g >> 1) + (lane >> 2 & 3), c8 = lane & 3;
+#pragma unroll
+        for (int a = 0; a < MA; ++a) {
+            const int at = (wm * 64 + 32 * a + 16 * (g & 1)) / 8 + (c8 >> 1);
+            fraga[a] = row * RA + (at ^ swz_a(row)) * 16 + (c8 & 1) * 8;
+        }
+    }
 
     if (s0 < s1) {
         fetch(0, s0);
@@ -234,13 +261,13 @@ __global__ void __launch_bounds__(256, 2) ig_kernel(const IgParams P) {
         for (int s = s0; s < s1; ++s) {
             const int buf = (s - s0) & 1;
             if (s + 1 < s1) fetch(1 - buf, s + 1);
-            const char* la = lds + buf * STAGE + wm * 64 * 128;
+            const char* la = lds + buf * STAGE + (TR ? 0 : wm * 64 * 128);
             const char* lb = lds + buf * STAGE + A_BYTES + wn * 64 * 128;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 bf16x8 fa[MA], fb[2];
 #pragma unroll
-                for (int a = 0; a < MA; ++a) fa[a] = *(const bf16x8*)(la + a * 4096 + frag[k]);
+                for (int a = 0; a < MA; ++a) fa[a] = TR ? tr_frag(la + fraga[a] + k * 16 * RA, RA) : *(const bf16x8*)(la + a * 4096 + frag[k]);
 #pragma unroll
                 for (int b = 0; b < 2; ++b) fb[b] = *(const bf16x8*)(lb + b * 4096 + frag[k]);
 #pragma unroll
@@ -420,6 +447,13 @@ bool is_flat(const Geom& g, int pass) {
     return C % BK != 0 && (C % 32 != 0 || g.sD == 1) && narrow_planes(g, pass);   // (halves of an input come in 32s: C is a multiple of 64)
 }
 
+// Weights of the data gradient read as they are (TR) rather than from a transposed copy.  Ragged channels keep the copy: their
+// repair of non-finite weights takes its flags from it.
+bool reads_tr(const Geom& g, int pass) {
+    return pass == MI3D_PASS_DGRAD && g.Cin % 32 == 0 && g.Cout % 32 == 0 && narrow_planes(g, pass) && !is_flat(g, pass);
+}
+size_t copy_bytes(const Geom& g, int pass) { return pass == MI3D_PASS_DGRAD && !reads_tr(g, pass) ? weight_bytes(g) : 0; }
+
 // Tiles of all classes for tiles of bm x bn, the steps of all of them, and of the longest
 long long count_tiles(const Geom& g, int pass, int bm, int bn, long long* work, int* most) {
     const bool flip = pass == MI3D_PASS_DGRAD, classes = flip && g.sD == 2;
@@ -459,7 +493,7 @@ IgPlan make_plan(const Geom& g, int pass, size_t ws_bytes) {
         for (const int S : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 40, 48, 64}) {
             if (S > most) break;
             if (S > 1 && (S * out_elems * 4 > ((size_t)64 << 20) || tiles * S > 4 * slots)) break;
-            if (S > 1 && S * out_elems * 4 + (flip ? weight_bytes(g) : 0) > ws_bytes) break;
+            if (S > 1 && S * out_elems * 4 + copy_bytes(g, pass) > ws_bytes) break;
             const double rounds = classes ? (double)work / most * S / slots + 0.5 : (double)((tiles * S + slots - 1) / slots);
             const double us = rounds * ((most + S - 1) / S) * STEP_US[v] + START_US + (S > 1 ? START_US + S * (double)out_elems * 8 / PART_BYTES_PER_US : 0.0);
             if (us < best_us) {
@@ -522,10 +556,10 @@ bool ig_takes(const Geom& g, int pass) {
            (count_tiles(g, pass, 128, 128, &work, &most) <= MAX_TILES || count_tiles(g, pass, 64, 256, &work, &most) <= MAX_TILES);
 }
 
-size_t ig_min_workspace_bytes(const Geom& g, int pass) { return pass == MI3D_PASS_DGRAD ? weight_bytes(g) : 0; }
+size_t ig_min_workspace_bytes(const Geom& g, int pass) { return copy_bytes(g, pass); }
 size_t ig_workspace_bytes(const Geom& g, int pass) {
     const IgPlan p = make_plan(g, pass, ~(size_t)0);
-    return (pass == MI3D_PASS_DGRAD ? weight_bytes(g) : 0) + (p.splits > 1 ? p.splits * p.out_elems * sizeof(float) : 0);
+    return copy_bytes(g, pass) + (p.splits > 1 ? p.splits * p.out_elems * sizeof(float) : 0);
 }
 
 void ig_describe(const Geom& g, int pass, size_t ws_bytes, char* buf, size_t len) {
@@ -541,16 +575,17 @@ int ig_conv(const Geom& g, int pass, const void* in, const void* w, void* out, v
     const IgPlan plan = make_plan(g, pass, ws_bytes);
     if (g.hi && g.Cin % 64) return MI3D_ERR_UNSUPPORTED;
     int st = MI3D_OK;
-    if (flip) {
+    const bool tr = reads_tr(g, pass);
+    if (flip && !tr) {
         ig_transpose_kernel<<<dim3(27, (g.Cin + 63) / 64, (g.Cout + 63) / 64), 256, 0, s>>>((const uint16_t*)w, (uint16_t*)ws, 27, g.Cin, g.Cout, wflags);
         if ((st = check_launch())) return st;
     }
     IgParams P{};
     P.in = P.in_hi = (const uint16_t*)in;
-    P.w = (const uint16_t*)(flip ? ws : w);
+    P.w = (const uint16_t*)(flip && !tr ? ws : w);
     P.out = (uint16_t*)out;
     P.add = (const uint16_t*)g.add; P.ref = (const uint16_t*)g.ref; P.slope = g.slope;
-    P.part = plan.splits > 1 ? (float*)((char*)ws + (flip ? weight_bytes(g) : 0)) : nullptr;
+    P.part = plan.splits > 1 ? (float*)((char*)ws + copy_bytes(g, pass)) : nullptr;
     P.T = 27; P.splits = plan.splits; P.MT = plan.MT; P.ncls = plan.ncls; P.tiles = plan.tiles; P.out_elems = (long long)plan.out_elems;
     P.is = flip ? 1 : g.sD; P.os = flip ? g.sD : 1;
     if (!flip) {
@@ -602,9 +637,9 @@ int ig_conv(const Geom& g, int pass, const void* in, const void* w, void* out, v
     }
     const bool wide = !narrow_planes(g, pass), flat = is_flat(g, pass);
     typedef void (*Kernel)(IgParams);
-    static const Kernel kernels[3][3] = {{ig_kernel<2, 2, false, false>, ig_kernel<2, 2, true, false>, ig_kernel<2, 2, false, true>},
-                                         {ig_kernel<4, 2, false, false>, ig_kernel<4, 2, true, false>, ig_kernel<4, 2, false, true>},
-                                         {ig_kernel<4, 1, false, false>, ig_kernel<4, 1, true, false>, ig_kernel<4, 1, false, true>}};
+    static const Kernel kernels[3][4] = {{ig_kernel<2, 2, false, false>, ig_kernel<2, 2, true, false>, ig_kernel<2, 2, false, true>, ig_kernel<2, 2, false, false, true>},
+                                         {ig_kernel<4, 2, false, false>, ig_kernel<4, 2, true, false>, ig_kernel<4, 2, false, true>, ig_kernel<4, 2, false, false, true>},
+                                         {ig_kernel<4, 1, false, false>, ig_kernel<4, 1, true, false>, ig_kernel<4, 1, false, true>, ig_kernel<4, 1, false, false, true>}};
     auto lds = [](int v) { return (size_t)2 * (BMS[v] + BNS[v]) * 128; };
     static std::atomic<bool> attr_set{false};   // set once per process; a second thread racing here repeats an idempotent call
     if (!attr_set) {
@@ -615,7 +650,7 @@ int ig_conv(const Geom& g, int pass, const void* in, const void* w, void* out, v
             }
         attr_set = true;
     }
-    kernels[plan.v][wide ? 1 : flat ? 2 : 0]<<<(unsigned)(plan.tiles * plan.splits), 256, lds(plan.v), s>>>(P);
+    kernels[plan.v][wide ? 1 : flat ? 2 : tr ? 3 : 0]<<<(unsigned)(plan.tiles * plan.splits), 256, lds(plan.v), s>>>(P);
     st = check_launch();
     if (st || plan.splits == 1) return st;
     const long long n = P.out_elems;

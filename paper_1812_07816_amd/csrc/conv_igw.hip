@@ -30,8 +30,6 @@ namespace mi3d {
 namespace {
 
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
-typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4;
-typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8;
 typedef __attribute__((address_space(3))) char* lds_char;
 
 constexpr int BN = 128;                            // columns of a tile
@@ -128,20 +126,6 @@ __device__ __forceinline__ void store(const IgwParams& P, const Work& w, const f
 
 // ---- bf16 ----------------------------------------------------------------------------------------------------------------
 
-__device__ __forceinline__ bf16x8 tr_frag(const char* p, int row_bytes) {   // positions 0 to 3 and 4 to 7 behind p, of this lane's channel
-    typedef __attribute__((address_space(3))) s16x4* lptr;
-    s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lptr)(p));
-    s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lptr)(p + 4 * row_bytes));
-    s16x8 c = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
-    return __builtin_bit_cast(bf16x8, c);
-}
-
-// 16 bytes per lane from buffer r at byte offset off (zeros beyond its range) to the wave's 1 KB at LDS byte l.  Inline assembly:
-// behind the builtin the compiler waits for all loads before every LDS read.
-__device__ __forceinline__ void load_lds(__amdgpu_buffer_rsrc_t r, unsigned l, unsigned off) {
-    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(l), "v"(off), "s"(r) : "memory", "m0");
-}
-
 // BM = rows of a tile: 128 (waves 2 x 2 of 64 x 64) or 64 (2 x 2 of 32 x 64)
 template <int BM>
 __global__ void __launch_bounds__(256, 2) igw_kernel(const IgwParams P) {
@@ -183,9 +167,9 @@ __global__ void __launch_bounds__(256, 2) igw_kernel(const IgwParams P) {
         }
 #pragma unroll
         for (int i = 0; i < NA; ++i)
-            load_lds(r_dy, l + i * 4096, offa == OOB ? OOB : offa + base + (uint32_t)(i * 4 * LA) * rowa);   // (behind the last position: the end of dy)
+            load_lds_asm(r_dy, l + i * 4096, offa == OOB ? OOB : offa + base + (uint32_t)(i * 4 * LA) * rowa);   // (behind the last position: the end of dy)
 #pragma unroll
-        for (int i = 0; i < NB; ++i) load_lds(r_x, l + A_BYTES + i * 4096, (v[i].y & col.need) == col.need ? v[i].x + col.off : OOB);
+        for (int i = 0; i < NB; ++i) load_lds_asm(r_x, l + A_BYTES + i * 4096, (v[i].y & col.need) == col.need ? v[i].x + col.off : OOB);
     };
 
     f32x16 acc[AB][2];

@@ -44,4 +44,23 @@ inline AxisTaps axis_taps(int k, int s, int p, bool dgrad, int par) {
     return a;
 }
 
+// Fragment of v_mfma_f32_32x32x16_bf16 from rows of LDS that run along its other axis: rows 0 to 3 and 4 to 7 behind p, of this
+// lane's column (a group of 16 lanes reads four rows of 16 columns and gets them transposed)
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+__device__ __forceinline__ bf16x8 tr_frag(const char* p, int row_bytes) {
+    typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4;
+    typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8;
+    typedef __attribute__((address_space(3))) s16x4* lptr;
+    s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lptr)(p));
+    s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lptr)(p + 4 * row_bytes));
+    s16x8 c = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+    return __builtin_bit_cast(bf16x8, c);
+}
+
+// 16 bytes per lane from buffer r at byte offset off (zeros beyond its range) to the wave's 1 KB at LDS byte l.  Inline assembly:
+// behind the builtin the compiler waits for all loads before every transposing LDS read.
+__device__ __forceinline__ void load_lds_asm(__amdgpu_buffer_rsrc_t r, unsigned l, unsigned off) {
+    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(l), "v"(off), "s"(r) : "memory", "m0");
+}
+
 }  // namespace mi3d
