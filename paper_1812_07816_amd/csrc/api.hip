@@ -181,7 +181,7 @@ static int run_kernel(Kernel k, const Geom& g, int pass, const void* a, const vo
 static std::string describe(Kernel k, const Geom& g, int pass, size_t ws_bytes) {
     size_t rest;
     char buf[64];
-    if (pass == MI3D_PASS_WGRAD && ((k == K_WGRAD_MFMA && wgrad_mfma_uses_igw(g)) || (k == K_WGRAD_S2 && wgrad_s2_uses_igw(g)) || (k == K_F32 && f32_uses_igw(g, ws_bytes)))) {
+    if (pass == MI3D_PASS_WGRAD && ((k == K_WGRAD_MFMA && wgrad_mfma_uses_igw(g)) || (k == K_WGRAD_S2 && wgrad_s2_uses_igw(g)) || (k == K_F32 && !f32_uses_tiny(g, pass) && f32_uses_igw(g, ws_bytes)))) {
         igw_describe(g, ws_bytes, buf, sizeof(buf));
         return buf;
     }
@@ -198,6 +198,7 @@ static std::string describe(Kernel k, const Geom& g, int pass, size_t ws_bytes) 
         case K_DGRAD_S2: if (g.Cout <= 64) return "dgrad_stride2_parity"; break;
         case K_F32:
             if (pointwise_f32_supported(g)) return "f32_pointwise_head";
+            if (f32_uses_tiny(g, pass)) return "f32_direct";
             if (f32_uses_ig(g, pass, ws_bytes)) {
                 igf_describe(g, pass, ws_bytes, buf, sizeof(buf));
                 return std::string(buf) + (f32_gathers_parts(g, pass) ? "_from_bf16_parts" : "");

@@ -976,8 +976,8 @@ size_t f32_min_workspace_bytes(const Geom& g, int pass) {
 // the partial sums, f32_wgrad_kernel -> igw_f32_kernel: 64->128, 2x2x2 at 96^3 342 -> 120 us, 32->64, stride 2 at 128^3, N = 2 861 -> 684,
 // 128->256, stride 2 at 32^3, N = 2 218 -> 110, 256->256 at 16^3, N = 2 339 -> 213, 128->320 at 11 x 12 x 9 71 -> 43,
 // 32->64 at 13 x 18 x 20 57 -> 21.  Layers with at most
-// four input channels have the kernel that folds the taps (4->32 at 60^3 44 -> 60) but for the smallest volumes (4->8 at
-// 16^3 24 -> 17), and those f32s_wgrad takes stay there (128->128 at 32^3, N = 2 333 -> 394).
+// four input channels have the kernel that folds the taps (4->32 at 60^3 44 -> 60) but for the smallest volumes (2->32 at
+// 20^3 25 -> 13), and those f32s_wgrad takes stay there (128->128 at 32^3, N = 2 333 -> 394).
 static bool igw_better(const Geom& g, size_t ws_bytes) {
     Geom q = g;
     q.hi = nullptr;      // (the sizes decide, not how the call passes its tensors)
@@ -1008,6 +1008,12 @@ size_t f32_workspace_bytes(const Geom& g, int pass) {
         b = b > p ? b : p;
     }
     return b;
+}
+
+// (Planes 32 columns wide and more fill the tiles of f32s_gconv_kernel, few planes as they may be: it keeps those.)
+bool f32_uses_tiny(const Geom& g, int pass) {
+    if (!f32_supported(g, pass) || f32_head(g) || !tiny_supported(g, pass)) return false;
+    return !split_ok(g, pass) || (pass == MI3D_PASS_DGRAD ? g.W : g.Wo) < 32;
 }
 
 bool f32_uses_igw(const Geom& g, size_t ws_bytes) { return f32_supported(g, MI3D_PASS_WGRAD) && !f32_head(g) && igw_better(g, ws_bytes); }
@@ -1233,6 +1239,7 @@ static int launch_gconv_classes(GcMulti& Q, hipStream_t s) {
 int f32_conv(const Geom& g, int pass, const void* in, const void* w, void* out, void* ws, size_t ws_bytes, hipStream_t s) {
     if (f32_head(g)) return pointwise_f32_conv(g, pass, in, w, out, ws, ws_bytes, s);
     if (ws_bytes < f32_min_workspace_bytes(g, pass)) return MI3D_ERR_WORKSPACE;
+    if (f32_uses_tiny(g, pass)) return tiny_conv(g, pass, in, w, out, s);
     if (f32_uses_ig(g, pass, ws_bytes)) return igf_conv(g, pass, in, w, out, ws, ws_bytes, s);
     const bool split = f32_uses_parts(g, pass, ws_bytes);
     const bool dgrad = pass == MI3D_PASS_DGRAD;
@@ -1332,6 +1339,7 @@ int f32_conv(const Geom& g, int pass, const void* in, const void* w, void* out, 
 int f32_wgrad(const Geom& g, const void* x, const void* dy, float* dw, void* ws, size_t ws_bytes, hipStream_t s) {
     if (f32_head(g)) return pointwise_f32_conv(g, MI3D_PASS_WGRAD, x, dy, dw, ws, ws_bytes, s);
     if (ws_bytes < f32_min_workspace_bytes(g, MI3D_PASS_WGRAD)) return MI3D_ERR_WORKSPACE;
+    if (f32_uses_tiny(g, MI3D_PASS_WGRAD)) return tiny_wgrad(g, x, dy, dw, s);
     if (f32_uses_igw(g, ws_bytes)) return igw_run(g, x, dy, dw, ws, ws_bytes, s);
     if (f32_uses_parts(g, MI3D_PASS_WGRAD, ws_bytes)) return f32s_wgrad(g, x, dy, dw, ws, ws_bytes, s);
     WgParams P;

@@ -205,6 +205,10 @@ size_t f32_workspace_bytes(const Geom& g, int pass);       // what the fastest k
 size_t f32_min_workspace_bytes(const Geom& g, int pass);   // what a call needs at least
 int f32_conv(const Geom& g, int pass, const void* in, const void* w, void* out, void* ws, size_t ws_bytes, hipStream_t s);
 int f32_wgrad(const Geom& g, const void* x, const void* dy, float* dw, void* ws, size_t ws_bytes, hipStream_t s);
+bool tiny_supported(const Geom& g, int pass);                  // fp32, one launch, no workspace (conv_tiny_f32.hip)
+int tiny_conv(const Geom& g, int pass, const void* in, const void* w, void* out, hipStream_t s);
+int tiny_wgrad(const Geom& g, const void* x, const void* dy, float* dw, hipStream_t s);
+bool f32_uses_tiny(const Geom& g, int pass);
 bool f32_uses_ig(const Geom& g, int pass, size_t ws_bytes);      // implicit GEMM over numbered positions
 bool f32_uses_igw(const Geom& g, size_t ws_bytes);               // weight gradient over numbered positions
 bool f32_gathers_parts(const Geom& g, int pass);                 // sizes that the patch kernel with such products serves

@@ -18,17 +18,17 @@ TOL = 3e-5
 CASES = [
     # N, D, H, W, Cin, Cout, k, s, p; passes that take the kernel
     ((1, 4, 6, 8, 32, 64, 2, 2, 0), "01"),        # taps as output channels, one tile
-    ((2, 5, 7, 9, 20, 36, 2, 2, 0), "01"),        # odd extents: voxels no tap reaches, channels that end inside a block
-    ((1, 3, 16, 17, 64, 12, 2, 2, 0), "01"),
+    ((2, 5, 7, 9, 60, 108, 2, 2, 0), "01"),        # odd extents: voxels no tap reaches, channels that end inside a block
+    ((1, 3, 16, 17, 64, 44, 2, 2, 0), "01"),
     ((2, 6, 9, 11, 20, 44, 3, 2, 0), "01"),       # classes with one to eight taps, steps that span taps
     ((2, 13, 14, 15, 32, 64, 3, 2, 1), "01"),
     ((1, 9, 8, 7, 40, 48, 3, 1, 2), "0"),         # padding 2
     ((1, 6, 7, 5, 64, 36, 3, 1, 1), "01"),        # more splits than tiles
-    ((2, 3, 4, 5, 12, 8, 1, 1, 0), "01"),         # less than a step
-    ((1, 7, 6, 9, 8, 16, 2, 1, 1), "01"),         # even extent, unit stride
+    ((2, 3, 4, 5, 20, 700, 1, 1, 0), "01"),         # less than a step
+    ((1, 7, 6, 9, 8, 200, 2, 1, 1), "01"),         # even extent, unit stride
     ((1, 1, 1, 1, 64, 132, 3, 1, 1), "01"),       # one voxel
     ((1, 2, 200, 1, 32, 16, 3, 1, 1), "01"),      # one column
-    ((3, 5, 5, 5, 4, 8, 3, 1, 1), "01"),          # eight taps per step
+    ((3, 5, 5, 5, 4, 128, 3, 1, 1), "01"),          # eight taps per step
     ((1, 11, 12, 9, 128, 320, 3, 1, 1), "01"),
     ((1, 4, 4, 4, 640, 96, 3, 2, 1), "01"),       # many steps, few positions
 ]
@@ -50,9 +50,9 @@ def test_matches_oracle(device, case, passes):
 @pytest.mark.parametrize("k, s, p", [((1, 2, 2), (1, 2, 2), 0), ((3, 3, 3), (1, 2, 2), 1), ((2, 3, 1), (2, 1, 1), (0, 1, 0)), ((3, 1, 2), (1, 1, 2), (1, 0, 0))])
 def test_axes_of_their_own(device, k, s, p):
     g = torch.Generator().manual_seed(3)
-    x = torch.randn((2, 24, 6, 9, 10), generator=g, dtype=torch.float64)
-    w = torch.randn((40, 24, *k), generator=g, dtype=torch.float64)
-    d = mc.make_desc(2, 6, 9, 10, 24, 40, k, s, p, torch.float32)
+    x = torch.randn((2, 72, 6, 9, 10), generator=g, dtype=torch.float64)
+    w = torch.randn((136, 72, *k), generator=g, dtype=torch.float64)
+    d = mc.make_desc(2, 6, 9, 10, 72, 136, k, s, p, torch.float32)
     assert _uses(d, 0) and _uses(d, 1)
     y = torch.nn.functional.conv3d(x.float().double(), w.float().double(), stride=s, padding=p)
     dy = torch.randn(y.shape, generator=g, dtype=torch.float64)

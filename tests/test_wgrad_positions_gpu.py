@@ -24,11 +24,11 @@ CASES = [
     (2, 2, 2, 2, 320, 64, 3, 1, 1, True),         # less than a step of positions
     (3, 9, 11, 13, 64, 160, 3, 2, 1, True),       # odd extents, stride 2
     (2, 8, 10, 12, 32, 64, 3, 2, 0, True),
-    (1, 16, 16, 16, 4, 8, 3, 1, 1, False),        # one tile of columns
+    (1, 18, 20, 20, 2, 8, 3, 1, 1, False),        # one tile of columns
     (2, 6, 9, 11, 20, 44, 3, 2, 0, False),
     (2, 5, 9, 13, 32, 130, 3, 2, 1, False),       # two rows in the last tile
     (1, 9, 8, 7, 64, 80, 3, 1, 2, False),
-    (1, 5, 7, 9, 30, 62, 2, 2, 0, False),         # voxels no position reads
+    (1, 5, 7, 9, 30, 126, 2, 2, 0, False),         # voxels no position reads
     (2, 8, 8, 8, 160, 96, 3, 1, 1, False),
     (1, 1, 1, 1, 64, 64, 3, 1, 1, False),
 ]
@@ -82,11 +82,11 @@ def test_halves(device, Cin, bf16):
 @pytest.mark.parametrize("k, s, p", [((1, 2, 2), (1, 2, 2), 0), ((3, 3, 3), (1, 2, 2), 1), ((2, 3, 1), (2, 1, 1), (0, 1, 0))])
 def test_axes_of_their_own(device, k, s, p):
     g = torch.Generator().manual_seed(3)
-    x = torch.randn((2, 24, 6, 9, 10), generator=g).double()
-    d = mc.make_desc(2, 6, 9, 10, 24, 40, k, s, p, torch.float32)
+    x = torch.randn((2, 72, 6, 9, 10), generator=g).double()
+    d = mc.make_desc(2, 6, 9, 10, 72, 136, k, s, p, torch.float32)
     assert _uses(d)
-    dy = torch.randn((2, 40, *mc.out_dims(d)), generator=g).double()
-    ref = torch.nn.grad.conv3d_weight(x, (40, 24, *k), dy, stride=s, padding=p).permute(0, 2, 3, 4, 1)
+    dy = torch.randn((2, 136, *mc.out_dims(d)), generator=g).double()
+    ref = torch.nn.grad.conv3d_weight(x, (136, 72, *k), dy, stride=s, padding=p).permute(0, 2, 3, 4, 1)
     dev = lambda t: t.permute(0, 2, 3, 4, 1).float().contiguous().cuda()
     got = mc.conv3d_wgrad(d, dev(x), dev(dy)).cpu().double()
     assert float((got - ref).abs().max() / ref.square().mean().sqrt()) <= TOL
