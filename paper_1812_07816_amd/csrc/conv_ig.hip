@@ -494,7 +494,10 @@ IgPlan make_plan(const Geom& g, int pass, size_t ws_bytes) {
             if (S > most) break;
             if (S > 1 && (S * out_elems * 4 > ((size_t)64 << 20) || tiles * S > 4 * slots)) break;
             if (S > 1 && S * out_elems * 4 + copy_bytes(g, pass) > ws_bytes) break;
-            const double rounds = classes ? (double)work / most * S / slots + 0.5 : (double)((tiles * S + slots - 1) / slots);
+            // (classes of one to eight taps fill each other's rounds, but none is over before its longest workgroup: 320->256 of
+            // the data gradient at 16^3, stride 2, whole 42 us, in four parts 28; with 16 steps or fewer splitting gives what it costs)
+            double rounds = classes ? (double)work / most * S / slots + 0.5 : (double)((tiles * S + slots - 1) / slots);
+            if (rounds < 1.0 && most > 16) rounds = 1.0;
             const double us = rounds * ((most + S - 1) / S) * STEP_US[v] + START_US + (S > 1 ? START_US + S * (double)out_elems * 8 / PART_BYTES_PER_US : 0.0);
             if (us < best_us) {
                 best_us = us;

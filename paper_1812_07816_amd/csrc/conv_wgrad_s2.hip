@@ -304,15 +304,17 @@ static int wgrad_s2_slots(const Geom& g) {
     return (int)slots;
 }
 
-// The matrix product over numbered positions where its model expects it to be faster than 25 us and 700 TFLOP/s, about what
-// this kernel reaches at its best (it stages a patch four times the tile for 32 input channels at a time).  With the
-// launch that adds the partial sums, this kernel -> igw_kernel: 64->128 at 96^3, N = 2 169 -> 132 us, 128->256 at 48^3, N = 2 91 -> 66,
-// 256->320 at 24^3, N = 2 101 -> 33, 32->64 at 32^3, N = 2 29 -> 15; but 32->64 at 192^3 153 -> 213 (seven tiles of columns read
-// every position again).
+// The matrix product over numbered positions where its model expects it to be faster than this kernel, which (with the launch that adds
+// the partial sums) takes 23 us and the time of its whole patches at 870 TFLOP/s, 760 with 32 or 64 output channels and 465 with
+// other numbers that 128 does not divide: within 7 % of 20 layers measured.  This kernel -> igw_kernel: 64->128 at 96^3, N = 2 177 -> 133 us, 128->256 at 48^3, N = 2 92 -> 67,
+// 256->320 at 24^3, N = 2 101 -> 49, at 32^3, N = 2 161 -> 57, 64->320 at 56^3, N = 2 138 -> 74, 32->320 at 128^3 340 -> 231, 32->64 at
+// 80 x 80 x 70, N = 2 47 -> 30; but 32->256 at 128^3, N = 2 294 -> 322, 64->256 at 120 x 128 x 128 274 -> 300 and 32->64 at 192^3
+// 153 -> 213 (seven tiles of columns read every position again): whole patches, many of them, stay.
 bool wgrad_s2_uses_igw(const Geom& g) {
     if (!igw_supported(g)) return false;
-    const double us = 25.0 + 2.0 * g.out_voxels() * 27 * g.Cin * (double)g.Cout / 7e8;
-    return igw_us(g, ~(size_t)0) < us;
+    const long long patches = (long long)g.N * g.Do * ((g.Ho + TH - 1) / TH) * ((g.Wo + TW - 1) / TW);
+    const double rate = g.Cout % 128 == 0 ? 8.7e8 : g.Cout <= 64 ? 7.6e8 : 4.65e8;
+    return igw_us(g, ~(size_t)0) < 23.0 + 2.0 * patches * (TH * TW) * 27 * g.Cin * (double)g.Cout / rate;
 }
 
 size_t wgrad_s2_workspace_bytes(const Geom& g) {

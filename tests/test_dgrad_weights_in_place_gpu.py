@@ -13,7 +13,7 @@ CASES = [
     # N, D, H, W, Cin, Cout, s, rows of a tile
     (1, 17, 16, 18, 32, 96, 2, 32),       # rows of 64 bytes; 1.5 steps
     (1, 19, 15, 18, 32, 320, 2, 32),
-    (1, 33, 31, 35, 64, 160, 2, 64),      # rows of 128 bytes; 2.5 steps
+    (1, 61, 62, 60, 64, 160, 2, 64),      # rows of 128 bytes; 2.5 steps
     (1, 6, 7, 8, 224, 128, 1, 128),       # rows of 256 bytes; 3/4 of the last tile's in use
     (2, 6, 5, 6, 96, 192, 1, 128),
     (2, 3, 4, 5, 320, 96, 2, 128),
