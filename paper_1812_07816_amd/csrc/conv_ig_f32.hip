@@ -467,8 +467,7 @@ size_t flags_at(long long frags) { return (size_t)frags * (3 * 512 * 2); }
 size_t pack_bytes(long long frags) { return (flags_at(frags) + (size_t)frags * 4 + 255) & ~(size_t)255; }
 
 // Workgroups of `mean` steps each (the longest: most): full rounds of RES per CU, and what is left over
-double plan_us(int v, long long wgs, double most, double mean) {
-    const int cus = cu_count();
+double plan_us(int v, int cus, long long wgs, double most, double mean) {
     const long long full = wgs / ((long long)RES[v] * cus), rest = wgs - full * RES[v] * cus;
     const int k = (int)((rest + cus - 1) / cus);
     auto round = [&](int n, double steps) { return steps * STEP_US[v][n - 1] + START_US[v] * n; };
@@ -501,7 +500,7 @@ IgfPlan make_plan(const Geom& g, int pass, size_t ws_bytes) {
             if (most > S * (long long)MAX_STEPS) continue;
             if (S > 1 && (S > most || S * out_elems * 4 > (32ll << 20) || tiles * S > 8 * cus)) break;
             if (S > 1 && S * (size_t)out_elems * 4 + pack_bytes(best.frags) > ws_bytes) break;
-            const double us = plan_us(v, tiles * S, (most + S - 1) / S, work / (tiles ? tiles : 1) / S) + (S > 1 ? LAUNCH_US + S * (double)out_elems * 8 / PART_BYTES_PER_US : 0.0);
+            const double us = plan_us(v, cus, tiles * S, (most + S - 1) / S, work / (tiles ? tiles : 1) / S) + (S > 1 ? LAUNCH_US + S * (double)out_elems * 8 / PART_BYTES_PER_US : 0.0);
             if (us < best.us) {
                 best.us = us;
                 best.v = v; best.splits = S; best.MT = MT; best.tiles = tiles;
@@ -520,7 +519,7 @@ bool igf_supported(const Geom& g, int pass) {
     if ((dgrad ? g.Cout : g.Cin) % 4) return false;
     const long long in = dgrad ? g.out_voxels() * g.Cout : g.in_voxels() * g.Cin;
     if (in * 4 > MAX_BYTES || g.in_voxels() >= (1ll << 31) - 1024 || g.out_voxels() >= (1ll << 31) - 1024 || g.w_elems() >= (1ll << 28)) return false;
-    return make_plan(g, pass, ~(size_t)0).v >= 0;
+    return make_plan(g, pass, 0).v >= 0;   // (whole contractions: whether there is a tile shape)
 }
 
 double igf_us(const Geom& g, int pass) { return LAUNCH_US + make_plan(g, pass, ~(size_t)0).us; }
