@@ -81,7 +81,8 @@ int mi3d_conv3d_out_dims(const mi3d_conv_desc *desc, int *Do, int *Ho, int *Wo);
  * Returns 0 for an invalid descriptor as well; the pass itself reports it.
  *
  * A call with less, down to mi3d_conv3d_min_workspace_bytes, is served too, by a slower kernel: fp32 layers by the fp32
- * matrix instructions, deep bf16 layers with a contraction in fewer parts, channel counts that are not multiples of 32 by
+ * matrix instructions (the smallest ones need none of it and run as they are), deep bf16 layers and weight gradients over
+ * numbered positions with a contraction in fewer parts, channel counts that are not multiples of 32 (or of 8 by 3x3x3) by
  * the plain kernels (150 times slower on large volumes).  The sums are then formed in another order, so the bits of a
  * result depend on the size of the workspace; with the same size repeated calls give identical bits.  Below the minimum
  * a call returns MI3D_ERR_WORKSPACE and launches nothing.  The entry points with statistics or sums

@@ -1,6 +1,6 @@
-// Implicit-GEMM convolution for the deep layers (bf16, 3x3x3, channels in multiples of 32; v_mfma_f32_32x32x16_bf16, fp32
-// accumulation): stride-1 forward and data gradient on volumes too small to fill the chip with planes, stride-2
-// forward with more than 32 input channels, stride-2 data gradient with more than 64 output channels.
+// Implicit-GEMM convolution for the deep layers (bf16, 3x3x3; v_mfma_f32_32x32x16_bf16, fp32 accumulation): stride-1
+// forward and data gradient on volumes too small to fill the chip with planes, stride-2 forward with more than 32 input channels,
+// stride-2 data gradient with more than 64 output channels, and channel counts in multiples of 8 that 32 does not divide.
 //
 // One product: out[m, j] = sum over taps t and contracted channels c of w[m, t, c] * in[is j + delta_t, c].  Positions j are
 // numbered through all samples, so a tile of positions is full whatever the extents of the volume (the plane-streaming
@@ -8,7 +8,7 @@
 // class of the output voxel, each with the 1, 2, 4 or 8 taps that hit it.  Where the tiles leave CUs idle the steps of the
 // contraction are split and fp32 partial sums are added in index order by ig_sum_kernel.
 //
-// A workgroup (4 waves, two workgroups per CU) owns 128 m x 128 j (or 64 x 256), a wave 64 x 64; a step contracts 64
+// A workgroup (4 waves, two workgroups per CU) owns 128 m x 128 j (or 64 x 256, 32 x 256), a wave 64 x 64; a step contracts 64
 // channels of one tap: rows of 128 bytes of weights and activations are fetched with direct-to-LDS loads (the range check
 // of the buffer supplies the zero padding), double buffered.  The piece a lane fetches is permuted inside its row so
 // that the 16-byte fragment reads of neighbouring rows fall into different banks.
@@ -16,7 +16,9 @@
 // Bound: 1 KB of fragment reads per MFMA is what the LDS delivers at 64 % of the MFMA rate; on the smallest volumes the
 // weights' way from HBM and the launches.  Forward / data gradient with their packing and summing launches, former
 // chunked kernels -> this one: 128->256 at 48^3, stride 2, N = 2 112 / 301 -> 62 / 70 us (794 / 698 TFLOP/s), 64->128 at
-// 96^3, stride 2, N = 2 260 / 551 -> 142 / 204, 320->320 at 12^3 74 / 74 -> 32 / 37, 256->256 at 24^3 101 / 101 -> 69 / 72.
+// 96^3, stride 2, N = 2 260 / 551 -> 142 / 204, 320->320 at 12^3 74 / 74 -> 30 / 30, 256->256 at 24^3 101 / 101 -> 69 / 69.
+// Measured and left out: a ring of 32-channel steps (rows of 64 bytes; 48^3 60 -> 67, 12^3 30 -> 35), deeper rings, fragments read a
+// product ahead, and 128 x 256 tiles on eight waves (no change): fragment reads and the loads' way into LDS are the bound.
 #include <cstdio>
 
 #include "ig_common.h"
