@@ -50,9 +50,10 @@ __device__ __forceinline__ u32x4 make_rsrc(const void* p, unsigned bytes) {
     return u32x4{(unsigned)b, (unsigned)(b >> 32) & 0xffffu, bytes, 0x00020000u};
 }
 // One direct-to-LDS load: lane l moves the 16 bytes at byte offset voff (its own) of the buffer to LDS address
-// lds_addr + 16 l (lds_addr uniform).  Counts in vmcnt like any vector-memory load.
+// lds_addr + 16 l (lds_addr uniform).  Counts in vmcnt like any vector-memory load.  (s_nop: M0 is taken one wait state after it
+// is written, which the compiler does not see to inside an asm block.)
 __device__ __forceinline__ void dma16(u32x4 rsrc, unsigned lds_addr, int voff) {
-    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_addr), "v"(voff), "s"(rsrc) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_addr), "v"(voff), "s"(rsrc) : "memory", "m0");
 }
 
 struct Wg2Params {

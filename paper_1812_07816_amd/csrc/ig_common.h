@@ -58,9 +58,10 @@ __device__ __forceinline__ bf16x8 tr_frag(const char* p, int row_bytes) {
 }
 
 // 16 bytes per lane from buffer r at byte offset off (zeros beyond its range) to the wave's 1 KB at LDS byte l.  Inline assembly:
-// behind the builtin the compiler waits for all loads before every transposing LDS read.
+// behind the builtin the compiler waits for all loads before every transposing LDS read.  A load to LDS takes M0 one wait state after
+// a scalar instruction has written it: the compiler puts that in behind its builtin, inside an asm block nobody does.
 __device__ __forceinline__ void load_lds_asm(__amdgpu_buffer_rsrc_t r, unsigned l, unsigned off) {
-    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(l), "v"(off), "s"(r) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(l), "v"(off), "s"(r) : "memory", "m0");
 }
 
 }  // namespace mi3d
