@@ -20,7 +20,9 @@ enum State { ST_NEW = 0, ST_OUT_ISSUED, ST_HOST, ST_IN_ISSUED, ST_BACK, ST_DONE 
 
 struct Copy {
     hipEvent_t start = nullptr, done = nullptr;
+    hipEvent_t summed = nullptr;    // behind the checksum that follows the copy (checksum mode)
     bool issued = false;
+    hipEvent_t end() const { return summed ? summed : done; }
 };
 
 struct Tensor {
@@ -177,16 +179,11 @@ void release_streams(mi3d_swap_engine* e) {
     (void)hipStreamDestroy(s.in);
 }
 
-// All copies of this engine have ended (those of others may still be under way, unless one of its own is waited for)
+// All copies of this engine have ended, with their checksums.  Others use the streams too: it waits for events of its own.
 int wait_for_copies(mi3d_swap_engine* e) {
-    bool out = e->verify, in = e->verify;      // (a checksum follows its copy's event)
-    for (auto& kv : e->tensors) {
-        const Tensor& t = kv.second;
-        out = out || (t.out.issued && hipEventQuery(t.out.done) != hipSuccess);
-        in = in || (t.in.issued && hipEventQuery(t.in.done) != hipSuccess);
-    }
-    if (out) HIP_TRY(hipStreamSynchronize(e->s_out));
-    if (in) HIP_TRY(hipStreamSynchronize(e->s_in));
+    for (auto& kv : e->tensors)
+        for (const Copy* c : {&kv.second.out, &kv.second.in})
+            if (c->issued && hipEventQuery(c->end()) != hipSuccess) HIP_TRY(hipEventSynchronize(c->end()));
     return MI3D_OK;
 }
 
@@ -290,6 +287,7 @@ void reset_step_state(mi3d_swap_engine* e) {
         for (Copy* c : {&t.out, &t.in}) {
             if (c->start) e->free_events_timed.push_back(c->start);
             if (c->done) e->free_events_timed.push_back(c->done);
+            if (c->summed) e->free_events_plain.push_back(c->summed);
             *c = Copy();
         }
         t.state = ST_NEW;
@@ -723,6 +721,8 @@ int mi3d_swap_in(mi3d_swap_engine* e, int id, void* dev_dst, void* consumer_stre
         auto it = e->sum_slot.find(id);
         if (it == e->sum_slot.end()) return MI3D_ERR_BAD_STATE;
         if ((st = enqueue_checksum(dev_dst, t->plan.bytes, e->sums_scratch + CK_BLOCKS, e->sums_host + 2 * it->second + 1, e->s_in))) return st;
+        if ((st = get_event(e, false, &t->in.summed))) return st;
+        HIP_TRY(hipEventRecord(t->in.summed, e->s_in));
     }
 #endif
     t->in.issued = true;

@@ -225,6 +225,51 @@ static void test_reset_returns_blocks_of_a_step_that_ended_early() {
     CHECK(mi3d_swap_destroy(e) == MI3D_OK);
 }
 
+// n tensors of 1 KiB out of an arena, all swapped
+struct Small {
+    std::vector<unsigned char> backing;
+    mi3d_swap_engine* e;
+    explicit Small(int n) : backing((size_t)n * 1024 + 256) {
+        e = make(1 << 20, (void*)(((uintptr_t)backing.data() + 255) & ~(uintptr_t)255), (size_t)n * 1024, (size_t)n * 4096 + 4096, MI3D_SWAP_ALL);
+        chain(e, std::vector<size_t>(n, 1024));
+        CHECK(mi3d_swap_plan(e) == MI3D_OK);
+    }
+    void* out(int id, hipStream_t s) {
+        void* p = nullptr;
+        CHECK(mi3d_swap_alloc(e, 1024, s, &p) == MI3D_OK && mi3d_swap_out(e, id, p, s) == MI3D_OK && mi3d_swap_release(e, id, s) == MI3D_OK);
+        return p;
+    }
+    void back(int id, hipStream_t s) {
+        void* p = nullptr;
+        CHECK(mi3d_swap_alloc(e, 1024, s, &p) == MI3D_OK && mi3d_swap_in(e, id, p, s) == MI3D_OK && mi3d_swap_wait_in(e, id, s) == MI3D_OK);
+        CHECK(mi3d_swap_done(e, id) == MI3D_OK && mi3d_swap_free(e, p, s) == MI3D_OK);
+    }
+};
+
+static hipStream_t stream_of_caller() {
+    hipStream_t s = nullptr;
+    CHECK(hipStreamCreateWithFlags(&s, 0) == hipSuccess);
+    return s;
+}
+
+static void test_an_engine_waits_for_its_own_copies_only() {
+    hipStream_t s = stream_of_caller();
+    Small a(2), b(2);
+    hipstub_hold_events() = true;             // its own copies are under way for a while
+    a.out(0, s); a.back(0, s);
+    hipstub_hold_events() = false;
+    hipstub_stall(s);                         // behind this the caller's stream stands still ...
+    b.out(0, s);                              // ... and with it the other engine's copy
+    mi3d_swap_stats_t st;
+    CHECK(mi3d_swap_sync(a.e) == MI3D_OK && mi3d_swap_stats(a.e, &st) == MI3D_OK && mi3d_swap_reset_step(a.e) == MI3D_OK);
+    CHECK(mi3d_swap_destroy(a.e) == MI3D_OK);
+    CHECK(hipstub_hangs() == 0);
+    hipstub_unstall(s);
+    CHECK(mi3d_swap_destroy(b.e) == MI3D_OK);
+    (void)hipStreamDestroy(s);
+    hipstub_hangs() = 0;
+}
+
 static void test_argument_checks() {
     mi3d_swap_engine* e = nullptr;
     mi3d_swap_config c;
@@ -259,6 +304,7 @@ int main() {
     test_free_space_behind_a_copy_merges_when_nothing_else_fits();
     test_planned_places_are_handed_out_and_reused_behind_a_copy();
     test_reset_returns_blocks_of_a_step_that_ended_early();
+    test_an_engine_waits_for_its_own_copies_only();
     test_argument_checks();
     CHECK(hipstub_live_objects() == 0);   // every stream, event and pinned allocation was given back
     if (failures) { std::printf("%d check(s) failed\n", failures); return 1; }

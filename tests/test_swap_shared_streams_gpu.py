@@ -84,3 +84,22 @@ def test_engines_of_several_threads(device):
     for t in threads:
         t.join()
     assert ok == [6, 6, 6]
+
+
+def test_checksums_still_under_way_when_the_mode_is_switched_off(device):
+    """The checksum of a swapped-in tensor runs behind the copy that the caller waits for."""
+    src = [torch.arange(64 << 20, device="cuda", dtype=torch.int32)]
+    e = _engine([src[0].numel() * 4])
+    for _ in range(3):
+        e.reset_step()
+        e.set_verify(True)
+        _out(e, src)
+        back = torch.empty_like(src[0])
+        e.swap_in(0, back.data_ptr())
+        e.wait_in(0)
+        torch.cuda.current_stream().synchronize()     # the copy has landed
+        e.set_verify(False)
+        st = e.stats()
+        assert (st["n_checksummed"], st["n_checksum_mismatch"]) == (1, 0)
+        assert torch.equal(back, src[0])
+    e.close()
