@@ -108,6 +108,7 @@ struct mi3d_swap_engine {
     char* host_pool = nullptr;
     hipStream_t s_out = nullptr, s_in = nullptr;
     hipEvent_t base = nullptr;
+    bool untracked = false;   // a copy was enqueued without the event behind it
     std::vector<hipEvent_t> free_events_timed, free_events_plain;
 
     std::vector<ArenaBlock> blocks;
@@ -179,13 +180,29 @@ void release_streams(mi3d_swap_engine* e) {
     (void)hipStreamDestroy(s.in);
 }
 
-// All copies of this engine have ended, with their checksums.  Others use the streams too: it waits for events of its own.
+// All copies of this engine have ended, with their checksums.  Others use the streams too: it waits for events of its own, and
+// for whole streams only where a copy that failed halfway left none.  An error does not keep it from waiting for the rest.
 int wait_for_copies(mi3d_swap_engine* e) {
+    hipError_t err = hipSuccess;
+    auto wait = [&](hipError_t r) { if (r != hipSuccess) err = r; };
     for (auto& kv : e->tensors)
         for (const Copy* c : {&kv.second.out, &kv.second.in})
-            if (c->issued && hipEventQuery(c->end()) != hipSuccess) HIP_TRY(hipEventSynchronize(c->end()));
+            if (c->issued && hipEventQuery(c->end()) != hipSuccess) wait(hipEventSynchronize(c->end()));
+    if (e->untracked) {
+        wait(hipStreamSynchronize(e->s_out));
+        wait(hipStreamSynchronize(e->s_in));
+    }
+    HIP_TRY(err);
+    e->untracked = false;
     return MI3D_OK;
 }
+
+// While a copy and its events are being enqueued: an early return leaves work that no event of the engine stands for
+struct Enqueueing {
+    mi3d_swap_engine* e;
+    bool complete = false;
+    ~Enqueueing() { if (!complete) e->untracked = true; }
+};
 
 int get_event(mi3d_swap_engine* e, bool timed, hipEvent_t* ev) {
     std::vector<hipEvent_t>& pool = timed ? e->free_events_timed : e->free_events_plain;
@@ -658,6 +675,7 @@ int mi3d_swap_out(mi3d_swap_engine* e, int id, const void* dev_src, void* produc
     int st = get_event(e, false, &dep);
     if (st) return st;
     HIP_TRY(hipEventRecord(dep, (hipStream_t)producer_stream));
+    Enqueueing work{e};
     HIP_TRY(hipStreamWaitEvent(e->s_out, dep, 0));
     e->free_events_plain.push_back(dep);  // the enqueued wait refers to the record above; the handle may be re-recorded
     if ((st = get_event(e, true, &t->out.start)) || (st = get_event(e, true, &t->out.done))) return st;
@@ -674,7 +692,7 @@ int mi3d_swap_out(mi3d_swap_engine* e, int id, const void* dev_src, void* produc
     HIP_TRY(hipEventRecord(t->out.start, e->s_out));
     HIP_TRY(hipMemcpyAsync(e->host_pool + t->plan.host_offset, dev_src, t->plan.bytes, hipMemcpyDeviceToHost, e->s_out));
     HIP_TRY(hipEventRecord(t->out.done, e->s_out));
-    t->out.issued = true;
+    t->out.issued = work.complete = true;
     t->dev_src = dev_src;
     t->state = ST_OUT_ISSUED;
     e->bytes_out += t->plan.bytes;
@@ -709,6 +727,7 @@ int mi3d_swap_in(mi3d_swap_engine* e, int id, void* dev_dst, void* consumer_stre
     int st = get_event(e, false, &dep);
     if (st) return st;
     HIP_TRY(hipEventRecord(dep, (hipStream_t)consumer_stream));
+    Enqueueing work{e};
     HIP_TRY(hipStreamWaitEvent(e->s_in, dep, 0));
     e->free_events_plain.push_back(dep);
     HIP_TRY(hipStreamWaitEvent(e->s_in, t->out.done, 0));  // the host copy must be complete
@@ -725,7 +744,7 @@ int mi3d_swap_in(mi3d_swap_engine* e, int id, void* dev_dst, void* consumer_stre
         HIP_TRY(hipEventRecord(t->in.summed, e->s_in));
     }
 #endif
-    t->in.issued = true;
+    t->in.issued = work.complete = true;
     t->state = ST_IN_ISSUED;
     e->bytes_in += t->plan.bytes;
     e->n_in++;

@@ -48,6 +48,8 @@ inline void hipstub_unstall(hipStream_t s) { for (hipstub_op& o : hipstub_ops()[
 inline int& hipstub_hangs() { static int n = 0; return n; }
 inline int& hipstub_fail_event_syncs() { static int n = 0; return n; }   // the next n waits for an event report an error
 inline int& hipstub_fail_event_records() { static int n = 0; return n; } // a record of an event fails when this counts down to zero
+inline int& hipstub_event_syncs() { static int n = 0; return n; }        // host calls that waited for an event ...
+inline int& hipstub_stream_syncs() { static int n = 0; return n; }       // ... and for a stream
 inline std::set<hipStream_t>& hipstub_streams() { static std::set<hipStream_t> s; return s; }   // created and not destroyed
 inline int& hipstub_live_objects() { static int n = 0; return n; }   // streams + events + host allocations not yet destroyed
 
@@ -62,6 +64,7 @@ inline hipError_t hipHostFree(void* p) { std::free(p); --hipstub_live_objects();
 inline hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = (hipStream_t)std::malloc(1); hipstub_streams().insert(*s); hipstub_ops()[*s].clear(); ++hipstub_live_objects(); return hipSuccess; }
 inline hipError_t hipStreamDestroy(hipStream_t s) { hipstub_streams().erase(s); std::free(s); --hipstub_live_objects(); return hipSuccess; }
 inline hipError_t hipStreamSynchronize(hipStream_t s) {
+    ++hipstub_stream_syncs();
     if (!hipstub_runs(s, hipstub_ops()[s].size())) ++hipstub_hangs();
     hipstub_fire_events();
     return hipSuccess;
@@ -85,9 +88,11 @@ inline hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
 }
 inline hipError_t hipEventQuery(hipEvent_t e) { return !e->recorded || (e->fired && hipstub_runs(e->stream, e->at)) ? hipSuccess : hipErrorNotReady; }
 inline hipError_t hipEventSynchronize(hipEvent_t e) {
+    ++hipstub_event_syncs();
     if (hipstub_fail_event_syncs()) { --hipstub_fail_event_syncs(); return hipErrorInvalidValue; }
     if (e->recorded && !hipstub_runs(e->stream, e->at)) ++hipstub_hangs();
-    hipstub_fire_events();
+    e->fired = true;
+    hipstub_pending().erase(e);
     return hipSuccess;
 }
 inline hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 0.f; return hipSuccess; }

@@ -270,6 +270,35 @@ static void test_an_engine_waits_for_its_own_copies_only() {
     hipstub_hangs() = 0;
 }
 
+static void test_destroy_waits_for_everything_in_spite_of_errors() {
+    hipStream_t s = stream_of_caller();
+    {
+        Small a(2);                           // the first of four waits reports an error: the others are waited for all the same
+        hipstub_hold_events() = true;
+        for (int i : {0, 1}) a.out(i, s);
+        for (int i : {1, 0}) a.back(i, s);
+        hipstub_hold_events() = false;
+        const int before = hipstub_event_syncs();
+        hipstub_fail_event_syncs() = 1;
+        CHECK(mi3d_swap_destroy(a.e) == MI3D_ERR_HIP);
+        CHECK(hipstub_event_syncs() - before == 4 && hipstub_fail_event_syncs() == 0);
+    }
+    for (bool in : {false, true}) {           // the event behind a copy fails: the copy is under way without one
+        Small a(1);
+        void* p = nullptr;
+        if (in) a.out(0, s);
+        CHECK(mi3d_swap_alloc(a.e, 1024, s, &p) == MI3D_OK);
+        hipstub_fail_event_records() = 3;     // behind the one the copy waits for and the one before it
+        CHECK((in ? mi3d_swap_in(a.e, 0, p, s) : mi3d_swap_out(a.e, 0, p, s)) == MI3D_ERR_HIP);
+        const int before = hipstub_stream_syncs();
+        CHECK(mi3d_swap_sync(a.e) == MI3D_OK && hipstub_stream_syncs() - before >= 2);
+        CHECK(mi3d_swap_sync(a.e) == MI3D_OK && hipstub_stream_syncs() - before == 2);   // (once)
+        CHECK(mi3d_swap_destroy(a.e) == MI3D_OK);
+    }
+    hipstub_fire_events();
+    (void)hipStreamDestroy(s);
+}
+
 static void test_argument_checks() {
     mi3d_swap_engine* e = nullptr;
     mi3d_swap_config c;
@@ -305,6 +334,7 @@ int main() {
     test_planned_places_are_handed_out_and_reused_behind_a_copy();
     test_reset_returns_blocks_of_a_step_that_ended_early();
     test_an_engine_waits_for_its_own_copies_only();
+    test_destroy_waits_for_everything_in_spite_of_errors();
     test_argument_checks();
     CHECK(hipstub_live_objects() == 0);   // every stream, event and pinned allocation was given back
     if (failures) { std::printf("%d check(s) failed\n", failures); return 1; }
