@@ -408,10 +408,13 @@ typedef struct {
 typedef struct mi3d_swap_engine mi3d_swap_engine;
 
 /* Creates an engine on the current device.  With host_pool_bytes > 0 it
- * allocates that much pinned host memory and two side streams (one per copy
- * direction, default priority).  Returns MI3D_ERR_HIP if that fails. */
+ * allocates that much pinned host memory and uses two side streams (one per
+ * copy direction, default priority).  Engines whose copies follow the same
+ * compute stream (the streams passed to mi3d_swap_out and mi3d_swap_in) share
+ * a pair; an engine never waits for copies that follow another one.  Returns
+ * MI3D_ERR_HIP if an allocation or a stream fails. */
 int mi3d_swap_create(const mi3d_swap_config *cfg, mi3d_swap_engine **out);
-/* Waits for outstanding copies, frees the pool, streams and events. */
+/* Waits for the engine's outstanding copies, frees the pool, events and, with their last user, the streams. */
 int mi3d_swap_destroy(mi3d_swap_engine *e);
 
 /* Ops 0..n_fwd_ops-1 are the forward pass, n_fwd_ops..n_ops-1 the backward pass. */

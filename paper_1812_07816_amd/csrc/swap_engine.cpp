@@ -1,5 +1,5 @@
 // Run-time half of the data-swapping engine (Sections 3.1 and 3.3): pinned
-// host pool, one side stream per copy direction and device, events that order copies
+// host pool, side streams for the copies of either direction, events that order copies
 // against the compute stream, an event-aware device arena, and counters.
 #include <algorithm>
 #include <cstring>
@@ -25,12 +25,15 @@ struct Copy {
     hipEvent_t end() const { return summed ? summed : done; }
 };
 
+struct CopyStreams;
+
 struct Tensor {
     PlanTensor plan;
     int allocs = 0;     // placements handed out by mi3d_swap_alloc_tensor in this step (0: first stay, 1: second)
     State state = ST_NEW;
     const void* dev_src = nullptr;
     Copy out, in;
+    std::shared_ptr<void> left;   // event behind the swap-out of an arena block, for the block (which can keep it longer than the step)
 };
 
 // An event a freed block waits for.  copy: recorded on one of the engine's copy streams (behind a swap-out that
@@ -106,8 +109,9 @@ struct mi3d_swap_engine {
     bool live = false;  // owns HIP objects
     int device = 0;
     char* host_pool = nullptr;
-    hipStream_t s_out = nullptr, s_in = nullptr;
-    hipEvent_t base = nullptr;
+    CopyStreams* streams = nullptr;    // of its copies from now on
+    CopyStreams* former = nullptr;     // of copies of this step before it got a pair of its own
+    hipEvent_t base = nullptr;         // before the first copy of a step
     bool untracked = false;   // a copy was enqueued without the event behind it
     std::vector<hipEvent_t> free_events_timed, free_events_plain;
 
@@ -142,42 +146,101 @@ namespace {
         }                                     \
     } while (0)
 
-// The copy streams of a device, one per direction, shared by all its engines and destroyed with the last of them.  The
-// runtime deals streams out to a few hardware queues (4): with a pair per engine a third engine's copies came to share the
-// queue of the compute stream, where a copy that waits for an event holds up every kernel behind it (fp32 step at 128^3,
-// N = 2, under a budget, three engines in turn: 40, 40 and 75 ms a pass; sharing: 40 each).  Engines share the link anyway.
-// Whatever waits on these streams waits for work enqueued before it, so engines cannot wait for each other in a circle.
+// A pair of copy streams, one per direction, shared by the engines of a device that work for the same compute stream and
+// destroyed with the last of them.  The runtime deals streams out to a few hardware queues (4): with a pair per engine a
+// third engine's copies came to share the queue of the compute stream, where a copy that waits for an event holds up every
+// kernel behind it (fp32 step at 128^3, N = 2, under a budget, three engines in turn on one stream: 40, 40 and 75 ms a pass;
+// sharing: 40 each).  Engines share the link anyway.
+// Sharing holds nobody up: a copy waits for what its compute stream held when the copy was enqueued, and whatever lies before
+// it on the copy stream waits for something earlier on the same compute stream (`order` keeps the two orders alike where
+// several threads use one stream).  A copy behind another compute stream's could wait for work that itself waits for
+// that copy, so other compute streams have other pairs, and an engine whose copies in one step follow several has its own.
 struct CopyStreams {
+    int device;
     hipStream_t out = nullptr, in = nullptr;
-    int users = 0;
+    bool bound = false;                // to a compute stream: the one of the first copy
+    void* compute = nullptr;
+    bool own = false;                  // of an engine that follows several compute streams
+    int users = 1;
+    std::mutex order;
 };
-std::mutex g_streams_mutex;
-std::map<int, CopyStreams> g_streams;
+std::mutex g_streams_mutex;                 // guards the list and all members but the streams and `order`
+std::vector<CopyStreams*> g_streams;
 
-hipError_t acquire_streams(mi3d_swap_engine* e) {
-    std::lock_guard<std::mutex> lock(g_streams_mutex);
-    CopyStreams& s = g_streams[e->device];
-    if (s.users == 0) {
-        hipError_t err = hipStreamCreateWithFlags(&s.out, hipStreamNonBlocking);
-        if (err != hipSuccess) return err;
-        err = hipStreamCreateWithFlags(&s.in, hipStreamNonBlocking);
-        if (err != hipSuccess) {
-            (void)hipStreamDestroy(s.out);
-            return err;
-        }
+hipError_t create_streams(int device, CopyStreams** out) {
+    CopyStreams* s = new (std::nothrow) CopyStreams;
+    if (!s) return hipErrorOutOfMemory;
+    s->device = device;
+    hipError_t err = hipStreamCreateWithFlags(&s->out, hipStreamNonBlocking);
+    if (err == hipSuccess) {
+        err = hipStreamCreateWithFlags(&s->in, hipStreamNonBlocking);
+        if (err != hipSuccess) (void)hipStreamDestroy(s->out);
     }
-    ++s.users;
-    e->s_out = s.out;
-    e->s_in = s.in;
+    if (err != hipSuccess) {
+        delete s;
+        return err;
+    }
+    g_streams.push_back(s);
+    *out = s;
     return hipSuccess;
 }
 
-void release_streams(mi3d_swap_engine* e) {
+void release_streams(CopyStreams* s) {
+    if (--s->users) return;
+    g_streams.erase(std::find(g_streams.begin(), g_streams.end(), s));
+    (void)hipStreamDestroy(s->out);
+    (void)hipStreamDestroy(s->in);
+    delete s;
+}
+
+// For a new engine: a pair of its device, to be exchanged at the first copy if that follows another compute stream
+hipError_t first_streams(mi3d_swap_engine* e) {
     std::lock_guard<std::mutex> lock(g_streams_mutex);
-    CopyStreams& s = g_streams[e->device];
-    if (--s.users) return;
-    (void)hipStreamDestroy(s.out);
-    (void)hipStreamDestroy(s.in);
+    for (CopyStreams* s : g_streams)
+        if (s->device == e->device && !s->own) {
+            ++s->users;
+            e->streams = s;
+            return hipSuccess;
+        }
+    return create_streams(e->device, &e->streams);
+}
+
+// e->streams becomes the pair for copies that follow `compute`
+int follow(mi3d_swap_engine* e, void* compute) {
+    std::lock_guard<std::mutex> lock(g_streams_mutex);
+    CopyStreams* s = e->streams;
+    const bool several = compute == (void*)hipStreamPerThread;    // (one handle for a stream of every thread)
+    if (s->own || (s->bound && s->compute == compute && !several)) return MI3D_OK;
+    if (!several && !e->n_out && !e->n_in && !e->untracked) {     // no copy under way: the engine may move
+        for (CopyStreams* q : g_streams)
+            if (q->device == e->device && !q->own && q->bound && q->compute == compute) {
+                ++q->users;
+                release_streams(s);
+                e->streams = q;
+                return MI3D_OK;
+            }
+        if (s->bound && s->users > 1) {
+            HIP_TRY(create_streams(e->device, &e->streams));
+            release_streams(s);
+        }
+        e->streams->bound = true;
+        e->streams->compute = compute;
+        return MI3D_OK;
+    }
+    CopyStreams* q;
+    HIP_TRY(create_streams(e->device, &q));
+    q->own = true;
+    // the copies so far stay in front, as on one stream (they share the scratch of the checksums)
+    hipError_t err = hipSuccess;
+    for (auto& kv : e->tensors) {
+        const Copy &o = kv.second.out, &i = kv.second.in;
+        if (err == hipSuccess && o.issued) err = hipStreamWaitEvent(q->out, o.end(), 0);
+        if (err == hipSuccess && i.issued) err = hipStreamWaitEvent(q->in, i.end(), 0);
+    }
+    e->streams = q;
+    e->former = s;
+    HIP_TRY(err);
+    return MI3D_OK;
 }
 
 // All copies of this engine have ended, with their checksums.  Others use the streams too: it waits for events of its own, and
@@ -188,12 +251,18 @@ int wait_for_copies(mi3d_swap_engine* e) {
     for (auto& kv : e->tensors)
         for (const Copy* c : {&kv.second.out, &kv.second.in})
             if (c->issued && hipEventQuery(c->end()) != hipSuccess) wait(hipEventSynchronize(c->end()));
-    if (e->untracked) {
-        wait(hipStreamSynchronize(e->s_out));
-        wait(hipStreamSynchronize(e->s_in));
-    }
+    for (const CopyStreams* s : {e->streams, e->former})
+        if (s && e->untracked) {
+            wait(hipStreamSynchronize(s->out));
+            wait(hipStreamSynchronize(s->in));
+        }
     HIP_TRY(err);
     e->untracked = false;
+    if (e->former) {
+        std::lock_guard<std::mutex> lock(g_streams_mutex);
+        release_streams(e->former);
+        e->former = nullptr;
+    }
     return MI3D_OK;
 }
 
@@ -309,6 +378,7 @@ void reset_step_state(mi3d_swap_engine* e) {
         }
         t.state = ST_NEW;
         t.dev_src = nullptr;
+        t.left.reset();
         t.allocs = 0;
     }
     e->bytes_out = e->bytes_in = 0;
@@ -336,13 +406,15 @@ int mi3d_swap_create(const mi3d_swap_config* cfg, mi3d_swap_engine** out) {
         if (err == hipSuccess) err = hipHostMalloc((void**)&e->host_pool, cfg->host_pool_bytes, hipHostMallocDefault);
         // touch every page once: the first DMA into untouched pinned pages runs at a fraction of link speed
         if (err == hipSuccess) memset(e->host_pool, 0, cfg->host_pool_bytes);
-        if (err == hipSuccess) err = acquire_streams(e);
+        if (err == hipSuccess) err = first_streams(e);
         if (err == hipSuccess) err = hipEventCreate(&e->base);
-        if (err == hipSuccess) err = hipEventRecord(e->base, e->s_out);
         if (err != hipSuccess) {
             note_hip_error(err);
             if (e->base) (void)hipEventDestroy(e->base);
-            if (e->s_out) release_streams(e);
+            if (e->streams) {
+                std::lock_guard<std::mutex> lock(g_streams_mutex);
+                release_streams(e->streams);
+            }
             if (e->host_pool) (void)hipHostFree(e->host_pool);
             delete e;
             return MI3D_ERR_HIP;
@@ -368,7 +440,11 @@ int mi3d_swap_destroy(mi3d_swap_engine* e) {
 #endif
     if (e->live) {
         (void)hipEventDestroy(e->base);
-        release_streams(e);
+        {
+            std::lock_guard<std::mutex> lock(g_streams_mutex);
+            for (CopyStreams* s : {e->streams, e->former})
+                if (s) release_streams(s);
+        }
         (void)hipHostFree(e->host_pool);
     }
     delete e;
@@ -672,11 +748,14 @@ int mi3d_swap_out(mi3d_swap_engine* e, int id, const void* dev_src, void* produc
     if (!t || !e->have_plan || !t->plan.planned || t->state != ST_NEW || !e->live) return MI3D_ERR_BAD_STATE;
     if (t->plan.host_offset + t->plan.bytes > e->cfg.host_pool_bytes) return MI3D_ERR_HOST_POOL;
     hipEvent_t dep;
-    int st = get_event(e, false, &dep);
-    if (st) return st;
+    int st = follow(e, producer_stream);
+    if (st || (st = get_event(e, false, &dep))) return st;
+    std::lock_guard<std::mutex> lock(e->streams->order);
     HIP_TRY(hipEventRecord(dep, (hipStream_t)producer_stream));
+    const hipStream_t s_out = e->streams->out;
     Enqueueing work{e};
-    HIP_TRY(hipStreamWaitEvent(e->s_out, dep, 0));
+    if (!e->n_out) HIP_TRY(hipEventRecord(e->base, s_out));
+    HIP_TRY(hipStreamWaitEvent(s_out, dep, 0));
     e->free_events_plain.push_back(dep);  // the enqueued wait refers to the record above; the handle may be re-recorded
     if ((st = get_event(e, true, &t->out.start)) || (st = get_event(e, true, &t->out.done))) return st;
 #if defined(__HIPCC__)
@@ -686,12 +765,13 @@ int mi3d_swap_out(mi3d_swap_engine* e, int id, const void* dev_src, void* produc
         e->sum_slot[id] = slot;
         e->sums_host[2 * slot] = 0;
         e->sums_host[2 * slot + 1] = 1;   // differs from the first word until the swap-in has been checked
-        if ((st = enqueue_checksum(dev_src, t->plan.bytes, e->sums_scratch, e->sums_host + 2 * slot, e->s_out))) return st;
+        if ((st = enqueue_checksum(dev_src, t->plan.bytes, e->sums_scratch, e->sums_host + 2 * slot, s_out))) return st;
     }
 #endif
-    HIP_TRY(hipEventRecord(t->out.start, e->s_out));
-    HIP_TRY(hipMemcpyAsync(e->host_pool + t->plan.host_offset, dev_src, t->plan.bytes, hipMemcpyDeviceToHost, e->s_out));
-    HIP_TRY(hipEventRecord(t->out.done, e->s_out));
+    HIP_TRY(hipEventRecord(t->out.start, s_out));
+    HIP_TRY(hipMemcpyAsync(e->host_pool + t->plan.host_offset, dev_src, t->plan.bytes, hipMemcpyDeviceToHost, s_out));
+    HIP_TRY(hipEventRecord(t->out.done, s_out));
+    if (in_arena(e, dev_src) && (st = record_shared(e, s_out, &t->left))) return st;
     t->out.issued = work.complete = true;
     t->dev_src = dev_src;
     t->state = ST_OUT_ISSUED;
@@ -705,14 +785,14 @@ int mi3d_swap_release(mi3d_swap_engine* e, int id, void* last_consumer_stream) {
     Tensor* t = find(e, id);
     if (!t || t->state != ST_OUT_ISSUED) return MI3D_ERR_BAD_STATE;
     if (in_arena(e, t->dev_src)) {
-        std::shared_ptr<void> consumer, copy;
+        std::shared_ptr<void> consumer;
         int st = record_shared(e, (hipStream_t)last_consumer_stream, &consumer);
         if (st) return st;
-        if ((st = record_shared(e, e->s_out, &copy))) return st;  // s_out is in order: fires after this tensor's copy
-        if ((st = arena_free(e, t->dev_src, {Pending{consumer, false}, Pending{copy, true}}))) return st;
+        if ((st = arena_free(e, t->dev_src, {Pending{consumer, false}, Pending{t->left, true}}))) return st;
     } else {
         HIP_TRY(hipStreamWaitEvent((hipStream_t)last_consumer_stream, t->out.done, 0));
     }
+    t->left.reset();
     t->dev_src = nullptr;
     t->state = ST_HOST;
     return MI3D_OK;
@@ -724,24 +804,26 @@ int mi3d_swap_in(mi3d_swap_engine* e, int id, void* dev_dst, void* consumer_stre
     if (!t || t->state != ST_HOST || !e->live) return MI3D_ERR_BAD_STATE;
     if (t->plan.host_offset + t->plan.bytes > e->cfg.host_pool_bytes) return MI3D_ERR_HOST_POOL;
     hipEvent_t dep;
-    int st = get_event(e, false, &dep);
-    if (st) return st;
+    int st = follow(e, consumer_stream);
+    if (st || (st = get_event(e, false, &dep))) return st;
+    std::lock_guard<std::mutex> lock(e->streams->order);
     HIP_TRY(hipEventRecord(dep, (hipStream_t)consumer_stream));
+    const hipStream_t s_in = e->streams->in;
     Enqueueing work{e};
-    HIP_TRY(hipStreamWaitEvent(e->s_in, dep, 0));
+    HIP_TRY(hipStreamWaitEvent(s_in, dep, 0));
     e->free_events_plain.push_back(dep);
-    HIP_TRY(hipStreamWaitEvent(e->s_in, t->out.done, 0));  // the host copy must be complete
+    HIP_TRY(hipStreamWaitEvent(s_in, t->out.done, 0));  // the host copy must be complete
     if ((st = get_event(e, true, &t->in.start)) || (st = get_event(e, true, &t->in.done))) return st;
-    HIP_TRY(hipEventRecord(t->in.start, e->s_in));
-    HIP_TRY(hipMemcpyAsync(dev_dst, e->host_pool + t->plan.host_offset, t->plan.bytes, hipMemcpyHostToDevice, e->s_in));
-    HIP_TRY(hipEventRecord(t->in.done, e->s_in));
+    HIP_TRY(hipEventRecord(t->in.start, s_in));
+    HIP_TRY(hipMemcpyAsync(dev_dst, e->host_pool + t->plan.host_offset, t->plan.bytes, hipMemcpyHostToDevice, s_in));
+    HIP_TRY(hipEventRecord(t->in.done, s_in));
 #if defined(__HIPCC__)
     if (e->verify) {   // what arrived back on the device (behind the done event: the consumer does not wait for it)
         auto it = e->sum_slot.find(id);
         if (it == e->sum_slot.end()) return MI3D_ERR_BAD_STATE;
-        if ((st = enqueue_checksum(dev_dst, t->plan.bytes, e->sums_scratch + CK_BLOCKS, e->sums_host + 2 * it->second + 1, e->s_in))) return st;
+        if ((st = enqueue_checksum(dev_dst, t->plan.bytes, e->sums_scratch + CK_BLOCKS, e->sums_host + 2 * it->second + 1, s_in))) return st;
         if ((st = get_event(e, false, &t->in.summed))) return st;
-        HIP_TRY(hipEventRecord(t->in.summed, e->s_in));
+        HIP_TRY(hipEventRecord(t->in.summed, s_in));
     }
 #endif
     t->in.issued = work.complete = true;
@@ -831,7 +913,6 @@ int mi3d_swap_reset_step(mi3d_swap_engine* e) {
         coalesce(e);
     }
     reset_step_state(e);
-    if (e->live) HIP_TRY(hipEventRecord(e->base, e->s_out));
     return MI3D_OK;
 }
 

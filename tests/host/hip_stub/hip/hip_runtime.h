@@ -20,8 +20,9 @@
 #define __launch_bounds__(...)
 
 typedef int hipError_t;
-enum { hipSuccess = 0, hipErrorNotReady = 600, hipErrorInvalidValue = 1 };
+enum { hipSuccess = 0, hipErrorNotReady = 600, hipErrorInvalidValue = 1, hipErrorOutOfMemory = 2 };
 typedef struct hipstub_stream* hipStream_t;
+#define hipStreamPerThread ((hipStream_t)2)
 struct hipstub_event { bool recorded = false; bool fired = false; hipStream_t stream = nullptr; size_t at = 0; };
 typedef hipstub_event* hipEvent_t;
 enum { hipHostMallocDefault = 0, hipStreamNonBlocking = 1, hipEventDefault = 0, hipEventDisableTiming = 2 };

@@ -299,6 +299,67 @@ static void test_destroy_waits_for_everything_in_spite_of_errors() {
     (void)hipStreamDestroy(s);
 }
 
+static void test_engines_of_one_compute_stream_share_and_others_do_not_wait_for_each_other() {
+    hipStream_t s = stream_of_caller(), other = stream_of_caller();
+    const size_t none = hipstub_streams().size();
+    {
+        Small a(2), b(2), c(2), d(2);
+        CHECK(hipstub_streams().size() == none + 2);           // one pair for all of them ...
+        a.out(0, s); b.out(0, s);
+        CHECK(hipstub_streams().size() == none + 2);
+        hipstub_stall(s);
+        a.out(1, s);                                           // stands still with its compute stream
+        c.out(0, other); c.out(1, other);                      // ... until one follows another compute stream
+        d.out(0, other);
+        CHECK(hipstub_streams().size() == none + 4);
+        c.back(1, other); c.back(0, other);
+        mi3d_swap_stats_t st;
+        CHECK(mi3d_swap_stats(c.e, &st) == MI3D_OK && st.n_swapped_in == 2 && mi3d_swap_reset_step(c.e) == MI3D_OK);
+        d.back(0, other);
+        CHECK(mi3d_swap_destroy(d.e) == MI3D_OK);
+        CHECK(hipstub_hangs() == 0);                           // nobody waited for the stalled stream
+        hipstub_unstall(s);
+        b.back(0, s);
+        CHECK(mi3d_swap_reset_step(b.e) == MI3D_OK);
+        b.out(0, other); b.back(0, other);                     // a later step may follow the other stream: it shares that pair then
+        CHECK(hipstub_streams().size() == none + 4);
+        CHECK(mi3d_swap_destroy(c.e) == MI3D_OK && mi3d_swap_destroy(b.e) == MI3D_OK);
+        CHECK(hipstub_streams().size() == none + 2);
+        a.back(1, s); a.back(0, s);
+        CHECK(mi3d_swap_reset_step(a.e) == MI3D_OK);
+        a.out(0, other);                                       // alone: the pair moves with it
+        CHECK(hipstub_streams().size() == none + 2);
+        CHECK(mi3d_swap_destroy(a.e) == MI3D_OK);
+    }
+    {
+        Small a(3), b(2);                                      // one step on two compute streams: a pair of its own from the second on
+        a.out(0, s); b.out(0, s);
+        hipstub_stall(s);
+        b.out(1, s);
+        a.out(1, other);
+        CHECK(hipstub_streams().size() == none + 4);
+        a.out(2, s);                                           // (waits for its compute stream, and what it enqueues next for this copy)
+        a.back(0, other);
+        CHECK(mi3d_swap_sync(b.e) == MI3D_OK && hipstub_hangs() == 1);   // b's own copy does stand still
+        hipstub_hangs() = 0;
+        hipstub_unstall(s);
+        a.back(1, other); a.back(2, s);
+        CHECK(mi3d_swap_reset_step(a.e) == MI3D_OK && hipstub_streams().size() == none + 4);
+        a.out(0, s); a.back(0, s);                             // it keeps that pair
+        CHECK(mi3d_swap_destroy(a.e) == MI3D_OK && mi3d_swap_destroy(b.e) == MI3D_OK);
+    }
+    {
+        Small a(1), b(1);                                      // the handle that means another stream in every thread is shared with nobody
+        a.out(0, hipStreamPerThread); b.out(0, hipStreamPerThread);
+        CHECK(hipstub_streams().size() == none + 6);           // (the pair of the start is held as a's and b's former one)
+        CHECK(mi3d_swap_sync(a.e) == MI3D_OK && mi3d_swap_sync(b.e) == MI3D_OK && hipstub_streams().size() == none + 4);
+        CHECK(mi3d_swap_destroy(a.e) == MI3D_OK && mi3d_swap_destroy(b.e) == MI3D_OK);
+    }
+    CHECK(hipstub_streams().size() == none && hipstub_hangs() == 0);
+    (void)hipStreamDestroy(s);
+    (void)hipStreamDestroy(other);
+}
+
 static void test_argument_checks() {
     mi3d_swap_engine* e = nullptr;
     mi3d_swap_config c;
@@ -335,6 +396,7 @@ int main() {
     test_reset_returns_blocks_of_a_step_that_ended_early();
     test_an_engine_waits_for_its_own_copies_only();
     test_destroy_waits_for_everything_in_spite_of_errors();
+    test_engines_of_one_compute_stream_share_and_others_do_not_wait_for_each_other();
     test_argument_checks();
     CHECK(hipstub_live_objects() == 0);   // every stream, event and pinned allocation was given back
     if (failures) { std::printf("%d check(s) failed\n", failures); return 1; }

@@ -1,4 +1,4 @@
-"""Engines of a device share one copy stream per direction: round trips that overlap in time, from one thread and from several,
+"""Engines that follow the same compute stream share one copy stream per direction: round trips that overlap in time, from one thread and from several,
 and an engine that goes away while another one's copies are under way."""
 import threading
 
