@@ -82,8 +82,10 @@ int mi3d_conv3d_out_dims(const mi3d_conv_desc *desc, int *Do, int *Ho, int *Wo);
  *
  * A call with less, down to mi3d_conv3d_min_workspace_bytes, is served too, by a slower kernel: fp32 layers by the fp32
  * matrix instructions (the smallest ones need none of it and run as they are), deep bf16 layers and weight gradients over
- * numbered positions with a contraction in fewer parts, channel counts that are not multiples of 32 (or of 8 by 3x3x3) by
- * the plain kernels (150 times slower on large volumes).  The sums are then formed in another order, so the bits of a
+ * numbered positions with a contraction in fewer parts, channel counts that are padded to multiples of 32 by the plain
+ * kernels (150 times slower on large volumes).  3x3x3 layers with channels in multiples of 8 are read as they are (forward
+ * pass and data gradient from 1024 output voxels): of those only the data gradient needs room, for a copy of its weights,
+ * and goes to the plain kernel below that.  The sums are then formed in another order, so the bits of a
  * result depend on the size of the workspace; with the same size repeated calls give identical bits.  Below the minimum
  * a call returns MI3D_ERR_WORKSPACE and launches nothing.  The entry points with statistics or sums
  * (mi3d_conv3d_fwd_stats, mi3d_conv3d_dgrad_insums) need the full size. */
@@ -227,8 +229,10 @@ int mi3d_conv3d_dgrad_lrelu(const mi3d_conv_desc *desc, const void *dy, const vo
 
 /* Writes the name of the kernel family the dispatcher routes this geometry and pass to (for reports and tests).  A
  * family can hold several device kernels: "mfma_plane_stream", "mfma_stride2_plane_stream" and
- * "mfma_dgrad_stride2_parity" run small volumes and many channels as an implicit GEMM, "mfma_f32_gather" forms its
- * products with the fp32 or the bf16 matrix instructions. */
+ * "mfma_dgrad_stride2_parity" run small volumes and many channels as an implicit GEMM, "mfma_wgrad_plane_stream" and
+ * "mfma_wgrad_stride2" as a product over numbered positions, "mfma_via_channel_padding" takes channels in multiples of 8
+ * without padding where it can, "mfma_f32_gather" forms its products with the fp32 or the bf16 matrix instructions or, in
+ * the smallest layers, without either.  mi3d_conv3d_kernel_detail tells them apart. */
 int mi3d_conv3d_kernel_name(const mi3d_conv_desc *desc, int pass, char *buf, size_t buf_len);
 
 /* The device kernel that forms the products of a call with ws_bytes of workspace, with the embeddings that lead to it

@@ -59,7 +59,7 @@ static bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 enum Kernel {
     K_DIRECT = 0, K_SP, K_WGRAD_MFMA, K_S2_FWD, K_WGRAD_S2, K_DGRAD_S2, K_C4_FWD, K_C4_DGRAD, K_C4_WGRAD, K_POINTWISE,
-    K_EMBED_C, K_EMBED_S, K_EMBED_K2, K_K2, K_F32
+    K_RAGGED, K_EMBED_C, K_EMBED_S, K_EMBED_K2, K_K2, K_F32
 };
 
 static Kernel choose(const Geom& g, int pass) {
@@ -74,6 +74,7 @@ static Kernel choose(const Geom& g, int pass) {
     if (pass == MI3D_PASS_DGRAD && c4_dgrad_supported(g)) return K_C4_DGRAD;
     if (pass == MI3D_PASS_WGRAD && c4_wgrad_supported(g)) return K_C4_WGRAD;
     if (k2_supported(g, pass)) return K_K2;
+    if (ragged_supported(g, pass)) return K_RAGGED;
     if (embed_c_supported(g, pass)) return K_EMBED_C;
     if (embed_s_supported(g, pass)) return K_EMBED_S;
     if (embed_k2_supported(g, pass)) return K_EMBED_K2;
@@ -92,7 +93,7 @@ static const char* kernel_name(Kernel k) {
         case K_C4_FWD: return "mfma_cin4_folded_taps";
         case K_C4_DGRAD: return "mfma_dgrad_cin4_folded_taps";
         case K_C4_WGRAD: return "mfma_wgrad_cin4_folded_taps";
-        case K_EMBED_C: return "mfma_via_channel_padding";
+        case K_RAGGED: case K_EMBED_C: return "mfma_via_channel_padding";
         case K_EMBED_S: return "mfma_via_unit_stride";
         case K_EMBED_K2: return "mfma_via_k3s2_embedding";
         case K_K2: return "mfma_k2s2_panel_gemm";
@@ -113,6 +114,7 @@ static size_t kernel_workspace(Kernel k, const Geom& g, int pass) {
         case K_C4_DGRAD: return c4_dgrad_workspace_bytes(g);
         case K_C4_WGRAD: return c4_wgrad_workspace_bytes(g);
         case K_POINTWISE: return pointwise_workspace_bytes(g, pass);
+        case K_RAGGED: return ragged_workspace_bytes(g, pass);
         case K_EMBED_C: return embed_c_workspace_bytes(g, pass);
         case K_EMBED_S: return embed_s_workspace_bytes(g, pass);
         case K_EMBED_K2: return embed_k2_workspace_bytes(g, pass);
@@ -131,6 +133,7 @@ static size_t kernel_min_workspace(Kernel k, const Geom& g, int pass) {
         case K_WGRAD_S2: return wgrad_s2_min_workspace_bytes(g);
         case K_S2_FWD: return s2_fwd_min_workspace_bytes(g);
         case K_DGRAD_S2: return dgrad_s2_min_workspace_bytes(g);
+        case K_RAGGED: return ragged_min_workspace_bytes(g, pass);
         case K_EMBED_C: return embed_c_min_workspace_bytes(g, pass);
         case K_EMBED_S: return embed_s_min_workspace_bytes(g, pass);
         case K_EMBED_K2: return embed_k2_min_workspace_bytes(g, pass);
@@ -139,12 +142,12 @@ static size_t kernel_min_workspace(Kernel k, const Geom& g, int pass) {
     }
 }
 
-// The kernel for a given workspace: a layer whose padded copies do not fit goes to the 3x3x3 embedding or to the plain
+// The kernel for a given workspace: a layer whose padded copies (or the copy of a ragged one's weights) do not fit goes to the 3x3x3 embedding or to the plain
 // kernel, which need none or little (the callers' size query reports what the padding wants; the static scratch has a
 // fixed size).
 static Kernel choose_within(const Geom& g, int pass, size_t ws_bytes) {
     const Kernel k = choose(g, pass);
-    if (k != K_EMBED_C || kernel_min_workspace(k, g, pass) <= ws_bytes) return k;
+    if ((k != K_EMBED_C && k != K_RAGGED) || kernel_min_workspace(k, g, pass) <= ws_bytes) return k;
     for (Kernel q : {K_EMBED_K2, K_DIRECT})
         if ((q == K_DIRECT || embed_k2_supported(g, pass)) && kernel_min_workspace(q, g, pass) <= ws_bytes) return q;
     return k;
@@ -166,6 +169,7 @@ static int run_kernel(Kernel k, const Geom& g, int pass, const void* a, const vo
         case K_C4_DGRAD: return c4_dgrad(g, a, b, out, ws, ws_bytes, s);
         case K_C4_WGRAD: return c4_wgrad(g, a, b, (float*)out, ws, ws_bytes, s);
         case K_POINTWISE: return pointwise_conv(g, pass, a, b, out, ws, ws_bytes, s);
+        case K_RAGGED: return ragged_conv(g, pass, a, b, out, ws, ws_bytes, s);
         case K_EMBED_C: return embed_c_conv(g, pass, a, b, out, ws, ws_bytes, s);
         case K_EMBED_S: return embed_s_conv(g, pass, a, b, out, ws, ws_bytes, s);
         case K_EMBED_K2: return embed_k2_conv(g, pass, a, b, out, ws, ws_bytes, s);
@@ -187,6 +191,7 @@ static std::string describe(Kernel k, const Geom& g, int pass, size_t ws_bytes) 
     }
     auto behind = [&](const char* how, const Geom& p) { return std::string(how) + " > " + describe(choose(p, pass), p, pass, rest); };
     switch (k) {
+        case K_RAGGED: ragged_describe(g, pass, ws_bytes, buf, sizeof(buf)); return buf;
         case K_EMBED_C: { const Geom p = embed_c_inner(g, pass, ws_bytes, &rest); return behind("padded_channels", p); }
         case K_EMBED_S: {
             const Geom p = embed_s_inner(g, ws_bytes, &rest);
@@ -307,7 +312,7 @@ size_t mi3d_conv3d_min_workspace_bytes(const mi3d_conv_desc* desc, int pass) {
     if (make_geom(desc, &g) || pass < 0 || pass > 2) return 0;
     const Kernel k = choose(g, pass);
     size_t b = kernel_min_workspace(k, g, pass);
-    if (k == K_EMBED_C) {
+    if (k == K_EMBED_C || k == K_RAGGED) {
         b = std::min(b, kernel_min_workspace(K_DIRECT, g, pass));
         if (embed_k2_supported(g, pass)) b = std::min(b, kernel_min_workspace(K_EMBED_K2, g, pass));
     }

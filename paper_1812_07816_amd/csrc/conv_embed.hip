@@ -284,9 +284,13 @@ size_t embed_c_min_workspace_bytes(const Geom& g, int pass) {
     return e.xb + e.yb + e.wb + auto_min_workspace_bytes(e.p, pass);
 }
 
-// Layers whose channels come in eights and that the kernels over numbered positions take as they are.
-static bool ragged_as_is(const Geom& g, int pass) {
-    if (g.Cin % 8 || g.Cout % 8 || g.kD != 3 || g.kH != 3 || g.kW != 3) return false;
+// ---- channel counts in eights that 32 does not divide ------------------------
+// 3x3x3 layers that the kernels over numbered positions take as they are, without copies of the operands (padded -> as they
+// are, 48 -> 48 at 37 x 50 x 61: 225 -> 124 us for the three passes); smaller volumes are padded.
+bool ragged_supported(const Geom& g, int pass) {
+    if (g.dtype != MI3D_BF16 || g.Cin % 8 || g.Cout % 8 || g.kD != 3 || g.kH != 3 || g.kW != 3) return false;
+    const Geom p = padded_geom(g, pass);
+    if ((p.Cin == g.Cin && p.Cout == g.Cout) || !auto_is_mfma(p, pass)) return false;
     if (pass == MI3D_PASS_WGRAD) return igw_supported(g);
     return ig_takes(g, pass) && g.out_voxels() >= 1024;
 }
@@ -294,8 +298,22 @@ static int weight_flag_words(const Geom& g, int pass) {
     return pass == MI3D_PASS_FWD ? (int)((g.w_elems() / 8 + 255) / 256) : 27 * ((g.Cin + 63) / 64) * ((g.Cout + 63) / 64);
 }
 
-// The layer as it is; its NaN are formed again like those of a padded one
-static int ragged_conv(const Geom& g, int pass, const void* a, const void* b, void* out, void* ws, size_t ws_bytes, hipStream_t s) {
+static size_t weight_flag_bytes(const Geom& g, int pass) { return pass == MI3D_PASS_WGRAD ? 0 : align256((size_t)weight_flag_words(g, pass) * 4); }
+
+size_t ragged_min_workspace_bytes(const Geom& g, int pass) { return pass == MI3D_PASS_WGRAD ? 0 : ig_min_workspace_bytes(g, pass); }
+size_t ragged_workspace_bytes(const Geom& g, int pass) { return pass == MI3D_PASS_WGRAD ? igw_workspace_bytes(g) : weight_flag_bytes(g, pass) + ig_workspace_bytes(g, pass); }
+// (less than the flags want on top of the least: every result is looked at)
+static size_t ragged_flags_within(const Geom& g, int pass, size_t ws_bytes) {
+    const size_t fb = weight_flag_bytes(g, pass);
+    return ws_bytes >= fb + ragged_min_workspace_bytes(g, pass) ? fb : 0;
+}
+void ragged_describe(const Geom& g, int pass, size_t ws_bytes, char* buf, size_t len) {
+    if (pass == MI3D_PASS_WGRAD) igw_describe(g, ws_bytes, buf, len);
+    else ig_describe(g, pass, ws_bytes - ragged_flags_within(g, pass, ws_bytes), buf, len);
+}
+
+// Its NaN are formed again like those of a padded layer
+int ragged_conv(const Geom& g, int pass, const void* a, const void* b, void* out, void* ws, size_t ws_bytes, hipStream_t s) {
     int st;
     if (pass == MI3D_PASS_WGRAD) {
         if ((st = igw_run(g, a, b, (float*)out, ws, ws_bytes, s))) return st;
@@ -303,13 +321,13 @@ static int ragged_conv(const Geom& g, int pass, const void* a, const void* b, vo
         return check_launch();
     }
     const int nflags = weight_flag_words(g, pass);
-    const size_t fb = align256((size_t)nflags * 4);
-    uint32_t* flags = ws_bytes >= fb + ig_min_workspace_bytes(g, pass) ? (uint32_t*)ws : nullptr;   // (no room: every result is looked at)
+    const size_t fb = ragged_flags_within(g, pass, ws_bytes);
+    uint32_t* flags = fb ? (uint32_t*)ws : nullptr;
     if (flags && pass == MI3D_PASS_FWD) {
         weight_flags_kernel<<<(unsigned)nflags, 256, 0, s>>>((const uint16_t*)b, g.w_elems() / 8, flags);
         if ((st = check_launch())) return st;
     }
-    if ((st = ig_conv(g, pass, a, b, out, (char*)ws + (flags ? fb : 0), ws_bytes - (flags ? fb : 0), s, flags))) return st;
+    if ((st = ig_conv(g, pass, a, b, out, (char*)ws + fb, ws_bytes - fb, s, flags))) return st;
     const long long n4 = (pass == MI3D_PASS_FWD ? g.out_voxels() * g.Cout : g.in_voxels() * g.Cin) / 4;
     exact_in_place_kernel<<<(unsigned)(n4 < 256 * 256 ? (n4 + 255) / 256 : 256), 256, 0, s>>>(g, pass, (const uint16_t*)a, (const uint16_t*)b, (uint16_t*)out, n4, flags, nflags);
     return check_launch();
@@ -328,7 +346,6 @@ Geom embed_c_inner(const Geom& g, int pass, size_t ws_bytes, size_t* rest) {
 // the plain kernels are left with the geometries no matrix-core kernel takes.
 int embed_c_conv(const Geom& g, int pass, const void* a, const void* b, void* out, void* ws, size_t ws_bytes, hipStream_t s) {
     if (ws_bytes < embed_c_min_workspace_bytes(g, pass)) return MI3D_ERR_WORKSPACE;
-    if (ragged_as_is(g, pass)) return ragged_conv(g, pass, a, b, out, ws, ws_bytes, s);
     EmbedC e = embed_c_layout(g, pass);
     if (ws_bytes < embed_c_workspace_bytes(g, pass)) e.fb = 0;      // no room for flags: every result is looked at
     const Geom& p = e.p;

@@ -129,6 +129,12 @@ int s2_fwd(const Geom& g, const void* x, const void* w, void* y, void* ws, size_
 bool embed_c_supported(const Geom& g, int pass);
 size_t embed_c_workspace_bytes(const Geom& g, int pass);
 size_t embed_c_min_workspace_bytes(const Geom& g, int pass);
+// bf16 3x3x3 layers with channel counts in multiples of 8 that 32 does not divide, as they are (conv_embed.hip)
+bool ragged_supported(const Geom& g, int pass);
+size_t ragged_workspace_bytes(const Geom& g, int pass);
+size_t ragged_min_workspace_bytes(const Geom& g, int pass);
+void ragged_describe(const Geom& g, int pass, size_t ws_bytes, char* buf, size_t len);
+int ragged_conv(const Geom& g, int pass, const void* a, const void* b, void* out, void* ws, size_t ws_bytes, hipStream_t s);
 Geom embed_c_inner(const Geom& g, int pass, size_t ws_bytes, size_t* rest);   // the layer behind the padding and the workspace left for it
 int embed_c_conv(const Geom& g, int pass, const void* a, const void* b, void* out, void* ws, size_t ws_bytes, hipStream_t s);
 bool embed_s_supported(const Geom& g, int pass);

@@ -106,3 +106,19 @@ def test_kernel_detail_names_what_runs_and_refuses_what_a_call_refuses():
     assert l.mi3d_conv3d_kernel_detail(ctypes.byref(d), 3, least, buf, 64) == -1
     assert l.mi3d_conv3d_kernel_detail(ctypes.byref(d), 1, least, None, 0) == -1
     assert l.mi3d_conv3d_kernel_detail(None, 1, least, buf, 64) == -1
+
+
+def test_ragged_layers_ask_for_what_they_use():
+    """3x3x3 with channels in eights: the layer is read as it is, so no pass wants room for copies of its tensors, and with the
+    least its own kernels take (a copy of the weights for the data gradient, nothing else) it stays on them."""
+    import torch
+    from paper_1812_07816_amd import conv3d as mc
+    for args in ((1, 128, 128, 128, 48, 48, 3, 1, 1), (1, 37, 50, 61, 48, 48, 3, 1, 1), (1, 47, 44, 47, 40, 72, 3, 1, 1), (2, 30, 31, 32, 24, 40, 3, 2, 1)):
+        d = mc.make_desc(*args, torch.bfloat16)
+        copy = (27 * d.Cin * d.Cout * 2 + 255) // 256 * 256
+        assert all(mc.workspace_bytes(d, q) <= 64 << 20 for q in range(3)), args
+        for q, least in ((0, 0), (1, copy), (2, 0)):
+            for n in (least, mc.workspace_bytes(d, q)):
+                assert mc.kernel_detail(d, q, n).startswith("wgrad_implicit_gemm" if q == 2 else "implicit_gemm"), (args, q, n, mc.kernel_detail(d, q, n))
+    d = mc.make_desc(1, 64, 96, 96, 41, 40, 3, 1, 1, torch.bfloat16)      # not in eights: behind the padding
+    assert mc.kernel_detail(d, 0) == "padded_channels > plane_stream"
