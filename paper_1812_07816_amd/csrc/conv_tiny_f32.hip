@@ -63,9 +63,7 @@ __global__ void __launch_bounds__(256) tiny_conv_kernel(const TinyParams P) {
         h[t] = source(P, 1, oh, t, P.iH);
         w[t] = source(P, 2, ow, t, P.iW);
     }
-    vec acc;
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) acc[e] = 0.f;
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};   // four sums side by side: of every fourth channel, or of every fourth tap
     for (int c = 0; c < P.K; c += VEC) {
 #pragma unroll
         for (int td = 0; td < 3; ++td) {
@@ -83,11 +81,11 @@ __global__ void __launch_bounds__(256) tiny_conv_kernel(const TinyParams P) {
                 if ((h[th] | w[tw]) < 0) continue;   // (not a product with zero: weights may be infinite)
                 const vec f = *(const vec*)(wm + ((td * P.k[1] + th) * P.k[2] + tw) * P.K + c);
 #pragma unroll
-                for (int e = 0; e < VEC; ++e) acc[e] = fmaf(v[i][e], f[e], acc[e]);
+                for (int e = 0; e < VEC; ++e) acc[VEC == 4 ? e : (td * 9 + i) & 3] = fmaf(v[i][e], f[e], acc[VEC == 4 ? e : (td * 9 + i) & 3]);
             }
         }
     }
-    float v = VEC == 4 ? (acc[0] + acc[1]) + (acc[2 % VEC] + acc[3 % VEC]) : acc[0];
+    float v = (acc[0] + acc[1]) + (acc[2] + acc[3]);
     if (P.add) v += P.add[idx];
     P.out[idx] = (P.ref ? P.ref[idx] : v) > 0.f ? v : P.slope * v;
 }
