@@ -74,7 +74,7 @@ static Kernel choose(const Geom& g, int pass) {
     if (pass == MI3D_PASS_DGRAD && c4_dgrad_supported(g)) return K_C4_DGRAD;
     if (pass == MI3D_PASS_WGRAD && c4_wgrad_supported(g)) return K_C4_WGRAD;
     if (k2_supported(g, pass)) return K_K2;
-    if (ragged_supported(g, pass)) return K_RAGGED;
+    if (ragged_supported(g, pass) && ragged_better(g, pass)) return K_RAGGED;
     if (embed_c_supported(g, pass)) return K_EMBED_C;
     if (embed_s_supported(g, pass)) return K_EMBED_S;
     if (embed_k2_supported(g, pass)) return K_EMBED_K2;
@@ -142,14 +142,19 @@ static size_t kernel_min_workspace(Kernel k, const Geom& g, int pass) {
     }
 }
 
-// The kernel for a given workspace: a layer whose padded copies (or the copy of a ragged one's weights) do not fit goes to the 3x3x3 embedding or to the plain
-// kernel, which need none or little (the callers' size query reports what the padding wants; the static scratch has a
-// fixed size).
+// What else takes a layer whose padded copies (or the copy of a ragged one's weights) do not fit into a caller's workspace:
+// the kernels that read it as it is, the 3x3x3 embedding, the plain kernels, which need none or little (the size query
+// reports what the better way wants; the static scratch has a fixed size)
+static bool takes(Kernel k, const Geom& g, int pass) {
+    return k == K_RAGGED ? ragged_supported(g, pass) : k == K_EMBED_K2 ? embed_k2_supported(g, pass) : k == K_DIRECT;
+}
+static const Kernel INSTEAD[] = {K_RAGGED, K_EMBED_K2, K_DIRECT};
+
 static Kernel choose_within(const Geom& g, int pass, size_t ws_bytes) {
     const Kernel k = choose(g, pass);
     if ((k != K_EMBED_C && k != K_RAGGED) || kernel_min_workspace(k, g, pass) <= ws_bytes) return k;
-    for (Kernel q : {K_EMBED_K2, K_DIRECT})
-        if ((q == K_DIRECT || embed_k2_supported(g, pass)) && kernel_min_workspace(q, g, pass) <= ws_bytes) return q;
+    for (Kernel q : INSTEAD)
+        if (takes(q, g, pass) && kernel_min_workspace(q, g, pass) <= ws_bytes) return q;
     return k;
 }
 
@@ -313,8 +318,8 @@ size_t mi3d_conv3d_min_workspace_bytes(const mi3d_conv_desc* desc, int pass) {
     const Kernel k = choose(g, pass);
     size_t b = kernel_min_workspace(k, g, pass);
     if (k == K_EMBED_C || k == K_RAGGED) {
-        b = std::min(b, kernel_min_workspace(K_DIRECT, g, pass));
-        if (embed_k2_supported(g, pass)) b = std::min(b, kernel_min_workspace(K_EMBED_K2, g, pass));
+        for (Kernel q : INSTEAD)
+            if (takes(q, g, pass)) b = std::min(b, kernel_min_workspace(q, g, pass));
     }
     return b;
 }

@@ -287,6 +287,40 @@ size_t embed_c_min_workspace_bytes(const Geom& g, int pass) {
 // ---- channel counts in eights that 32 does not divide ------------------------
 // 3x3x3 layers that the kernels over numbered positions take as they are, without copies of the operands (padded -> as they
 // are, 48 -> 48 at 37 x 50 x 61: 225 -> 124 us for the three passes); smaller volumes are padded.
+//
+// Where padding serves them better, from about 500 layers measured both ways (padded / as they are, us).  A tensor whose
+// channels 32 divides needs no copy, and on large volumes the kernels behind the padding, which read a voxel once for all of its
+// taps, beat those that read it for each.
+// - Unit stride, contracted channels a multiple of 32, more than one round of 512 tiles of 256 positions: forward 96->16 at
+//   288144 voxels 92 / 126, 160->8 at 905760 257 / 604, data gradient 16->160 at 254016 101 / 240 (below: 96->16 at 102131 55 / 48,
+//   128->48 at 88560 70 / 65).  The exceptions: 128->40 at 303030 200 / 176.  (Not where the implicit GEMM runs behind the
+//   padding as well: 128->8 at 155288 103 / 87.)
+// - Unit stride, outputs a multiple of 32: steps of so few channels pay only where tiles of outputs are badly filled (24 channels: 24->96
+//   at 687792 153 / 179, 24->32 at 913140 110 / 133; 16->32 at 864270 104 / 115, 8->160 at 905760 253 / 317, but 16->64 at
+//   909455 142 / 129 and 40->96 at 313000 155 / 122).
+// - Stride 2, forward: only 32 channels have a kernel of their own behind the padding (32->48 at 300300 80 / 125, at 36704 29 / 37;
+//   64->24 at 110880 55 / 51).  Data gradient: up to 64 contracted channels have one, which wins on large volumes (64->24 at
+//   859473 voxels 55 / 64, 48->32 at 2365860 113 / 136, 24->64 at 17 M 684 / 1353; 64->48 at 9.5 M 777 / 840, at 254040 42 / 29).
+// - Weight gradient: by the models of the time of both, padding at 2 TB/s (within 7 % of the better one but for 96->24 with
+//   stride 2): 64->16 at 1044576 168 / 446, 128->24 at 499824 121 / 405, 104->8 at 304732 146 / 200; but 48->48 at
+//   37 x 50 x 61 as it is.
+static bool padding_better(const Geom& g, const Geom& p, int pass) {
+    const bool ci = p.Cin != g.Cin, co = p.Cout != g.Cout;
+    if (pass == MI3D_PASS_WGRAD) {
+        const bool s1 = wgrad_mfma_supported(p);
+        if (s1 ? wgrad_mfma_uses_igw(p) : !wgrad_s2_supported(p) || wgrad_s2_uses_igw(p)) return false;   // (the same kernel, or one behind further copies)
+        const double bytes = (ci ? g.in_voxels() * 2.0 * (g.Cin + p.Cin) : 0.0) + (co ? g.out_voxels() * 2.0 * (g.Cout + p.Cout) : 0.0);
+        return igw_us(g, ~(size_t)0) > (s1 ? wgrad_mfma_patches_us(p) + 8.0 + bytes / 2e6 : 1.2 * (wgrad_s2_patches_us(p) + 8.0 + bytes / 2e6));
+    }
+    const bool dgrad = pass == MI3D_PASS_DGRAD, k_whole = dgrad ? !co : !ci, m_whole = dgrad ? !ci : !co;
+    const int K = dgrad ? g.Cout : g.Cin, M = dgrad ? g.Cin : g.Cout;
+    const long long voxels = dgrad ? g.in_voxels() : g.out_voxels();
+    if ((!k_whole && !m_whole) || (sp_supported(p, pass) && sp_uses_ig(p, pass))) return false;
+    if (g.sD == 1) return k_whole ? voxels > 512 * 256 : K <= 24 && voxels > (1 << 18) && (K == 24 || M == 32 || (M > 128 && M % 64 == 32));
+    if (!dgrad) return K == 32 && voxels > (1 << 15);
+    return p.Cout <= 64 && voxels > (!k_whole || M <= 32 ? 1 << 19 : 1 << 22);
+}
+
 bool ragged_supported(const Geom& g, int pass) {
     if (g.dtype != MI3D_BF16 || g.Cin % 8 || g.Cout % 8 || g.kD != 3 || g.kH != 3 || g.kW != 3) return false;
     const Geom p = padded_geom(g, pass);
@@ -294,6 +328,7 @@ bool ragged_supported(const Geom& g, int pass) {
     if (pass == MI3D_PASS_WGRAD) return igw_supported(g);
     return ig_takes(g, pass) && g.out_voxels() >= 1024;
 }
+bool ragged_better(const Geom& g, int pass) { return !embed_c_supported(g, pass) || !padding_better(g, padded_geom(g, pass), pass); }
 static int weight_flag_words(const Geom& g, int pass) {
     return pass == MI3D_PASS_FWD ? (int)((g.w_elems() / 8 + 255) / 256) : 27 * ((g.Cin + 63) / 64) * ((g.Cout + 63) / 64);
 }

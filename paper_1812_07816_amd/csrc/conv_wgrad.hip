@@ -405,6 +405,14 @@ static bool wgrad_rows12(const Geom& g) {
 
 bool wgrad_mfma_supported(const Geom& g) { return th16::supported(g); }
 
+double wgrad_mfma_patches_us(const Geom& g) {
+    const size_t parts = wgrad_rows12(g) ? th12::workspace_bytes(g) : th16::workspace_bytes(g);
+    const double pairs = (double)(g.Cin / 32) * (g.Cout / 32), slots = (double)parts / (4.0 * g.w_elems());
+    const int rows = wgrad_rows12(g) ? 12 : 16;
+    const double units = (double)g.N * g.D * ((g.Ho + rows - 1) / rows) * ((g.Wo + 31) / 32);
+    return 14.0 + 3.8 * rows / 12 * ceil(units / slots) * (pairs * slots > cu_count() ? 1.5 : 1.0) + (double)parts * 2 / 5e6;
+}
+
 // The matrix product over numbered positions where the patches of this kernel are too few, too empty or too many partial
 // sums, by the two models of the time (this kernel: patches a workgroup walks, doubled up where there are more workgroups
 // than CUs, and the way of the partial sums).  With the launch that adds them, this kernel -> igw_kernel: 320->320 at 12^3
@@ -415,12 +423,7 @@ bool wgrad_mfma_uses_igw(const Geom& g) {
     Geom q = g;
     q.hi = nullptr;      // (the sizes decide, not how the call passes its tensors)
     if (!igw_supported(q)) return false;
-    const size_t parts = wgrad_rows12(g) ? th12::workspace_bytes(g) : th16::workspace_bytes(g);
-    const double pairs = (double)(g.Cin / 32) * (g.Cout / 32), slots = (double)parts / (4.0 * g.w_elems());
-    const int rows = wgrad_rows12(g) ? 12 : 16;
-    const double units = (double)g.N * g.D * ((g.Ho + rows - 1) / rows) * ((g.Wo + 31) / 32);
-    const double us = 14.0 + 3.8 * rows / 12 * ceil(units / slots) * (pairs * slots > cu_count() ? 1.5 : 1.0) + (double)parts * 2 / 5e6;
-    return igw_us(q, ~(size_t)0) < 0.9 * us;
+    return igw_us(q, ~(size_t)0) < 0.9 * wgrad_mfma_patches_us(g);
 }
 
 size_t wgrad_mfma_workspace_bytes(const Geom& g) {

@@ -305,6 +305,12 @@ static int wgrad_s2_slots(const Geom& g) {
     return (int)slots;
 }
 
+double wgrad_s2_patches_us(const Geom& g) {
+    const long long patches = (long long)g.N * g.Do * ((g.Ho + TH - 1) / TH) * ((g.Wo + TW - 1) / TW);
+    const double rate = g.Cout % 128 == 0 ? 8.7e8 : g.Cout <= 64 ? 7.6e8 : 4.65e8;
+    return 23.0 + 2.0 * patches * (TH * TW) * 27 * g.Cin * (double)g.Cout / rate;
+}
+
 // The matrix product over numbered positions where its model expects it to be faster than this kernel, which (with the launch that adds
 // the partial sums) takes 23 us and the time of its whole patches at 870 TFLOP/s, 760 with 32 or 64 output channels and 465 with
 // other numbers that 128 does not divide: within 7 % of 20 layers measured.  This kernel -> igw_kernel: 64->128 at 96^3, N = 2 177 -> 133 us, 128->256 at 48^3, N = 2 92 -> 67,
@@ -313,9 +319,7 @@ static int wgrad_s2_slots(const Geom& g) {
 // 153 -> 213 (seven tiles of columns read every position again): whole patches, many of them, stay.
 bool wgrad_s2_uses_igw(const Geom& g) {
     if (!igw_supported(g)) return false;
-    const long long patches = (long long)g.N * g.Do * ((g.Ho + TH - 1) / TH) * ((g.Wo + TW - 1) / TW);
-    const double rate = g.Cout % 128 == 0 ? 8.7e8 : g.Cout <= 64 ? 7.6e8 : 4.65e8;
-    return igw_us(g, ~(size_t)0) < 23.0 + 2.0 * patches * (TH * TW) * 27 * g.Cin * (double)g.Cout / rate;
+    return igw_us(g, ~(size_t)0) < wgrad_s2_patches_us(g);
 }
 
 size_t wgrad_s2_workspace_bytes(const Geom& g) {

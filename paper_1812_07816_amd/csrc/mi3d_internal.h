@@ -114,6 +114,7 @@ int igw_run(const Geom& g, const void* x, const void* dy, float* dw, void* ws, s
 bool wgrad_mfma_supported(const Geom& g);
 size_t wgrad_mfma_workspace_bytes(const Geom& g);
 size_t wgrad_mfma_min_workspace_bytes(const Geom& g);
+double wgrad_mfma_patches_us(const Geom& g);            // what its model expects the kernel on patches to take
 bool wgrad_mfma_uses_igw(const Geom& g);                // volumes that its patches cover badly or fill the chip with badly
 int wgrad_mfma(const Geom& g, const void* x, const void* dy, float* dw, void* ws, size_t ws_bytes, hipStream_t s);
 
@@ -131,6 +132,7 @@ size_t embed_c_workspace_bytes(const Geom& g, int pass);
 size_t embed_c_min_workspace_bytes(const Geom& g, int pass);
 // bf16 3x3x3 layers with channel counts in multiples of 8 that 32 does not divide, as they are (conv_embed.hip)
 bool ragged_supported(const Geom& g, int pass);
+bool ragged_better(const Geom& g, int pass);   // than behind the padding, where there is room for both
 size_t ragged_workspace_bytes(const Geom& g, int pass);
 size_t ragged_min_workspace_bytes(const Geom& g, int pass);
 void ragged_describe(const Geom& g, int pass, size_t ws_bytes, char* buf, size_t len);
@@ -148,6 +150,7 @@ int embed_s_conv(const Geom& g, int pass, const void* a, const void* b, void* ou
 bool wgrad_s2_supported(const Geom& g);
 size_t wgrad_s2_workspace_bytes(const Geom& g);
 size_t wgrad_s2_min_workspace_bytes(const Geom& g);
+double wgrad_s2_patches_us(const Geom& g);
 bool wgrad_s2_uses_igw(const Geom& g);
 int wgrad_s2(const Geom& g, const void* x, const void* dy, float* dw, void* ws, size_t ws_bytes, hipStream_t s);
 

@@ -122,3 +122,20 @@ def test_ragged_layers_ask_for_what_they_use():
                 assert mc.kernel_detail(d, q, n).startswith("wgrad_implicit_gemm" if q == 2 else "implicit_gemm"), (args, q, n, mc.kernel_detail(d, q, n))
     d = mc.make_desc(1, 64, 96, 96, 41, 40, 3, 1, 1, torch.bfloat16)      # not in eights: behind the padding
     assert mc.kernel_detail(d, 0) == "padded_channels > plane_stream"
+
+
+def test_ragged_layers_are_padded_where_that_was_measured_to_be_faster():
+    """One layer on either side of each line, and both ways for a caller whose workspace holds no copies."""
+    import torch
+    from paper_1812_07816_amd import conv3d as mc
+    for args, q, padded in (((1, 103, 92, 115, 8, 96, 3, 1, 1), 1, True), ((1, 43, 53, 44, 8, 96, 3, 1, 1), 1, False),        # contracted channels whole
+                            ((1, 72, 69, 58, 96, 16, 3, 1, 1), 0, True), ((1, 45, 50, 45, 96, 16, 3, 1, 1), 0, False),
+                            ((1, 88, 89, 88, 24, 96, 3, 1, 1), 0, True), ((1, 98, 97, 96, 16, 64, 3, 1, 1), 0, False),        # outputs whole
+                            ((1, 150, 100, 160, 48, 48, 3, 1, 1), 0, False), ((1, 150, 100, 160, 48, 48, 3, 1, 1), 1, False), # neither
+                            ((1, 140, 131, 129, 32, 48, 3, 2, 1), 0, True), ((1, 140, 131, 129, 64, 48, 3, 2, 1), 0, False),  # stride 2
+                            ((1, 89, 87, 111, 64, 24, 3, 2, 1), 1, True), ((1, 80, 60, 53, 64, 48, 3, 2, 1), 1, False),
+                            ((1, 102, 101, 101, 64, 16, 3, 1, 1), 2, True), ((1, 37, 50, 61, 48, 48, 3, 1, 1), 2, False),
+                            ((2, 40, 40, 40, 24, 48, 3, (1, 2, 2), 1), 2, False)):
+        d = mc.make_desc(*args, torch.bfloat16)
+        assert mc.kernel_detail(d, q).startswith("padded_channels") == padded, (args, q, mc.kernel_detail(d, q))
+        assert "implicit_gemm" in mc.kernel_detail(d, q, 27 * 128 * 128 * 2), (args, q)

@@ -127,3 +127,18 @@ def test_layers_whose_padded_copies_would_pass_16_gib(device, C):
             at = at[ok]
             ref[(slice(None), *t)] = dy[0, u[ok][:, 0], u[ok][:, 1], u[ok][:, 2]].double().T @ x[0, at[:, 0], at[:, 1], at[:, 2]].double()
         assert float((dw - ref).abs().max() / ref.square().mean().sqrt()) <= 3e-5
+
+
+@pytest.mark.parametrize("args, q", [((1, 66, 66, 67, 16, 96, 3, 1, 1), 1), ((1, 66, 66, 67, 96, 16, 3, 1, 1), 0), ((2, 52, 53, 51, 24, 96, 3, 1, 1), 0),
+                                     ((1, 90, 91, 92, 32, 48, 3, 2, 1), 0), ((1, 89, 80, 79, 64, 24, 3, 2, 1), 1), ((1, 60, 61, 62, 128, 24, 3, 1, 1), 2)])
+def test_padded_and_as_they_are(device, args, q):
+    """Layers beyond the lines of the dispatch: behind the padding with the workspace of the query, as they are with too little for the copies."""
+    d = mc.make_desc(*args, torch.bfloat16)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    xs, ws, ys = mc._shapes(d)
+    x, w, dy = (torch.randn(s, generator=gen, device="cuda").bfloat16() for s in (xs, ws, ys))
+    small = (27 * d.Cin * d.Cout * 2 + 255) // 256 * 256 if q < 2 else 16 << 20
+    assert mc.kernel_detail(d, q).startswith("padded_channels") and "padded" not in mc.kernel_detail(d, q, small)
+    a, b = (_run(d, q, x, w, dy, n).double() for n in (mc.workspace_bytes(d, q), small))
+    # each rounds to bf16 once (weight gradients: fp32 sums of 113460 products at most, in other orders)
+    assert float((a - b).norm() / a.norm()) <= (3e-6 if q == 2 else 2.0 ** -8)
