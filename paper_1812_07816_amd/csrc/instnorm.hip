@@ -231,7 +231,7 @@ __global__ void __launch_bounds__(256) in_bwd_kernel(typename Piece<T>::raw* __r
 // Bound: latency, of one trip to memory, a reduction and the launch, where the kernels above and below take a trip and a launch
 // for each of their two or three steps; from 1000 voxels the accesses (16 bytes at a stride of a voxel, a request per lane).
 // Measured, kernels alone, N = 2, bf16: statistics of 64 voxels of 256 channels 3.3 + 4.1 -> 2.9 us, of 4096 of 64 4.3 + 4.0 -> 5.4;
-// backward pass 3.7 + 4.0 + 2.8 -> 3.3 and 6.2 + 4.8 + 2.8 -> 13.6 (fp32 there 30 with four pieces of both tensors a thread: spills).
+// backward pass 3.7 + 4.0 + 2.8 -> 3.3 (fp32 with four pieces of both tensors a thread: spills; two at most).  Beside in_small, the lines.
 // Consecutive items go to one XCD: a line of 128 bytes belongs to eight of them, and lines written by pieces from
 // several XCDs cost 33 us where they cost 14 now (4096 voxels of 512 channels).
 // Everything is added in double: per thread in voxel order, then across the lanes of a wave (a lane gives away half of the
@@ -334,9 +334,20 @@ __global__ void __launch_bounds__(1024) in_small_kernel(T* __restrict__ x, const
         *(raw*)(xn + (long long)v * C) = Piece<T>::pack(f);
     }
 }
-// up to four pieces a thread; two where both tensors are fp32 (see above)
+// Where one launch is faster, from 1 to 512 samples of 8 to 320 channels (the launches of the other kernels / this one, us).  Two things
+// end it: the backward pass of few workgroups, whose four pieces of two tensors come one after the other (bf16, 2 x 64 channels:
+// 2600 voxels 11.0 / 10.4, 3500 11.2 / 12.5; with 64 workgroups 4096 still 13.1 / 11.6, and on rows of up to 32 channels 10.8 / 10.2; fp32 from
+// 1500: 10.4 / 11.9 at 1800), and many workgroups on wide rows, whose lines of 128 bytes are cut up among eight of them (64 x 320
+// channels: bf16 backward 3072 voxels 167 / 133, 4096 207 / 255, fp32 statistics 3072 92 / 69, 3500 102 / 112; 256 x 320 from
+// 3072: 646 / 659 and 337 / 386; 512 x 64 channels, 4096 voxels: 583 / 352 and 348 / 186).
 template <int MODE, typename T>
-bool in_small(size_t voxels) { return voxels <= (MODE == 0 || sizeof(T) == 2 ? 4096 : 2048); }
+bool in_small(int N, size_t voxels, int C) {
+    const long long items = (long long)N * (C / 8);
+    const bool whole_lines = C <= 128 || items <= 1280;
+    if (MODE == 0) return voxels <= 2560 || (voxels <= 3072 && items <= 4096) || (voxels <= 4096 && (sizeof(T) == 2 || whole_lines));
+    if (sizeof(T) == 2) return voxels <= 2560 || (voxels <= 3072 && items >= 32 && items <= 4096) || (voxels <= 4096 && (C <= 32 || (items >= 64 && whole_lines)));
+    return voxels <= 1536 || (voxels <= 2048 && (C <= 16 || items >= 32));
+}
 template <int MODE, typename T>
 int in_small_run(T* x, const T* a, const float* stats, int N, size_t voxels, int C, float slope, float eps, float* out, hipStream_t s) {
     const unsigned threads = voxels >= 1024 ? 1024u : (unsigned)((voxels + 63) / 64 * 64), grid = (unsigned)(N * (C / 8));
@@ -374,7 +385,7 @@ template <typename T>
 int in_stats(const void* z, int N, size_t voxels, int C, float eps, float* stats, void* ws, size_t ws_bytes, void* stream) {
     if (!z || !stats || !ws || !a16(z) || !in_args_ok(N, voxels, C) || !(eps > 0.f)) return MI3D_ERR_INVALID_ARG;
     if (ws_bytes < mi3d_instnorm_workspace_bytes(N, C)) return MI3D_ERR_WORKSPACE;
-    if (in_small<0, T>(voxels)) return in_small_run<0, T>((T*)z, nullptr, nullptr, N, voxels, C, 1.f, eps, stats, (hipStream_t)stream);
+    if (in_small<0, T>(N, voxels, C)) return in_small_run<0, T>((T*)z, nullptr, nullptr, N, voxels, C, 1.f, eps, stats, (hipStream_t)stream);
     const int blocks = in_blocks(voxels);
     in_reduce_kernel<0, T><<<dim3(blocks, N), 256, 0, (hipStream_t)stream>>>((const T*)z, nullptr, (long long)voxels, C, 1.f, (float*)ws);
     int st = check_launch();
@@ -397,7 +408,7 @@ int in_bwd(void* da, const void* a, const float* stats, int N, size_t voxels, in
     typedef typename Piece<T>::raw raw;
     if (!da || !a || !stats || !ws || !a16(da) || !a16(a) || !in_args_ok(N, voxels, C) || !(slope > 0.f && slope <= 1.f)) return MI3D_ERR_INVALID_ARG;
     if (ws_bytes < mi3d_instnorm_workspace_bytes(N, C)) return MI3D_ERR_WORKSPACE;
-    if (in_small<1, T>(voxels)) return in_small_run<1, T>((T*)da, (const T*)a, stats, N, voxels, C, slope, 0.f, nullptr, (hipStream_t)stream);
+    if (in_small<1, T>(N, voxels, C)) return in_small_run<1, T>((T*)da, (const T*)a, stats, N, voxels, C, slope, 0.f, nullptr, (hipStream_t)stream);
     const int blocks = in_blocks(voxels);
     float* part = (float*)ws;
     float* sums = part + (size_t)N * IN_BLOCKS * 2 * C;

@@ -14,7 +14,8 @@ SLOPE, EPS = 0.01, 1e-5
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("N,V,C", [(1, 1, 8), (3, 2, 40), (2, 63, 512), (1, 64, 24), (2, 65, 72), (1, 1023, 8), (2, 1024, 32), (3, 1025, 40),
-                                   (1, 2048, 64), (1, 2049, 16), (1, 3300, 320), (2, 4096, 72)])
+                                   (1, 2048, 64), (1, 2049, 16), (1, 3300, 320), (2, 4096, 72),
+                                   (1, 1536, 24), (1, 1537, 24), (4, 2048, 64), (2, 2560, 16), (2, 2561, 16), (8, 4096, 64), (32, 2600, 312)])
 def test_small_volumes_match_fp64(device, dtype, N, V, C):
     gen = torch.Generator(device="cuda").manual_seed(V + C)
     rnd = lambda: torch.randn((N, V, 1, 1, C), generator=gen, device="cuda")
