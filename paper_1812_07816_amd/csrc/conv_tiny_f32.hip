@@ -177,13 +177,27 @@ TinyParams params(const Geom& g, int pass) {
 //   8->16, 2x2x2 at 16^3 13.0 -> 5.9, 12.2 -> 5.5, 8.3 -> 4.5
 // The lines: weights of a workgroup within 48 KB, copied by each; 2^24 multiply-adds (14 M: 9.7 us) and sums of 864
 // (1080: 17.7 -> 28.3, 648: 17.5 -> 19.4 with a launch less): one thread's chain; weight gradients to 8192 positions (10.5 us),
-// 4096 where channels come one at a time (8000: 12.6 -> 33).  Not halves of an input, nor the whole tensors of layers that have
+// 4096 where channels come one at a time (8000: 12.6 -> 33), and of those that igw_f32_kernel takes the ones for which wgrad_us
+// expects less than that (5 us below its model at these sizes): a workgroup fetches whole lines for 16 and 32 bytes of a voxel's channels
+// (igw_f32_kernel / this one, 2x2x2 32->64: 729 positions 10.4 / 7.8, 1728 11.2 / 14.0, 8000 15.6 / 48.8; 16->16 at 20^3 15.8 / 11.9;
+// 1x1x1 32->32 at 16^3 9.6 / 9.3, at 20^3 11.5 / 14.8).  Not halves of an input, nor the whole tensors of layers that have
 // them: both ways give the same bits.
+static double wgrad_us(const Geom& g, long long groups) {
+    const double V = (double)g.out_voxels();
+    const int x = 4 * g.Cin * g.sW, y = 4 * g.Cout, line = 128, bytes = (x < line ? x : line) + (y < line ? y : line);   // per position
+    const double us[3] = {0.85 * V / 1024, V * bytes / 150e3, groups * V * bytes / 20e6};    // trips of a thread, one CU's rate, what the L2s deliver
+    return 2.5 + (us[0] > us[1] ? us[0] > us[2] ? us[0] : us[2] : us[1] > us[2] ? us[1] : us[2]);
+}
 bool tiny_supported(const Geom& g, int pass) {
     if (g.dtype != MI3D_F32 || g.Cin % 64 == 0 || g.kD > 3 || g.kH > 3 || g.kW > 3 || g.sD > 2 || g.sH > 2 || g.sW > 2) return false;
     const long long T = g.taps(), V = pass == MI3D_PASS_DGRAD ? g.in_voxels() : g.out_voxels();
     const long long K = pass == MI3D_PASS_DGRAD ? g.Cout : g.Cin, M = pass == MI3D_PASS_DGRAD ? g.Cin : g.Cout;
-    if (pass == MI3D_PASS_WGRAD) return V <= (K % 4 || M % 4 ? 4096 : 8192) && T * ((K + TK - 1) / TK) * ((M + TM - 1) / TM) <= 512;
+    if (pass == MI3D_PASS_WGRAD) {
+        const long long groups = T * ((K + TK - 1) / TK) * ((M + TM - 1) / TM);
+        if (V > (K % 4 || M % 4 ? 4096 : 8192) || groups > 512) return false;
+        const double us = wgrad_us(g, groups);
+        return us < 9.0 || !igw_supported(g) || us < igw_us(g, ~(size_t)0) - 5.0;    // (that model is never below 14)
+    }
     return M * lds_row((int)T, (int)K) <= MAX_W && T * K <= 864 && V * M * T * K <= (16ll << 20);
 }
 

@@ -139,3 +139,14 @@ def test_ragged_layers_are_padded_where_that_was_measured_to_be_faster():
         d = mc.make_desc(*args, torch.bfloat16)
         assert mc.kernel_detail(d, q).startswith("padded_channels") == padded, (args, q, mc.kernel_detail(d, q))
         assert "implicit_gemm" in mc.kernel_detail(d, q, 27 * 128 * 128 * 2), (args, q)
+
+
+def test_the_smallest_fp32_weight_gradients_keep_to_their_line():
+    """One launch of workgroups that fetch whole lines for a few channels, up to where the matrix product over positions is faster."""
+    import torch
+    from paper_1812_07816_amd import conv3d as mc
+    for args, tiny in (((1, 18, 18, 18, 32, 64, 2, 2, 0), True), ((1, 24, 24, 24, 32, 64, 2, 2, 0), False), ((1, 40, 38, 32, 32, 64, 2, 2, 0), False),
+                       ((1, 24, 24, 24, 32, 32, 2, 2, 0), True), ((1, 32, 32, 32, 32, 32, 2, 2, 0), False), ((1, 20, 20, 20, 32, 32, 1, 1, 0), False),
+                       ((1, 20, 20, 20, 16, 16, 3, 1, 1), True), ((1, 20, 20, 20, 4, 8, 3, 1, 1), True), ((1, 32, 32, 32, 32, 16, 3, 2, 1), False)):
+        how = mc.kernel_detail(mc.make_desc(*args, torch.float32), 2)
+        assert how == "f32_direct" if tiny else "wgrad_implicit_gemm" in how, (args, how)
