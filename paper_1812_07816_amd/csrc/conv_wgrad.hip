@@ -409,7 +409,8 @@ double wgrad_mfma_patches_us(const Geom& g) {
     const size_t parts = wgrad_rows12(g) ? th12::workspace_bytes(g) : th16::workspace_bytes(g);
     const double pairs = (double)(g.Cin / 32) * (g.Cout / 32), slots = (double)parts / (4.0 * g.w_elems());
     const int rows = wgrad_rows12(g) ? 12 : 16;
-    const double units = (double)g.N * g.D * ((g.Ho + rows - 1) / rows) * ((g.Wo + 31) / 32);
+    double units = (double)g.N * g.D * ((g.Ho + rows - 1) / rows) * ((g.Wo + 31) / 32);
+    if (rows == 12 && g.Wo <= 16 && g.Ho > 12) units *= 0.7;    // (two patch rows at a time: 256->128 at 19 x 18 x 16, N = 2 37 us, igw_kernel 48)
     return 14.0 + 3.8 * rows / 12 * ceil(units / slots) * (pairs * slots > cu_count() ? 1.5 : 1.0) + (double)parts * 2 / 5e6;
 }
 

@@ -150,3 +150,12 @@ def test_the_smallest_fp32_weight_gradients_keep_to_their_line():
                        ((1, 20, 20, 20, 16, 16, 3, 1, 1), True), ((1, 20, 20, 20, 4, 8, 3, 1, 1), True), ((1, 32, 32, 32, 32, 16, 3, 2, 1), False)):
         how = mc.kernel_detail(mc.make_desc(*args, torch.float32), 2)
         assert how == "f32_direct" if tiny else "wgrad_implicit_gemm" in how, (args, how)
+
+
+def test_narrow_planes_of_paired_patch_rows_keep_their_weight_gradient():
+    """Planes of at most 16 columns are taken two patch rows at a time: the model of the patches' time counts them so."""
+    import torch
+    from paper_1812_07816_amd import conv3d as mc
+    for args, how in (((2, 19, 18, 16, 256, 128, 3, 1, 1), "mfma_wgrad_plane_stream"), ((2, 19, 18, 17, 256, 128, 3, 1, 1), "wgrad_implicit_gemm"),
+                      ((1, 12, 12, 12, 320, 320, 3, 1, 1), "wgrad_implicit_gemm")):
+        assert mc.kernel_detail(mc.make_desc(*args, torch.bfloat16), 2).startswith(how), args
