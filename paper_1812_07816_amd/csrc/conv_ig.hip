@@ -478,7 +478,7 @@ long long count_tiles(const Geom& g, int pass, int bm, int bn, long long* work, 
 constexpr long long MAX_TILES = 1ll << 26;   // (of a grid; no volume whose planes are this small has more)
 
 // (with less workspace than the best plan wants: fewer splits, down to whole contractions, which need none)
-IgPlan make_plan(const Geom& g, int pass, size_t ws_bytes) {
+IgPlan plan_for(const Geom& g, int pass, size_t ws_bytes) {
     const bool flip = pass == MI3D_PASS_DGRAD, classes = flip && g.sD == 2;
     const int M = flip ? g.Cin : g.Cout, slots = 2 * cu_count();
     IgPlan best{};
@@ -509,6 +509,7 @@ IgPlan make_plan(const Geom& g, int pass, size_t ws_bytes) {
     }
     return best;
 }
+IgPlan make_plan(const Geom& g, int pass, size_t ws_bytes) { return kept_plan<IgPlan>(g, pass, ws_bytes, [&] { return plan_for(g, pass, ws_bytes); }); }
 
 // Bytes from the first to the last voxel at the positions of a tile (256 of them at most), and the voxels by which a position
 // can lie before an earlier one: positions beyond the volume they read from (it is the smaller one where a data gradient

@@ -478,7 +478,7 @@ double plan_us(int v, int cus, long long wgs, double most, double mean) {
 }
 
 // (with less workspace than the best plan wants: fewer splits, down to whole contractions, which need the packed weights alone)
-IgfPlan make_plan(const Geom& g, int pass, size_t ws_bytes) {
+IgfPlan plan_for(const Geom& g, int pass, size_t ws_bytes) {
     IgfParams P;
     long long J[8];
     int most;
@@ -509,6 +509,7 @@ IgfPlan make_plan(const Geom& g, int pass, size_t ws_bytes) {
     }
     return best;
 }
+IgfPlan make_plan(const Geom& g, int pass, size_t ws_bytes) { return kept_plan<IgfPlan>(g, pass, ws_bytes, [&] { return plan_for(g, pass, ws_bytes); }); }
 
 }  // namespace
 

@@ -413,7 +413,7 @@ constexpr int RES[2] = {2, 3};
 constexpr double STEP_US[2][2][3] = {{{0.38, 0.52, 0.52}, {0.30, 0.38, 0.49}}, {{2.45, 3.6, 3.6}, {2.05, 2.9, 3.9}}};
 constexpr double START_US = 4.0, LAUNCH_US = 4.0, PART_BYTES_PER_US = 3.5e6, READ_BYTES_PER_US = 13e6;   // (what all CUs read from the L2s)
 
-IgwPlan make_plan(const Geom& g, size_t ws_bytes) {
+IgwPlan plan_for(const Geom& g, size_t ws_bytes) {
     const bool f32 = g.dtype == MI3D_F32;
     const int cus = cu_count(), C = g.hi ? g.Cin / 2 : g.Cin;
     IgwPlan best{0, 1, 0, 0, g.hi ? 2 : 1, 0, 1e30};
@@ -441,6 +441,7 @@ IgwPlan make_plan(const Geom& g, size_t ws_bytes) {
     }
     return best;
 }
+IgwPlan make_plan(const Geom& g, size_t ws_bytes) { return kept_plan<IgwPlan>(g, MI3D_PASS_WGRAD, ws_bytes, [&] { return plan_for(g, ws_bytes); }); }
 
 }  // namespace
 

@@ -2,9 +2,42 @@
 // taps in one word, and the parity classes of a strided data gradient.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
+#include <string.h>
+
+#include "mi3d_internal.h"
 
 namespace mi3d {
+
+// make(): the plan for these sizes and this workspace.  A call asks for its plan up to five times (kernel choice, least
+// workspace, models of the time, run) and one takes 1 to 3 us, a tenth of what the smallest layers take in all; so a thread keeps the
+// last ones, by everything that make() may look at (the pointers of the geometry only as being there or not).
+template <class Plan, class Make>
+inline Plan kept_plan(const Geom& g, int pass, size_t ws_bytes, Make make) {
+    struct Key {
+        int sizes[19], pass, halves, cus;
+        size_t ws_bytes;
+    };
+    struct Slot {
+        Key key;
+        Plan plan;
+    };
+    static_assert(offsetof(Geom, dtype) == 18 * sizeof(int), "the sizes are the first members of Geom");
+    static thread_local Slot slots[32];       // (a key of zeros is that of no layer)
+    Key k;
+    memset(&k, 0, sizeof(k));
+    memcpy(k.sizes, &g, sizeof(k.sizes));
+    k.pass = pass; k.halves = g.hi ? 1 : 0; k.cus = cu_count(); k.ws_bytes = ws_bytes;
+    uint64_t h = k.pass + 3 * k.ws_bytes;
+    for (int v : k.sizes) h = h * 0x9E3779B97F4A7C15ull + (uint32_t)v;
+    Slot& s = slots[h >> 59];
+    if (memcmp(&s.key, &k, sizeof(k))) {
+        s.plan = make();
+        s.key = k;
+    }
+    return s.plan;
+}
 
 // x / d for 0 <= x < 2^31 by multiplication (Granlund and Montgomery, "Division by Invariant Integers using
 // Multiplication", PLDI 1994): s = ceil(log2 d), m = floor(2^32 (2^s - d) / d) + 1

@@ -159,3 +159,41 @@ def test_narrow_planes_of_paired_patch_rows_keep_their_weight_gradient():
     for args, how in (((2, 19, 18, 16, 256, 128, 3, 1, 1), "mfma_wgrad_plane_stream"), ((2, 19, 18, 17, 256, 128, 3, 1, 1), "wgrad_implicit_gemm"),
                       ((1, 12, 12, 12, 320, 320, 3, 1, 1), "wgrad_implicit_gemm")):
         assert mc.kernel_detail(mc.make_desc(*args, torch.bfloat16), 2).startswith(how), args
+
+
+def test_plans_do_not_depend_on_what_was_asked_before():
+    """A thread keeps its last plans: what runs, for which workspace, is the same in any order and in any thread."""
+    import random
+    import threading
+    import torch
+    from paper_1812_07816_amd import conv3d as mc
+    r = random.Random(3)
+    asks = []
+    for _ in range(150):
+        c = [r.choice([8, 24, 32, 64, 96, 256]) for _ in range(2)]
+        k, s, p = r.choice([(3, 1, 1), (3, 2, 1), (2, 2, 0), (3, 1, 0)])
+        dt = r.choice([torch.bfloat16, torch.float32])
+        d = mc.make_desc(r.randint(1, 2), *(r.randint(4, 60) for _ in range(3)), *c, k, s, p, dt)
+        for q in range(3):
+            full = mc.workspace_bytes(d, q)
+            asks += [(d, q, n) for n in {full, (full + mc.min_workspace_bytes(d, q)) // 2, mc.min_workspace_bytes(d, q)}]
+    said = [mc.kernel_detail(*a) for a in asks]
+    order = list(range(len(asks)))
+    r.shuffle(order)
+    wrong = []
+
+    def again(idx):
+        wrong.extend(i for i in idx if mc.kernel_detail(*asks[i]) != said[i])
+
+    threads = [threading.Thread(target=again, args=(o,)) for o in (order, order[::-1], sorted(order))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
+    for d, q, n in (asks[i] for i in order[:60]):       # one size away, and back
+        e = type(d).from_buffer_copy(d)
+        e.W += 1
+        first = mc.kernel_detail(d, q, n)
+        mc.workspace_bytes(e, q)
+        assert mc.kernel_detail(d, q, n) == first
