@@ -211,7 +211,7 @@ static std::string describe(Kernel k, const Geom& g, int pass, size_t ws_bytes) 
             if (f32_uses_tiny(g, pass)) return "f32_direct";
             if (f32_uses_ig(g, pass, ws_bytes)) {
                 igf_describe(g, pass, ws_bytes, buf, sizeof(buf));
-                return std::string(buf) + (f32_gathers_parts(g, pass) ? "_from_bf16_parts" : "");
+                return buf;
             }
             if (f32_uses_parts(g, pass, ws_bytes)) return pass == MI3D_PASS_WGRAD ? "f32_wgrad_from_bf16_parts" : "f32_gather_from_bf16_parts";
             if (pass == MI3D_PASS_WGRAD) return f32_wgrad_folds_taps(g) ? "f32_wgrad_folded_taps" : "f32_wgrad";

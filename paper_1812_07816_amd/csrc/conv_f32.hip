@@ -1018,8 +1018,6 @@ bool f32_uses_tiny(const Geom& g, int pass) {
 
 bool f32_uses_igw(const Geom& g, size_t ws_bytes) { return f32_supported(g, MI3D_PASS_WGRAD) && !f32_head(g) && igw_better(g, ws_bytes); }
 
-bool f32_gathers_parts(const Geom& g, int pass) { return split_ok(g, pass); }
-
 bool f32_uses_ig(const Geom& g, int pass, size_t ws_bytes) {
     return f32_supported(g, pass) && !f32_head(g) && ig_better(g, pass) && ws_bytes >= igf_min_workspace_bytes(g, pass);
 }

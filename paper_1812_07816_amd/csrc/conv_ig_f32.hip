@@ -531,7 +531,7 @@ size_t igf_workspace_bytes(const Geom& g, int pass) {
 }
 void igf_describe(const Geom& g, int pass, size_t ws_bytes, char* buf, size_t len) {
     const IgfPlan p = make_plan(g, pass, ws_bytes);
-    snprintf(buf, len, "f32_implicit_gemm_%dx%d_parts_%d", BMS[p.v], BN, p.splits);
+    snprintf(buf, len, "f32_implicit_gemm_%dx%d_parts_%d_from_bf16_parts", BMS[p.v], BN, p.splits);
 }
 
 // in: activations read (x of the forward pass, dy of the data gradient); out: y or dx

@@ -220,7 +220,6 @@ int tiny_wgrad(const Geom& g, const void* x, const void* dy, float* dw, hipStrea
 bool f32_uses_tiny(const Geom& g, int pass);
 bool f32_uses_ig(const Geom& g, int pass, size_t ws_bytes);      // implicit GEMM over numbered positions
 bool f32_uses_igw(const Geom& g, size_t ws_bytes);               // weight gradient over numbered positions
-bool f32_gathers_parts(const Geom& g, int pass);                 // sizes that the patch kernel with such products serves
 bool f32_uses_parts(const Geom& g, int pass, size_t ws_bytes);   // other kernels with products from bf16 matrix instructions
 bool f32_wgrad_folds_taps(const Geom& g);   // at most 4 input channels: (tap, channel) pairs as the columns of the MFMA block
 bool f32_takes_halves(const Geom& g, int pass);   // the tensor of x's shape as two halves along the channels

@@ -100,6 +100,9 @@ def test_kernel_detail_names_what_runs_and_refuses_what_a_call_refuses():
     d = mc.make_desc(1, 64, 64, 64, 64, 64, 3, 1, 1, torch.float32)
     least = mc.min_workspace_bytes(d, 1)
     assert mc.kernel_detail(d, 1) == "f32_gather_from_bf16_parts" and mc.kernel_detail(d, 1, least) == "f32_gather"
+    for args in ((1, 48, 48, 48, 64, 128, 2, 2, 0), (2, 12, 14, 16, 32, 64, 3, 2, 1), (1, 10, 9, 8, 20, 44, 3, 1, 1)):   # (whatever the patch kernel takes)
+        e = mc.make_desc(*args, torch.float32)
+        assert mc.kernel_detail(e, 0).startswith("f32_implicit_gemm") and mc.kernel_detail(e, 0).endswith("_from_bf16_parts")
     buf = ctypes.create_string_buffer(64)
     l = _lib.lib()
     assert l.mi3d_conv3d_kernel_detail(ctypes.byref(d), 1, least - 1, buf, 64) == -3

@@ -26,10 +26,10 @@ CASES = [
     ((2, 3, 7, 31, 32, 80, 3, 1, 0), "01"),       # row-major tiles, no padding, last block of 64 half full
     ((1, 3, 5, 12, 64, 5, 3, 1, 2), "0"),        # padding 2, few output channels
     ((1, 4, 1, 1, 32, 16, 3, 1, 1), "01"),        # one column: planes above and below are zero
-    ((1, 2, 200, 1, 32, 16, 3, 1, 1), ""),      # patch of a one-column plane too large: the fp32 instructions
+    ((1, 2, 200, 1, 32, 16, 3, 1, 1), "01"),    # patch of a one-column plane too large: the implicit GEMM
     ((1, 3, 12, 12, 320, 320, 3, 1, 1), "01"),    # deepest level
-    ((1, 5, 11, 13, 32, 64, 3, 2, 1), "1"),      # parity classes of an odd extent
-    ((2, 4, 6, 70, 16, 64, 3, 2, 0), "1"),       # no padding: classes with one and two taps change places
+    ((1, 5, 11, 13, 32, 64, 3, 2, 1), "01"),     # parity classes of an odd extent (forward: the implicit GEMM)
+    ((2, 4, 6, 70, 16, 64, 3, 2, 0), "01"),      # no padding: classes with one and two taps change places
     ((2, 49, 41, 65, 32, 32, 3, 1, 1), "012"),     # weight gradient: one row and column beyond its 4 x 32 patches
     ((1, 55, 30, 31, 64, 96, 3, 1, 0), "012"),
     ((3, 30, 15, 28, 96, 64, 3, 1, 2), "012"),     # padding 2: dy planes beyond both ends
