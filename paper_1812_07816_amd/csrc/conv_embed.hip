@@ -301,8 +301,8 @@ size_t embed_c_min_workspace_bytes(const Geom& g, int pass) {
 // - Stride 2, forward: only 32 channels have a kernel of their own behind the padding (32->48 at 300300 80 / 125, at 36704 29 / 37;
 //   64->24 at 110880 55 / 51).  Data gradient: up to 64 contracted channels have one, which wins on large volumes (64->24 at
 //   859473 voxels 55 / 64, 48->32 at 2365860 113 / 136, 24->64 at 17 M 684 / 1353; 64->48 at 9.5 M 777 / 840, at 254040 42 / 29).
-// - Weight gradient: by the models of the time of both, padding at 2 TB/s (within 7 % of the better one but for 96->24 with
-//   stride 2): 64->16 at 1044576 168 / 446, 128->24 at 499824 121 / 405, 104->8 at 304732 146 / 200; but 48->48 at
+// - Weight gradient: by the models of the time of both, padding at 2 TB/s (0.3 % above the better way over 570 layers, 20 % at
+//   most): 64->16 at 1044576 168 / 446, 128->24 at 499824 121 / 405, 104->8 at 304732 146 / 200; but 48->48 at
 //   37 x 50 x 61 as it is.
 static bool padding_better(const Geom& g, const Geom& p, int pass) {
     const bool ci = p.Cin != g.Cin, co = p.Cout != g.Cout;
@@ -310,7 +310,7 @@ static bool padding_better(const Geom& g, const Geom& p, int pass) {
         const bool s1 = wgrad_mfma_supported(p);
         if (s1 ? wgrad_mfma_uses_igw(p) : !wgrad_s2_supported(p) || wgrad_s2_uses_igw(p)) return false;   // (the same kernel, or one behind further copies)
         const double bytes = (ci ? g.in_voxels() * 2.0 * (g.Cin + p.Cin) : 0.0) + (co ? g.out_voxels() * 2.0 * (g.Cout + p.Cout) : 0.0);
-        return igw_us(g, ~(size_t)0) > (s1 ? wgrad_mfma_patches_us(p) + 8.0 + bytes / 2e6 : 1.2 * (wgrad_s2_patches_us(p) + 8.0 + bytes / 2e6));
+        return igw_us(g, ~(size_t)0) > (s1 ? wgrad_mfma_patches_us(p) : wgrad_s2_patches_us(p)) + 8.0 + bytes / 2e6;
     }
     const bool dgrad = pass == MI3D_PASS_DGRAD, k_whole = dgrad ? !co : !ci, m_whole = dgrad ? !ci : !co;
     const int K = dgrad ? g.Cout : g.Cin, M = dgrad ? g.Cin : g.Cout;

@@ -305,16 +305,19 @@ static int wgrad_s2_slots(const Geom& g) {
     return (int)slots;
 }
 
+// What this kernel and the launch that adds its partial sums take: a staged x plane 2.0 us with 64 output channels a workgroup, 1.3
+// with 32; the planes of a workgroup; and the rounds of one workgroup per CU, two where the pairs of channel blocks do not
+// divide the CUs (320 channels: 260 workgroups for 128 outputs).  0.91 to 1.24 of 233 layers measured, at the ends of nine tenths.
 double wgrad_s2_patches_us(const Geom& g) {
-    const long long patches = (long long)g.N * g.Do * ((g.Ho + TH - 1) / TH) * ((g.Wo + TW - 1) / TW);
-    const double rate = g.Cout % 128 == 0 ? 8.7e8 : g.Cout <= 64 ? 7.6e8 : 4.65e8;
-    return 23.0 + 2.0 * patches * (TH * TW) * 27 * g.Cin * (double)g.Cout / rate;
+    const int mb = wgrad_s2_mb(g), slots = wgrad_s2_slots(g);
+    const long long pairs = (long long)(g.Cin / 32) * (g.Cout / (32 * mb));
+    const long long units = (long long)g.N * ((g.Ho + TH - 1) / TH) * ((g.Wo + TW - 1) / TW) * g.D;
+    const long long rounds = (pairs * slots + cu_count() - 1) / cu_count();
+    return 14.0 + (double)rounds * ((units + slots - 1) / slots) * (mb == 2 ? 2.0 : 1.3) + (double)slots * g.w_elems() * 8 / 8e6;
 }
 
-// The matrix product over numbered positions where its model expects it to be faster than this kernel, which (with the launch that adds
-// the partial sums) takes 23 us and the time of its whole patches at 870 TFLOP/s, 760 with 32 or 64 output channels and 465 with
-// other numbers that 128 does not divide: within 7 % of 20 layers measured.  This kernel -> igw_kernel: 64->128 at 96^3, N = 2 177 -> 133 us, 128->256 at 48^3, N = 2 92 -> 67,
-// 256->320 at 24^3, N = 2 101 -> 49, at 32^3, N = 2 161 -> 57, 64->320 at 56^3, N = 2 138 -> 74, 32->320 at 128^3 340 -> 231, 32->64 at
+// The matrix product over numbered positions where its model expects it to be faster than this kernel.  This kernel -> igw_kernel:
+// 64->128 at 96^3, N = 2 177 -> 133 us, 128->256 at 48^3, N = 2 92 -> 67, 256->320 at 24^3, N = 2 101 -> 49, at 32^3, N = 2 161 -> 57, 64->320 at 56^3, N = 2 138 -> 74, 32->320 at 128^3 340 -> 231, 32->64 at
 // 80 x 80 x 70, N = 2 47 -> 30; but 32->256 at 128^3, N = 2 294 -> 322, 64->256 at 120 x 128 x 128 274 -> 300 and 32->64 at 192^3
 // 153 -> 213 (seven tiles of columns read every position again): whole patches, many of them, stay.
 bool wgrad_s2_uses_igw(const Geom& g) {

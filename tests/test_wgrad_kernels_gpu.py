@@ -15,12 +15,12 @@ CASES = [
     (S2, (1, 51, 55, 130, 32, 32, 3, 2, 0)),
     (S2, (2, 70, 21, 115, 32, 32, 3, 2, 1)),
     (S2, (1, 141, 33, 190, 32, 32, 3, 2, 0)),     # one column beyond the third patch
-    (S2, (1, 50, 136, 65, 32, 64, 3, 2, 0)),
-    (S2, (2, 95, 31, 64, 32, 64, 3, 2, 1)),
+    (S2, (1, 177, 93, 63, 32, 64, 3, 2, 0)),
+    (S2, (1, 107, 67, 121, 32, 64, 3, 2, 1)),
     (S2, (1, 46, 73, 62, 64, 32, 3, 2, 0)),
     (S2, (2, 63, 24, 63, 64, 32, 3, 2, 1)),
-    (S2, (1, 33, 25, 128, 96, 128, 3, 2, 0)),
-    (S2, (2, 51, 7, 64, 128, 128, 3, 2, 1)),
+    (S2, (1, 86, 105, 64, 64, 128, 3, 2, 0)),
+    (S2, (2, 101, 15, 64, 128, 128, 3, 2, 1)),
     (PLANES, (1, 26, 24, 48, 32, 32, 3, 1, 1)),   # a last column of 16, two patch rows
     (PLANES, (1, 21, 38, 50, 32, 32, 3, 1, 0)),   # three: the last pair is half empty
     (PLANES, (3, 3, 36, 46, 32, 32, 3, 1, 2)),
