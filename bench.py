@@ -1,10 +1,10 @@
 #!/usr/bin/env python3
 """Benchmark of the hot path on one MI355X.
 
-A step = forward, data-gradient and weight-gradient passes of the full-size
-first U-Net level (192^3: Conv3D 4->32, 32->32 and the stride-2 32->64) with
-the data-swapping engine moving saved activations to pinned host memory and
-back under a device budget.  Prints ONE JSON line.
+A step = one training step of the 5-level 3D U-Net at 192^3, N = 2, in bf16: every convolution's forward, data-gradient and
+weight-gradient pass, instance normalisation, loss, SGD, and the data-swapping engine under a device budget.  Prints ONE JSON
+line with the step's figures on stdout; the whole report (kernels, swap sweeps, fp32 steps, CPU baseline) goes to stderr,
+as one JSON line as well.
 """
 import argparse
 import json
@@ -652,6 +652,27 @@ def level0_chain(args):
             "roofline": roof}
 
 
+def summary(out):
+    """The line on stdout: what identifies and rates the run, short enough for whoever keeps only the end of an output."""
+    def short(v):
+        return float("%.6g" % v) if isinstance(v, float) else v
+    line = {k: short(out[k]) for k in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling",
+                                       "vs_baseline", "dtype", "data")}
+    line["config"] = {"model": "5-level 3D U-Net, channels 32/64/128/256/320, 192^3", "global_batch": 2, "parallelism": "one GPU",
+                      **{k: out["config"][k] for k in ("instance_norm", "budget_bytes", "conv_flop_per_step")}}
+    line["pct_mfma_peak"] = short(out["pct_mfma_peak"])
+    line["roofline"] = {k: short(out["roofline"].get(k)) for k in ("kernel", "bound", "achieved", "peak", "unit", "frac", "ms_per_launch", "launches_per_step")}
+    line["swap"] = {k: out["swap"][k] for k in ("n_swapped", "bytes_out", "measured_peak_device_bytes", "measured_peak_within_budget")}
+    line["loss"] = short(out["loss"])
+    fp32 = out.get("targets", {}).get("swap_hidden_ge_0.8_at_16GiB", {}).get("fp32_N2")
+    if isinstance(fp32, dict):
+        line["swap_hidden_fp32_N2_16GiB"] = {"volume": fp32["volume"], "hidden_frac": short(fp32["hidden_frac"]), "bytes_out": fp32["bytes_out"]}
+    cpu = out.get("cpu_baseline")
+    if cpu:
+        line["cpu_baseline"] = {k: short(cpu[k]) for k in ("value", "unit", "cores", "kind")}
+    return line
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -803,7 +824,8 @@ def main():
         out["unet_layers"] = unet_layer_table(1)
     if not args.no_cpu_baseline and not args.headline_only:
         out["cpu_baseline"] = cpu_baseline()
-    print(json.dumps(out))
+    print(json.dumps(out), file=sys.stderr, flush=True)
+    print(json.dumps(summary(out)), flush=True)
 
 
 if __name__ == "__main__":
