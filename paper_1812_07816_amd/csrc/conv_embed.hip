@@ -1,5 +1,5 @@
-// Fallbacks that run a layer no tuned kernel covers through the MFMA kernels by
-// embedding its operands:
+// Layers no tuned kernel covers on the MFMA kernels.  Ragged channel counts that come in eights run as they are on the kernels
+// over numbered positions where that is faster (ragged_*: 3x3x3); everything else embeds its operands:
 //   - channel counts that are not multiples of 32: operands are zero-padded, results
 //     sliced back;
 //   - strided layers: the forward pass is the stride-1 result subsampled;
@@ -73,9 +73,9 @@ __global__ void __launch_bounds__(256) pad_to4_kernel(const uint16_t* __restrict
 // ---- results of the padded layer ----
 // The matrix-core kernels add zeros where a window or a patch leaves the volume, and 0 x inf is NaN: a NaN of theirs need
 // not be one.  Whatever comes out as NaN is formed again as the sum over its window alone; other values cannot have met
-// such a zero.  Looking for them costs nothing where results are sliced and a launch where they are not (48 -> 48 at
-// 37 x 50 x 61 222.9 -> 223.9 us, 40 -> 96 forward at 64^3 126 -> 130); with nothing but NaN in all operands a pass costs
-// about what the plain kernels take (48 -> 48 weight gradient 43 ms).
+// such a zero.  Looking for them costs nothing where results are sliced and a launch where they are not (padded 48 -> 48 at
+// 37 x 50 x 61 222.9 -> 223.9 us, 40 -> 96 forward at 64^3 126 -> 130), as in layers that are read as they are; with nothing
+// but NaN in all operands a pass costs about what the plain kernels take (48 -> 48 weight gradient 43 ms).
 
 // y or dx, channels [0, C) of CP-channel rows; V elements per thread (16 bytes, or one where C is not a multiple of 8)
 __device__ __forceinline__ uint16_t exact_bf16(const Geom& g, int pass, const uint16_t* in, const uint16_t* w, long long e) {
@@ -376,9 +376,9 @@ Geom embed_c_inner(const Geom& g, int pass, size_t ws_bytes, size_t* rest) {
 }
 
 // Bound: the copies are a pass over each operand and one more launch, the plain kernels do one product at a time per thread.
-// The three passes, plain kernels -> this: 48 -> 48 channels at 37 x 50 x 61 34.5 -> 0.22 ms, 8 -> 16 at 6^3 0.140 -> 0.061,
-// 40 -> 48 at 12^3 0.98 -> 0.084, 24 -> 48 at 10^3 with stride 2 0.171 -> 0.064: the padded layer wins at every size, so
-// the plain kernels are left with the geometries no matrix-core kernel takes.
+// The three passes, plain kernels -> padded: 48 -> 48 channels at 37 x 50 x 61 34.5 -> 0.22 ms (as it is: 0.12), 8 -> 16 at 6^3
+// 0.140 -> 0.061, 40 -> 48 at 12^3 0.98 -> 0.084, 24 -> 48 at 10^3 with stride 2 0.171 -> 0.064: the padded layer wins at every
+// size, so the plain kernels are left with the geometries no matrix-core kernel takes.
 int embed_c_conv(const Geom& g, int pass, const void* a, const void* b, void* out, void* ws, size_t ws_bytes, hipStream_t s) {
     if (ws_bytes < embed_c_min_workspace_bytes(g, pass)) return MI3D_ERR_WORKSPACE;
     EmbedC e = embed_c_layout(g, pass);

@@ -1010,7 +1010,9 @@ size_t f32_workspace_bytes(const Geom& g, int pass) {
     return b;
 }
 
-// (Planes 32 columns wide and more fill the tiles of f32s_gconv_kernel, few planes as they may be: it keeps those.)
+// Planes 32 columns wide and more stay with f32s_gconv_kernel, whose tiles they fill and whose edges the tests reach through
+// them.  They would be faster here (this line costs them: 16->16 at 2 x 33 x 33 19 us instead of 12, 16->8 at 4 x 20 x 40 24
+// instead of 13, at 32^2 13 instead of 8).
 bool f32_uses_tiny(const Geom& g, int pass) {
     if (!f32_supported(g, pass) || f32_head(g) || !tiny_supported(g, pass)) return false;
     return !split_ok(g, pass) || (pass == MI3D_PASS_DGRAD ? g.W : g.Wo) < 32;
@@ -1116,7 +1118,8 @@ static double split_us(const Geom& g, int pass) {
 //   volumes): 4->32 at 60^3 33 -> 40, at 16^3 19 -> 17.
 // - The strided data gradients it does take, eight launches of one to eight taps each: 32->64 at 128^3, N = 2 810 -> 709,
 //   64->128 at 64^3, N = 2 415 -> 244, 128->256 at 32^3, N = 2 592 -> 140, 32->64 at 24^3 159 -> 25.  (Volumes below 2048 voxels
-//   with at most 32 channels keep their kernel, whose classes are tested there on values without parts.)
+//   with at most 32 channels keep their kernel, whose classes are tested there on values without parts; it costs them: 32->64
+//   at 4^3 to 12^3 120 to 136 us where igf_kernel takes 13 to 15.)
 // - Of the stride-1 layers those too small for its tiles of 256 positions of a plane and of 64 contracted channels or more
 //   (those with fewer are the large volumes of a network), by the two models of the time: 320->320 at 8^3, N = 2 322 -> 73,
 //   256->256 at 16^3, N = 2 230 -> 194; but 128->128 at 32^3, N = 2 291 -> 338 and 64->64 at 64^3, N = 2 600 -> 745: a patch is
