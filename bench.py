@@ -7,6 +7,7 @@ line with the step's figures on stdout; the whole report (kernels, swap sweeps, 
 as one JSON line as well.
 """
 import argparse
+import gc
 import json
 import os
 import sys
@@ -349,6 +350,7 @@ class CallRecorder:
 
     def __enter__(self):
         import torch
+        gc.collect()    # a full collection takes 40 ms: inside a call's event pair it counts as that kernel's time
         for name, pass_ in self.NAMES.items():
             fn = getattr(self.mc, name)
             self.saved[name] = fn
