@@ -82,7 +82,8 @@ int mi3d_conv3d_out_dims(const mi3d_conv_desc *desc, int *Do, int *Ho, int *Wo);
  *
  * A call with less, down to mi3d_conv3d_min_workspace_bytes, is served too, by a slower kernel: fp32 layers by the fp32
  * matrix instructions (the smallest ones need none of it and run as they are), deep bf16 layers and weight gradients over
- * numbered positions with a contraction in fewer parts, channel counts that are padded to multiples of 32 by the plain
+ * numbered positions with a contraction in fewer parts, most other bf16 weight gradients as a product over numbered
+ * positions (which needs no room at all), channel counts that are padded to multiples of 32 by the plain
  * kernels (150 times slower on large volumes).  3x3x3 layers with channels in multiples of 8 are read as they are (forward
  * pass and data gradient from 1024 output voxels): of those only the data gradient needs room, for a copy of its weights,
  * and goes to the plain kernel below that.  The sums are then formed in another order, so the bits of a

@@ -190,7 +190,7 @@ static int run_kernel(Kernel k, const Geom& g, int pass, const void* a, const vo
 static std::string describe(Kernel k, const Geom& g, int pass, size_t ws_bytes) {
     size_t rest;
     char buf[64];
-    if (pass == MI3D_PASS_WGRAD && ((k == K_WGRAD_MFMA && wgrad_mfma_uses_igw(g)) || (k == K_WGRAD_S2 && wgrad_s2_uses_igw(g)) || (k == K_F32 && !f32_uses_tiny(g, pass) && f32_uses_igw(g, ws_bytes)))) {
+    if (pass == MI3D_PASS_WGRAD && ((k == K_WGRAD_MFMA && wgrad_mfma_uses_igw(g, ws_bytes)) || (k == K_WGRAD_S2 && wgrad_s2_uses_igw(g, ws_bytes)) || (k == K_F32 && !f32_uses_tiny(g, pass) && f32_uses_igw(g, ws_bytes)))) {
         igw_describe(g, ws_bytes, buf, sizeof(buf));
         return buf;
     }

@@ -308,7 +308,7 @@ static bool padding_better(const Geom& g, const Geom& p, int pass) {
     const bool ci = p.Cin != g.Cin, co = p.Cout != g.Cout;
     if (pass == MI3D_PASS_WGRAD) {
         const bool s1 = wgrad_mfma_supported(p);
-        if (s1 ? wgrad_mfma_uses_igw(p) : !wgrad_s2_supported(p) || wgrad_s2_uses_igw(p)) return false;   // (the same kernel, or one behind further copies)
+        if (s1 ? wgrad_mfma_uses_igw(p, ~(size_t)0) : !wgrad_s2_supported(p) || wgrad_s2_uses_igw(p, ~(size_t)0)) return false;   // (the same kernel, or one behind further copies)
         const double bytes = (ci ? g.in_voxels() * 2.0 * (g.Cin + p.Cin) : 0.0) + (co ? g.out_voxels() * 2.0 * (g.Cout + p.Cout) : 0.0);
         return igw_us(g, ~(size_t)0) > (s1 ? wgrad_mfma_patches_us(p) : wgrad_s2_patches_us(p)) + 8.0 + bytes / 2e6;
     }
@@ -464,7 +464,7 @@ static size_t embed_s_bytes(const Geom& g, int pass, bool least) {
     if (!embed_s_supported(g, pass)) return 0;
     Geom u = unit_stride_geom(g);
     size_t up = align256((size_t)u.out_voxels() * g.Cout * 2);
-    if (pass == MI3D_PASS_WGRAD) return up + align256(wgrad_mfma_workspace_bytes(u));
+    if (pass == MI3D_PASS_WGRAD) return up + (least ? wgrad_mfma_min_workspace_bytes(u) : align256(wgrad_mfma_workspace_bytes(u)));
     return up + (least ? sp_min_workspace_bytes(u, pass) : align256(sp_workspace_bytes(u, pass)));
 }
 size_t embed_s_workspace_bytes(const Geom& g, int pass) { return embed_s_bytes(g, pass, false); }

@@ -405,8 +405,9 @@ static bool wgrad_rows12(const Geom& g) {
 
 bool wgrad_mfma_supported(const Geom& g) { return th16::supported(g); }
 
+static size_t patches_workspace_bytes(const Geom& g) { return wgrad_rows12(g) ? th12::workspace_bytes(g) : th16::workspace_bytes(g); }
 double wgrad_mfma_patches_us(const Geom& g) {
-    const size_t parts = wgrad_rows12(g) ? th12::workspace_bytes(g) : th16::workspace_bytes(g);
+    const size_t parts = patches_workspace_bytes(g);
     const double pairs = (double)(g.Cin / 32) * (g.Cout / 32), slots = (double)parts / (4.0 * g.w_elems());
     const int rows = wgrad_rows12(g) ? 12 : 16;
     double units = (double)g.N * g.D * ((g.Ho + rows - 1) / rows) * ((g.Wo + 31) / 32);
@@ -420,20 +421,20 @@ double wgrad_mfma_patches_us(const Geom& g) {
 // 51 -> 30 us, at 8^3 41 -> 13, 256->256 at 4^3, N = 2 30 -> 11, 128->128 at 16^3 28 -> 21, at 8^3, N = 2 27 -> 15; but
 // 256->256 at 24^3, N = 2 106 -> 129, 128->128 at 48^3, N = 2 148 -> 222, 64->64 at 37 x 50 x 61 42 -> 63: here an LDS fragment
 // feeds nine products.
-bool wgrad_mfma_uses_igw(const Geom& g) {
+// It also takes layers of this kernel, up to twice the time, whose caller has no room for the partial sums: it needs none.
+// (Layers near the line have asked for less when the line lay elsewhere; beyond, up to 1024->1024 at 16 x 16 x 32 three
+// times, a call is refused.)
+bool wgrad_mfma_uses_igw(const Geom& g, size_t ws_bytes) {
     Geom q = g;
     q.hi = nullptr;      // (the sizes decide, not how the call passes its tensors)
     if (!igw_supported(q)) return false;
-    return igw_us(q, ~(size_t)0) < 0.9 * wgrad_mfma_patches_us(g);
+    return igw_us(q, ~(size_t)0) < (ws_bytes < patches_workspace_bytes(g) ? 2.0 : 0.9) * wgrad_mfma_patches_us(g);
 }
 
-size_t wgrad_mfma_workspace_bytes(const Geom& g) {
-    if (wgrad_mfma_uses_igw(g)) return igw_workspace_bytes(g);
-    return wgrad_rows12(g) ? th12::workspace_bytes(g) : th16::workspace_bytes(g);
-}
-size_t wgrad_mfma_min_workspace_bytes(const Geom& g) { return wgrad_mfma_uses_igw(g) ? 0 : wgrad_mfma_workspace_bytes(g); }
+size_t wgrad_mfma_workspace_bytes(const Geom& g) { return wgrad_mfma_uses_igw(g, ~(size_t)0) ? igw_workspace_bytes(g) : patches_workspace_bytes(g); }
+size_t wgrad_mfma_min_workspace_bytes(const Geom& g) { return wgrad_mfma_uses_igw(g, 0) ? 0 : patches_workspace_bytes(g); }
 int wgrad_mfma(const Geom& g, const void* x, const void* dy, float* dw, void* ws, size_t ws_bytes, hipStream_t s) {
-    if (wgrad_mfma_uses_igw(g)) return igw_run(g, x, dy, dw, ws, ws_bytes, s);
+    if (wgrad_mfma_uses_igw(g, ws_bytes)) return igw_run(g, x, dy, dw, ws, ws_bytes, s);
     return wgrad_rows12(g) ? th12::run(g, x, dy, dw, ws, ws_bytes, s) : th16::run(g, x, dy, dw, ws, ws_bytes, s);
 }
 #endif

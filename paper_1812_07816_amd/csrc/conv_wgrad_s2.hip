@@ -320,21 +320,22 @@ double wgrad_s2_patches_us(const Geom& g) {
 // 64->128 at 96^3, N = 2 177 -> 133 us, 128->256 at 48^3, N = 2 92 -> 67, 256->320 at 24^3, N = 2 101 -> 49, at 32^3, N = 2 161 -> 57, 64->320 at 56^3, N = 2 138 -> 74, 32->320 at 128^3 340 -> 231, 32->64 at
 // 80 x 80 x 70, N = 2 47 -> 30; but 32->256 at 128^3, N = 2 294 -> 322, 64->256 at 120 x 128 x 128 274 -> 300 and 32->64 at 192^3
 // 153 -> 213 (seven tiles of columns read every position again): whole patches, many of them, stay.
-bool wgrad_s2_uses_igw(const Geom& g) {
+// Up to twice the time it also takes layers of this kernel whose caller has no room for the partial sums (as at unit stride).
+static size_t patches_workspace_bytes(const Geom& g) { return (size_t)wgrad_s2_slots(g) * g.w_elems() * sizeof(float); }
+bool wgrad_s2_uses_igw(const Geom& g, size_t ws_bytes) {
     if (!igw_supported(g)) return false;
-    return igw_us(g, ~(size_t)0) < wgrad_s2_patches_us(g);
+    return igw_us(g, ~(size_t)0) < (ws_bytes < patches_workspace_bytes(g) ? 2.0 : 1.0) * wgrad_s2_patches_us(g);
 }
 
 size_t wgrad_s2_workspace_bytes(const Geom& g) {
     if (!wgrad_s2_supported(g)) return 0;
-    if (wgrad_s2_uses_igw(g)) return igw_workspace_bytes(g);
-    return (size_t)wgrad_s2_slots(g) * g.w_elems() * sizeof(float);
+    return wgrad_s2_uses_igw(g, ~(size_t)0) ? igw_workspace_bytes(g) : patches_workspace_bytes(g);
 }
-size_t wgrad_s2_min_workspace_bytes(const Geom& g) { return wgrad_s2_supported(g) && wgrad_s2_uses_igw(g) ? 0 : wgrad_s2_workspace_bytes(g); }
+size_t wgrad_s2_min_workspace_bytes(const Geom& g) { return !wgrad_s2_supported(g) || wgrad_s2_uses_igw(g, 0) ? 0 : patches_workspace_bytes(g); }
 
 int wgrad_s2(const Geom& g, const void* x, const void* dy, float* dw, void* ws, size_t ws_bytes, hipStream_t s) {
-    if (wgrad_s2_uses_igw(g)) return igw_run(g, x, dy, dw, ws, ws_bytes, s);
-    if (ws_bytes < wgrad_s2_workspace_bytes(g)) return MI3D_ERR_WORKSPACE;
+    if (wgrad_s2_uses_igw(g, ws_bytes)) return igw_run(g, x, dy, dw, ws, ws_bytes, s);
+    if (ws_bytes < patches_workspace_bytes(g)) return MI3D_ERR_WORKSPACE;
     Wg2Params P;
     P.x = (const uint16_t*)x; P.dy = (const uint16_t*)dy; P.part = (float*)ws;
     P.N = g.N; P.D = g.D; P.H = g.H; P.W = g.W; P.Cin = g.Cin; P.Cout = g.Cout;

@@ -115,7 +115,7 @@ bool wgrad_mfma_supported(const Geom& g);
 size_t wgrad_mfma_workspace_bytes(const Geom& g);
 size_t wgrad_mfma_min_workspace_bytes(const Geom& g);
 double wgrad_mfma_patches_us(const Geom& g);            // what its model expects the kernel on patches to take
-bool wgrad_mfma_uses_igw(const Geom& g);                // volumes that its patches cover badly or fill the chip with badly
+bool wgrad_mfma_uses_igw(const Geom& g, size_t ws_bytes);    // volumes that its patches cover badly or fill the chip with badly
 int wgrad_mfma(const Geom& g, const void* x, const void* dy, float* dw, void* ws, size_t ws_bytes, hipStream_t s);
 
 
@@ -151,7 +151,7 @@ bool wgrad_s2_supported(const Geom& g);
 size_t wgrad_s2_workspace_bytes(const Geom& g);
 size_t wgrad_s2_min_workspace_bytes(const Geom& g);
 double wgrad_s2_patches_us(const Geom& g);
-bool wgrad_s2_uses_igw(const Geom& g);
+bool wgrad_s2_uses_igw(const Geom& g, size_t ws_bytes);
 int wgrad_s2(const Geom& g, const void* x, const void* dy, float* dw, void* ws, size_t ws_bytes, hipStream_t s);
 
 

@@ -200,3 +200,19 @@ def test_plans_do_not_depend_on_what_was_asked_before():
         first = mc.kernel_detail(d, q, n)
         mc.workspace_bytes(e, q)
         assert mc.kernel_detail(d, q, n) == first
+
+
+def test_weight_gradients_run_in_the_workspace_that_earlier_builds_reported():
+    """A saved size stays enough: layers that went back to the kernels on patches run in what the product over positions asked for."""
+    import torch
+    from paper_1812_07816_amd import conv3d as mc
+    for args, before in (((1, 11, 18, 12, 256, 192, 3, 1, 2), 15925248), ((4, 12, 19, 15, 512, 160, 3, 1, 1), 17694720),
+                         ((2, 44, 37, 49, 512, 64, 3, 2, 1), 14155776), ((4, 32, 35, 36, 128, 32, 3, 2, 1), 7962624),
+                         ((4, 14, 22, 9, 256, 32, 3, (1, 2, 2), 1), 8672256),
+                         ((1, 123, 73, 136, 256, 49, 3, 2, 1), 35892224), ((2, 23, 21, 14, 512, 87, 3, 1, 1), 29138688),
+                         ((2, 159, 141, 83, 11, 64, 3, 2, 1), 252556544), ((2, 31, 20, 16, 119, 192, 3, 1, 1), 31621120)):
+        d = mc.make_desc(*args, torch.bfloat16)
+        assert mc.workspace_bytes(d, 2) > before >= mc.min_workspace_bytes(d, 2), args
+        assert "wgrad_implicit_gemm" in mc.kernel_detail(d, 2, before) and "wgrad_implicit_gemm" not in mc.kernel_detail(d, 2), args
+    d = mc.make_desc(1, 16, 16, 32, 1024, 1024, 3, 1, 1, torch.bfloat16)     # three times the time: refused, as before
+    assert mc.min_workspace_bytes(d, 2) == mc.workspace_bytes(d, 2)

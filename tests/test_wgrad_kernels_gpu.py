@@ -1,9 +1,12 @@
 """Weight-gradient kernels on patches, at sizes that the product over numbered positions leaves to them: the stride-2 kernel with
 32 and 64 output channels a workgroup, columns taken two patch rows at a time, and the fp32 instructions; odd extents, padding 0
 to 2, patches that end outside the volume.  Against the fp64 oracle (large volumes: a sample of the elements)."""
+import numpy as np
 import pytest
 import torch
 
+import synth_inputs as si
+from oracle import conv3d as oc
 from paper_1812_07816_amd import conv3d as mc
 from tests import parity
 
@@ -50,3 +53,25 @@ def test_matches_oracle(device, how, case):
     errs = parity.run_case(94, 5000 + 10 * CASES.index((how, case)), *case, bf16=how != F32, passes=("wgrad",), full=small, n_wgrad_samples=400)
     # fp32 sums of up to a million products of random sign in at most 256 parts: a thousand half roundings of 2^-24 at random
     assert errs["wgrad"] <= 3e-5, errs
+
+
+@pytest.mark.parametrize("case", [(3, 14, 48, 14, 32, 32, 3, 1, 2), (1, 3, 22, 44, 64, 128, 3, 1, 2), (2, 63, 24, 63, 64, 32, 3, 2, 1),
+                                  (4, 14, 22, 9, 256, 32, 3, (1, 2, 2), 1), (1, 46, 73, 62, 50, 32, 3, 2, 0)],
+                         ids=["planes", "planes_wide", "strided", "unit_stride", "padded"])
+def test_without_room_for_the_partial_sums(device, case):
+    """A call with less than the kernel on patches asks for runs the product over positions, down to the least workspace."""
+    d = mc.make_desc(*case, torch.bfloat16)
+    want, least = mc.workspace_bytes(d, 2), mc.min_workspace_bytes(d, 2)
+    assert mc.kernel_detail(d, 2).split(" > ")[-1] in (S2, PLANES)
+    x, w, dy = si.conv_case(94, 5900 + want % 1000, *case, True)
+    g = oc.shape(*case)
+    xd, dyd = parity.to_device(x, True), parity.to_device(dy, True)
+    at = np.random.default_rng(7).integers(0, 27 * d.Cin * d.Cout, 300)
+    ref = oc.wgrad_at(g, x, dy, at)
+    for n in (want - 256, (want + least) // 2 // 256 * 256, least):
+        assert "wgrad_implicit_gemm" in mc.kernel_detail(d, 2, n) or (case[4] == 50 and n < want - 256), n   # (no room for the padded copies)
+        ws = torch.empty(n + 16, dtype=torch.uint8, device="cuda")[:n]
+        dw = torch.full((d.Cout, 3, 3, 3, d.Cin), 7.0, device="cuda")
+        mc.conv3d_wgrad(d, xd, dyd, dw, ws)
+        # (one part: a chain of at most 20000 steps of 32 positions, rounded half a step of 2^-24 at random each)
+        assert parity._sampled_err(parity.to_host(dw).ravel()[at], ref) <= 3e-5, n
